@@ -9,6 +9,7 @@
 #include <cstring>
 #include <mutex>
 #include <numeric>
+#include <unordered_map>
 #include <utility>
 #include <vector>
 
@@ -135,22 +136,96 @@ int validate_problem(const fcp_problem* p) {
   return FCP_OK;
 }
 
-int compute_layout(const fcp_problem* p, WsLayout* L) {
-  std::memset(L, 0, sizeof(*L));
-  L->fwd_tile_m = kFwdTileM;
-  {
-    // forward items pair two query heads of a KV head when the group size is even, else two row tiles
-    const int G = p->n_q_heads / p->n_kv_heads;
-    for (int s = 0; s < p->n_slots; s++) {
-      const int64_t n_tiles = ceil_div(p->q_blocks[p->slots[s].q_blk].tok_len, L->fwd_tile_m);
-      const int64_t n = (G % 2 == 0) ? n_tiles * (p->n_q_heads / 2) : ceil_div(n_tiles, 2) * p->n_q_heads;
-      L->n_fwd_items += n;
-      if (p->slots[s].n_pairs == 1 && (p->pairs[p->slots[s].pair_begin].kind & 2)) L->n_fwd_packed_items += n;
+void expand_problem(const fcp_problem* p, Expanded* x) {
+  // members of each packed KV block: segments are by (kv_blk, tok_off)
+  std::vector<int32_t> seg_begin(p->n_kv_blocks + 1, 0);
+  for (int i = 0; i < p->n_segments; i++) seg_begin[p->segments[i].kv_blk + 1]++;
+  for (int b = 0; b < p->n_kv_blocks; b++) seg_begin[b + 1] += seg_begin[b];
+  auto n_members = [&](int kb) { return seg_begin[kb + 1] - seg_begin[kb]; };
+  std::vector<int32_t> slot_begin(p->n_q_blocks + 1, 0);       // slots of a query block are consecutive
+  for (int s = 0; s < p->n_slots; s++) slot_begin[p->slots[s].q_blk + 1]++;
+  for (int b = 0; b < p->n_q_blocks; b++) slot_begin[b + 1] += slot_begin[b];
+  const bool spill = (p->flags & FCP_FLAG_BWD_SPILL_DS) != 0, direct = (p->flags & FCP_FLAG_DIRECT_SINGLE) != 0;
+
+  // query side: pairs (with the query rows and the KV segment each joins), forward and dQ segments
+  struct Join { int32_t q_start, q_len, kv_seg; };
+  std::vector<Join> joins;
+  std::vector<int32_t> kv_seg_of(p->n_kv_blocks);              // first KV segment of a block
+  for (int b = 0; b < p->n_kv_blocks; b++) {
+    const fcp_block& kb = p->kv_blocks[b];
+    kv_seg_of[b] = (int32_t)x->kv.size();
+    if (n_members(b) == 0) x->kv.push_back({kb.tok_start, kb.tok_len, kb.seq, 0, 0});
+    for (int m = seg_begin[b]; m < seg_begin[b + 1]; m++)
+      x->kv.push_back({kb.tok_start + p->segments[m].tok_off, p->segments[m].tok_len, p->segments[m].seq, 0, 0});
+  }
+  int64_t frag = kDsSinkFrags;
+  auto add_pair = [&](int q_start, int q_len, int kv_seg, int kind) {
+    const KvSeg& k = x->kv[kv_seg];
+    x->pairs.push_back({k.start, k.len, kind, spill ? (int32_t)frag : 0});
+    joins.push_back({q_start, q_len, kv_seg});
+    x->kv[kv_seg].n_deps++;
+    frag += p->n_q_heads * ds_frags_per_head(kind, q_len, k.len);
+  };
+  for (int b = 0; b < p->n_q_blocks; b++) {
+    const fcp_block& qb = p->q_blocks[b];
+    const int s0 = slot_begin[b], s1 = slot_begin[b + 1];
+    const int to_final = (direct && s1 - s0 == 1) ? 1 : 0;
+    int packed_kv = -1;                                        // the KV block of its PACKED pair
+    for (int s = s0; s < s1; s++)
+      for (int i = p->slots[s].pair_begin; i < p->slots[s].pair_begin + p->slots[s].n_pairs; i++)
+        if (p->pairs[i].kind & 2) packed_kv = p->pairs[i].kv_blk;
+    // one query segment per member, the whole block if it has none; the pairs of a segment are consecutive
+    for (int m = 0; m < (packed_kv < 0 ? 1 : n_members(packed_kv)); m++) {
+      const int32_t off = packed_kv < 0 ? 0 : p->segments[seg_begin[packed_kv] + m].tok_off;
+      const int32_t len = packed_kv < 0 ? qb.tok_len : p->segments[seg_begin[packed_kv] + m].tok_len;
+      const int32_t seq = packed_kv < 0 ? qb.seq : p->segments[seg_begin[packed_kv] + m].seq;
+      const int32_t q0 = qb.tok_start + off, p0 = (int32_t)x->pairs.size();
+      for (int s = s0; s < s1; s++) {
+        const fcp_slot& sl = p->slots[s];
+        x->fwd.push_back({q0, len, sl.row_start + off, (int32_t)x->pairs.size(), sl.n_pairs, seq, to_final});
+        for (int i = sl.pair_begin; i < sl.pair_begin + sl.n_pairs; i++) {
+          const fcp_pair& pr = p->pairs[i];
+          add_pair(q0, len, kv_seg_of[pr.kv_blk] + ((pr.kind & 2) ? m : 0), pr.kind & 1);
+        }
+      }
+      x->dq.push_back({q0, len, q0, p0, (int32_t)x->pairs.size() - p0, seq, 0});
     }
   }
-  for (int b = 0; b < p->n_kv_blocks; b++)
-    L->n_bwd_items += ceil_div(p->kv_blocks[b].tok_len, kBwdTileN) * p->n_kv_heads;
-  L->n_bwd_deps = p->n_pairs;
+  x->n_ds_frags = frag;
+
+  // KV side: the dependencies of each KV segment, in query order, the DIAG one last: the tiles of one KV segment then
+  // walk the FULL dependencies in lockstep (identical step sequences, same XCD), so the Q / dO stream they share stays
+  // in L2; they only diverge on the diagonal, where each tile starts at its own row.
+  int32_t d = 0;
+  for (KvSeg& k : x->kv) { k.dep_begin = d; d += k.n_deps; k.n_deps = 0; }
+  x->deps.resize(x->pairs.size());
+  for (size_t i = 0; i < joins.size(); i++) {
+    KvSeg& k = x->kv[joins[i].kv_seg];
+    x->deps[k.dep_begin + k.n_deps++] = {joins[i].q_start, joins[i].q_len, x->pairs[i].kind, x->pairs[i].ds_frag};
+  }
+  for (const KvSeg& k : x->kv)
+    std::stable_partition(x->deps.begin() + k.dep_begin, x->deps.begin() + k.dep_begin + k.n_deps, [](const BwdDep& e) { return !(e.kind & 1); });
+}
+
+// Query-stationary items of a segment: two query heads of a KV head share one when the group size is even, else two row tiles.
+static int64_t q_items_of(const QSeg& s, int n_q_heads, int G) {
+  const int64_t n_tiles = ceil_div(s.len, kFwdTileM);
+  return (G % 2 == 0) ? n_tiles * (n_q_heads / 2) : ceil_div(n_tiles, 2) * n_q_heads;
+}
+
+int compute_layout(const fcp_problem* p, WsLayout* L) {
+  Expanded x;
+  expand_problem(p, &x);
+  return compute_layout(p, x, L);
+}
+
+int compute_layout(const fcp_problem* p, const Expanded& x, WsLayout* L) {
+  std::memset(L, 0, sizeof(*L));
+  const int G = p->n_q_heads / p->n_kv_heads;
+  for (const QSeg& s : x.fwd) L->n_fwd_items += q_items_of(s, p->n_q_heads, G);
+  for (const QSeg& s : x.dq) L->n_dq_items += q_items_of(s, p->n_q_heads, G);
+  for (const KvSeg& k : x.kv) L->n_bwd_items += ceil_div(k.len, kBwdTileN) * p->n_kv_heads;
+  L->n_pairs = (int64_t)x.pairs.size();
   std::vector<int32_t> slots_of(p->n_q_blocks, 0);
   for (int s = 0; s < p->n_slots; s++) slots_of[p->slots[s].q_blk]++;
   const bool direct = (p->flags & FCP_FLAG_DIRECT_SINGLE) != 0;
@@ -165,39 +240,27 @@ int compute_layout(const fcp_problem* p, WsLayout* L) {
   for (int b = 0; b < p->n_q_blocks; b++) {
     if (!(direct && slots_of[b] == 1))
       L->n_merge_items += ceil_div((int64_t)p->q_blocks[b].tok_len * p->n_q_heads, L->merge_chunk);
-    {
-      const int G = p->n_q_heads / p->n_kv_heads;
-      const int64_t n_tiles = ceil_div(p->q_blocks[b].tok_len, kFwdTileM);
-      L->n_dq_items += (G % 2 == 0) ? n_tiles * (p->n_q_heads / 2) : ceil_div(n_tiles, 2) * p->n_q_heads;
-    }
     L->t_q += p->q_blocks[b].tok_len;
   }
-  for (int b = 0; b < p->n_kv_blocks; b++) L->t_kv += p->kv_blocks[b].tok_len;
   if (L->t_q * p->n_q_heads > INT32_MAX) { set_error("more than 2^31-1 (query row, head) entries"); return FCP_ERR_UNSUPPORTED; }
-  if (L->n_fwd_items > INT32_MAX || L->n_bwd_items > INT32_MAX || L->n_merge_items > INT32_MAX) {
+  if (L->n_fwd_items > INT32_MAX || L->n_bwd_items > INT32_MAX || L->n_merge_items > INT32_MAX || L->n_dq_items > INT32_MAX) {
     set_error("too many work items"); return FCP_ERR_UNSUPPORTED;
   }
   auto align = [](size_t x) { return (x + 255) & ~(size_t)255; };
   size_t off = align(sizeof(WsHeader));
-  L->off_pairs = off;       off = align(off + sizeof(DevPair) * (size_t)std::max(1, p->n_pairs));
+  L->off_pairs = off;       off = align(off + sizeof(DevPair) * (size_t)std::max<int64_t>(1, L->n_pairs));
   L->off_fwd_items = off;   off = align(off + sizeof(QItem) * (size_t)std::max<int64_t>(1, L->n_fwd_items));
-  L->off_q_seg = off;       off = align(off + (p->n_segments ? sizeof(uint32_t) * (size_t)L->t_q : 0));
-  L->off_bwd_deps = off;    off = align(off + sizeof(BwdDep) * (size_t)std::max<int64_t>(1, L->n_bwd_deps));
+  L->off_bwd_deps = off;    off = align(off + sizeof(BwdDep) * (size_t)std::max<int64_t>(1, L->n_pairs));
   L->off_bwd_items = off;   off = align(off + sizeof(BwdItem) * (size_t)std::max<int64_t>(1, L->n_bwd_items));
   L->off_merge_items = off; off = align(off + sizeof(MergeItem) * (size_t)std::max<int64_t>(1, L->n_merge_items));
   L->off_slot_rh = off;     off = align(off + sizeof(int32_t) * (size_t)std::max(1, p->n_slots));
   L->off_dq_items = off;    off = align(off + sizeof(QItem) * (size_t)std::max<int64_t>(1, L->n_dq_items));
-  L->off_kv_seg = off;      off = align(off + (p->n_segments ? sizeof(uint32_t) * (size_t)L->t_kv : 0));
   // backward scratch, head-major [Hq][T_q] fp32: D * scale, then LSE * log2(e)
   L->off_dls = off;         off = align(off + sizeof(float) * (size_t)std::max<int64_t>(1, L->t_q * p->n_q_heads));
   L->off_lse2 = off;        off = align(off + sizeof(float) * (size_t)std::max<int64_t>(1, L->t_q * p->n_q_heads));
   L->off_ds = off;
   if (p->flags & FCP_FLAG_BWD_SPILL_DS) {
-    int64_t frags = kDsSinkFrags;
-    for (int i = 0; i < p->n_pairs; i++)
-      frags += p->n_q_heads * ds_frags_per_head(p->pairs[i].kind, p->q_blocks[p->pairs[i].q_blk].tok_len,
-                                                p->kv_blocks[p->pairs[i].kv_blk].tok_len);
-    frags += 1;   // the dQ kernel requests fragments in pairs: one past the last may be named (never used)
+    const int64_t frags = x.n_ds_frags + 1;   // the dQ kernel requests fragments in pairs: one past the last may be named (never used)
     if (frags > INT32_MAX) { set_error("FCP_FLAG_BWD_SPILL_DS: more than 2^31-1 dS fragments"); return FCP_ERR_UNSUPPORTED; }
     L->n_ds_frags = frags;
     off = align(off + (size_t)frags * kDsFragBytes);
@@ -251,30 +314,15 @@ int layout_for(const fcp_problem* p, const void* workspace, WsLayout* L) {
 
 namespace {
 
-// 64-row KV tiles that a query-stationary item visits: every pair in full, a DIAG pair up to the item's last row,
-// a PACKED pair the item's column range.
-void count_tiles(QItem* it, const DevPair* dpairs) {
+// 64-row KV tiles that a query-stationary item visits: every pair in full, a DIAG pair up to the item's last row.
+void count_tiles(QItem* it, const std::vector<DevPair>& pairs) {
   const int row_hi = std::max(it->tile_off[0] + it->q_rows[0], it->tile_off[1] + it->q_rows[1]);
   int n = 0;
   for (int i = it->pair_begin; i < it->pair_begin + it->n_pairs; i++) {
-    if (dpairs[i].kind & 2) { n += (it->col_end - it->col_begin + kQTileN - 1) / kQTileN; continue; }
-    const int nc = dpairs[i].kind == FCP_KIND_DIAG ? std::min(dpairs[i].kv_len, row_hi) : dpairs[i].kv_len;
+    const int nc = (pairs[i].kind & 1) ? std::min(pairs[i].kv_len, row_hi) : pairs[i].kv_len;
     n += (nc + kQTileN - 1) / kQTileN;
   }
   it->n_tiles = n;
-}
-
-// Column range of an item of a packed query block: from the first column any of its rows can see (rounded down
-// to a tile) to one past the last.  seg = the member bounds of the block's rows (seg_word), row 0 of the block first.
-void packed_columns(QItem* it, const uint32_t* seg, bool causal) {
-  int lo = INT32_MAX, hi = 0;
-  for (int k = 0; k < 2; k++)
-    for (int r = it->tile_off[k]; r < it->tile_off[k] + it->q_rows[k]; r++) {
-      lo = std::min(lo, (int)(seg[r] & 0xffff));
-      hi = std::max(hi, causal ? std::min((int)(seg[r] >> 16), r + 1) : (int)(seg[r] >> 16));
-    }
-  it->col_begin = hi ? (lo / kQTileN) * kQTileN : 0;
-  it->col_end = hi;
 }
 
 // XCD affinity: groups with the same key (sequence, KV head) become one group (items concatenated in the order the
@@ -284,28 +332,20 @@ void packed_columns(QItem* it, const uint32_t* seg, bool causal) {
 // a batch dominated by one sequence keeps the finer groups, which balance better.
 template <class Item>
 void merge_groups_by_key(std::vector<std::vector<Item>>& groups, std::vector<int64_t>& weight, const std::vector<int64_t>& key) {
-  {
-    std::vector<int64_t> k2, w2;
-    int64_t total = 0, largest = 0;
-    for (size_t i = 0; i < groups.size(); i++) {
-      size_t j = 0;
-      while (j < k2.size() && k2[j] != key[i]) j++;
-      if (j == k2.size()) { k2.push_back(key[i]); w2.push_back(0); }
-      w2[j] += weight[i];
-      total += weight[i];
-      largest = std::max(largest, w2[j]);
-    }
-    if (largest * kNumXcd * 4 > total * 3) return;
-  }
-  std::vector<std::vector<Item>> g2;
-  std::vector<int64_t> w2, k2;
+  std::unordered_map<int64_t, size_t> where;      // key -> merged group, in order of first appearance
+  std::vector<size_t> to(groups.size());
+  std::vector<int64_t> w2;
+  int64_t total = 0, largest = 0;
   for (size_t i = 0; i < groups.size(); i++) {
-    size_t j = 0;
-    while (j < k2.size() && k2[j] != key[i]) j++;
-    if (j == k2.size()) { k2.push_back(key[i]); g2.emplace_back(); w2.push_back(0); }
-    g2[j].insert(g2[j].end(), groups[i].begin(), groups[i].end());
-    w2[j] += weight[i];
+    to[i] = where.emplace(key[i], w2.size()).first->second;
+    if (to[i] == w2.size()) w2.push_back(0);
+    w2[to[i]] += weight[i];
+    total += weight[i];
+    largest = std::max(largest, w2[to[i]]);
   }
+  if (largest * kNumXcd * 4 > total * 3) return;
+  std::vector<std::vector<Item>> g2(w2.size());
+  for (size_t i = 0; i < groups.size(); i++) g2[to[i]].insert(g2[to[i]].end(), groups[i].begin(), groups[i].end());
   groups.swap(g2); weight.swap(w2);
 }
 
@@ -335,21 +375,57 @@ void spread_over_xcds(std::vector<std::vector<Item>>& groups, std::vector<int64_
   begin[kNumXcd] = (int32_t)out->size();
 }
 
-// Column range [lo, hi) of the dQ item that holds each 128-row tile of a packed query block (the items pair
-// neighbouring row tiles when the group size is odd, exactly as the dQ queue builder below does).
-void packed_tile_columns(int tok_len, int G, const uint32_t* seg, bool causal, std::vector<int>* lo, std::vector<int>* hi) {
-  const int n_tiles = (int)ceil_div(tok_len, kFwdTileM);
-  lo->assign(n_tiles, 0); hi->assign(n_tiles, 0);
-  auto range = [&](int t0, int t1) {      // the item of tiles t0 (and t1, or -1)
-    QItem it{};
-    it.tile_off[0] = t0 * kFwdTileM; it.q_rows[0] = std::min(kFwdTileM, tok_len - t0 * kFwdTileM);
-    if (t1 >= 0) { it.tile_off[1] = t1 * kFwdTileM; it.q_rows[1] = std::min(kFwdTileM, tok_len - t1 * kFwdTileM); }
-    packed_columns(&it, seg, causal);
-    (*lo)[t0] = it.col_begin; (*hi)[t0] = it.col_end;
-    if (t1 >= 0) { (*lo)[t1] = it.col_begin; (*hi)[t1] = it.col_end; }
-  };
-  if (G % 2 == 0) for (int t = 0; t < n_tiles; t++) range(t, -1);
-  else for (int t = n_tiles - 1; t >= 0; t -= 2) range(t, t >= 1 ? t - 1 : -1);
+// The query-stationary items (forward, dQ) of a list of segments, one group per (segment, KV head): its items share
+// K/V.  An item joins two sub-tiles: heads (2j, 2j+1) of the group on one row tile when G is even, else row tiles
+// (2j, 2j+1) of one head.
+void q_items(const fcp_problem* p, const std::vector<QSeg>& segs, const std::vector<DevPair>& pairs, std::vector<QItem>* flat,
+             int32_t begin[kNumXcd + 1]) {
+  const int G = p->n_q_heads / p->n_kv_heads;
+  std::vector<std::vector<QItem>> groups;
+  std::vector<int64_t> weight, gkey;
+  groups.reserve(segs.size() * p->n_kv_heads);
+  std::vector<int64_t> tile_w;
+  for (const QSeg& sg : segs) {
+    const int n_tiles = (int)ceil_div(sg.len, kFwdTileM);
+    tile_w.assign(n_tiles, 0);
+    for (int t = 0; t < n_tiles; t++) {
+      const int off = t * kFwdTileM, rows = std::min(kFwdTileM, sg.len - off);
+      for (int i = sg.pair_begin; i < sg.pair_begin + sg.n_pairs; i++)
+        tile_w[t] += (int64_t)rows * ((pairs[i].kind & 1) ? std::min(pairs[i].kv_len, off + rows) : pairs[i].kv_len);
+    }
+    auto sub = [&](QItem* it, int k, int t, int head) {
+      const int off = t * kFwdTileM;
+      it->q_start[k] = sg.start + off; it->q_rows[k] = std::min(kFwdTileM, sg.len - off);
+      it->out_row[k] = sg.out_row + off; it->tile_off[k] = off; it->head[k] = head;
+    };
+    for (int g = 0; g < p->n_kv_heads; g++) {
+      std::vector<QItem> items;
+      int64_t w = 0;
+      auto add = [&](int t0, int h0, int t1, int h1) {      // t1 < 0: no second sub-tile
+        QItem it{};
+        it.pair_begin = sg.pair_begin; it.n_pairs = sg.n_pairs; it.to_final = sg.to_final; it.q_blk_len = sg.len;
+        sub(&it, 0, t0, h0);
+        w += tile_w[t0];
+        if (t1 >= 0) { sub(&it, 1, t1, h1); w += tile_w[t1]; }
+        else { it.q_start[1] = it.q_start[0]; it.q_rows[1] = 0; it.out_row[1] = it.out_row[0]; it.tile_off[1] = it.tile_off[0]; it.head[1] = it.head[0]; }
+        count_tiles(&it, pairs);
+        items.push_back(it);
+      };
+      // later tiles of a DIAG pair are heavier: they come first
+      if (G % 2 == 0) {
+        for (int t = n_tiles - 1; t >= 0; t--)
+          for (int hh = 0; hh < G; hh += 2) add(t, g * G + hh, t, g * G + hh + 1);
+      } else {
+        for (int t = n_tiles - 1; t >= 0; t -= 2)
+          for (int hh = 0; hh < G; hh++) add(t, g * G + hh, t - 1, g * G + hh);
+      }
+      groups.push_back(std::move(items));
+      weight.push_back(w);
+      gkey.push_back((int64_t)sg.seq * p->n_kv_heads + g);
+    }
+  }
+  merge_groups_by_key(groups, weight, gkey);
+  spread_over_xcds(groups, weight, flat, begin);
 }
 
 }  // namespace
@@ -659,265 +735,57 @@ extern "C" int fcp_workspace_bytes(const fcp_problem* p, size_t* bytes) {
 // ranges, zero / +inf pages), resolved pairs, forward items and, unless forward_only, the backward,
 // dQ and merge tables.  `host` is resized to the image (everything before the backward scratch
 // region, or before the backward dependency lists when forward_only).
-int fcp::build_queue_image(const fcp_problem* p, const WsLayout& L, bool forward_only, std::vector<unsigned char>* image) {
+int fcp::build_queue_image(const fcp_problem* p, const Expanded& x, const WsLayout& L, bool forward_only, std::vector<unsigned char>* image) {
   const size_t upload = forward_only ? L.off_bwd_deps : L.off_dls;
   image->assign(upload, 0);
   std::vector<unsigned char>& host = *image;
   WsHeader* hdr = reinterpret_cast<WsHeader*>(host.data());
-  for (float& x : hdr->infs) x = INFINITY;
-  DevPair* dpairs = reinterpret_cast<DevPair*>(host.data() + L.off_pairs);
-  {
-    const bool spill = (p->flags & FCP_FLAG_BWD_SPILL_DS) != 0;
-    int64_t frag = kDsSinkFrags;
-    for (int i = 0; i < p->n_pairs; i++) {
-      const fcp_block& kb = p->kv_blocks[p->pairs[i].kv_blk];
-      dpairs[i] = {kb.tok_start, kb.tok_len, p->pairs[i].kind, spill ? (int32_t)frag : 0};
-      frag += p->n_q_heads * ds_frags_per_head(p->pairs[i].kind, p->q_blocks[p->pairs[i].q_blk].tok_len, kb.tok_len);
-    }
-  }
-  // ---- member bounds of the rows of packed blocks, per Q-buffer row and (with the backward tables) per KV-buffer row
-  const uint32_t* q_seg = nullptr;
-  if (p->n_segments) {
-    std::vector<int32_t> seg_begin(p->n_kv_blocks + 1, 0);
-    for (int i = 0; i < p->n_segments; i++) seg_begin[p->segments[i].kv_blk + 1]++;
-    for (int b = 0; b < p->n_kv_blocks; b++) seg_begin[b + 1] += seg_begin[b];
-    uint32_t* qs = reinterpret_cast<uint32_t*>(host.data() + L.off_q_seg);
-    uint32_t* ks = forward_only ? nullptr : reinterpret_cast<uint32_t*>(host.data() + L.off_kv_seg);
-    for (int i = 0; i < p->n_pairs; i++) {
-      if (!(p->pairs[i].kind & 2)) continue;
-      const int kb = p->pairs[i].kv_blk;
-      const int32_t q0 = p->q_blocks[p->pairs[i].q_blk].tok_start;
-      for (int m = seg_begin[kb]; m < seg_begin[kb + 1]; m++)
-        for (int r = 0; r < p->segments[m].tok_len; r++)
-          qs[q0 + p->segments[m].tok_off + r] = seg_word(p->segments[m].tok_off, p->segments[m].tok_off + p->segments[m].tok_len);
-    }
-    if (ks)
-      for (int m = 0; m < p->n_segments; m++)
-        for (int r = 0; r < p->segments[m].tok_len; r++)
-          ks[p->kv_blocks[p->segments[m].kv_blk].tok_start + p->segments[m].tok_off + r] =
-              seg_word(p->segments[m].tok_off, p->segments[m].tok_off + p->segments[m].tok_len);
-    q_seg = qs;
-  }
-  const int G = p->n_q_heads / p->n_kv_heads;
-  // ---- forward: one group per (slot, KV head): its items share K/V.  An item joins two sub-tiles:
-  // heads (2j, 2j+1) of the group on one row tile when G is even, else row tiles (2j, 2j+1) of one head.
-  {
-    std::vector<std::vector<QItem>> groups, groups_p;      // _p: items of packed query blocks, queued apart
-    std::vector<int64_t> weight, gkey, weight_p;
-    groups.reserve((size_t)p->n_slots * p->n_kv_heads);
-    std::vector<int32_t> n_slots_of(p->n_q_blocks, 0);
-    for (int s = 0; s < p->n_slots; s++) n_slots_of[p->slots[s].q_blk]++;
-    for (int s = 0; s < p->n_slots; s++) {
-      const fcp_slot& sl = p->slots[s];
-      const fcp_block& qb = p->q_blocks[sl.q_blk];
-      const int n_tiles = (int)ceil_div(qb.tok_len, L.fwd_tile_m);
-      std::vector<int64_t> tile_w(n_tiles, 0);
-      for (int t = n_tiles - 1; t >= 0; t--) {
-        const int off = t * L.fwd_tile_m;
-        const int rows = std::min(L.fwd_tile_m, qb.tok_len - off);
-        for (int i = sl.pair_begin; i < sl.pair_begin + sl.n_pairs; i++) {
-          const int kvlen = dpairs[i].kv_len;
-          const int cols = (dpairs[i].kind & 1) ? std::min(kvlen, off + rows) : kvlen;
-          tile_w[t] += (int64_t)rows * cols;
-        }
-      }
-      const int packed_kind = (sl.n_pairs == 1 && (dpairs[sl.pair_begin].kind & 2)) ? dpairs[sl.pair_begin].kind : 0;
-      auto finish = [&](QItem* it) {
-        if (packed_kind) packed_columns(it, q_seg + qb.tok_start, (packed_kind & 1) != 0);
-        count_tiles(it, dpairs);
-      };
-      const int to_final = ((p->flags & FCP_FLAG_DIRECT_SINGLE) && n_slots_of[sl.q_blk] == 1) ? 1 : 0;
-      auto sub = [&](QItem* it, int k, int t, int head) {
-        const int off = t * L.fwd_tile_m;
-        it->q_start[k] = qb.tok_start + off; it->q_rows[k] = std::min(L.fwd_tile_m, qb.tok_len - off);
-        it->out_row[k] = sl.row_start + off; it->tile_off[k] = off; it->head[k] = head;
-      };
-      for (int g = 0; g < p->n_kv_heads; g++) {
-        std::vector<QItem> items;
-        int64_t w = 0;
-        if (G % 2 == 0) {
-          for (int t = n_tiles - 1; t >= 0; t--)         // later tiles of a DIAG pair are heavier
-            for (int hh = 0; hh < G; hh += 2) {
-              QItem it{};
-              it.pair_begin = sl.pair_begin; it.n_pairs = sl.n_pairs; it.to_final = to_final;
-              sub(&it, 0, t, g * G + hh); sub(&it, 1, t, g * G + hh + 1);
-              finish(&it);
-              items.push_back(it);
-              w += 2 * tile_w[t];
-            }
-        } else {
-          for (int t = n_tiles - 1; t >= 0; t -= 2)
-            for (int hh = 0; hh < G; hh++) {
-              QItem it{};
-              it.pair_begin = sl.pair_begin; it.n_pairs = sl.n_pairs; it.to_final = to_final;
-              sub(&it, 0, t, g * G + hh);
-              if (t >= 1) { sub(&it, 1, t - 1, g * G + hh); w += tile_w[t - 1]; }
-              else { it.q_start[1] = it.q_start[0]; it.q_rows[1] = 0; it.out_row[1] = it.out_row[0]; it.tile_off[1] = it.tile_off[0]; it.head[1] = it.head[0]; }
-              finish(&it);
-              items.push_back(it);
-              w += tile_w[t];
-            }
-        }
-        if (packed_kind) {
-          groups_p.push_back(std::move(items));
-          weight_p.push_back(w);
-        } else {
-          groups.push_back(std::move(items));
-          weight.push_back(w);
-          gkey.push_back((int64_t)qb.seq * p->n_kv_heads + g);
-        }
-      }
-    }
-    merge_groups_by_key(groups, weight, gkey);
-    std::vector<QItem> flat, flat_p;
-    spread_over_xcds(groups, weight, &flat, hdr->fwd_begin);
-    spread_over_xcds(groups_p, weight_p, &flat_p, hdr->fwdp_begin);
-    for (int x = 0; x <= kNumXcd; x++) hdr->fwdp_begin[x] += (int32_t)flat.size();      // they follow the others
-    if ((int64_t)flat.size() != L.n_fwd_items - L.n_fwd_packed_items || (int64_t)flat_p.size() != L.n_fwd_packed_items) {
-      set_error("internal: forward item count mismatch"); return FCP_ERR_INVALID_ARG;
-    }
-    flat.insert(flat.end(), flat_p.begin(), flat_p.end());
-    if (!flat.empty()) std::memcpy(host.data() + L.off_fwd_items, flat.data(), flat.size() * sizeof(QItem));
-  }
+  for (float& v : hdr->infs) v = INFINITY;
+  auto put = [&](size_t off, const auto& v) { if (!v.empty()) std::memcpy(host.data() + off, v.data(), v.size() * sizeof(v[0])); };
+  put(L.off_pairs, x.pairs);
+  std::vector<QItem> flat;
+  q_items(p, x.fwd, x.pairs, &flat, hdr->fwd_begin);
+  if ((int64_t)flat.size() != L.n_fwd_items) { set_error("internal: forward item count mismatch"); return FCP_ERR_INVALID_ARG; }
+  put(L.off_fwd_items, flat);
   if (forward_only) return FCP_OK;
-  // ---- backward: dependency lists per KV block, one group per (KV block, KV head).
+  // ---- dQ: query-stationary items over all pairs of a query segment
+  q_items(p, x.dq, x.pairs, &flat, hdr->dq_begin);
+  if ((int64_t)flat.size() != L.n_dq_items) { set_error("internal: dQ item count mismatch"); return FCP_ERR_INVALID_ARG; }
+  put(L.off_dq_items, flat);
+  // ---- dK / dV: dependency lists per KV segment, one group per (KV segment, KV head)
   {
-    std::vector<int32_t> dep_count(p->n_kv_blocks + 1, 0);
-    for (int i = 0; i < p->n_pairs; i++) dep_count[p->pairs[i].kv_blk + 1]++;
-    for (int b = 0; b < p->n_kv_blocks; b++) dep_count[b + 1] += dep_count[b];
-    std::vector<int32_t> cursor(dep_count.begin(), dep_count.end() - 1);
-    BwdDep* deps = reinterpret_cast<BwdDep*>(host.data() + L.off_bwd_deps);
-    for (int i = 0; i < p->n_pairs; i++) {           // pairs are visited in q order -> deps ascend in q
-      const fcp_block& qb = p->q_blocks[p->pairs[i].q_blk];
-      deps[cursor[p->pairs[i].kv_blk]++] = {qb.tok_start, qb.tok_len, p->pairs[i].kind, dpairs[i].ds_frag};
-    }
-    // The DIAG dependency goes last: the tiles of one KV block then walk the FULL dependencies in
-    // lockstep (identical step sequences, same XCD), so the Q / dO stream they share stays in L2;
-    // they only diverge on the diagonal block, where each tile starts at its own row.
-    for (int b = 0; b < p->n_kv_blocks; b++)
-      std::stable_partition(deps + dep_count[b], deps + dep_count[b + 1],
-                            [](const BwdDep& d) { return !(d.kind & 1); });
+    const int G = p->n_q_heads / p->n_kv_heads;
+    put(L.off_bwd_deps, x.deps);
     std::vector<std::vector<BwdItem>> groups;
     std::vector<int64_t> weight, gkey;
-    groups.reserve((size_t)p->n_kv_blocks * p->n_kv_heads);
-    for (int b = 0; b < p->n_kv_blocks; b++) {
-      const fcp_block& kb = p->kv_blocks[b];
-      const int n_tiles = (int)ceil_div(kb.tok_len, kBwdTileN);
-      const int d0 = dep_count[b], nd = dep_count[b + 1] - dep_count[b];
-      std::vector<int64_t> tile_w(n_tiles, 0);
+    groups.reserve(x.kv.size() * p->n_kv_heads);
+    std::vector<int64_t> tile_w;
+    for (const KvSeg& k : x.kv) {
+      const int n_tiles = (int)ceil_div(k.len, kBwdTileN);
+      tile_w.assign(n_tiles, 0);
       for (int t = 0; t < n_tiles; t++) {
-        const int off = t * kBwdTileN;
-        const int rows = std::min(kBwdTileN, kb.tok_len - off);
-        for (int i = d0; i < d0 + nd; i++) {
-          const int qrows = (deps[i].kind & 1) ? std::max(0, deps[i].q_len - off) : deps[i].q_len;
-          tile_w[t] += (int64_t)rows * qrows * G;
-        }
-      }
-      const int packed_kind = (nd == 1 && (deps[d0].kind & 2)) ? deps[d0].kind : 0;
-      std::vector<int> q_end(n_tiles, 0);
-      if (packed_kind) {
-        // a KV tile serves the dQ items whose columns meet its own: a contiguous run of row tiles, since the members
-        // follow each other; under a causal mask it starts at the tile itself
-        std::vector<int> lo, hi;
-        packed_tile_columns(kb.tok_len, G, q_seg + deps[d0].q_start, (packed_kind & 1) != 0, &lo, &hi);
-        for (int t = 0; t < n_tiles; t++) {
-          const int c0 = t * kBwdTileN, c1 = std::min(kb.tok_len, c0 + kBwdTileN);
-          for (int k = 0; k < (int)lo.size(); k++)
-            if (lo[k] < c1 && hi[k] > c0) q_end[t] = std::min(kb.tok_len, (k + 1) * kFwdTileM);
-          tile_w[t] = (int64_t)(c1 - c0) * std::max(0, q_end[t] - ((packed_kind & 1) ? c0 : 0)) * G;
-        }
+        const int off = t * kBwdTileN, rows = std::min(kBwdTileN, k.len - off);
+        for (int i = k.dep_begin; i < k.dep_begin + k.n_deps; i++)
+          tile_w[t] += (int64_t)rows * G * ((x.deps[i].kind & 1) ? std::max(0, x.deps[i].q_len - off) : x.deps[i].q_len);
       }
       for (int g = 0; g < p->n_kv_heads; g++) {
         std::vector<BwdItem> items;
         int64_t w = 0;
         for (int t = 0; t < n_tiles; t++) {            // earlier tiles of a DIAG pair are heavier
           const int off = t * kBwdTileN;
-          items.push_back({kb.tok_start + off, std::min(kBwdTileN, kb.tok_len - off), off, d0, nd, g, kb.tok_len,
-                           packed_kind, q_end[t], 0});
+          items.push_back({k.start + off, std::min(kBwdTileN, k.len - off), off, k.dep_begin, k.n_deps, g, k.len});
           w += tile_w[t];
         }
         groups.push_back(std::move(items));
         weight.push_back(w);
-        gkey.push_back((int64_t)kb.seq * p->n_kv_heads + g);
+        gkey.push_back((int64_t)k.seq * p->n_kv_heads + g);
       }
     }
     merge_groups_by_key(groups, weight, gkey);
-    std::vector<BwdItem> flat;
-    spread_over_xcds(groups, weight, &flat, hdr->bwd_begin);
-    if ((int64_t)flat.size() != L.n_bwd_items) { set_error("internal: backward item count mismatch"); return FCP_ERR_INVALID_ARG; }
-    if (!flat.empty()) std::memcpy(host.data() + L.off_bwd_items, flat.data(), flat.size() * sizeof(BwdItem));
-  }
-  // ---- backward dQ: query-stationary items over ALL pairs of a query block (its slots are
-  // consecutive, so their pairs form one range); one group per (query block, KV head); items
-  // join two sub-tiles like the forward's.
-  {
-    std::vector<int32_t> pb(p->n_q_blocks, 0), pn(p->n_q_blocks, 0);
-    for (int s = 0; s < p->n_slots; s++) {
-      const fcp_slot& sl = p->slots[s];
-      if (pn[sl.q_blk] == 0) pb[sl.q_blk] = sl.pair_begin;
-      pn[sl.q_blk] += sl.n_pairs;
-    }
-    std::vector<std::vector<QItem>> groups;
-    std::vector<int64_t> weight, gkey;
-    groups.reserve((size_t)p->n_q_blocks * p->n_kv_heads);
-    for (int b = 0; b < p->n_q_blocks; b++) {
-      const fcp_block& qb = p->q_blocks[b];
-      const int n_tiles = (int)ceil_div(qb.tok_len, kFwdTileM);
-      std::vector<int64_t> tile_w(n_tiles, 0);
-      for (int t = 0; t < n_tiles; t++) {
-        const int off = t * kFwdTileM;
-        const int rows = std::min(kFwdTileM, qb.tok_len - off);
-        for (int i = pb[b]; i < pb[b] + pn[b]; i++) {
-          const int cols = (dpairs[i].kind & 1) ? std::min(dpairs[i].kv_len, off + rows) : dpairs[i].kv_len;
-          tile_w[t] += (int64_t)rows * cols;
-        }
-      }
-      const int packed_kind = (pn[b] == 1 && (dpairs[pb[b]].kind & 2)) ? dpairs[pb[b]].kind : 0;
-      auto finish = [&](QItem* it) {
-        if (packed_kind) packed_columns(it, q_seg + qb.tok_start, (packed_kind & 1) != 0);
-        count_tiles(it, dpairs);
-      };
-      auto sub = [&](QItem* it, int k, int t, int head) {
-        const int off = t * kFwdTileM;
-        it->q_start[k] = qb.tok_start + off; it->q_rows[k] = std::min(kFwdTileM, qb.tok_len - off);
-        it->out_row[k] = qb.tok_start + off; it->tile_off[k] = off; it->head[k] = head;
-      };
-      for (int g = 0; g < p->n_kv_heads; g++) {
-        std::vector<QItem> items;
-        int64_t w = 0;
-        if (G % 2 == 0) {
-          for (int t = n_tiles - 1; t >= 0; t--)
-            for (int hh = 0; hh < G; hh += 2) {
-              QItem it{};
-              it.pair_begin = pb[b]; it.n_pairs = pn[b]; it.q_blk_len = qb.tok_len;
-              sub(&it, 0, t, g * G + hh); sub(&it, 1, t, g * G + hh + 1);
-              finish(&it);
-              items.push_back(it);
-              w += 2 * tile_w[t];
-            }
-        } else {
-          for (int t = n_tiles - 1; t >= 0; t -= 2)
-            for (int hh = 0; hh < G; hh++) {
-              QItem it{};
-              it.pair_begin = pb[b]; it.n_pairs = pn[b]; it.q_blk_len = qb.tok_len;
-              sub(&it, 0, t, g * G + hh);
-              if (t >= 1) { sub(&it, 1, t - 1, g * G + hh); w += tile_w[t - 1]; }
-              else { it.q_start[1] = it.q_start[0]; it.q_rows[1] = 0; it.out_row[1] = it.out_row[0]; it.tile_off[1] = it.tile_off[0]; it.head[1] = it.head[0]; }
-              finish(&it);
-              items.push_back(it);
-              w += tile_w[t];
-            }
-        }
-        groups.push_back(std::move(items));
-        weight.push_back(w);
-        gkey.push_back((int64_t)qb.seq * p->n_kv_heads + g);
-      }
-    }
-    merge_groups_by_key(groups, weight, gkey);
-    std::vector<QItem> flat;
-    spread_over_xcds(groups, weight, &flat, hdr->dq_begin);
-    if ((int64_t)flat.size() != L.n_dq_items) { set_error("internal: dQ item count mismatch"); return FCP_ERR_INVALID_ARG; }
-    if (!flat.empty()) std::memcpy(host.data() + L.off_dq_items, flat.data(), flat.size() * sizeof(QItem));
+    std::vector<BwdItem> bwd;
+    spread_over_xcds(groups, weight, &bwd, hdr->bwd_begin);
+    if ((int64_t)bwd.size() != L.n_bwd_items) { set_error("internal: backward item count mismatch"); return FCP_ERR_INVALID_ARG; }
+    put(L.off_bwd_items, bwd);
   }
   // ---- merge: row-head chunks per query block; slots of a query block are consecutive.
   {
@@ -949,8 +817,10 @@ int fcp::build_queue_image(const fcp_problem* p, const WsLayout& L, bool forward
 extern "C" int fcp_queue_build(const fcp_problem* p, void* workspace, size_t workspace_bytes, void* stream) {
   int rc = validate_problem(p);
   if (rc) return rc;
+  Expanded x;
+  expand_problem(p, &x);
   WsLayout L;
-  rc = compute_layout(p, &L);
+  rc = compute_layout(p, x, &L);
   if (rc) return rc;
   if (!workspace || ((uintptr_t)workspace & 255)) {
     set_error("fcp_queue_build: workspace is NULL or not 256-byte aligned"); return FCP_ERR_INVALID_ARG;
@@ -960,7 +830,7 @@ extern "C" int fcp_queue_build(const fcp_problem* p, void* workspace, size_t wor
     return FCP_ERR_BUFFER_TOO_SMALL;
   }
   std::vector<unsigned char> host;
-  rc = build_queue_image(p, L, false, &host);
+  rc = build_queue_image(p, x, L, false, &host);
   if (rc) return rc;
   hipError_t e = hipMemcpyAsync(workspace, host.data(), host.size(), hipMemcpyHostToDevice, (hipStream_t)stream);
   if (e == hipSuccess) e = hipStreamSynchronize((hipStream_t)stream);

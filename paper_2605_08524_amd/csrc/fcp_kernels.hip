@@ -267,14 +267,12 @@ struct FwdArgs {
   void* o; float* lse; int32_t o_is_f32;     // final outputs for query blocks with a single slot (or NULL)
   int32_t running;                            // fold every slot into the running (o, lse) in place (fp32 o)
   WsHeader* hdr; const DevPair* pairs; const QItem* items;
-  int32_t* counter; const int32_t* begin; int32_t* done;   // the XCD queues this launch drains (header fields)
-  const uint32_t* q_seg;                      // member bounds per Q-buffer row (packed blocks only)
   int32_t n_q_heads, n_kv_heads;
   float scale_log2;   // softmax scale * log2(e)
 };
 
 // Iterator over the KV tiles of an item's pairs, in pair order.  For a DIAG pair only the
-// columns up to the tile's last query row are visited, for a PACKED pair the item's column range.
+// columns up to the tile's last query row are visited.
 struct TileIter {
   const DevPair* pairs;
   int pair, pair_end, c0, ncols, row_hi;   // row_hi = tile_off + q_rows (first row past the tile)
@@ -294,8 +292,6 @@ struct TileIter {
     cur = DevPair{0, 0, 0, 0};
     more = it.n_pairs > 0;
     if (more) load_pair();
-    // a PACKED pair is the only pair of its item: the item's column range replaces the pair's, here and nowhere else
-    if (it.col_end > 0) { c0 = it.col_begin; ncols = it.col_end; }
   }
   __device__ __forceinline__ void advance() {
     c0 += kFwdTileN;
@@ -311,10 +307,7 @@ struct TileIter {
 // A tile past the end of the item has len = 0: everything is masked.
 struct TileMeta { int c0, len, kind; };
 
-// PACKED: the instance for the items of packed blocks (several short sequences in one block), which have queues of
-// their own and a launch of their own; only it carries the per-row member bounds and the second mask, which cost
-// the other instance 4 % when they were compiled into it.
-template <int D, bool PACKED>
+template <int D>
 __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
   constexpr int KC = D / 16;      // k-chunks of the QK^T contraction
   constexpr int DT = D / 32;      // row tiles of O^T
@@ -327,7 +320,6 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
   constexpr int CPR = D / 8, RPI = 64 / CPR, NDMA = kFwdTileN / RPI / 8;   // LDS-DMA geometry, see issue()
   constexpr int DMA_PER_TILE = 2 * NDMA;
   __shared__ __attribute__((aligned(1024))) unsigned char lds_kv[NB][BUF];
-  __shared__ uint32_t s_seg[512];   // member bounds of each lane's query row in a packed block (written and read by that lane)
   __shared__ int s_item;
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -368,7 +360,7 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
   __syncthreads();
 
   ItemStream items;
-  if (tid == 0) { items.init(a.counter, a.begin); items.request(); s_item = items.resolve(); }
+  if (tid == 0) { items.init(a.hdr->fwd_counter, a.hdr->fwd_begin); items.request(); s_item = items.resolve(); }
   __syncthreads();
   for (;;) {
     const int item_idx = __builtin_amdgcn_readfirstlane(s_item);   // uniform: tables are read with scalar loads
@@ -384,10 +376,6 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
     const int my_limit = tile_off_q + my_row;                // last visible column of a DIAG pair for this lane
     const uint16_t* kbase = a.k + (int64_t)kvh * D;
     const uint16_t* vbase = a.v + (int64_t)kvh * D;
-    // packed block: the columns this lane's row may see, parked in LDS until a tile is masked (rows past the end: none)
-    if constexpr (PACKED) {
-      if (it.col_end > 0) s_seg[tid] = row_ok ? a.q_seg[(sub ? it.q_start[1] : it.q_start[0]) + my_row] : 0u;
-    }
 
     // Q^T fragments (B operand of S^T = K Q^T): lane = query row, 8 consecutive d per k-chunk.
     bf16x8 qf[KC];
@@ -535,29 +523,15 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
         // readfirstlane: the condition is wave-uniform, but the compiler does not know it and would
         // otherwise run the rare path on every tile as 64 compares and selects
         const int need_mask = __builtin_amdgcn_readfirstlane(
-            (int)(tm.len == 0 || tm.c0 + kFwdTileN > tm.len || (PACKED && (tm.kind & 2)) || ((tm.kind & 1) && tm.c0 + kFwdTileN - 1 > wave_row_lo)));
+            (int)(tm.len == 0 || tm.c0 + kFwdTileN > tm.len || ((tm.kind & 1) && tm.c0 + kFwdTileN - 1 > wave_row_lo)));
         if (need_mask) {
-          if (PACKED && __builtin_amdgcn_readfirstlane(tm.kind & 2)) {
-            // packed block: the row sees the columns of its own member (up to itself under a causal mask)
-            const uint32_t sg = s_seg[tid];
-            const int first = (int)(sg & 0xffff) - tm.c0 - 4 * g;
-            const int last = ((tm.kind & 1) ? min((int)(sg >> 16) - 1, my_limit) : (int)(sg >> 16) - 1) - tm.c0 - 4 * g;
+          // last visible column for this lane, relative to the tile's first column
+          const int limit = ((tm.kind & 1) ? min(tm.len - 1, my_limit) : tm.len - 1) - tm.c0 - 4 * g;
 #pragma unroll
-            for (int rt = 0; rt < 2; rt++)
+          for (int rt = 0; rt < 2; rt++)
 #pragma unroll
-              for (int r = 0; r < 16; r++) {
-                const int c = rt * 32 + 8 * (r >> 2) + (r & 3);
-                if (c > last || c < first) sn[rt][r] = -INFINITY;
-              }
-          } else {
-            // last visible column for this lane, relative to the tile's first column
-            const int limit = ((tm.kind & 1) ? min(tm.len - 1, my_limit) : tm.len - 1) - tm.c0 - 4 * g;
-#pragma unroll
-            for (int rt = 0; rt < 2; rt++)
-#pragma unroll
-              for (int r = 0; r < 16; r++)
-                if (rt * 32 + 8 * (r >> 2) + (r & 3) > limit) sn[rt][r] = -INFINITY;
-          }
+            for (int r = 0; r < 16; r++)
+              if (rt * 32 + 8 * (r >> 2) + (r & 3) > limit) sn[rt][r] = -INFINITY;
         }
       }
       if constexpr (!LAST) {
@@ -670,7 +644,7 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
     if (tid == 0) s_item = items.resolve();
     __syncthreads();
   }
-  if (tid == 0) retire(a.counter, a.done);
+  if (tid == 0) retire(a.hdr->fwd_counter, &a.hdr->fwd_done);
 }
 
 // =====================================================================================
@@ -880,41 +854,38 @@ struct BwdArgs {
   void* dq; void* dk; void* dv;    // fp32, or bf16 in the GRAD_BF16 instances of the kernels
   unsigned char* ds;               // dS spill buffer (2 KB fragments), or NULL
   WsHeader* hdr; const DevPair* pairs; const BwdDep* deps; const BwdItem* items; const QItem* dq_items;
-  const uint32_t* q_seg; const uint32_t* kv_seg;   // member bounds per Q-buffer row / KV-buffer row (packed blocks only)
   int64_t t_q;
   int32_t n_q_heads, n_kv_heads;
   float scale, scale_log2;
 };
 
 // Iterator over the 32-row query steps of a backward item: rows, then the G query heads of
-// the group, then the dependent query blocks.  A DIAG (or PACKED_DIAG) dependency starts at the tile's own rows.
+// the group, then the dependent query blocks.  A DIAG dependency starts at the tile's own rows.
 struct StepIter {
   const BwdDep* deps;
-  int dep, n_deps, hh, group, q0, first_diag, q_stop;   // q_stop: first row past the rows to walk in the current dependency
+  int dep, n_deps, hh, group, q0, first_diag;
   BwdDep cur;
   bool more;
   __device__ __forceinline__ int first_q0() const { return (cur.kind & 1) ? first_diag : 0; }
-  // packed_q_end: of an item of a packed block (whose one dependency is walked up to that row only), else 0
-  __device__ __forceinline__ void init(const BwdDep* d, int n, int group_, int tile_off, int packed_q_end) {
-    deps = d; dep = 0; n_deps = n; hh = 0; group = group_; first_diag = tile_off & ~31; q0 = 0; q_stop = 0;
+  __device__ __forceinline__ void init(const BwdDep* d, int n, int group_, int tile_off) {
+    deps = d; dep = 0; n_deps = n; hh = 0; group = group_; first_diag = tile_off & ~31; q0 = 0;
     cur = BwdDep{0, 0, 0, 0};
     more = n > 0;
     if (more) {
       cur = deps[0]; q0 = first_q0();
-      q_stop = packed_q_end > 0 ? packed_q_end : cur.q_len;
-      more = q0 < q_stop;
+      more = q0 < cur.q_len;
     }
   }
   __device__ __forceinline__ void advance() {
     q0 += 32;
-    if (q0 >= q_stop) {
+    if (q0 >= cur.q_len) {
       hh++;
       if (hh < group) {
         q0 = first_q0();
       } else {
         hh = 0;
         dep++;
-        if (dep < n_deps) { cur = deps[dep]; q0 = first_q0(); q_stop = cur.q_len; } else { more = false; }
+        if (dep < n_deps) { cur = deps[dep]; q0 = first_q0(); } else { more = false; }
       }
     }
   }
@@ -938,7 +909,6 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
   __shared__ __attribute__((aligned(1024))) unsigned char lds_t[NB][BUF];
   __shared__ __attribute__((aligned(1024))) unsigned char lds_h[2][4][4096];   // [parity][KV sub-tile][operand][lane] 16 B
   __shared__ __attribute__((aligned(256))) float lds_sc[NB][64];   // [LSE*log2e x 32 | D*scale x 32]
-  __shared__ int s_khi[256];        // packed block: first query row past the member of each producer lane's KV row, minus 4g
   __shared__ int s_item;
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -981,12 +951,11 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
     for (int d = 0; d < it.n_deps; d++) {
       const BwdDep dd = a.deps[it.dep_begin + d];
       const int first = (dd.kind & 1) ? (it.tile_off & ~31) : 0;
-      const int stop = it.packed ? it.q_end : dd.q_len;
-      n_iv += group * (max(0, stop - first + 31) / 32);
+      n_iv += group * (max(0, dd.q_len - first + 31) / 32);
     }
     n_iv = (n_iv + 1) & ~1;
     StepIter si;
-    si.init(a.deps + it.dep_begin, it.n_deps, group, it.tile_off, it.packed ? it.q_end : 0);
+    si.init(a.deps + it.dep_begin, it.n_deps, group, it.tile_off);
 
     if (consumer) {
       // =============================== consumer ===============================
@@ -1135,14 +1104,6 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
     } else {
       // =============================== producer ===============================
       int kvg = it.tile_off + my_kv - 4 * g;       // masked iff kvg > q0 + 8*(r/4) + r%4 on a DIAG step
-      if (it.packed) {
-        // Packed block: a KV row is seen by the query rows of its own member only, [first, last + 1) inside the
-        // block: kvg becomes that first row under a full mask (under a causal one it is the row itself, as
-        // above), and the bound past the last row waits in LDS for the masked intervals.
-        const uint32_t sg = kv_ok ? a.kv_seg[it.kv_start + my_kv] : 0u;
-        if (!(it.packed & 1)) kvg = (int)(sg & 0xffff) - 4 * g;
-        s_khi[tid] = (int)(sg >> 16) - 4 * g;
-      }
       // SPILL: the dS this wave forms also goes to memory, one 2 KB fragment per step, for the dQ pass.  There a
       // KV row past the ragged end of the tile must carry dS = 0 (here its column of dK^T / dV^T is simply never
       // stored): such lanes get a threshold nothing passes, and a ragged tile runs every step through the masked
@@ -1190,10 +1151,8 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
 
       // One interval: MFMAs of A(i+2) into (sn, dpn); B(i+1) on (sc, dpc) between them.
       auto interval = [&](auto masked, f32x16& sc, f32x16& dpc, f32x16& sn, f32x16& dpn) {
-        constexpr int MASK = decltype(masked)::value;     // 0: no mask, 1: diagonal / ragged end, 2: packed block
+        constexpr bool MASK = decltype(masked)::value;    // diagonal / ragged end
         const int thr_s = __builtin_amdgcn_readfirstlane(thr_t);
-        int hlim = 0;                                     // packed: rows 8*(r/4) + r%4 >= hlim of the step are past the member
-        if constexpr (MASK == 2) hlim = s_khi[tid] - thr_s;
         f32x4 lse_c = lse_n, dl_c = dl_n;      // scalars of rows 8*q4 + 4g .. +3, one group of four ahead
         uint32_t pk[16];           // [0..7] P pairs, [8..15] dS pairs: four B operands for the consumer
         float p_prev = 0.f, ds_prev = 0.f;
@@ -1245,8 +1204,7 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
               p_ahead = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[r + 1], a.scale_log2, -lse_q));
             }
             const float dl_r = dl_c[r & 3];
-            if constexpr (MASK == 1) p = (kvg > thr_s + 8 * (r >> 2) + (r & 3)) ? 0.f : p;
-            if constexpr (MASK == 2) p = (kvg > thr_s + 8 * (r >> 2) + (r & 3) || 8 * (r >> 2) + (r & 3) >= hlim) ? 0.f : p;
+            if constexpr (MASK) p = (kvg > thr_s + 8 * (r >> 2) + (r & 3)) ? 0.f : p;
             const float ds = p * __builtin_fmaf(dpc[r], a.scale, -dl_r);
             if (r & 1) {
               pk[r >> 1] = pack_bf16(p_prev, p); pk[8 + (r >> 1)] = pack_bf16(ds_prev, ds);
@@ -1293,20 +1251,11 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
         hb ^= 1;
       };
       // the first interval handles B(-1) (nothing) and A(0), the second B(0) and A(1), ...
-      const std::integral_constant<int, 0> no_mask;
-      const std::integral_constant<int, 1> with_mask;
-      const std::integral_constant<int, 2> packed_mask;
-      if (it.packed) {
-        // every step masked by member; outside the item's steps thr_t names no row at all, which masks everything
-        for (int iv = 0; iv < n_iv; iv += 2) {
-          interval(packed_mask, s_a, dp_a, s_b, dp_b);
-          interval(packed_mask, s_b, dp_b, s_a, dp_a);
-        }
-      } else {
-        for (int iv = 0; iv < n_iv; iv += 2) {
-          if (thr_t != kNoMask) interval(with_mask, s_a, dp_a, s_b, dp_b); else interval(no_mask, s_a, dp_a, s_b, dp_b);
-          if (thr_t != kNoMask) interval(with_mask, s_b, dp_b, s_a, dp_a); else interval(no_mask, s_b, dp_b, s_a, dp_a);
-        }
+      const std::false_type no_mask;
+      const std::true_type with_mask;
+      for (int iv = 0; iv < n_iv; iv += 2) {
+        if (thr_t != kNoMask) interval(with_mask, s_a, dp_a, s_b, dp_b); else interval(no_mask, s_a, dp_a, s_b, dp_b);
+        if (thr_t != kNoMask) interval(with_mask, s_b, dp_b, s_a, dp_a); else interval(no_mask, s_b, dp_b, s_a, dp_a);
       }
     }
     __syncthreads();
@@ -1324,15 +1273,12 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
 // Columns past the diagonal or past a ragged end get P = 0.  Every dQ row has one writer: plain
 // stores, deterministic.
 // =====================================================================================
-// PACKED: the problem has packed blocks; only that instance carries the per-row member bounds (as in the forward).
-// It exists without WITH_D only: on such a problem the launcher runs the stand-alone D pass first.
-template <int D, bool WITH_D, bool GRAD_BF16, bool PACKED = false>
+template <int D, bool WITH_D, bool GRAD_BF16>
 __global__ void __launch_bounds__(512, 2) dq_kernel(BwdArgs a) {
   constexpr int KC = D / 16;
   constexpr int DT = D / 32;
   constexpr int TB = tile_bytes<D>(kFwdTileN);
   __shared__ __attribute__((aligned(1024))) unsigned char lds_kv[2][2 * TB];   // [buffer][K tile | V tile]
-  __shared__ uint32_t s_seg[512];   // member bounds of each lane's query row in a packed block (written and read by that lane)
   __shared__ int s_item;
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -1379,9 +1325,6 @@ __global__ void __launch_bounds__(512, 2) dq_kernel(BwdArgs a) {
     const int wave_row_lo = tile_off_q + wq * 32;
     const uint16_t* kbase = a.k + (int64_t)kvh * D;
     const uint16_t* vbase = a.v + (int64_t)kvh * D;
-    if constexpr (PACKED) {
-      if (it.col_end > 0) s_seg[tid] = row_ok ? a.q_seg[q_start + my_row] : 0u;   // packed block: visible columns of the row
-    }
 
     bf16x8 qf[KC], dof[KC];
     float lse_l = INFINITY, dl_l = 0.f;     // rows past the end: P = exp2(-inf) = 0
@@ -1472,7 +1415,7 @@ __global__ void __launch_bounds__(512, 2) dq_kernel(BwdArgs a) {
       }
     };
     DevPair tp = ti.cur;
-    int tc0 = ti.c0;       // not always 0: an item of a packed block starts at its own first column
+    int tc0 = 0;
     bool have = ti.more;
     if (have) { dma(buf); ti.advance(); }
     dma_wait();
@@ -1483,19 +1426,13 @@ __global__ void __launch_bounds__(512, 2) dq_kernel(BwdArgs a) {
       const bool nhave = ti.more;
       if (nhave) { dma(buf ^ 1); ti.advance(); }
 
-      const bool diag = (tp.kind & 1) != 0, packed = PACKED && (tp.kind & 2) != 0;
+      const bool diag = (tp.kind & 1) != 0;
       if (!(diag && tc0 > wave_row_lo + 31)) {      // else nothing visible for this wave
         // wave-uniform: tiles that straddle the diagonal, and tiles that hold a ragged end (their K rows past
         // the end are zero in LDS, but S = 0 there still gives P = exp2(-LSE), which overflows for a row whose
         // logits are all strongly negative; inf * 0 would then poison the whole dQ row)
-        const bool need_mask = packed || (diag && tc0 + kFwdTileN - 1 > wave_row_lo) || tc0 + kFwdTileN > tp.kv_len;
-        int limit = diag ? tile_off_q + my_row : tp.kv_len - 1;      // last visible column for this lane
-        int first = 0;                                               // first one (a packed block: the row's own member)
-        if (packed) {
-          const uint32_t sg = s_seg[tid];
-          first = (int)(sg & 0xffff);
-          limit = min(limit, (int)(sg >> 16) - 1);
-        }
+        const bool need_mask = (diag && tc0 + kFwdTileN - 1 > wave_row_lo) || tc0 + kFwdTileN > tp.kv_len;
+        const int limit = diag ? tile_off_q + my_row : tp.kv_len - 1;      // last visible column for this lane
         // the two 32-row halves of the KV tile one after the other: half the live accumulators
 #pragma unroll
         for (int rt = 0; rt < 2; rt++) {
@@ -1527,7 +1464,7 @@ __global__ void __launch_bounds__(512, 2) dq_kernel(BwdArgs a) {
 #pragma unroll
             for (int r = 0; r < 16; r++) {
               const int c = tc0 + rt * 32 + 8 * (r >> 2) + 4 * g + (r & 3);
-              if (c > limit || c < first) s[r] = 0.f;
+              if (c > limit) s[r] = 0.f;
             }
           }
 #pragma unroll
@@ -1846,24 +1783,11 @@ static int launch_fwd(const char* who, const fcp_problem* p, const void* q, cons
   a.hdr = reinterpret_cast<WsHeader*>(ws);
   a.pairs = reinterpret_cast<const DevPair*>(ws + L.off_pairs);
   a.items = reinterpret_cast<const QItem*>(ws + L.off_fwd_items);
-  a.q_seg = reinterpret_cast<const uint32_t*>(ws + L.off_q_seg);
   a.n_q_heads = p->n_q_heads; a.n_kv_heads = p->n_kv_heads;
   a.scale_log2 = resolve_scale(p) * kLog2e;
-  // two launches: the items of ordinary blocks, then (if any) those of packed blocks through the instance for them;
-  // they write different rows, and the stream keeps them in order
-  const int64_t n_plain = L.n_fwd_items - L.n_fwd_packed_items;
-  if (n_plain > 0) {
-    a.counter = a.hdr->fwd_counter; a.begin = a.hdr->fwd_begin; a.done = &a.hdr->fwd_done;
-    const int grid = (int)std::min<int64_t>(n_plain, (int64_t)cu_count() * kFwdWgPerCu);
-    if (p->head_dim == 128) hipLaunchKernelGGL((fwd_kernel<128, false>), dim3(grid), dim3(512), 0, (hipStream_t)stream, a);
-    else hipLaunchKernelGGL((fwd_kernel<64, false>), dim3(grid), dim3(512), 0, (hipStream_t)stream, a);
-  }
-  if (L.n_fwd_packed_items > 0) {
-    a.counter = a.hdr->fwdp_counter; a.begin = a.hdr->fwdp_begin; a.done = &a.hdr->fwdp_done;
-    const int grid = (int)std::min<int64_t>(L.n_fwd_packed_items, (int64_t)cu_count() * kFwdWgPerCu);
-    if (p->head_dim == 128) hipLaunchKernelGGL((fwd_kernel<128, true>), dim3(grid), dim3(512), 0, (hipStream_t)stream, a);
-    else hipLaunchKernelGGL((fwd_kernel<64, true>), dim3(grid), dim3(512), 0, (hipStream_t)stream, a);
-  }
+  const int grid = (int)std::min<int64_t>(L.n_fwd_items, (int64_t)cu_count() * kFwdWgPerCu);
+  if (p->head_dim == 128) hipLaunchKernelGGL(fwd_kernel<128>, dim3(grid), dim3(512), 0, (hipStream_t)stream, a);
+  else hipLaunchKernelGGL(fwd_kernel<64>, dim3(grid), dim3(512), 0, (hipStream_t)stream, a);
   return check_launch(who);
 }
 
@@ -1907,8 +1831,10 @@ extern "C" int fcp_block_attn_fwd_static(const fcp_problem* p, const void* q, co
     set_error("fcp_block_attn_fwd_static: FCP_FLAG_DIRECT_SINGLE is not supported here (all slots go to the partial buffers)");
     return FCP_ERR_INVALID_ARG;
   }
+  Expanded x;
+  expand_problem(p, &x);
   WsLayout L;
-  rc = compute_layout(p, &L);
+  rc = compute_layout(p, x, &L);
   if (rc) return rc;
   if (L.off_bwd_deps > kStaticScratchBytes) {
     set_error("fcp_block_attn_fwd_static: the forward's queue tables need %zu bytes, the fixed scratch array holds %zu "
@@ -1923,7 +1849,7 @@ extern "C" int fcp_block_attn_fwd_static(const fcp_problem* p, const void* q, co
   // zeroed counters, resolved pairs, forward items.  Host memory only; one copy; the copy is waited for
   // because its source dies with this frame.
   std::vector<unsigned char> image;
-  rc = build_queue_image(p, L, true, &image);
+  rc = build_queue_image(p, x, L, true, &image);
   if (rc) return rc;
   hipError_t e = hipMemcpyAsync(ws, image.data(), image.size(), hipMemcpyHostToDevice, (hipStream_t)stream);
   if (e == hipSuccess) e = hipStreamSynchronize((hipStream_t)stream);
@@ -1987,8 +1913,6 @@ static int fill_bwd_args(const fcp_problem* p, WsLayout* L, BwdArgs* a, void* wo
   a->deps = reinterpret_cast<const BwdDep*>(ws + L->off_bwd_deps);
   a->items = reinterpret_cast<const BwdItem*>(ws + L->off_bwd_items);
   a->dq_items = reinterpret_cast<const QItem*>(ws + L->off_dq_items);
-  a->q_seg = reinterpret_cast<const uint32_t*>(ws + L->off_q_seg);
-  a->kv_seg = reinterpret_cast<const uint32_t*>(ws + L->off_kv_seg);
   a->n_q_heads = p->n_q_heads; a->n_kv_heads = p->n_kv_heads;
   a->scale = resolve_scale(p); a->scale_log2 = a->scale * kLog2e;
   a->dq = nullptr; a->dk = nullptr; a->dv = nullptr;
@@ -2031,18 +1955,7 @@ static int launch_dq(const char* who, const fcp_problem* p, const void* q, const
   a.q = (const uint16_t*)q; a.k = (const uint16_t*)k; a.v = (const uint16_t*)v; a.d_o = (const uint16_t*)d_o;
   a.dq = dq;
   const int grid = (int)std::min<int64_t>(L.n_dq_items, (int64_t)cu_count() * kDqWgPerCu);
-  const bool gb = (p->flags & FCP_FLAG_GRAD_BF16) != 0, d128 = p->head_dim == 128, packed = p->n_segments > 0;
-  if (packed) {
-    // the kernel instance for packed blocks reads D and LSE from the workspace: run the D pass here if the caller has not
-    if (o) {
-      rc = fcp_bwd_preprocess(p, o, lse, d_o, workspace, stream);
-      if (rc) return rc;
-    }
-    void (*kern)(BwdArgs) = d128 ? (gb ? dq_kernel<128, false, true, true> : dq_kernel<128, false, false, true>)
-                                 : (gb ? dq_kernel<64, false, true, true> : dq_kernel<64, false, false, true>);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(512), 0, (hipStream_t)stream, a);
-    return check_launch(who);
-  }
+  const bool gb = (p->flags & FCP_FLAG_GRAD_BF16) != 0, d128 = p->head_dim == 128;
   const bool with_d = o != nullptr;
   if (with_d) {
     unsigned char* ws = static_cast<unsigned char*>(workspace);
