@@ -182,13 +182,13 @@ void expand_problem(const fcp_problem* p, Expanded* x) {
       const int32_t q0 = qb.tok_start + off, p0 = (int32_t)x->pairs.size();
       for (int s = s0; s < s1; s++) {
         const fcp_slot& sl = p->slots[s];
-        x->fwd.push_back({q0, len, sl.row_start + off, (int32_t)x->pairs.size(), sl.n_pairs, seq, to_final});
+        x->fwd.push_back({q0, len, sl.row_start + off, (int32_t)x->pairs.size(), sl.n_pairs, seq, to_final, s - s0});
         for (int i = sl.pair_begin; i < sl.pair_begin + sl.n_pairs; i++) {
           const fcp_pair& pr = p->pairs[i];
           add_pair(q0, len, kv_seg_of[pr.kv_blk] + ((pr.kind & 2) ? m : 0), pr.kind & 1);
         }
       }
-      x->dq.push_back({q0, len, q0, p0, (int32_t)x->pairs.size() - p0, seq, 0});
+      x->dq.push_back({q0, len, q0, p0, (int32_t)x->pairs.size() - p0, seq, 0, 0});
     }
   }
   x->n_ds_frags = frag;
@@ -326,20 +326,20 @@ void count_tiles(QItem* it, const std::vector<DevPair>& pairs) {
   it->diag_last = it->n_pairs > 0 && (pairs[it->pair_begin + it->n_pairs - 1].kind & 1);
 }
 
-// XCD affinity: groups with the same key (sequence, KV head) become one group (items concatenated in the order the
-// groups came), so that all work that streams the K / V (forward, dQ) or Q / dO (dK/dV) rows of one sequence and KV
-// head runs on one XCD and finds them in that XCD's L2 (measured on the training step: forward -1.2 %, dK/dV -0.6 %,
-// dQ from dS -2 %).  Only done while the largest merged group stays below three quarters of an XCD's fair share:
-// a batch dominated by one sequence keeps the finer groups, which balance better.
+// XCD affinity: groups whose keys agree after division by `div` become one group (items concatenated in the order the
+// groups came; the keys are divided).  With a key per (sequence, KV head) all work that streams the K / V (forward, dQ)
+// or Q / dO (dK/dV) rows of one sequence and KV head runs on one XCD and finds them in that XCD's L2 (measured on the
+// training step: forward -1.2 %, dK/dV -0.6 %, dQ from dS -2 %).  Only done while the largest merged group stays below
+// three quarters of an XCD's fair share: a batch dominated by one sequence keeps the finer groups, which balance better.
 template <class Item>
-void merge_groups_by_key(std::vector<std::vector<Item>>& groups, std::vector<int64_t>& weight, const std::vector<int64_t>& key) {
+void merge_groups_by_key(std::vector<std::vector<Item>>& groups, std::vector<int64_t>& weight, std::vector<int64_t>& key, int64_t div) {
   std::unordered_map<int64_t, size_t> where;      // key -> merged group, in order of first appearance
   std::vector<size_t> to(groups.size());
-  std::vector<int64_t> w2;
+  std::vector<int64_t> w2, key2;
   int64_t total = 0, largest = 0;
   for (size_t i = 0; i < groups.size(); i++) {
-    to[i] = where.emplace(key[i], w2.size()).first->second;
-    if (to[i] == w2.size()) w2.push_back(0);
+    to[i] = where.emplace(key[i] / div, w2.size()).first->second;
+    if (to[i] == w2.size()) { w2.push_back(0); key2.push_back(key[i] / div); }
     w2[to[i]] += weight[i];
     total += weight[i];
     largest = std::max(largest, w2[to[i]]);
@@ -347,7 +347,7 @@ void merge_groups_by_key(std::vector<std::vector<Item>>& groups, std::vector<int
   if (largest * kNumXcd * 4 > total * 3) return;
   std::vector<std::vector<Item>> g2(w2.size());
   for (size_t i = 0; i < groups.size(); i++) g2[to[i]].insert(g2[to[i]].end(), groups[i].begin(), groups[i].end());
-  groups.swap(g2); weight.swap(w2);
+  groups.swap(g2); weight.swap(w2); key.swap(key2);
 }
 
 // Longest-processing-time assignment of weighted groups to the XCD queues: groups in
@@ -386,6 +386,8 @@ void q_items(const fcp_problem* p, const std::vector<QSeg>& segs, const std::vec
   std::vector<int64_t> weight, gkey;
   groups.reserve(segs.size() * p->n_kv_heads);
   std::vector<int64_t> tile_w;
+  int64_t n_ord = 1;
+  for (const QSeg& sg : segs) n_ord = std::max<int64_t>(n_ord, sg.ordinal + 1);
   for (const QSeg& sg : segs) {
     const int n_tiles = (int)ceil_div(sg.len, kFwdTileM);
     tile_w.assign(n_tiles, 0);
@@ -422,10 +424,15 @@ void q_items(const fcp_problem* p, const std::vector<QSeg>& segs, const std::vec
       }
       groups.push_back(std::move(items));
       weight.push_back(w);
-      gkey.push_back((int64_t)sg.seq * p->n_kv_heads + g);
+      gkey.push_back(((int64_t)sg.seq * p->n_kv_heads + g) * n_ord + sg.ordinal);
     }
   }
-  merge_groups_by_key(groups, weight, gkey);
+  // First the slots that cover the same KV range of a sequence (the r-th slot of each of its query blocks), then the
+  // whole sequence: the workgroups of an XCD then walk one KV range at a time, which stays in that XCD's L2, instead of
+  // as many ranges as a query block has slots (forward of 13000 rows at the end of a 200000-token sequence, 16 KV heads, slots of 4096
+  // columns, plus 118000 tokens of short sequences: 11.2 -> 9.7 ms).
+  merge_groups_by_key(groups, weight, gkey, 1);
+  merge_groups_by_key(groups, weight, gkey, n_ord);
   spread_over_xcds(groups, weight, flat, begin);
 }
 
@@ -782,7 +789,7 @@ int fcp::build_queue_image(const fcp_problem* p, const Expanded& x, const WsLayo
         gkey.push_back((int64_t)k.seq * p->n_kv_heads + g);
       }
     }
-    merge_groups_by_key(groups, weight, gkey);
+    merge_groups_by_key(groups, weight, gkey, 1);
     std::vector<BwdItem> bwd;
     spread_over_xcds(groups, weight, &bwd, hdr->bwd_begin);
     if ((int64_t)bwd.size() != L.n_bwd_items) { set_error("internal: backward item count mismatch"); return FCP_ERR_INVALID_ARG; }

@@ -74,8 +74,8 @@ struct WsLayout {
 };
 
 // The problem as the kernels see it.  Segment = rows that share a pair list: a query block (KV block), or one member of
-// a packed one.
-struct QSeg { int32_t start, len, out_row, pair_begin, n_pairs, seq, to_final; };   // rows in the Q buffer / partial buffers
+// a packed one.  ordinal: which slot of its query block a forward segment is (0 for dQ).
+struct QSeg { int32_t start, len, out_row, pair_begin, n_pairs, seq, to_final, ordinal; };   // rows in the Q buffer / partial buffers
 struct KvSeg { int32_t start, len, seq, dep_begin, n_deps; };
 struct Expanded {
   std::vector<DevPair> pairs;
