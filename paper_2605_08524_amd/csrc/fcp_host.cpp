@@ -323,6 +323,7 @@ void count_tiles(QItem* it, const std::vector<DevPair>& pairs) {
     n += (nc + kQTileN - 1) / kQTileN;
   }
   it->n_tiles = n;
+  if (it->n_pairs > 0) it->first = pairs[it->pair_begin];
   it->diag_last = it->n_pairs > 0 && (pairs[it->pair_begin + it->n_pairs - 1].kind & 1);
 }
 

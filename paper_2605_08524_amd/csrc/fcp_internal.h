@@ -28,8 +28,9 @@ struct DevPair { int32_t kv_start, kv_len, kind, ds_frag; };
 // to_final != 0 (forward items only): the slot is the only one of its query block.
 // q_blk_len (dQ items only): rows of the whole query block (of the member, in a packed block).
 // n_tiles: 64-row KV tiles the item walks (a DIAG pair only up to the item's last query row).
+// first: the first of its pairs (in the record, so that an item's first tile needs no second table read).
 // diag_last: the last pair is DIAG (a wave whose rows end early need not compute the tiles past them).
-struct QItem { int32_t q_start[2], q_rows[2], out_row[2], tile_off[2], head[2], pair_begin, n_pairs, to_final, q_blk_len, n_tiles, diag_last; };
+struct QItem { int32_t q_start[2], q_rows[2], out_row[2], tile_off[2], head[2], pair_begin, n_pairs, to_final, q_blk_len, n_tiles, diag_last; DevPair first; };
 constexpr int kQTileN = 64;         // KV rows per LDS tile of the query-stationary kernels
 struct BwdDep  { int32_t q_start, q_len, kind, ds_frag; };
 struct BwdItem { int32_t kv_start, kv_rows, tile_off, dep_begin, n_deps, kv_head, kv_blk_len; };

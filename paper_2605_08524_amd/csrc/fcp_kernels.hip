@@ -188,23 +188,13 @@ __device__ __forceinline__ void tile_dma(unsigned char* lds_tile, const uint16_t
 }
 __device__ __forceinline__ void dma_wait() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0)
 
-template <int D> constexpr int tile_bytes(int rows) { return rows * D * 2; }
-
-// Pop one item index from the eight XCD queues, own queue first, then stealing.  Returns -1
-// when every queue is dry.  Every call terminates: each queue is probed at most once.
-__device__ __forceinline__ int pop_item(int32_t* counter, const int32_t* begin) {
-  // The XCD this workgroup actually runs on: hardware register XCC_ID (id 20), bits [3:0].
-  const int home = __builtin_amdgcn_s_getreg((3 << 11) | 20) & (kNumXcd - 1);
-  for (int t = 0; t < kNumXcd; t++) {
-    const int q = (home + t) % kNumXcd;
-    const int n = begin[q + 1] - begin[q];
-    if (n <= 0) continue;
-    if (__hip_atomic_load(&counter[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= n) continue;
-    const int i = atomicAdd(&counter[q], 1);
-    if (i < n) return begin[q] + i;
-  }
-  return -1;
+// Workgroup barrier that waits for this wave's LDS accesses only (__syncthreads() may also wait for its stores).
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_s_waitcnt(0xC07F);      // lgkmcnt(0)
+  asm volatile("s_barrier" ::: "memory");
 }
+
+template <int D> constexpr int tile_bytes(int rows) { return rows * D * 2; }
 
 // The last workgroup to run dry clears the counters for the next launch.
 __device__ __forceinline__ void retire(int32_t* counter, int32_t* done) {
@@ -215,33 +205,71 @@ __device__ __forceinline__ void retire(int32_t* counter, int32_t* done) {
   }
 }
 
-// The item sequence of one persistent workgroup of a query-stationary kernel.  The index of the NEXT item is
-// requested when the current one starts (one atomic add on the home queue by thread 0, not waited for) and
-// published through LDS when the current one ends, so the round trip to the counter overlaps the item's work
-// instead of sitting between two items.  Once the home queue runs dry the slower pop_item (which also steals
-// from the other queues) takes over; every workgroup leaves the loop when all queues are dry.
+// The item sequence of one persistent workgroup.  Item indices are tickets of the eight XCD queues.  The first ticket of a workgroup is fixed by its block index: the chip hands
+// workgroups to the XCDs in turn, and no counter has to be asked before the first item starts.  The others come from the
+// queue of the XCD the workgroup runs on (hardware register XCC_ID) and, once that is dry, from the other queues.
+// request() asks for a ticket without waiting, take() turns it into an item index some tiles later; both near the end of
+// the current item (early draws unbalance the end of a launch), so that neither round trip is waited for.  Both are for
+// wave 0.  Every workgroup leaves its loop when all queues are dry.
 struct ItemStream {
   int32_t* counter; const int32_t* begin;
-  int home, home_n, home_begin, ticket;
-  bool home_dry;
-  __device__ __forceinline__ void init(int32_t* c, const int32_t* b) {
-    counter = c; begin = b;
-    home = __builtin_amdgcn_s_getreg((3 << 11) | 20) & (kNumXcd - 1);
-    home_begin = b[home]; home_n = b[home + 1] - home_begin;
-    home_dry = home_n <= 0; ticket = 0;
+  int ticket;
+  bool dry;
+  __device__ __forceinline__ static int home_queue() { return __builtin_amdgcn_s_getreg((3 << 11) | 20) & (kNumXcd - 1); }   // XCC_ID (id 20), bits [3:0]
+  __device__ __forceinline__ static int fixed(int q) { return ((int)gridDim.x + kNumXcd - 1 - q) / kNumXcd; }   // tickets of queue q given by block index
+  // the first item, or -1
+  __device__ __forceinline__ int start(int32_t* c, const int32_t* b, int lane) {
+    counter = c; begin = b; ticket = 0; dry = false;
+    const int q = blockIdx.x % kNumXcd, t = blockIdx.x / kNumXcd;
+    const int b0 = begin[q], n = begin[q + 1] - b0;
+    return t < n ? b0 + t : steal(lane);
   }
-  // thread 0 only: ask for the next item (returns at once; the ticket arrives while the item runs)
-  __device__ __forceinline__ void request() { if (!home_dry) ticket = atomicAdd(&counter[home], 1); }
-  // thread 0 only: the item the ticket stands for, or one stolen elsewhere, or -1
-  __device__ __forceinline__ int resolve() {
-    if (!home_dry) {
-      if (ticket < home_n) return home_begin + ticket;
-      home_dry = true;
+  __device__ __forceinline__ void request(int lane) { if (!dry && lane == 0) ticket = atomicAdd(&counter[home_queue()], 1); }
+  __device__ __forceinline__ int take(int lane) {
+    if (!dry) {
+      const int home = home_queue(), b0 = begin[home], t = __builtin_amdgcn_readfirstlane(ticket) + fixed(home);
+      if (t < begin[home + 1] - b0) return b0 + t;
+      dry = true;
     }
-    return pop_item(counter, begin);
+    return steal(lane);
+  }
+  // Lane t looks at queue home + t: one round trip for all eight counters, a second one for a ticket if any is left.
+  // Asking one queue after the other put 5 us at the end of every launch (4000 tokens, d = 64, 144 items: forward
+  // kernel 28.7 -> 19.9 us together with the fixed first ticket and the prefetched record).
+  __device__ __forceinline__ int steal(int lane) {
+    const int home = home_queue(), q = (home + lane) % kNumXcd, b0 = begin[q];
+    const int n = begin[q + 1] - b0 - fixed(q);
+    uint64_t left = __builtin_amdgcn_ballot_w64(lane < kNumXcd && n > 0 && __hip_atomic_load(&counter[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < n);
+    while (left) {
+      const int l = __builtin_ctzll(left);
+      left &= left - 1;
+      const int ql = (home + l) % kNumXcd;
+      int i = 0;
+      if (lane == 0) i = atomicAdd(&counter[ql], 1);
+      i = __builtin_amdgcn_readfirstlane(i);
+      if (i < __builtin_amdgcn_readlane(n, l)) return __builtin_amdgcn_readlane(b0, l) + fixed(ql) + i;
+    }
+    return -1;
   }
 };
 
+// The record of the next item travels through LDS: wave 0 requests it by LDS-DMA before the current item ends, so the
+// cold table reads (record, then its first pair: 4 us of a 14 us item of short sequences) are not in front of the next.
+constexpr int kQItemWords = sizeof(QItem) / 4;
+static_assert(sizeof(QItem) % 16 == 0 && kQItemWords <= 64, "QItem is read in 16-byte pieces and fetched by one instruction");
+__device__ __forceinline__ void fetch_item(const QItem* items, int idx, int32_t* rec, int lane) {
+  lds_dma4(reinterpret_cast<const float*>(items + idx) + min(lane, kQItemWords - 1), lds_addr(rec));
+}
+__device__ __forceinline__ QItem read_item(const int32_t* rec) {
+  union { QItem it; u32x4 w[sizeof(QItem) / 16]; } u;
+#pragma unroll
+  for (int i = 0; i < (int)(sizeof(QItem) / 16); i++) {
+    const u32x4 v = *reinterpret_cast<const u32x4*>(rec + 4 * i);
+#pragma unroll
+    for (int j = 0; j < 4; j++) u.w[i][j] = (uint32_t)__builtin_amdgcn_readfirstlane((int)v[j]);   // wave-uniform: scalar registers
+  }
+  return u.it;
+}
 // =====================================================================================
 // Forward: partial attention.  Item = (slot, two 128-row query sub-tiles that share the slot's
 // K/V stream: two query heads of one KV head, or two neighbouring row tiles of one head);
@@ -281,20 +309,23 @@ struct TileIter {
   int pair, pair_end, c0, ncols, row_hi;   // row_hi = tile_off + q_rows (first row past the tile)
   DevPair cur;
   bool more;
-  __device__ __forceinline__ void load_pair() {
+  __device__ __forceinline__ void set(int kv_start, int kv_len, int kind, int ds_frag) {
     // the pair index is wave-uniform; readfirstlane says so to the compiler, which then keeps the record (and
     // everything derived from it) in scalar registers and branches on it with scalar branches
-    const DevPair p = pairs[pair];
-    cur.kv_start = __builtin_amdgcn_readfirstlane(p.kv_start); cur.kv_len = __builtin_amdgcn_readfirstlane(p.kv_len);
-    cur.kind = __builtin_amdgcn_readfirstlane(p.kind); cur.ds_frag = __builtin_amdgcn_readfirstlane(p.ds_frag);
+    cur.kv_start = __builtin_amdgcn_readfirstlane(kv_start); cur.kv_len = __builtin_amdgcn_readfirstlane(kv_len);
+    cur.kind = __builtin_amdgcn_readfirstlane(kind); cur.ds_frag = __builtin_amdgcn_readfirstlane(ds_frag);
     ncols = (cur.kind & 1) ? min(cur.kv_len, row_hi) : cur.kv_len;
+  }
+  __device__ __forceinline__ void load_pair() {
+    const DevPair p = pairs[pair];
+    set(p.kv_start, p.kv_len, p.kind, p.ds_frag);
   }
   __device__ __forceinline__ void init(const DevPair* p, const QItem& it) {
     pairs = p; pair = it.pair_begin; pair_end = it.pair_begin + it.n_pairs; c0 = 0; ncols = 0;
     row_hi = max(it.tile_off[0] + it.q_rows[0], it.tile_off[1] + it.q_rows[1]);
     cur = DevPair{0, 0, 0, 0};
     more = it.n_pairs > 0;
-    if (more) load_pair();
+    if (more) set(it.first.kv_start, it.first.kv_len, it.first.kind, it.first.ds_frag);
   }
   __device__ __forceinline__ void advance() {
     c0 += kFwdTileN;
@@ -323,13 +354,11 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
   constexpr int CPR = D / 8, RPI = 64 / CPR, NDMA = kFwdTileN / RPI / 8;   // LDS-DMA geometry, see issue()
   constexpr int DMA_PER_TILE = 2 * NDMA;
   __shared__ __attribute__((aligned(1024))) unsigned char lds_kv[NB][BUF];
-  __shared__ int s_item;
+  __shared__ __attribute__((aligned(16))) int32_t s_rec[2][64];   // records of this item and the next
+  __shared__ int s_next;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform, kept in a scalar register
-  // Sub-item, 32-row group inside it.  The groups of sub-item 1 run backwards over the waves: waves w and w + 4 share a
-  // SIMD, so the group that sees least of a diagonal (or nothing, past a ragged end) sits next to one that sees most.
-  const int sub = wave >> 2, wq = sub ? 3 - (wave & 3) : wave & 3;
   const int l32 = lane & 31, g = lane >> 5;
   const int group = a.n_q_heads / a.n_kv_heads;
   const int64_t q_row_stride = (int64_t)a.n_q_heads * D;     // elements
@@ -338,13 +367,11 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
   // LDS-DMA of a 64-row tile: instruction n of this wave fills LDS rows r_n = (8n + wave) * RPI + lane / CPR.
   // A lane fetches chunk (pc ^ swz(r_n)) of global row min(r_n, valid - 1): rows past a ragged end
   // repeat the last valid row (finite values; those columns are masked).
-  uint32_t dma_row[NDMA], dma_chunk[NDMA];
-#pragma unroll
-  for (int n = 0; n < NDMA; n++) {
-    const int r = (8 * n + wave) * RPI + lane / CPR, pc = lane % CPR;
-    dma_row[n] = (uint32_t)(r * kv_row_stride * 2);
-    dma_chunk[n] = (uint32_t)((pc ^ swz<D>(r)) << 4);
-  }
+  // (r_n and r_0 differ by a multiple of 16, the period of the swizzle: one chunk offset serves all n.)
+  static_assert(8 * RPI % 16 == 0, "swizzle period");
+  const uint32_t dma_row0 = (uint32_t)((wave * RPI + lane / CPR) * kv_row_stride * 2);
+  const uint32_t dma_chunk = (uint32_t)(((lane % CPR) ^ swz<D>(wave * RPI + lane / CPR)) << 4);
+  const uint32_t dma_step = (uint32_t)(8 * RPI * kv_row_stride * 2);
   // transpose-read pattern inside a 16-lane group: row tr_row, 4 columns from tr_col
   const int tr_row = (lane & 15) >> 2, tr_col = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
   // Ring positions, advanced by one buffer per tile and kept across items: in iteration i the
@@ -362,13 +389,19 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
   for (int kc = 0; kc < KC; kc++) kk_off[kc] = lds_addr(lds_kv[b_k]) + tile_off<D>(l32, 2 * kc + g);
 
   ItemStream items;
-  if (tid == 0) { items.init(a.hdr->fwd_counter, a.hdr->fwd_begin); items.request(); s_item = items.resolve(); }
+  if (wave == 0) {
+    const int first = items.start(a.hdr->fwd_counter, a.hdr->fwd_begin, lane);
+    if (first >= 0) fetch_item(a.items, first, s_rec[0], lane);
+    if (lane == 0) s_next = first;
+    dma_wait();
+  }
   __syncthreads();
-  for (;;) {
-    const int item_idx = __builtin_amdgcn_readfirstlane(s_item);   // uniform: tables are read with scalar loads
-    if (item_idx < 0) break;
-    if (tid == 0) items.request();      // the item after this one
-    const QItem it = a.items[item_idx];
+  int item_idx = __builtin_amdgcn_readfirstlane(s_next);   // wave-uniform
+  for (int par = 0; item_idx >= 0; par ^= 1) {
+    const QItem it = read_item(s_rec[par]);
+    // Sub-item, 32-row group inside it.  The groups of sub-item 1 run backwards over the waves: waves w and w + 4 share a
+    // SIMD, so the group that sees least of a diagonal (or nothing, past a ragged end) sits next to one that sees most.
+    const int sub = wave >> 2, wq = sub ? 3 - (wave & 3) : wave & 3;
     // selects, not it.q_rows[sub]: a run-time index would put the whole item into private memory
     const int q_rows = (sub ? it.q_rows[1] : it.q_rows[0]), tile_off_q = (sub ? it.tile_off[1] : it.tile_off[0]), head = (sub ? it.head[1] : it.head[0]);
     const int kvh = it.head[0] / group;
@@ -403,9 +436,10 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
     // last row; none if its rows lie past the ragged end.  What remains it only loads and waits for.
     const int row_hi = max(it.tile_off[0] + it.q_rows[0], it.tile_off[1] + it.q_rows[1]);
     const int wave_row_hi = min(wave_row_lo + 32, tile_off_q + q_rows);
+    const int n_tiles = it.n_tiles;
     const int n_vis = wq * 32 >= q_rows ? 0
-                    : it.diag_last ? it.n_tiles - ((row_hi + kFwdTileN - 1) / kFwdTileN - (wave_row_hi + kFwdTileN - 1) / kFwdTileN)
-                                   : it.n_tiles;
+                    : it.diag_last ? n_tiles - ((row_hi + kFwdTileN - 1) / kFwdTileN - (wave_row_hi + kFwdTileN - 1) / kFwdTileN)
+                                   : n_tiles;
 
     // The load of one tile in two parts.  describe(): scalar bookkeeping with branches, run at
     // an iteration boundary.  issue(): branch-free, sits between the MFMAs.
@@ -428,12 +462,14 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
       const uint32_t lbase = lds_addr(lds_kv[0]) + b_dma * BUF;
 #pragma unroll
       for (int n = 0; n < NDMA; n++) {
-        const uint32_t voff = min(dma_row[n], d_lim) + dma_chunk[n];
+        const uint32_t voff = min(dma_row0 + n * dma_step, d_lim) + dma_chunk;
         lds_dma16_s(reinterpret_cast<const unsigned char*>(d_k), voff, lbase + (8 * n + wave) * 1024);
         lds_dma16_s(reinterpret_cast<const unsigned char*>(d_v), voff, lbase + TB + (8 * n + wave) * 1024);
       }
       b_dma = (b_dma == NB - 1) ? 0 : b_dma + 1;
     };
+    const bool short_item = n_vis < 7;         // too short to ask for the next ticket later than here
+    if (wave == 0 && short_item) items.request(lane);
     // prologue: tiles 0 and 1 into the two buffers before the next one to load
     TileMeta meta[3];                 // tiles i+1, i+2, i+3 (shift register)
     b_dma = (b_dma + NB - 2) % NB;
@@ -582,14 +618,27 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
     const std::true_type yes;
     const std::false_type no;
     // The item takes n_tiles + 1 iterations (barriers); a wave computes in the first n_vis + 1 of them.
-    int idle = it.n_tiles + 1;
+    // The next item (wave 0): its ticket is requested some tiles before it is turned into an index, and the record behind
+    // that index is requested before the item's last tile barrier, which publishes both.
+    auto next_item = [&]() {
+      const int nx = items.take(lane);
+      if (lane == 0) s_next = nx;
+      if (nx >= 0) fetch_item(a.items, nx, s_rec[par ^ 1], lane);
+    };
+    int idle = n_tiles - n_vis;
     if (n_vis > 0) {
-      idle = it.n_tiles - n_vis;
       iteration(yes, no, s_a, s_b);        // S^T of tile 0
-      int rem = n_vis - 1;                 // iterations that do both phases; they alternate (s_b, s_a), (s_a, s_b)
-      for (; rem >= 2; rem -= 2) {
-        iteration(no, no, s_b, s_a);
-        iteration(no, no, s_a, s_b);
+      // iterations that do both phases; they alternate (s_b, s_a), (s_a, s_b)
+      int rem = n_vis - 1;
+      for (int left = 4; left >= 0; left -= 2) {      // down to 4 (5) of them, to 2 (3), to 0 (1)
+        for (; rem >= left + 2; rem -= 2) {
+          iteration(no, no, s_b, s_a);
+          iteration(no, no, s_a, s_b);
+        }
+        if (wave == 0) {
+          if (left == 4 && !short_item) items.request(lane);
+          if (left == 2) next_item();
+        }
       }
       if (rem) {
         iteration(no, no, s_b, s_a);       // a tail, not a branch inside the loop (which costs dozens of spills)
@@ -598,20 +647,28 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
         for (int rt = 0; rt < 2; rt++) s_a[rt] = s_b[rt];
       }
       iteration(no, yes, s_a, s_b);        // O += V P of the last tile
+    } else {
+      issue(); tile_barrier(); rotate();
+      if (wave == 0) next_item();
     }
     for (; idle > 0; idle--) { issue(); tile_barrier(); rotate(); }
+    if (n_tiles == 0) { dma_wait(); __syncthreads(); }      // an item without tiles has no barrier behind next_item()
     dma_wait();         // the look-ahead loads past the end of the item (zero tiles)
 
-    // ---- epilogue: normalise, write the partial (fp32) and its LSE
+    // ---- epilogue (the record is read again, not kept in registers through the tile loop): normalise, write the partial (fp32) and its LSE
+    const QItem e = read_item(s_rec[par]);
+    const int e_row = wq * 32 + l32, e_head = sub ? e.head[1] : e.head[0];
+    const bool e_ok = e_row < (sub ? e.q_rows[1] : e.q_rows[0]);
+    const int64_t e_q_row = (int64_t)((sub ? e.q_start[1] : e.q_start[0]) + e_row);
     const float l_tot = l_run + xor32(l_run);
     const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
-    if (row_ok && a.running) {
+    if (e_ok && a.running) {
       // Two-way reduction in place: the running (O, LSE) of this row and head, as the earlier stages left it, and
       // this slot's (o / l_tot, lse_s) combine with weights exp(LSE - m); a running LSE of -inf means "nothing
       // yet" (whatever O holds then is ignored).  One writer per row and launch; stages are ordered by the stream.
-      const int64_t row = (int64_t)((sub ? it.q_start[1] : it.q_start[0]) + my_row);
-      float* op = reinterpret_cast<float*>(a.o) + row * q_row_stride + (int64_t)head * D;
-      float* lp = a.lse + row * a.n_q_heads + head;
+      const int64_t row = e_q_row;
+      float* op = reinterpret_cast<float*>(a.o) + row * q_row_stride + (int64_t)e_head * D;
+      float* lp = a.lse + row * a.n_q_heads + e_head;
       const float lse_s = l_tot > 0.f ? (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2 : -INFINITY;
       const float lse_o = *lp;
       const float m = fmaxf(lse_o, lse_s);
@@ -630,11 +687,11 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
           *ptr = old * c_o + cur * c_s;
         }
       if (g == 0) *lp = tot > 0.f ? m + __logf(tot) : -INFINITY;
-    } else if (row_ok) {
+    } else if (e_ok) {
       // the only slot of its query block: this is the final result, not a partial
-      const bool to_final = it.to_final != 0;
-      const int64_t row = to_final ? (int64_t)((sub ? it.q_start[1] : it.q_start[0]) + my_row) : (int64_t)((sub ? it.out_row[1] : it.out_row[0]) + my_row);
-      const int64_t off = row * q_row_stride + (int64_t)head * D;
+      const bool to_final = e.to_final != 0;
+      const int64_t row = to_final ? e_q_row : (int64_t)((sub ? e.out_row[1] : e.out_row[0]) + e_row);
+      const int64_t off = row * q_row_stride + (int64_t)e_head * D;
       if (to_final ? !a.o_is_f32 : a.part_is_bf16) {
         uint16_t* op = reinterpret_cast<uint16_t*>(to_final ? a.o : a.o_part) + off;
 #pragma unroll
@@ -651,12 +708,11 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
       }
       if (g == 0) {
         const float lse = l_tot > 0.f ? (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2 : -INFINITY;
-        (to_final ? a.lse : a.lse_part)[row * a.n_q_heads + head] = lse;
+        (to_final ? a.lse : a.lse_part)[row * a.n_q_heads + e_head] = lse;
       }
     }
-    __syncthreads();   // every wave has read s_item
-    if (tid == 0) s_item = items.resolve();
-    __syncthreads();
+    // No barrier here: behind the last tile barrier no wave reads the ring, and the next item's loads start at once.
+    item_idx = __builtin_amdgcn_readfirstlane(s_next);
   }
   if (tid == 0) retire(a.hdr->fwd_counter, &a.hdr->fwd_done);
 }
@@ -953,9 +1009,13 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
   int b_c = NB - 2, b_p = 0, b_s = NB - 1, b_dma = 4, hb = 0;
   __syncthreads();
 
+  ItemStream items;             // of wave 4, a consumer: the producers have no register to spare
+  if (wave == 4) {
+    const int first = items.start(a.hdr->bwd_counter, a.hdr->bwd_begin, lane);
+    if (lane == 0) s_item = first;
+  }
+  __syncthreads();
   for (;;) {
-    if (tid == 0) s_item = pop_item(a.hdr->bwd_counter, a.hdr->bwd_begin);
-    __syncthreads();
     const int item_idx = __builtin_amdgcn_readfirstlane(s_item);   // uniform: tables are read with scalar loads
     if (item_idx < 0) break;
     const BwdItem it = a.items[item_idx];
@@ -1067,7 +1127,12 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
 #pragma unroll
       for (int jw = 0; jw < 4; jw++) aop[jw] = fetch_a(jw);
       next_tile();
+      if (wave == 4 && n_iv < 6) items.request(lane);
       for (int iv = 0; iv < n_iv; iv++) {
+        if (wave == 4) {                 // the next item; every wave has read s_item
+          if (n_iv - iv == 6) items.request(lane);
+          if (n_iv - iv == 2) { const int nx = items.take(lane); if (lane == 0) s_item = nx; }
+        }
         const uint32_t hb_src = hsrc + hb * (4 * 4096);
         // MFMA u = (2j + w) * NN + n reads operand (w ? 2 : 0) + j of KV group n0 + n
         auto fetch_b = [&](int u) {
@@ -1274,7 +1339,7 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
     }
     __syncthreads();
   }
-  if (tid == 0) retire(a.hdr->bwd_counter, &a.hdr->bwd_done);
+  if (wave == 4 && lane == 0) retire(a.hdr->bwd_counter, &a.hdr->bwd_done);
 }
 
 // =====================================================================================
@@ -1293,7 +1358,8 @@ __global__ void __launch_bounds__(512, 2) dq_kernel(BwdArgs a) {
   constexpr int DT = D / 32;
   constexpr int TB = tile_bytes<D>(kFwdTileN);
   __shared__ __attribute__((aligned(1024))) unsigned char lds_kv[2][2 * TB];   // [buffer][K tile | V tile]
-  __shared__ int s_item;
+  __shared__ __attribute__((aligned(16))) int32_t s_rec[64];   // next item's record, as in fwd_kernel
+  __shared__ int s_next;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform, kept in a scalar register
@@ -1325,13 +1391,16 @@ __global__ void __launch_bounds__(512, 2) dq_kernel(BwdArgs a) {
   };
 
   ItemStream items;
-  if (tid == 0) { items.init(a.hdr->dq_counter, a.hdr->dq_begin); items.request(); s_item = items.resolve(); }
+  if (wave == 0) {
+    const int first = items.start(a.hdr->dq_counter, a.hdr->dq_begin, lane);
+    if (first >= 0) fetch_item(a.dq_items, first, s_rec, lane);
+    if (lane == 0) s_next = first;
+    dma_wait();
+  }
   __syncthreads();
-  for (;;) {
-    const int item_idx = __builtin_amdgcn_readfirstlane(s_item);   // uniform: tables are read with scalar loads
-    if (item_idx < 0) break;
-    if (tid == 0) items.request();      // the item after this one
-    const QItem it = a.dq_items[item_idx];
+  int item_idx = __builtin_amdgcn_readfirstlane(s_next);   // wave-uniform
+  while (item_idx >= 0) {
+    const QItem it = read_item(s_rec);
     const int q_start = (sub ? it.q_start[1] : it.q_start[0]), q_rows = (sub ? it.q_rows[1] : it.q_rows[0]), tile_off_q = (sub ? it.tile_off[1] : it.tile_off[0]), head = (sub ? it.head[1] : it.head[0]);
     const int kvh = it.head[0] / group;
     const int my_row = wq * 32 + l32;
@@ -1433,9 +1502,26 @@ __global__ void __launch_bounds__(512, 2) dq_kernel(BwdArgs a) {
     int tc0 = 0;
     bool have = ti.more;
     if (have) { dma(buf); ti.advance(); }
+    int left = it.n_tiles;
+    if (wave == 0 && left < 3) items.request(lane);
     dma_wait();
     __syncthreads();
+    auto next_item = [&]() {             // wave 0, see fwd_kernel
+      const int nx = items.take(lane);
+      if (lane == 0) s_next = nx;
+      if (nx >= 0) fetch_item(a.dq_items, nx, s_rec, lane);
+    };
+    if (!have) {                         // no tile barrier to publish the next item
+      if (wave == 0) next_item();
+      dma_wait();
+      __syncthreads();
+    }
     while (have) {
+      if (wave == 0) {
+        if (left == 3) items.request(lane);
+        if (left == 1) next_item();
+      }
+      left--;
       const DevPair np = ti.cur;
       const int nc0 = ti.c0;
       const bool nhave = ti.more;
@@ -1519,9 +1605,7 @@ __global__ void __launch_bounds__(512, 2) dq_kernel(BwdArgs a) {
           }
       }
     }
-    __syncthreads();   // every wave has read s_item
-    if (tid == 0) s_item = items.resolve();
-    __syncthreads();
+    item_idx = __builtin_amdgcn_readfirstlane(s_next);
   }
   if (tid == 0) retire(a.hdr->dq_counter, &a.hdr->dq_done);
 }
@@ -1552,7 +1636,8 @@ __global__ void __launch_bounds__(512, 2) dq_ds_kernel(BwdArgs a) {
   constexpr int CPR = D / 8, RPI = 64 / CPR, NDMA = kFwdTileN / RPI / 8;
   constexpr int DMA_PER_TILE = NDMA + WDS / 1024;
   __shared__ __attribute__((aligned(1024))) unsigned char lds_st[NB][STAGE];
-  __shared__ int s_item;
+  __shared__ __attribute__((aligned(16))) int32_t s_rec[64];   // next item's record, as in fwd_kernel
+  __shared__ int s_next;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1602,13 +1687,16 @@ __global__ void __launch_bounds__(512, 2) dq_ds_kernel(BwdArgs a) {
   };
 
   ItemStream items;
-  if (tid == 0) { items.init(a.hdr->dq_counter, a.hdr->dq_begin); items.request(); s_item = items.resolve(); }
+  if (wave == 0) {
+    const int first = items.start(a.hdr->dq_counter, a.hdr->dq_begin, lane);
+    if (first >= 0) fetch_item(a.dq_items, first, s_rec, lane);
+    if (lane == 0) s_next = first;
+    dma_wait();
+  }
   __syncthreads();
-  for (;;) {
-    const int item_idx = __builtin_amdgcn_readfirstlane(s_item);
-    if (item_idx < 0) break;
-    if (tid == 0) items.request();      // the item after this one
-    const QItem it = a.dq_items[item_idx];
+  int item_idx = __builtin_amdgcn_readfirstlane(s_next);   // wave-uniform
+  while (item_idx >= 0) {
+    const QItem it = read_item(s_rec);
     const int q_start = (sub ? it.q_start[1] : it.q_start[0]), q_rows = (sub ? it.q_rows[1] : it.q_rows[0]), tile_off_q = (sub ? it.tile_off[1] : it.tile_off[0]), head = (sub ? it.head[1] : it.head[0]);
     const int kvh = it.head[0] / group;
     const int my_row = wq * 32 + l32;
@@ -1671,12 +1759,22 @@ __global__ void __launch_bounds__(512, 2) dq_ds_kernel(BwdArgs a) {
     b_dma = b_c;
     describe(); issue(); vis[0] = d_vis;
     describe(); issue(); vis[1] = d_vis;
+    if (wave == 0 && n_tiles < 4) items.request(lane);
+    auto next_item = [&]() {             // wave 0, see fwd_kernel
+      const int nx = items.take(lane);
+      if (lane == 0) s_next = nx;
+      if (nx >= 0) fetch_item(a.dq_items, nx, s_rec, lane);
+    };
     for (int t = 0; t < n_tiles; t++) {
       // tile t has landed once at most one tile's loads are in flight; the barrier also says that every wave
       // is done with the stage that tile t + 2 goes into
       __builtin_amdgcn_s_waitcnt(0x0F70 | (DMA_PER_TILE & 15) | ((DMA_PER_TILE >> 4) << 14));
       __syncthreads();
       describe(); issue(); vis[2] = d_vis;
+      if (wave == 0) {
+        if (n_tiles - t == 4) items.request(lane);
+        if (n_tiles - t == 1) next_item();
+      }
       const int nv = __builtin_amdgcn_readfirstlane(vis[0]);
 #pragma unroll
       for (int f = 0; f < 2; f++) {
@@ -1696,7 +1794,9 @@ __global__ void __launch_bounds__(512, 2) dq_ds_kernel(BwdArgs a) {
       vis[0] = vis[1]; vis[1] = vis[2];
       advance_read_stage();
     }
+    if (wave == 0 && n_tiles == 0) next_item();
     dma_wait();          // the two look-ahead requests past the end of the item
+    lds_barrier();       // publishes the next item's record
     if (row_ok) {
       const int64_t off = (int64_t)(q_start + my_row) * q_row_stride + (int64_t)head * D;
       if constexpr (GRAD_BF16) {
@@ -1713,9 +1813,7 @@ __global__ void __launch_bounds__(512, 2) dq_ds_kernel(BwdArgs a) {
           }
       }
     }
-    __syncthreads();   // every wave has read s_item
-    if (tid == 0) s_item = items.resolve();
-    __syncthreads();
+    item_idx = __builtin_amdgcn_readfirstlane(s_next);
   }
   if (tid == 0) retire(a.hdr->dq_counter, &a.hdr->dq_done);
 }
