@@ -405,7 +405,7 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
   constexpr int DT = D / 32;      // row tiles of O^T
   constexpr int NS1 = 2 * KC;     // MFMAs of S^T (two 32-row halves of the KV tile)
   constexpr int NS2 = 4 * DT;     // MFMAs of O^T += V^T P^T
-  constexpr int PF = 4;           // an LDS operand is requested this many MFMAs before its use
+  constexpr int PF = 2;           // an LDS operand is requested this many MFMAs before its use (4: more spills, 1-3 % slower)
   constexpr int TB = tile_bytes<D>(kFwdTileN);
   constexpr int BUF = 2 * TB;     // [K tile | V tile]
   constexpr int NB = kFwdBufs;
