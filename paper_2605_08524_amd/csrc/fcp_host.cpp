@@ -768,21 +768,27 @@ int fcp::build_queue_image(const fcp_problem* p, const Expanded& x, const WsLayo
     std::vector<std::vector<BwdItem>> groups;
     std::vector<int64_t> weight, gkey;
     groups.reserve(x.kv.size() * p->n_kv_heads);
-    std::vector<int64_t> tile_w;
+    std::vector<int64_t> tile_w, tile_steps;
     for (const KvSeg& k : x.kv) {
       const int n_tiles = (int)ceil_div(k.len, kBwdTileN);
       tile_w.assign(n_tiles, 0);
+      tile_steps.assign(n_tiles, 0);
       for (int t = 0; t < n_tiles; t++) {
         const int off = t * kBwdTileN, rows = std::min(kBwdTileN, k.len - off);
-        for (int i = k.dep_begin; i < k.dep_begin + k.n_deps; i++)
-          tile_w[t] += (int64_t)rows * G * ((x.deps[i].kind & 1) ? std::max(0, x.deps[i].q_len - off) : x.deps[i].q_len);
+        for (int i = k.dep_begin; i < k.dep_begin + k.n_deps; i++) {
+          const int q_rows = (x.deps[i].kind & 1) ? std::max(0, x.deps[i].q_len - off) : x.deps[i].q_len;   // off is a multiple of 32
+          tile_w[t] += (int64_t)rows * G * q_rows;
+          tile_steps[t] += G * ceil_div(q_rows, 32);
+        }
+        if (tile_steps[t] + 3 > INT32_MAX) { set_error("too many steps in a backward work item"); return FCP_ERR_UNSUPPORTED; }
       }
       for (int g = 0; g < p->n_kv_heads; g++) {
         std::vector<BwdItem> items;
         int64_t w = 0;
         for (int t = 0; t < n_tiles; t++) {            // earlier tiles of a DIAG pair are heavier
           const int off = t * kBwdTileN;
-          items.push_back({k.start + off, std::min(kBwdTileN, k.len - off), off, k.dep_begin, k.n_deps, g, k.len});
+          items.push_back({k.start + off, std::min(kBwdTileN, k.len - off), off, k.dep_begin, k.n_deps, g, k.len, (int32_t)((tile_steps[t] + 3) & ~1),
+                           k.n_deps > 0 ? x.deps[k.dep_begin] : BwdDep{0, 0, 0, 0}});
           w += tile_w[t];
         }
         groups.push_back(std::move(items));

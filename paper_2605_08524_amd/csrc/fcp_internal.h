@@ -33,7 +33,9 @@ struct DevPair { int32_t kv_start, kv_len, kind, ds_frag; };
 struct QItem { int32_t q_start[2], q_rows[2], out_row[2], tile_off[2], head[2], pair_begin, n_pairs, to_final, q_blk_len, n_tiles, diag_last; DevPair first; };
 constexpr int kQTileN = 64;         // KV rows per LDS tile of the query-stationary kernels
 struct BwdDep  { int32_t q_start, q_len, kind, ds_frag; };
-struct BwdItem { int32_t kv_start, kv_rows, tile_off, dep_begin, n_deps, kv_head, kv_blk_len; };
+// n_iv: barrier intervals of the item: its 32-row steps (dependencies x query heads of the group; a DIAG dependency from the
+// tile's own rows on) plus two of pipeline fill, rounded up to even.  first: the first of its dependencies.
+struct BwdItem { int32_t kv_start, kv_rows, tile_off, dep_begin, n_deps, kv_head, kv_blk_len, n_iv; BwdDep first; };
 constexpr int kMaxPackedBlock = 65535;   // tokens of a packed block
 
 // The dS spill buffer (FCP_FLAG_BWD_SPILL_DS) is a sequence of 2 KB fragments, one per (pair, query head,

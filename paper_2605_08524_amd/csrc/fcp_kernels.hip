@@ -313,21 +313,23 @@ struct ItemStream {
 
 // The record of the next item travels through LDS: wave 0 requests it by LDS-DMA before the current item ends, so the
 // cold table reads (record, then its first pair: 4 us of a 14 us item of short sequences) are not in front of the next.
-constexpr int kQItemWords = sizeof(QItem) / 4;
-static_assert(sizeof(QItem) % 16 == 0 && kQItemWords <= 64, "QItem is read in 16-byte pieces and fetched by one instruction");
-__device__ __forceinline__ void fetch_item(const QItem* items, int idx, int32_t* rec, int lane) {
-  lds_dma4(reinterpret_cast<const float*>(items + idx) + min(lane, kQItemWords - 1), lds_addr(rec));
+template <class Item>
+__device__ __forceinline__ void fetch_item(const Item* items, int idx, int32_t* rec, int lane) {
+  static_assert(sizeof(Item) % 16 == 0 && sizeof(Item) <= 256, "read in 16-byte pieces, fetched by one instruction");
+  lds_dma4(reinterpret_cast<const float*>(items + idx) + min(lane, (int)sizeof(Item) / 4 - 1), lds_addr(rec));
 }
-__device__ __forceinline__ QItem read_item(const int32_t* rec) {
-  union { QItem it; u32x4 w[sizeof(QItem) / 16]; } u;
+template <class Item>
+__device__ __forceinline__ Item read_item(const int32_t* rec) {
+  union { Item it; u32x4 w[sizeof(Item) / 16]; } u;
 #pragma unroll
-  for (int i = 0; i < (int)(sizeof(QItem) / 16); i++) {
+  for (int i = 0; i < (int)(sizeof(Item) / 16); i++) {
     const u32x4 v = *reinterpret_cast<const u32x4*>(rec + 4 * i);
 #pragma unroll
     for (int j = 0; j < 4; j++) u.w[i][j] = (uint32_t)__builtin_amdgcn_readfirstlane((int)v[j]);   // wave-uniform: scalar registers
   }
   return u.it;
 }
+
 // =====================================================================================
 // Forward: partial attention.  Item = (slot, two 128-row query sub-tiles that share the slot's
 // K/V stream: two query heads of one KV head, or two neighbouring row tiles of one head);
@@ -457,7 +459,7 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
   __syncthreads();
   int item_idx = __builtin_amdgcn_readfirstlane(s_next);   // wave-uniform
   for (int par = 0; item_idx >= 0; par ^= 1) {
-    const QItem it = read_item(s_rec[par]);
+    const QItem it = read_item<QItem>(s_rec[par]);
     // Sub-item, 32-row group inside it.  The groups of sub-item 1 run backwards over the waves: waves w and w + 4 share a
     // SIMD, so the group that sees least of a diagonal (or nothing, past a ragged end) sits next to one that sees most.
     const int sub = wave >> 2, wq = sub ? 3 - (wave & 3) : wave & 3;
@@ -707,7 +709,7 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
     dma_wait();         // the look-ahead loads past the end of the item (zero tiles)
 
     // ---- epilogue (the record is read again, not kept in registers through the tile loop): normalise, write the partial (fp32) and its LSE
-    const QItem e = read_item(s_rec[par]);
+    const QItem e = read_item<QItem>(s_rec[par]);
     const int e_row = wq * 32 + l32, e_head = sub ? e.head[1] : e.head[0];
     const bool e_ok = e_row < (sub ? e.q_rows[1] : e.q_rows[0]);
     const int64_t e_q_row = (int64_t)((sub ? e.q_start[1] : e.q_start[0]) + e_row);
@@ -984,12 +986,12 @@ struct StepIter {
   BwdDep cur;
   bool more;
   __device__ __forceinline__ int first_q0() const { return (cur.kind & 1) ? first_diag : 0; }
-  __device__ __forceinline__ void init(const BwdDep* d, int n, int group_, int tile_off) {
-    deps = d; dep = 0; n_deps = n; hh = 0; group = group_; first_diag = tile_off & ~31; q0 = 0;
-    cur = BwdDep{0, 0, 0, 0};
-    more = n > 0;
+  __device__ __forceinline__ void init(const BwdDep* d, const BwdItem& it, int group_) {
+    deps = d + it.dep_begin; dep = 0; n_deps = it.n_deps; hh = 0; group = group_; first_diag = it.tile_off & ~31; q0 = 0;
+    cur = it.first;
+    more = n_deps > 0;
     if (more) {
-      cur = deps[0]; q0 = first_q0();
+      q0 = first_q0();
       more = q0 < cur.q_len;
     }
   }
@@ -1026,7 +1028,8 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
   __shared__ __attribute__((aligned(1024))) unsigned char lds_t[NB][BUF];
   __shared__ __attribute__((aligned(1024))) unsigned char lds_h[2][4][4096];   // [parity][KV sub-tile][operand][lane] 16 B
   __shared__ __attribute__((aligned(256))) float lds_sc[NB][64];   // [LSE*log2e x 32 | D*scale x 32]
-  __shared__ int s_item;
+  __shared__ int s_next;
+  __shared__ __attribute__((aligned(16))) int32_t s_rec[64];       // next item's record, as in fwd_kernel
   __shared__ __attribute__((aligned(16))) unsigned char s_stage[4][kStageBytes];   // producers at an item's start, consumers at its end
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -1042,11 +1045,11 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
   const uint32_t lds_sc0 = lds_addr(lds_sc[0]);
   const uint32_t lds_h0 = lds_addr(lds_h[0][sub]) + lane * 16;
 
-  // Zero the tile ring and the hand-over buffers, +inf / 0 into the scalars: the steps before the
-  // first one of the first item then contribute nothing.
-  for (int i = tid * 16; i < NB * BUF; i += 512 * 16)
-    *reinterpret_cast<u32x4*>(&lds_t[0][0] + i) = u32x4{0, 0, 0, 0};
-  for (int i = tid * 16; i < 2 * 4 * 4096; i += 512 * 16)
+  // The two steps before the first one of the first item must contribute nothing: zero into the two tile buffers and the
+  // hand-over buffer they read, +inf / 0 into the scalars.
+  for (int i = tid * 16; i < 2 * BUF; i += 512 * 16)
+    *reinterpret_cast<u32x4*>(&lds_t[NB - 2][0] + i) = u32x4{0, 0, 0, 0};
+  for (int i = tid * 16; i < 4 * 4096; i += 512 * 16)
     *reinterpret_cast<u32x4*>(&lds_h[0][0][0] + i) = u32x4{0, 0, 0, 0};
   for (int i = tid; i < NB * 64; i += 512) lds_sc[0][i] = (i & 32) ? 0.f : INFINITY;
   // Ring positions, advanced by one buffer per step and kept across items.  In interval i the
@@ -1055,29 +1058,21 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
   // and published by a barrier) two intervals before the producer's interval, so both roles can
   // request their first LDS operands of an interval before the barrier that opens it.
   int b_c = NB - 2, b_p = 0, b_s = NB - 1, b_dma = 4, hb = 0;
-  __syncthreads();
-
   ItemStream items;             // of wave 4, a consumer: the producers have no register to spare
   if (wave == 4) {
     const int first = items.start(a.hdr->bwd_counter, a.hdr->bwd_begin, lane);
-    if (lane == 0) s_item = first;
+    if (first >= 0) fetch_item(a.items, first, s_rec, lane);
+    if (lane == 0) s_next = first;
+    dma_wait();
   }
   __syncthreads();
-  for (;;) {
-    const int item_idx = __builtin_amdgcn_readfirstlane(s_item);   // uniform: tables are read with scalar loads
-    if (item_idx < 0) break;
-    const BwdItem it = a.items[item_idx];
+  while (__builtin_amdgcn_readfirstlane(s_next) >= 0) {
+    const BwdItem it = read_item<BwdItem>(s_rec);
     const int my_kv = sub * 32 + l32;                  // KV row inside the tile
     const bool kv_ok = my_kv < it.kv_rows;
-    int n_iv = 2;       // barrier intervals of the item: its steps plus two of pipeline fill, rounded up to even
-    for (int d = 0; d < it.n_deps; d++) {
-      const BwdDep dd = a.deps[it.dep_begin + d];
-      const int first = (dd.kind & 1) ? (it.tile_off & ~31) : 0;
-      n_iv += group * (max(0, dd.q_len - first + 31) / 32);
-    }
-    n_iv = (n_iv + 1) & ~1;
+    const int n_iv = it.n_iv;                          // barrier intervals of the item
     StepIter si;
-    si.init(a.deps + it.dep_begin, it.n_deps, group, it.tile_off);
+    si.init(a.deps, it, group);
 
     if (consumer) {
       // =============================== consumer ===============================
@@ -1177,9 +1172,13 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
       next_tile();
       if (wave == 4 && n_iv < 6) items.request(lane);
       for (int iv = 0; iv < n_iv; iv++) {
-        if (wave == 4) {                 // the next item; every wave has read s_item
+        if (wave == 4) {                 // the next item (every wave has read this one's record)
           if (n_iv - iv == 6) items.request(lane);
-          if (n_iv - iv == 2) { const int nx = items.take(lane); if (lane == 0) s_item = nx; }
+          if (n_iv - iv == 2) {
+            const int nx = items.take(lane);
+            if (lane == 0) s_next = nx;
+            if (nx >= 0) fetch_item(a.items, nx, s_rec, lane);
+          }
         }
         const uint32_t hb_src = hsrc + hb * (4 * 4096);
         // MFMA u = (2j + w) * NN + n reads operand (w ? 2 : 0) + j of KV group n0 + n
@@ -1430,7 +1429,7 @@ __global__ void __launch_bounds__(512, 2) dq_kernel(BwdArgs a) {
   __syncthreads();
   int item_idx = __builtin_amdgcn_readfirstlane(s_next);   // wave-uniform
   while (item_idx >= 0) {
-    const QItem it = read_item(s_rec);
+    const QItem it = read_item<QItem>(s_rec);
     const int q_start = (sub ? it.q_start[1] : it.q_start[0]), q_rows = (sub ? it.q_rows[1] : it.q_rows[0]), tile_off_q = (sub ? it.tile_off[1] : it.tile_off[0]), head = (sub ? it.head[1] : it.head[0]);
     const int kvh = it.head[0] / group;
     const int my_row = wq * 32 + l32;
@@ -1710,7 +1709,7 @@ __global__ void __launch_bounds__(512, 2) dq_ds_kernel(BwdArgs a) {
   __syncthreads();
   int item_idx = __builtin_amdgcn_readfirstlane(s_next);   // wave-uniform
   while (item_idx >= 0) {
-    const QItem it = read_item(s_rec);
+    const QItem it = read_item<QItem>(s_rec);
     const int q_start = (sub ? it.q_start[1] : it.q_start[0]), q_rows = (sub ? it.q_rows[1] : it.q_rows[0]), tile_off_q = (sub ? it.tile_off[1] : it.tile_off[0]), head = (sub ? it.head[1] : it.head[0]);
     const int kvh = it.head[0] / group;
     const int my_row = wq * 32 + l32;
