@@ -327,114 +327,128 @@ void count_tiles(QItem* it, const std::vector<DevPair>& pairs) {
   it->diag_last = it->n_pairs > 0 && (pairs[it->pair_begin + it->n_pairs - 1].kind & 1);
 }
 
-// XCD affinity: groups whose keys agree after division by `div` become one group (items concatenated in the order the
-// groups came; the keys are divided).  With a key per (sequence, KV head) all work that streams the K / V (forward, dQ)
-// or Q / dO (dK/dV) rows of one sequence and KV head runs on one XCD and finds them in that XCD's L2 (measured on the
-// training step: forward -1.2 %, dK/dV -0.6 %, dQ from dS -2 %).  Only done while the largest merged group stays below
-// three quarters of an XCD's fair share: a batch dominated by one sequence keeps the finer groups, which balance better.
+// Work items in groups that stay together: the items of a unit (one per (segment, KV head)) are consecutive in `items`, a
+// group is a run of units in `order`.
 template <class Item>
-void merge_groups_by_key(std::vector<std::vector<Item>>& groups, std::vector<int64_t>& weight, std::vector<int64_t>& key, int64_t div) {
-  std::unordered_map<int64_t, size_t> where;      // key -> merged group, in order of first appearance
-  std::vector<size_t> to(groups.size());
-  std::vector<int64_t> w2, key2;
-  int64_t total = 0, largest = 0;
-  for (size_t i = 0; i < groups.size(); i++) {
-    to[i] = where.emplace(key[i] / div, w2.size()).first->second;
-    if (to[i] == w2.size()) { w2.push_back(0); key2.push_back(key[i] / div); }
-    w2[to[i]] += weight[i];
-    total += weight[i];
-    largest = std::max(largest, w2[to[i]]);
+struct ItemGroups {
+  std::vector<Item> items;
+  std::vector<int32_t> unit_end;                   // items of unit u end here
+  std::vector<int32_t> order, group_end;           // units by group; units of group g end here in `order`
+  std::vector<int64_t> weight, key;                // per group
+  // the items pushed since the last call form one more unit, for now a group of its own
+  void close_unit(int64_t w, int64_t k) {
+    order.push_back((int32_t)unit_end.size());
+    unit_end.push_back((int32_t)items.size());
+    group_end.push_back((int32_t)order.size());
+    weight.push_back(w); key.push_back(k);
   }
-  if (largest * kNumXcd * 4 > total * 3) return;
-  std::vector<std::vector<Item>> g2(w2.size());
-  for (size_t i = 0; i < groups.size(); i++) g2[to[i]].insert(g2[to[i]].end(), groups[i].begin(), groups[i].end());
-  groups.swap(g2); weight.swap(w2); key.swap(key2);
-}
+  // XCD affinity: groups whose keys agree after division by `div` become one group (units concatenated in the order the
+  // groups came; the keys are divided).  With a key per (sequence, KV head) all work that streams the K / V (forward, dQ)
+  // or Q / dO (dK/dV) rows of one sequence and KV head runs on one XCD and finds them in that XCD's L2 (measured on the
+  // training step: forward -1.2 %, dK/dV -0.6 %, dQ from dS -2 %).  Only done while the largest merged group stays below
+  // three quarters of an XCD's fair share: a batch dominated by one sequence keeps the finer groups, which balance better.
+  void merge(int64_t div) {
+    const size_t n = weight.size();
+    std::unordered_map<int64_t, int32_t> where;    // key -> merged group, in order of first appearance
+    where.reserve(n);
+    std::vector<int32_t> to(n), end2;
+    std::vector<int64_t> w2, key2;
+    int64_t total = 0, largest = 0;
+    for (size_t i = 0; i < n; i++) {
+      to[i] = where.emplace(key[i] / div, (int32_t)w2.size()).first->second;
+      if (to[i] == (int32_t)w2.size()) { w2.push_back(0); key2.push_back(key[i] / div); end2.push_back(0); }
+      w2[to[i]] += weight[i];
+      total += weight[i];
+      largest = std::max(largest, w2[to[i]]);
+      end2[to[i]] += group_end[i] - (i ? group_end[i - 1] : 0);
+    }
+    if (largest * kNumXcd * 4 > total * 3) return;
+    std::vector<int32_t> pos(end2.size());         // where the next unit of a merged group goes
+    for (size_t g = 0, at = 0; g < end2.size(); g++) { pos[g] = (int32_t)at; at += end2[g]; end2[g] = (int32_t)at; }
+    std::vector<int32_t> order2(order.size());
+    for (size_t i = 0; i < n; i++)
+      for (int32_t u = i ? group_end[i - 1] : 0; u < group_end[i]; u++) order2[pos[to[i]]++] = order[u];
+    order.swap(order2); group_end.swap(end2); weight.swap(w2); key.swap(key2);
+  }
+  // Longest-processing-time assignment of weighted groups to the XCD queues: groups in
+  // descending weight, each to the currently lightest queue.  Ties resolve to the lower index.
+  void spread_over_xcds(std::vector<Item>* out, int32_t begin[kNumXcd + 1]) const {
+    std::vector<int> by_weight(weight.size());
+    std::iota(by_weight.begin(), by_weight.end(), 0);
+    std::stable_sort(by_weight.begin(), by_weight.end(), [&](int a, int b) { return weight[a] > weight[b]; });
+    std::vector<int> per_xcd[kNumXcd];
+    int64_t load[kNumXcd] = {0};
+    for (int g : by_weight) {
+      const int best = (int)(std::min_element(load, load + kNumXcd) - load);
+      per_xcd[best].push_back(g);
+      load[best] += weight[g];
+    }
+    out->clear();
+    out->reserve(items.size());
+    for (int x = 0; x < kNumXcd; x++) {
+      begin[x] = (int32_t)out->size();
+      for (int g : per_xcd[x])
+        for (int32_t u = g ? group_end[g - 1] : 0; u < group_end[g]; u++) {
+          const int32_t unit = order[u];
+          out->insert(out->end(), items.begin() + (unit ? unit_end[unit - 1] : 0), items.begin() + unit_end[unit]);
+        }
+    }
+    begin[kNumXcd] = (int32_t)out->size();
+  }
+};
 
-// Longest-processing-time assignment of weighted groups to the XCD queues: groups in
-// descending weight, each to the currently lightest queue.  Ties resolve to the lower index.
-template <class Item>
-void spread_over_xcds(std::vector<std::vector<Item>>& groups, std::vector<int64_t>& weight,
-                      std::vector<Item>* out, int32_t begin[kNumXcd + 1]) {
-  std::vector<int> order(groups.size());
-  std::iota(order.begin(), order.end(), 0);
-  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return weight[a] > weight[b]; });
-  std::vector<std::vector<int>> per_xcd(kNumXcd);
-  int64_t load[kNumXcd] = {0};
-  for (int g : order) {
-    int best = 0;
-    for (int x = 1; x < kNumXcd; x++)
-      if (load[x] < load[best]) best = x;
-    per_xcd[best].push_back(g);
-    load[best] += weight[g];
-  }
-  out->clear();
-  for (int x = 0; x < kNumXcd; x++) {
-    begin[x] = (int32_t)out->size();
-    for (int g : per_xcd[x])
-      for (const Item& it : groups[g]) out->push_back(it);
-  }
-  begin[kNumXcd] = (int32_t)out->size();
-}
-
-// The query-stationary items (forward, dQ) of a list of segments, one group per (segment, KV head): its items share
+// The query-stationary items (forward, dQ) of a list of segments, one unit per (segment, KV head): its items share
 // K/V.  An item joins two sub-tiles: heads (2j, 2j+1) of the group on one row tile when G is even, else row tiles
 // (2j, 2j+1) of one head.
-void q_items(const fcp_problem* p, const std::vector<QSeg>& segs, const std::vector<DevPair>& pairs, std::vector<QItem>* flat,
+void q_items(const fcp_problem* p, const std::vector<QSeg>& segs, const std::vector<DevPair>& pairs, int64_t n_items, std::vector<QItem>* flat,
              int32_t begin[kNumXcd + 1]) {
-  const int G = p->n_q_heads / p->n_kv_heads;
-  std::vector<std::vector<QItem>> groups;
-  std::vector<int64_t> weight, gkey;
-  groups.reserve(segs.size() * p->n_kv_heads);
+  const int G = p->n_q_heads / p->n_kv_heads, heads_per_item = G % 2 == 0 ? 2 : 1;
+  ItemGroups<QItem> groups;
+  groups.items.reserve(n_items);
   std::vector<int64_t> tile_w;
+  std::vector<QItem> rows;                        // the segment's items but for their heads
   int64_t n_ord = 1;
   for (const QSeg& sg : segs) n_ord = std::max<int64_t>(n_ord, sg.ordinal + 1);
   for (const QSeg& sg : segs) {
     const int n_tiles = (int)ceil_div(sg.len, kFwdTileM);
     tile_w.assign(n_tiles, 0);
     for (int t = 0; t < n_tiles; t++) {
-      const int off = t * kFwdTileM, rows = std::min(kFwdTileM, sg.len - off);
+      const int off = t * kFwdTileM, n_rows = std::min(kFwdTileM, sg.len - off);
       for (int i = sg.pair_begin; i < sg.pair_begin + sg.n_pairs; i++)
-        tile_w[t] += (int64_t)rows * ((pairs[i].kind & 1) ? std::min(pairs[i].kv_len, off + rows) : pairs[i].kv_len);
+        tile_w[t] += (int64_t)n_rows * ((pairs[i].kind & 1) ? std::min(pairs[i].kv_len, off + n_rows) : pairs[i].kv_len);
     }
-    auto sub = [&](QItem* it, int k, int t, int head) {
-      const int off = t * kFwdTileM;
-      it->q_start[k] = sg.start + off; it->q_rows[k] = std::min(kFwdTileM, sg.len - off);
-      it->out_row[k] = sg.out_row + off; it->tile_off[k] = off; it->head[k] = head;
-    };
-    for (int g = 0; g < p->n_kv_heads; g++) {
-      std::vector<QItem> items;
-      int64_t w = 0;
-      auto add = [&](int t0, int h0, int t1, int h1) {      // t1 < 0: no second sub-tile
-        QItem it{};
-        it.pair_begin = sg.pair_begin; it.n_pairs = sg.n_pairs; it.to_final = sg.to_final; it.q_blk_len = sg.len;
-        sub(&it, 0, t0, h0);
-        w += tile_w[t0];
-        if (t1 >= 0) { sub(&it, 1, t1, h1); w += tile_w[t1]; }
-        else { it.q_start[1] = it.q_start[0]; it.q_rows[1] = 0; it.out_row[1] = it.out_row[0]; it.tile_off[1] = it.tile_off[0]; it.head[1] = it.head[0]; }
-        count_tiles(&it, pairs);
-        items.push_back(it);
-      };
-      // later tiles of a DIAG pair are heavier: they come first
-      if (G % 2 == 0) {
-        for (int t = n_tiles - 1; t >= 0; t--)
-          for (int hh = 0; hh < G; hh += 2) add(t, g * G + hh, t, g * G + hh + 1);
-      } else {
-        for (int t = n_tiles - 1; t >= 0; t -= 2)
-          for (int hh = 0; hh < G; hh++) add(t, g * G + hh, t - 1, g * G + hh);
+    rows.clear();
+    int64_t w = 0;                                // of the segment and one KV head
+    // later tiles of a DIAG pair are heavier: they come first
+    for (int t = n_tiles - 1; t >= 0; t -= G % 2 == 0 ? 1 : 2) {
+      QItem it{};
+      it.pair_begin = sg.pair_begin; it.n_pairs = sg.n_pairs; it.to_final = sg.to_final; it.q_blk_len = sg.len;
+      for (int k = 0; k < 2; k++) {
+        const bool absent = G % 2 != 0 && k == 1 && t == 0;      // no second sub-tile: row 0 of the first, no rows
+        const int tile = G % 2 != 0 && k == 1 && t > 0 ? t - 1 : t, off = tile * kFwdTileM;
+        it.q_start[k] = sg.start + off; it.q_rows[k] = absent ? 0 : std::min(kFwdTileM, sg.len - off);
+        it.out_row[k] = sg.out_row + off; it.tile_off[k] = off;
+        if (!absent) w += tile_w[tile] * (G / heads_per_item);
       }
-      groups.push_back(std::move(items));
-      weight.push_back(w);
-      gkey.push_back(((int64_t)sg.seq * p->n_kv_heads + g) * n_ord + sg.ordinal);
+      count_tiles(&it, pairs);
+      rows.push_back(it);
+    }
+    for (int g = 0; g < p->n_kv_heads; g++) {
+      for (const QItem& r : rows)
+        for (int hh = 0; hh < G; hh += heads_per_item) {
+          groups.items.push_back(r);
+          groups.items.back().head[0] = g * G + hh; groups.items.back().head[1] = g * G + hh + heads_per_item - 1;
+        }
+      groups.close_unit(w, ((int64_t)sg.seq * p->n_kv_heads + g) * n_ord + sg.ordinal);
     }
   }
   // First the slots that cover the same KV range of a sequence (the r-th slot of each of its query blocks), then the
   // whole sequence: the workgroups of an XCD then walk one KV range at a time, which stays in that XCD's L2, instead of
-  // as many ranges as a query block has slots (forward of 13000 rows at the end of a 200000-token sequence, 16 KV heads, slots of 4096
-  // columns, plus 118000 tokens of short sequences: 11.2 -> 9.7 ms).
-  merge_groups_by_key(groups, weight, gkey, 1);
-  merge_groups_by_key(groups, weight, gkey, n_ord);
-  spread_over_xcds(groups, weight, flat, begin);
+  // as many ranges as a query block has slots (forward of 13000 rows at the end of a 200000-token sequence, 16 KV heads,
+  // slots of 4096 columns, plus 118000 tokens of short sequences: 11.2 -> 9.7 ms).
+  groups.merge(1);
+  groups.merge(n_ord);
+  groups.spread_over_xcds(flat, begin);
 }
 
 }  // namespace
@@ -753,21 +767,20 @@ int fcp::build_queue_image(const fcp_problem* p, const Expanded& x, const WsLayo
   auto put = [&](size_t off, const auto& v) { if (!v.empty()) std::memcpy(host.data() + off, v.data(), v.size() * sizeof(v[0])); };
   put(L.off_pairs, x.pairs);
   std::vector<QItem> flat;
-  q_items(p, x.fwd, x.pairs, &flat, hdr->fwd_begin);
+  q_items(p, x.fwd, x.pairs, L.n_fwd_items, &flat, hdr->fwd_begin);
   if ((int64_t)flat.size() != L.n_fwd_items) { set_error("internal: forward item count mismatch"); return FCP_ERR_INVALID_ARG; }
   put(L.off_fwd_items, flat);
   if (forward_only) return FCP_OK;
   // ---- dQ: query-stationary items over all pairs of a query segment
-  q_items(p, x.dq, x.pairs, &flat, hdr->dq_begin);
+  q_items(p, x.dq, x.pairs, L.n_dq_items, &flat, hdr->dq_begin);
   if ((int64_t)flat.size() != L.n_dq_items) { set_error("internal: dQ item count mismatch"); return FCP_ERR_INVALID_ARG; }
   put(L.off_dq_items, flat);
   // ---- dK / dV: dependency lists per KV segment, one group per (KV segment, KV head)
   {
     const int G = p->n_q_heads / p->n_kv_heads;
     put(L.off_bwd_deps, x.deps);
-    std::vector<std::vector<BwdItem>> groups;
-    std::vector<int64_t> weight, gkey;
-    groups.reserve(x.kv.size() * p->n_kv_heads);
+    ItemGroups<BwdItem> groups;
+    groups.items.reserve(L.n_bwd_items);
     std::vector<int64_t> tile_w, tile_steps;
     for (const KvSeg& k : x.kv) {
       const int n_tiles = (int)ceil_div(k.len, kBwdTileN);
@@ -782,23 +795,19 @@ int fcp::build_queue_image(const fcp_problem* p, const Expanded& x, const WsLayo
         }
         if (tile_steps[t] + 3 > INT32_MAX) { set_error("too many steps in a backward work item"); return FCP_ERR_UNSUPPORTED; }
       }
+      const int64_t w = std::accumulate(tile_w.begin(), tile_w.end(), (int64_t)0);
       for (int g = 0; g < p->n_kv_heads; g++) {
-        std::vector<BwdItem> items;
-        int64_t w = 0;
         for (int t = 0; t < n_tiles; t++) {            // earlier tiles of a DIAG pair are heavier
           const int off = t * kBwdTileN;
-          items.push_back({k.start + off, std::min(kBwdTileN, k.len - off), off, k.dep_begin, k.n_deps, g, k.len, (int32_t)((tile_steps[t] + 3) & ~1),
-                           k.n_deps > 0 ? x.deps[k.dep_begin] : BwdDep{0, 0, 0, 0}});
-          w += tile_w[t];
+          groups.items.push_back({k.start + off, std::min(kBwdTileN, k.len - off), off, k.dep_begin, k.n_deps, g, k.len, (int32_t)((tile_steps[t] + 3) & ~1),
+                                  k.n_deps > 0 ? x.deps[k.dep_begin] : BwdDep{0, 0, 0, 0}});
         }
-        groups.push_back(std::move(items));
-        weight.push_back(w);
-        gkey.push_back((int64_t)k.seq * p->n_kv_heads + g);
+        groups.close_unit(w, (int64_t)k.seq * p->n_kv_heads + g);
       }
     }
-    merge_groups_by_key(groups, weight, gkey, 1);
+    groups.merge(1);
     std::vector<BwdItem> bwd;
-    spread_over_xcds(groups, weight, &bwd, hdr->bwd_begin);
+    groups.spread_over_xcds(&bwd, hdr->bwd_begin);
     if ((int64_t)bwd.size() != L.n_bwd_items) { set_error("internal: backward item count mismatch"); return FCP_ERR_INVALID_ARG; }
     put(L.off_bwd_items, bwd);
   }
