@@ -678,3 +678,23 @@ def test_packed_blocks_of_many_tiny_sequences(seed):
     wl = workloads.custom_workload(lens, bs, causal, 2, hq, hkv, d, seed=900 + seed, name=f"tiny-members-{seed}")
     _packed_parity(wl, F32 | 16)
     _packed_parity(wl, F32)
+
+
+WAVE_EDGES = [
+    # seq_lens, block, causal, c, Hq, Hkv, d: where a wave's share of an item, the queue draws or the row staging change form
+    ([1, 31, 32, 33, 63, 64, 65, 95, 96, 97, 127, 129, 160, 193, 257], 512, 1, 0, 4, 2, 128),   # rows and visible tiles per wave
+    ([100, 128, 130, 300, 1], 128, 1, 0, 3, 1, 64),             # odd group: items without a second sub-tile
+    ([320, 384, 385, 448, 449, 512, 577], 1024, 1, 0, 2, 2, 128),   # items of 5 to 10 tiles: early and late ticket requests
+    ([320, 385, 449, 513], 1024, 0, 0, 4, 2, 64),               # the same without a diagonal
+    ([17], 128, 1, 0, 2, 1, 128),                               # one item: every other workgroup finds the queues dry
+    ([1500, 40], 128, 1, 2, 2, 1, 64),                          # one KV head: KV ranges, not sequences, go to the XCDs
+    ([33] * 150, 128, 1, 0, 8, 4, 64),                          # more items than compute units, one tile each
+]
+
+
+@pytest.mark.parametrize("spill", [0, 16])
+@pytest.mark.parametrize("case", range(len(WAVE_EDGES)))
+def test_wave_share_queue_and_staging_edges(case, spill):
+    lens, bs, causal, c, hq, hkv, d = WAVE_EDGES[case]
+    wl = workloads.custom_workload(lens, bs, causal, c, hq, hkv, d, seed=700 + case, name=f"wave-edge{case}")
+    _full_parity(wl, backward=True, flags=F32 | 2 | spill, partials=False)
