@@ -1647,7 +1647,7 @@ __global__ void __launch_bounds__(512, 2) dq_ds_kernel(BwdArgs a) {
   constexpr int STAGE = TBK + 8 * WDS;
   constexpr int NB = kDqDsBufs;
   constexpr int CPR = D / 8, RPI = 64 / CPR, NDMA = kFwdTileN / RPI / 8;
-  constexpr int DMA_PER_TILE = NDMA + WDS / 1024;
+  constexpr int DMA_PER_FRAG = kDsFragBytes / 1024;
   __shared__ __attribute__((aligned(1024))) unsigned char lds_st[NB][STAGE];
   __shared__ __attribute__((aligned(16))) int32_t s_rec[64];   // next item's record, as in fwd_kernel
   __shared__ int s_next;
@@ -1659,7 +1659,6 @@ __global__ void __launch_bounds__(512, 2) dq_ds_kernel(BwdArgs a) {
   const int group = a.n_q_heads / a.n_kv_heads;
   const int64_t q_row_stride = (int64_t)a.n_q_heads * D;
   const int64_t kv_row_stride = (int64_t)a.n_kv_heads * D;
-  const unsigned char* zeros = reinterpret_cast<const unsigned char*>(a.hdr->zeros);
   // K tile loads: as in the forward (rows past a ragged end repeat the last valid row: their dS is zero)
   uint32_t dma_row[NDMA], dma_chunk[NDMA];
 #pragma unroll
@@ -1729,13 +1728,16 @@ __global__ void __launch_bounds__(512, 2) dq_ds_kernel(BwdArgs a) {
     TileIter ti;
     ti.init(a.pairs, it);
     const int n_tiles = it.n_tiles;
-    // The load of one tile: describe() = scalar bookkeeping, issue() = branch-free requests.
+    // The load of one tile: describe() = scalar bookkeeping, issue() = the requests, which counts them: nothing past the
+    // item's end, and of the wave's two fragments only those its rows can see (a third of the loads of 16-256 token
+    // sequences were neither; this pass over them, 65536 tokens, GQA 32/8, d = 128: 375 -> 352 us).
     uint64_t d_k = 0, d_ds = 0;
     uint32_t d_lim = 0;
     int d_vis = 0;                  // columns of the tile that this wave's rows can see (0 .. 64)
+    bool d_have = false;            // there is such a tile
+    int n_req = 0;                  // load instructions of the tile requested last
     auto describe = [&]() {
-      d_k = reinterpret_cast<uint64_t>(zeros); d_lim = 0; d_vis = 0;
-      d_ds = reinterpret_cast<uint64_t>(a.ds);
+      d_have = ti.more; d_vis = 0;
       if (ti.more) {
         const int64_t row0 = (int64_t)(ti.cur.kv_start + ti.c0) * kv_row_stride;
         d_k = reinterpret_cast<uint64_t>(kbase + row0);
@@ -1757,14 +1759,24 @@ __global__ void __launch_bounds__(512, 2) dq_ds_kernel(BwdArgs a) {
     };
     auto issue = [&]() {
       const uint32_t lbase = lds_addr(lds_st[0]) + b_dma * STAGE;
+      n_req = 0;
+      if (d_have) {
 #pragma unroll
-      for (int n = 0; n < NDMA; n++) {
-        const uint32_t voff = min(dma_row[n], d_lim) + dma_chunk[n];
-        lds_dma16_s(reinterpret_cast<const unsigned char*>(d_k), voff, lbase + (8 * n + wave) * 1024);
+        for (int n = 0; n < NDMA; n++) {
+          const uint32_t voff = min(dma_row[n], d_lim) + dma_chunk[n];
+          lds_dma16_s(reinterpret_cast<const unsigned char*>(d_k), voff, lbase + (8 * n + wave) * 1024);
+        }
+        n_req = NDMA;
+#pragma unroll
+        for (int f = 0; f < 2; f++) {
+          if (d_vis > 32 * f) {
+#pragma unroll
+            for (int n = DMA_PER_FRAG * f; n < DMA_PER_FRAG * (f + 1); n++)
+              lds_dma16_s(reinterpret_cast<const unsigned char*>(d_ds), (uint32_t)(1024 * n + 16 * lane), lbase + TBK + wave * WDS + 1024 * n);
+            n_req += DMA_PER_FRAG;
+          }
+        }
       }
-#pragma unroll
-      for (int n = 0; n < WDS / 1024; n++)
-        lds_dma16_s(reinterpret_cast<const unsigned char*>(d_ds), (uint32_t)(1024 * n + 16 * lane), lbase + TBK + wave * WDS + 1024 * n);
       b_dma = (b_dma == NB - 1) ? 0 : b_dma + 1;
     };
     // prologue: tiles 0 and 1 of the item into the stage to be read first and the one after it
@@ -1779,10 +1791,13 @@ __global__ void __launch_bounds__(512, 2) dq_ds_kernel(BwdArgs a) {
       if (nx >= 0) fetch_item(a.dq_items, nx, s_rec, lane);
     };
     for (int t = 0; t < n_tiles; t++) {
-      // tile t has landed once at most one tile's loads are in flight; the barrier also says that every wave
+      // tile t has landed once only the loads of tile t + 1 are in flight; the barrier also says that every wave
       // is done with the stage that tile t + 2 goes into
-      __builtin_amdgcn_s_waitcnt(0x0F70 | (DMA_PER_TILE & 15) | ((DMA_PER_TILE >> 4) << 14));
-      __syncthreads();
+      if (n_req == NDMA + 2 * DMA_PER_FRAG) __builtin_amdgcn_s_waitcnt(0x0F70 | (NDMA + 2 * DMA_PER_FRAG));
+      else if (n_req == NDMA + DMA_PER_FRAG) __builtin_amdgcn_s_waitcnt(0x0F70 | (NDMA + DMA_PER_FRAG));
+      else if (n_req == NDMA) __builtin_amdgcn_s_waitcnt(0x0F70 | NDMA);
+      else dma_wait();
+      lds_barrier();
       describe(); issue(); vis[2] = d_vis;
       if (wave == 0) {
         if (n_tiles - t == 4) items.request(lane);
@@ -1808,7 +1823,7 @@ __global__ void __launch_bounds__(512, 2) dq_ds_kernel(BwdArgs a) {
       advance_read_stage();
     }
     if (wave == 0 && n_tiles == 0) next_item();
-    dma_wait();          // the two look-ahead requests past the end of the item
+    dma_wait();          // the next item's record
     lds_barrier();       // publishes the next item's record
     // the stage read last serves as the waves' staging areas: the next item's first two tiles go into the other two
     unsigned char* stage = lds_st[(b_c + NB - 1) % NB] + wave * kStageBytes;
