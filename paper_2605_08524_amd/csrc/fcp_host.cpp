@@ -213,6 +213,14 @@ static int64_t q_items_of(const QSeg& s, int n_q_heads, int G) {
   return (G % 2 == 0) ? n_tiles * (n_q_heads / 2) : ceil_div(n_tiles, 2) * n_q_heads;
 }
 
+size_t static_plan_bytes(const fcp_problem* p) {
+  int64_t items = 0;
+  for (int s = 0; s < p->n_slots; s++)
+    items += q_items_of(QSeg{0, p->q_blocks[p->slots[s].q_blk].tok_len, 0, 0, 0, 0, 0, 0}, p->n_q_heads, p->n_q_heads / p->n_kv_heads);
+  auto align = [](size_t x) { return (x + 255) & ~(size_t)255; };
+  return align(sizeof(WsHeader)) + align(16 * (size_t)std::max(1, p->n_pairs)) + align(72 * (size_t)std::max<int64_t>(1, items));
+}
+
 int compute_layout(const fcp_problem* p, WsLayout* L) {
   Expanded x;
   expand_problem(p, &x);

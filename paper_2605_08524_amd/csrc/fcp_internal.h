@@ -94,6 +94,8 @@ int compute_layout(const fcp_problem* p, const Expanded& x, WsLayout* L);
 // the layout of a problem on a workspace: from the registry that fcp_queue_build fills, else validated and computed
 int layout_for(const fcp_problem* p, const void* workspace, WsLayout* L);   // host
 void remember_layout(const fcp_problem* p, const void* workspace, const WsLayout& L);
+// what limits fcp_block_attn_fwd_static: header, 16 bytes per pair and 72 per forward item of the plan's query blocks
+size_t static_plan_bytes(const fcp_problem* p);
 void set_error(const char* fmt, ...);
 int build_queue_image(const fcp_problem* p, const Expanded& x, const WsLayout& L, bool forward_only, std::vector<unsigned char>* image);  // host
 

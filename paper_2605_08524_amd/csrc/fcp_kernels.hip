@@ -1931,7 +1931,9 @@ extern "C" int fcp_block_attn_fwd(const fcp_problem* p, const void* q, const voi
 
 // ---- forward without any allocation: the queue tables live in a fixed device array ----
 namespace fcp {
-constexpr size_t kStaticScratchBytes = 2u << 20;
+// A call is limited by the tables of its plan as given (static_plan_bytes, 2 MiB); the array is larger because a packed
+// block's members become items of their own (8 times the plan's tables covers members of 20 tokens and more).
+constexpr size_t kStaticPlanBytes = 2u << 20, kStaticScratchBytes = 16u << 20;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 // Device address of `scratch` on each device (the array's name is a host-side stand-in, not an
 // address a kernel can use; every device holds its own copy at its own address).
@@ -1969,9 +1971,12 @@ extern "C" int fcp_block_attn_fwd_static(const fcp_problem* p, const void* q, co
   WsLayout L;
   rc = compute_layout(p, x, &L);
   if (rc) return rc;
-  if (L.off_bwd_deps > kStaticScratchBytes) {
+  const size_t plan_bytes = static_plan_bytes(p);
+  if (plan_bytes > kStaticPlanBytes || L.off_bwd_deps > kStaticScratchBytes) {
+    const bool plan = plan_bytes > kStaticPlanBytes;
     set_error("fcp_block_attn_fwd_static: the forward's queue tables need %zu bytes, the fixed scratch array holds %zu "
-              "(use fcp_queue_build + fcp_block_attn_fwd with a workspace of your own)", L.off_bwd_deps, kStaticScratchBytes);
+              "(use fcp_queue_build + fcp_block_attn_fwd with a workspace of your own)", plan ? plan_bytes : L.off_bwd_deps,
+              plan ? kStaticPlanBytes : kStaticScratchBytes);
     return FCP_ERR_BUFFER_TOO_SMALL;
   }
   if (L.n_fwd_items == 0) return FCP_OK;
