@@ -1822,7 +1822,10 @@ __global__ void __launch_bounds__(512, 2) dq_ds_kernel(BwdArgs a) {
       vis[0] = vis[1]; vis[1] = vis[2];
       advance_read_stage();
     }
-    if (wave == 0 && n_tiles == 0) next_item();
+    if (n_tiles == 0) {      // no tile barrier since the waves read this item's index and record, which next_item() overwrites
+      lds_barrier();
+      if (wave == 0) next_item();
+    }
     dma_wait();          // the next item's record
     lds_barrier();       // publishes the next item's record
     // the stage read last serves as the waves' staging areas: the next item's first two tiles go into the other two

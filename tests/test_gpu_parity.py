@@ -698,3 +698,73 @@ def test_wave_share_queue_and_staging_edges(case, spill):
     lens, bs, causal, c, hq, hkv, d = WAVE_EDGES[case]
     wl = workloads.custom_workload(lens, bs, causal, c, hq, hkv, d, seed=700 + case, name=f"wave-edge{case}")
     _full_parity(wl, backward=True, flags=F32 | 2 | spill, partials=False)
+
+
+NO_SLOT = [
+    # seq_lens, block, causal, c, Hq, Hkv, d, n (only every n-th query block keeps its slots, from the first or the second on), first
+    ([300] * 40 + [77, 640], 128, 1, 2, 8, 4, 64, 2, 0),        # items with and without tiles in turn, more than compute units
+    ([300] * 40 + [77, 640], 128, 1, 2, 8, 4, 64, 2, 1),
+    ([900, 50, 1300, 256], 128, 1, 1, 8, 2, 128, 5, 1),         # most items without tiles
+    ([700, 333, 129], 128, 0, 2, 6, 2, 64, 3, 0),               # odd group, full pairs
+    ([260], 128, 1, 0, 2, 1, 128, 8, 1),                        # no slot at all
+]
+
+
+@pytest.mark.parametrize("spill", [0, 16])
+@pytest.mark.parametrize("case", range(len(NO_SLOT)))
+def test_query_blocks_without_slots(case, spill):
+    """Tables may hold query blocks without a slot (fcp_stage_tables makes such tables) and KV blocks that no pair names:
+    their work items have no tiles or steps.  O, dQ, dK, dV are exactly 0 and LSE is -inf there; everything else is what
+    the oracle gives for the blocks that have slots."""
+    from paper_2605_08524_amd import binding as B
+    from paper_2605_08524_amd.harness import to_dev_bf16
+    lens, bs, causal, c, hq, hkv, d, n, first = NO_SLOT[case]
+    wl = workloads.custom_workload(lens, bs, causal, c, hq, hkv, d, seed=800 + case, name=f"no-slot{case}")
+    _say(f"case {wl.name} spill={spill}")
+    dev = torch.device("cuda:0")
+    plan = dict(B.fcp_plan_blocks(wl.seq_lens, bs, causal, c))
+    keep = np.arange(len(plan["q_blocks"])) % n == first
+    slots, pairs = [], []
+    for q_blk, pair_begin, n_pairs, row_start in plan["slots"]:
+        if keep[q_blk]:
+            slots.append((q_blk, len(pairs), n_pairs, row_start))
+            pairs += [(p[0], p[1], p[2], len(slots) - 1) for p in plan["pairs"][pair_begin:pair_begin + n_pairs]]
+    plan["slots"] = np.asarray(slots, dtype=np.int32).reshape(-1, 4)
+    plan["pairs"] = np.asarray(pairs, dtype=np.int32).reshape(-1, 4)
+    prob = B.Problem(plan, hq, hkv, d, bs, 0.0, F32 | spill)
+    nbytes = B.fcp_workspace_bytes(prob)
+    ws = torch.full((nbytes + 256,), 0xFF, dtype=torch.uint8, device=dev)
+    ws_ptr = ws.data_ptr() + (-ws.data_ptr()) % 256
+    B.fcp_queue_build(prob, ws_ptr, nbytes)
+    q, k, v, d_o = (to_dev_bf16(x, dev) for x in (wl.q(), wl.k(), wl.v(), wl.d_o()))
+    nan = lambda *shape: torch.full(shape, float("nan"), dtype=torch.float32, device=dev)
+    o_part, lse_part = nan(max(1, prob.n_slot_rows), hq, d), nan(max(1, prob.n_slot_rows), hq)
+    o, lse, dq = nan(prob.t_q, hq, d), nan(prob.t_q, hq), nan(prob.t_q, hq, d)
+    dk, dv = nan(prob.t_kv, hkv, d), nan(prob.t_kv, hkv, d)
+    for _ in range(2):
+        for t in (dq, dk, dv):
+            t.fill_(float("nan"))
+        B.fcp_block_attn_fwd(prob, q, k, v, o_part, lse_part, ws_ptr)
+        B.fcp_merge_partials(prob, o_part, lse_part, o, lse, ws_ptr)
+        B.fcp_block_attn_bwd(prob, q, k, v, o, lse, d_o, dq, dk, dv, ws_ptr)
+        torch.cuda.synchronize(dev)
+    got = {name: t.cpu().numpy() for name, t in (("o", o), ("lse", lse), ("dq", dq), ("dk", dk), ("dv", dv))}
+    row_kept = np.repeat(keep, plan["q_blocks"][:, 3])
+    for name in ("o", "dq"):
+        assert np.all(got[name][~row_kept] == 0.0), name
+    assert np.all(np.isneginf(got["lse"][~row_kept]))
+    kv_named = np.zeros(len(plan["kv_blocks"]), dtype=bool)
+    kv_named[plan["pairs"][:, 1]] = True
+    kv_named = np.repeat(kv_named, plan["kv_blocks"][:, 3])
+    for name in ("dk", "dv"):
+        assert np.all(got[name][~kv_named] == 0.0), name
+    if not keep.any():
+        return
+    owned = [tuple(b) for b in plan["q_blocks"][keep, :2].tolist()]
+    o_ref, lse_ref = orc.worker_fwd(wl.q()[row_kept], wl.k(), wl.v(), wl.seq_lens, bs, causal, owned)
+    _check("o", got["o"][row_kept], o_ref)
+    _check_lse("lse", got["lse"][row_kept], lse_ref)
+    ref = orc.worker_bwd(wl.q()[row_kept], wl.k(), wl.v(), wl.d_o()[row_kept], wl.seq_lens, bs, causal, owned)
+    _check("dq", got["dq"][row_kept], ref[0])
+    _check("dk", got["dk"], ref[1])
+    _check("dv", got["dv"], ref[2])
