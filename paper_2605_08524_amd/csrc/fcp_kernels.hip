@@ -1728,17 +1728,18 @@ __global__ void __launch_bounds__(512, 2) dq_ds_kernel(BwdArgs a) {
     TileIter ti;
     ti.init(a.pairs, it);
     const int n_tiles = it.n_tiles;
-    // The load of one tile: describe() = scalar bookkeeping, issue() = the requests, which counts them: nothing past the
-    // item's end, and of the wave's two fragments only those its rows can see (a third of the loads of 16-256 token
-    // sequences were neither; this pass over them, 65536 tokens, GQA 32/8, d = 128: 375 -> 352 us).
+    // The load of one tile: describe() = scalar bookkeeping, issue() = the requests.  Up to the last four tiles of an item a
+    // tile is requested whole, without a branch: branches on what a wave's rows can see and on the count to wait for made
+    // long items 20 % slower (end of a 37133-token sequence, heads 2/1, d = 64: 741 us, without them 627).  The last four
+    // are requested as needed: nothing past the item's end, and of the wave's two fragments only those its rows can see (a
+    // third of the loads of 16-256 token sequences were neither; 65536 tokens, GQA 32/8, d = 128: 375 -> 352 us).
     uint64_t d_k = 0, d_ds = 0;
     uint32_t d_lim = 0;
-    int d_vis = 0;                  // columns of the tile that this wave's rows can see (0 .. 64)
-    bool d_have = false;            // there is such a tile
-    int n_req = 0;                  // load instructions of the tile requested last
-    auto describe = [&]() {
-      d_have = ti.more; d_vis = 0;
-      if (ti.more) {
+    int d_vis = 0;                  // columns of the tile that this wave's rows can see (0 .. 64); -1: there is no such tile
+    int req = 0;                    // d_vis of the tile requested last (64: it was requested whole)
+    auto describe = [&](auto exists) {
+      d_vis = -1;
+      if (exists || ti.more) {
         const int64_t row0 = (int64_t)(ti.cur.kv_start + ti.c0) * kv_row_stride;
         d_k = reinterpret_cast<uint64_t>(kbase + row0);
         const int valid = min(kFwdTileN, ti.cur.kv_len - ti.c0);
@@ -1757,52 +1758,51 @@ __global__ void __launch_bounds__(512, 2) dq_ds_kernel(BwdArgs a) {
         ti.advance();
       }
     };
-    auto issue = [&]() {
+    auto issue = [&](auto whole) {
       const uint32_t lbase = lds_addr(lds_st[0]) + b_dma * STAGE;
-      n_req = 0;
-      if (d_have) {
+      auto k_rows = [&]() {
 #pragma unroll
         for (int n = 0; n < NDMA; n++) {
           const uint32_t voff = min(dma_row[n], d_lim) + dma_chunk[n];
           lds_dma16_s(reinterpret_cast<const unsigned char*>(d_k), voff, lbase + (8 * n + wave) * 1024);
         }
-        n_req = NDMA;
+      };
+      auto fragment = [&](int f) {
 #pragma unroll
-        for (int f = 0; f < 2; f++) {
-          if (d_vis > 32 * f) {
-#pragma unroll
-            for (int n = DMA_PER_FRAG * f; n < DMA_PER_FRAG * (f + 1); n++)
-              lds_dma16_s(reinterpret_cast<const unsigned char*>(d_ds), (uint32_t)(1024 * n + 16 * lane), lbase + TBK + wave * WDS + 1024 * n);
-            n_req += DMA_PER_FRAG;
-          }
-        }
-      }
+        for (int n = DMA_PER_FRAG * f; n < DMA_PER_FRAG * (f + 1); n++)
+          lds_dma16_s(reinterpret_cast<const unsigned char*>(d_ds), (uint32_t)(1024 * n + 16 * lane), lbase + TBK + wave * WDS + 1024 * n);
+      };
+      req = whole ? kFwdTileN : d_vis;
+      if (whole || d_vis > 32) { k_rows(); fragment(0); fragment(1); }
+      else if (d_vis >= 0) { k_rows(); if (d_vis > 0) fragment(0); }
       b_dma = (b_dma == NB - 1) ? 0 : b_dma + 1;
     };
+    const std::true_type yes;
+    const std::false_type no;
     // prologue: tiles 0 and 1 of the item into the stage to be read first and the one after it
     int vis[3];
     b_dma = b_c;
-    describe(); issue(); vis[0] = d_vis;
-    describe(); issue(); vis[1] = d_vis;
-    if (wave == 0 && n_tiles < 4) items.request(lane);
+    if (n_tiles > 4) {
+      describe(yes); issue(yes); vis[0] = d_vis;
+      describe(yes); issue(yes); vis[1] = d_vis;
+    } else {
+      describe(no); issue(no); vis[0] = d_vis;
+      describe(no); issue(no); vis[1] = d_vis;
+    }
     auto next_item = [&]() {             // wave 0, see fwd_kernel
       const int nx = items.take(lane);
       if (lane == 0) s_next = nx;
       if (nx >= 0) fetch_item(a.dq_items, nx, s_rec, lane);
     };
-    for (int t = 0; t < n_tiles; t++) {
-      // tile t has landed once only the loads of tile t + 1 are in flight; the barrier also says that every wave
-      // is done with the stage that tile t + 2 goes into
-      if (n_req == NDMA + 2 * DMA_PER_FRAG) __builtin_amdgcn_s_waitcnt(0x0F70 | (NDMA + 2 * DMA_PER_FRAG));
-      else if (n_req == NDMA + DMA_PER_FRAG) __builtin_amdgcn_s_waitcnt(0x0F70 | (NDMA + DMA_PER_FRAG));
-      else if (n_req == NDMA) __builtin_amdgcn_s_waitcnt(0x0F70 | NDMA);
+    auto arrive = [&](auto whole) {
+      // the tile to be computed has landed once only the loads of the next one are in flight (those of a whole tile; if it has
+      // fewer, both are waited for); the barrier also says that every wave is done with the stage that the tile after next goes into
+      if (whole || req > 32) __builtin_amdgcn_s_waitcnt(0x0F70 | (NDMA + 2 * DMA_PER_FRAG));
       else dma_wait();
       lds_barrier();
-      describe(); issue(); vis[2] = d_vis;
-      if (wave == 0) {
-        if (n_tiles - t == 4) items.request(lane);
-        if (n_tiles - t == 1) next_item();
-      }
+      describe(whole); issue(whole); vis[2] = d_vis;
+    };
+    auto compute = [&]() {
       const int nv = __builtin_amdgcn_readfirstlane(vis[0]);
 #pragma unroll
       for (int f = 0; f < 2; f++) {
@@ -1821,11 +1821,17 @@ __global__ void __launch_bounds__(512, 2) dq_ds_kernel(BwdArgs a) {
       }
       vis[0] = vis[1]; vis[1] = vis[2];
       advance_read_stage();
-    }
-    if (n_tiles == 0) {      // no tile barrier since the waves read this item's index and record, which next_item() overwrites
-      lds_barrier();
-      if (wave == 0) next_item();
-    }
+    };
+    // The next item's ticket is drawn 4 tiles before the end (no test for it per tile: the queue's bookkeeping inside the
+    // loop slows every tile of a long item), its record behind the barrier of the last tile: until then a wave may not have
+    // read this item's index and record, which next_item() overwrites.  An item without tiles has a barrier for that alone.
+    int t = 0;
+    for (; t < n_tiles - 4; t++) { arrive(yes); compute(); }
+    if (wave == 0) items.request(lane);
+    for (; t < n_tiles - 1; t++) { arrive(no); compute(); }
+    if (n_tiles > 0) arrive(no); else lds_barrier();
+    if (wave == 0) next_item();
+    compute();
     dma_wait();          // the next item's record
     lds_barrier();       // publishes the next item's record
     // the stage read last serves as the waves' staging areas: the next item's first two tiles go into the other two
