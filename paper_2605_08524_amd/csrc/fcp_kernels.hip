@@ -1170,40 +1170,43 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
 #pragma unroll
       for (int jw = 0; jw < 4; jw++) aop[jw] = fetch_a(jw);
       next_tile();
-      if (wave == 4 && n_iv < 6) items.request(lane);
-      for (int iv = 0; iv < n_iv; iv++) {
+      // Down to 6 intervals before the end, to 2, to 0: a test for the next item in every interval costs long items 3-8 %
+      // (14 query blocks of a 19429-token sequence, heads 3/1, d = 128: 1412 -> 1305 us).
+      for (int iv = 0, left = 6; left >= 0; left = left == 6 ? 2 : left - 2) {
+        for (; iv < n_iv - left; iv++) {
+          const uint32_t hb_src = hsrc + hb * (4 * 4096);
+          // MFMA u = (2j + w) * NN + n reads operand (w ? 2 : 0) + j of KV group n0 + n
+          auto fetch_b = [&](int u) {
+            const int jw = u / NN, n = u % NN;
+            return lds_read16(hb_src + n * 4096 + (((jw & 1) ? 2 : 0) + (jw >> 1)) * 1024);
+          };
+          u32x4 bop[PFC];
+#pragma unroll
+          for (int u = 0; u < PFC; u++) bop[u] = fetch_b(u);
+#pragma unroll
+          for (int u = 0; u < NS; u++) {
+            const int jw = u / NN, n = u % NN;
+            if ((jw & 1) == 0) acc_v[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(aop[jw]), as_bf16x8(bop[u % PFC]), acc_v[n], 0, 0, 0);
+            else acc_k[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(aop[jw]), as_bf16x8(bop[u % PFC]), acc_k[n], 0, 0, 0);
+            if (u + PFC < NS) bop[u % PFC] = fetch_b(u + PFC);
+            if (n == NN - 1) aop[jw] = fetch_a(jw);
+            if (u == NS / 2) issue();
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          next_tile();
+          __builtin_amdgcn_s_waitcnt(0x0F70 | ((2 * DMA_PER_STEP) & 15) | (((2 * DMA_PER_STEP) >> 4) << 14));
+          asm volatile("s_barrier" ::: "memory");
+          describe();
+          hb ^= 1;
+        }
         if (wave == 4) {                 // the next item (every wave has read this one's record)
-          if (n_iv - iv == 6) items.request(lane);
-          if (n_iv - iv == 2) {
+          if (left == 6) items.request(lane);
+          if (left == 2) {
             const int nx = items.take(lane);
             if (lane == 0) s_next = nx;
             if (nx >= 0) fetch_item(a.items, nx, s_rec, lane);
           }
         }
-        const uint32_t hb_src = hsrc + hb * (4 * 4096);
-        // MFMA u = (2j + w) * NN + n reads operand (w ? 2 : 0) + j of KV group n0 + n
-        auto fetch_b = [&](int u) {
-          const int jw = u / NN, n = u % NN;
-          return lds_read16(hb_src + n * 4096 + (((jw & 1) ? 2 : 0) + (jw >> 1)) * 1024);
-        };
-        u32x4 bop[PFC];
-#pragma unroll
-        for (int u = 0; u < PFC; u++) bop[u] = fetch_b(u);
-#pragma unroll
-        for (int u = 0; u < NS; u++) {
-          const int jw = u / NN, n = u % NN;
-          if ((jw & 1) == 0) acc_v[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(aop[jw]), as_bf16x8(bop[u % PFC]), acc_v[n], 0, 0, 0);
-          else acc_k[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(aop[jw]), as_bf16x8(bop[u % PFC]), acc_k[n], 0, 0, 0);
-          if (u + PFC < NS) bop[u % PFC] = fetch_b(u + PFC);
-          if (n == NN - 1) aop[jw] = fetch_a(jw);
-          if (u == NS / 2) issue();
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        next_tile();
-        __builtin_amdgcn_s_waitcnt(0x0F70 | ((2 * DMA_PER_STEP) & 15) | (((2 * DMA_PER_STEP) >> 4) << 14));
-        asm volatile("s_barrier" ::: "memory");
-        describe();
-        hb ^= 1;
       }
       b_c = (b_c == 0) ? NB - 1 : b_c - 1;     // the tile looked ahead to belongs to the next item's first interval
       dma_wait();
@@ -1523,10 +1526,8 @@ __global__ void __launch_bounds__(512, 2) dq_kernel(BwdArgs a) {
     };
     DevPair tp = ti.cur;
     int tc0 = 0;
-    bool have = ti.more;
-    if (have) { dma(buf); ti.advance(); }
+    if (ti.more) { dma(buf); ti.advance(); }
     int left = it.n_tiles;
-    if (wave == 0 && left < 3) items.request(lane);
     dma_wait();
     __syncthreads();
     auto next_item = [&]() {             // wave 0, see fwd_kernel
@@ -1534,83 +1535,86 @@ __global__ void __launch_bounds__(512, 2) dq_kernel(BwdArgs a) {
       if (lane == 0) s_next = nx;
       if (nx >= 0) fetch_item(a.dq_items, nx, s_rec, lane);
     };
-    if (!have) {                         // no tile barrier to publish the next item
-      if (wave == 0) next_item();
+    if (left == 0) {                     // no tile barrier to publish the next item
+      if (wave == 0) { items.request(lane); next_item(); }
       dma_wait();
       __syncthreads();
     }
-    while (have) {
-      if (wave == 0) {
-        if (left == 3) items.request(lane);
-        if (left == 1) next_item();
-      }
-      left--;
-      const DevPair np = ti.cur;
-      const int nc0 = ti.c0;
-      const bool nhave = ti.more;
-      if (nhave) { dma(buf ^ 1); ti.advance(); }
+    // Down to 3 tiles, to 1, to 0: a test for the next item at every tile costs long items 3-5 % (end of a 103755-token
+    // sequence, 2 heads, d = 128: 2267 -> 2161 us).
+    for (int stop = 3; stop >= 0; stop = stop == 3 ? 1 : stop - 1) {
+      for (; left > stop; left--) {
+        const DevPair np = ti.cur;
+        const int nc0 = ti.c0;
+        const bool nhave = ti.more;
+        if (nhave) { dma(buf ^ 1); ti.advance(); }
 
-      const bool diag = (tp.kind & 1) != 0;
-      if (wave_ok && !(diag && tc0 > wave_row_lo + 31)) {      // else nothing visible for this wave
-        // wave-uniform: tiles that straddle the diagonal, and tiles that hold a ragged end (their K rows past
-        // the end are zero in LDS, but S = 0 there still gives P = exp2(-LSE), which overflows for a row whose
-        // logits are all strongly negative; inf * 0 would then poison the whole dQ row)
-        const bool need_mask = (diag && tc0 + kFwdTileN - 1 > wave_row_lo) || tc0 + kFwdTileN > tp.kv_len;
-        const int limit = diag ? tile_off_q + my_row : tp.kv_len - 1;      // last visible column for this lane
-        // the two 32-row halves of the KV tile one after the other: half the live accumulators
+        const bool diag = (tp.kind & 1) != 0;
+        if (wave_ok && !(diag && tc0 > wave_row_lo + 31)) {      // else nothing visible for this wave
+          // wave-uniform: tiles that straddle the diagonal, and tiles that hold a ragged end (their K rows past
+          // the end are zero in LDS, but S = 0 there still gives P = exp2(-LSE), which overflows for a row whose
+          // logits are all strongly negative; inf * 0 would then poison the whole dQ row)
+          const bool need_mask = (diag && tc0 + kFwdTileN - 1 > wave_row_lo) || tc0 + kFwdTileN > tp.kv_len;
+          const int limit = diag ? tile_off_q + my_row : tp.kv_len - 1;      // last visible column for this lane
+          // the two 32-row halves of the KV tile one after the other: half the live accumulators
 #pragma unroll
-        for (int rt = 0; rt < 2; rt++) {
-          f32x16 s, dp;
+          for (int rt = 0; rt < 2; rt++) {
+            f32x16 s, dp;
 #pragma unroll
-          for (int r = 0; r < 16; r++) { s[r] = 0.f; dp[r] = 0.f; }
-          // K and V rows are requested PFQ k-chunks (2 PFQ MFMAs) before the MFMAs that use them; left to
-          // the compiler each read is issued one MFMA ahead and waited for in full (depths 1 .. 4 measured: 2)
-          constexpr int PFQ = 2;
-          u32x4 opk[PFQ], opv[PFQ];
+            for (int r = 0; r < 16; r++) { s[r] = 0.f; dp[r] = 0.f; }
+            // K and V rows are requested PFQ k-chunks (2 PFQ MFMAs) before the MFMAs that use them; left to
+            // the compiler each read is issued one MFMA ahead and waited for in full (depths 1 .. 4 measured: 2)
+            constexpr int PFQ = 2;
+            u32x4 opk[PFQ], opv[PFQ];
 #pragma unroll
-          for (int i = 0; i < PFQ; i++) {
-            opk[i] = lds_read16(row_off[i] + rt * 32 * (D * 2));
-            opv[i] = lds_read16(row_off[i] + rt * 32 * (D * 2) + TB);
-          }
-#pragma unroll
-          for (int kc = 0; kc < KC; kc++) {
-            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(opk[kc % PFQ]), qf[kc], s, 0, 0, 0);
-            dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(opv[kc % PFQ]), dof[kc], dp, 0, 0, 0);
-            if (kc + PFQ < KC) {
-              opk[kc % PFQ] = lds_read16(row_off[kc + PFQ] + rt * 32 * (D * 2));
-              opv[kc % PFQ] = lds_read16(row_off[kc + PFQ] + rt * 32 * (D * 2) + TB);
+            for (int i = 0; i < PFQ; i++) {
+              opk[i] = lds_read16(row_off[i] + rt * 32 * (D * 2));
+              opv[i] = lds_read16(row_off[i] + rt * 32 * (D * 2) + TB);
             }
-            __builtin_amdgcn_sched_barrier(0);
-          }
 #pragma unroll
-          for (int r = 0; r < 16; r++) s[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], a.scale_log2, -lse_l));
-          if (need_mask) {                    // wave-uniform: only tiles that straddle the diagonal
-#pragma unroll
-            for (int r = 0; r < 16; r++) {
-              const int c = tc0 + rt * 32 + 8 * (r >> 2) + 4 * g + (r & 3);
-              if (c > limit) s[r] = 0.f;
+            for (int kc = 0; kc < KC; kc++) {
+              s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(opk[kc % PFQ]), qf[kc], s, 0, 0, 0);
+              dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(opv[kc % PFQ]), dof[kc], dp, 0, 0, 0);
+              if (kc + PFQ < KC) {
+                opk[kc % PFQ] = lds_read16(row_off[kc + PFQ] + rt * 32 * (D * 2));
+                opv[kc % PFQ] = lds_read16(row_off[kc + PFQ] + rt * 32 * (D * 2) + TB);
+              }
+              __builtin_amdgcn_sched_barrier(0);
             }
-          }
 #pragma unroll
-          for (int r = 0; r < 16; r++) s[r] *= __builtin_fmaf(dp[r], a.scale, -dl_l);
+            for (int r = 0; r < 16; r++) s[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], a.scale_log2, -lse_l));
+            if (need_mask) {                    // wave-uniform: only tiles that straddle the diagonal
 #pragma unroll
-          for (int j = 0; j < 2; j++) {
-            u32x4 db;
+              for (int r = 0; r < 16; r++) {
+                const int c = tc0 + rt * 32 + 8 * (r >> 2) + 4 * g + (r & 3);
+                if (c > limit) s[r] = 0.f;
+              }
+            }
 #pragma unroll
-            for (int i = 0; i < 4; i++) db[i] = pack_bf16(s[8 * j + 2 * i], s[8 * j + 2 * i + 1]);
-            const uint32_t rows = (rt * 32 + 16 * j) * (D * 2);
+            for (int r = 0; r < 16; r++) s[r] *= __builtin_fmaf(dp[r], a.scale, -dl_l);
 #pragma unroll
-            for (int dt = 0; dt < DT; dt++) {
-              const bf16x8 kt = lds_tr_pair_at(tr_lo[dt] + rows, tr_hi[dt] + rows);
-              acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kt, as_bf16x8(db), acc[dt], 0, 0, 0);
+            for (int j = 0; j < 2; j++) {
+              u32x4 db;
+#pragma unroll
+              for (int i = 0; i < 4; i++) db[i] = pack_bf16(s[8 * j + 2 * i], s[8 * j + 2 * i + 1]);
+              const uint32_t rows = (rt * 32 + 16 * j) * (D * 2);
+#pragma unroll
+              for (int dt = 0; dt < DT; dt++) {
+                const bf16x8 kt = lds_tr_pair_at(tr_lo[dt] + rows, tr_hi[dt] + rows);
+                acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kt, as_bf16x8(db), acc[dt], 0, 0, 0);
+              }
             }
           }
         }
+        tp = np; tc0 = nc0;
+        dma_wait();
+        __syncthreads();
+        switch_buffer();
       }
-      tp = np; tc0 = nc0; have = nhave;
-      dma_wait();
-      __syncthreads();
-      switch_buffer();
+      if (wave == 0 && it.n_tiles > 0) {
+        if (stop == 3) items.request(lane);
+        if (stop == 1) next_item();
+      }
     }
     {
       const int64_t off = (int64_t)(q_start + wq * 32) * q_row_stride + (int64_t)head * D;
