@@ -218,7 +218,7 @@ size_t static_plan_bytes(const fcp_problem* p) {
   for (int s = 0; s < p->n_slots; s++)
     items += q_items_of(QSeg{0, p->q_blocks[p->slots[s].q_blk].tok_len, 0, 0, 0, 0, 0, 0}, p->n_q_heads, p->n_q_heads / p->n_kv_heads);
   auto align = [](size_t x) { return (x + 255) & ~(size_t)255; };
-  return align(sizeof(WsHeader)) + align(16 * (size_t)std::max(1, p->n_pairs)) + align(72 * (size_t)std::max<int64_t>(1, items));
+  return 1024 + align(16 * (size_t)std::max(1, p->n_pairs)) + align(72 * (size_t)std::max<int64_t>(1, items));
 }
 
 int compute_layout(const fcp_problem* p, WsLayout* L) {

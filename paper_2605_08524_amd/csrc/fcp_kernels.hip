@@ -258,54 +258,58 @@ template <int D> constexpr int tile_bytes(int rows) { return rows * D * 2; }
 __device__ __forceinline__ void retire(int32_t* counter, int32_t* done) {
   const int prev = atomicAdd(done, 1);
   if (prev == (int)gridDim.x - 1) {
-    for (int q = 0; q < kNumXcd; q++) atomicExch(&counter[q], 0);
+    for (int q = 0; q < kNumXcd; q++) atomicExch(&counter[q * kCounterStride], 0);
     atomicExch(done, 0);
   }
 }
 
-// The item sequence of one persistent workgroup.  Item indices are tickets of the eight XCD queues.  The first ticket of a workgroup is fixed by its block index: the chip hands
-// workgroups to the XCDs in turn, and no counter has to be asked before the first item starts.  The others come from the
-// queue of the XCD the workgroup runs on (hardware register XCC_ID) and, once that is dry, from the other queues.
-// request() asks for a ticket without waiting, take() turns it into an item index some tiles later; both near the end of
-// the current item (early draws unbalance the end of a launch), so that neither round trip is waited for.  Both are for
-// wave 0.  Every workgroup leaves its loop when all queues are dry.
+// The item sequence of one persistent workgroup.  Item indices are tickets of the eight XCD queues, drawn from the queue of
+// the XCD the workgroup runs on (hardware register XCC_ID) and, once that is dry, from the other queues.  No item belongs to
+// a workgroup that has not started: one that has to wait for a compute unit (another stream's kernel may hold it for long)
+// finds the queues dry.  First tickets by block index save 0.2-0.8 us of a launch on an idle chip, but where another stream
+// held 32 compute units the heaviest items then ran last: training step of an 8-worker share (103746 tokens, heads 9/3,
+// d = 128) 5220 us, drawn 4576; 16384 tokens, 16 heads, d = 64: 830 and 763.  request() asks for a ticket without waiting, take() turns it into an item index some tiles later;
+// both near the end of the current item (early draws unbalance the end of a launch).  Both are for one wave.  Every
+// workgroup leaves its loop when all queues are dry.
 struct ItemStream {
   int32_t* counter; const int32_t* begin;
   int ticket;
   bool dry;
   __device__ __forceinline__ static int home_queue() { return __builtin_amdgcn_s_getreg((3 << 11) | 20) & (kNumXcd - 1); }   // XCC_ID (id 20), bits [3:0]
-  __device__ __forceinline__ static int fixed(int q) { return ((int)gridDim.x + kNumXcd - 1 - q) / kNumXcd; }   // tickets of queue q given by block index
-  // the first item, or -1
+  // The first item, or -1.  The queue's bounds (lane 0: its begin, lane 1: its end) are in flight beside the ticket: one
+  // round trip to memory in front of the first record instead of two.
   __device__ __forceinline__ int start(int32_t* c, const int32_t* b, int lane) {
     counter = c; begin = b; ticket = 0; dry = false;
-    const int q = blockIdx.x % kNumXcd, t = blockIdx.x / kNumXcd;
-    const int b0 = begin[q], n = begin[q + 1] - b0;
-    return t < n ? b0 + t : steal(lane);
+    const int bounds = begin[home_queue() + (lane & 1)];
+    request(lane);
+    const int t = __builtin_amdgcn_readfirstlane(ticket), b0 = __builtin_amdgcn_readlane(bounds, 0);
+    if (t < __builtin_amdgcn_readlane(bounds, 1) - b0) return b0 + t;
+    dry = true;
+    return steal(lane);
   }
-  __device__ __forceinline__ void request(int lane) { if (!dry && lane == 0) ticket = atomicAdd(&counter[home_queue()], 1); }
+  __device__ __forceinline__ void request(int lane) { if (!dry && lane == 0) ticket = atomicAdd(&counter[home_queue() * kCounterStride], 1); }
   __device__ __forceinline__ int take(int lane) {
     if (!dry) {
-      const int home = home_queue(), b0 = begin[home], t = __builtin_amdgcn_readfirstlane(ticket) + fixed(home);
+      const int home = home_queue(), b0 = begin[home], t = __builtin_amdgcn_readfirstlane(ticket);
       if (t < begin[home + 1] - b0) return b0 + t;
       dry = true;
     }
     return steal(lane);
   }
   // Lane t looks at queue home + t: one round trip for all eight counters, a second one for a ticket if any is left.
-  // Asking one queue after the other put 5 us at the end of every launch (4000 tokens, d = 64, 144 items: forward
-  // kernel 28.7 -> 19.9 us together with the fixed first ticket and the prefetched record).
+  // Asking one queue after the other put 5 us at the end of every launch.
   __device__ __forceinline__ int steal(int lane) {
     const int home = home_queue(), q = (home + lane) % kNumXcd, b0 = begin[q];
-    const int n = begin[q + 1] - b0 - fixed(q);
-    uint64_t left = __builtin_amdgcn_ballot_w64(lane < kNumXcd && n > 0 && __hip_atomic_load(&counter[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < n);
+    const int n = begin[q + 1] - b0;
+    uint64_t left = __builtin_amdgcn_ballot_w64(lane < kNumXcd && n > 0 && __hip_atomic_load(&counter[q * kCounterStride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < n);
     while (left) {
       const int l = __builtin_ctzll(left);
       left &= left - 1;
       const int ql = (home + l) % kNumXcd;
       int i = 0;
-      if (lane == 0) i = atomicAdd(&counter[ql], 1);
+      if (lane == 0) i = atomicAdd(&counter[ql * kCounterStride], 1);
       i = __builtin_amdgcn_readfirstlane(i);
-      if (i < __builtin_amdgcn_readlane(n, l)) return __builtin_amdgcn_readlane(b0, l) + fixed(ql) + i;
+      if (i < __builtin_amdgcn_readlane(n, l)) return __builtin_amdgcn_readlane(b0, l) + i;
     }
     return -1;
   }
