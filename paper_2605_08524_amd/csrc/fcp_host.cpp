@@ -70,8 +70,10 @@ int validate_problem(const fcp_problem* p) {
   }
   // members of packed blocks: by (kv_blk, tok_off), tiling their block exactly
   std::vector<char> segmented;
+  std::vector<int32_t> first_seg;              // of each packed KV block
   if (p->n_segments) {
     segmented.assign(p->n_kv_blocks, 0);
+    first_seg.assign(p->n_kv_blocks, 0);
     int32_t blk = -1, covered = 0;
     for (int i = 0; i <= p->n_segments; i++) {
       if (i == p->n_segments || p->segments[i].kv_blk != blk) {
@@ -82,7 +84,7 @@ int validate_problem(const fcp_problem* p) {
         const int32_t nb = p->segments[i].kv_blk;
         if (nb <= blk || nb >= p->n_kv_blocks) { set_error("segments[%d]: kv_blk out of range or not ascending", i); return FCP_ERR_INVALID_ARG; }
         if (p->kv_blocks[nb].tok_len > kMaxPackedBlock) { set_error("segments[%d]: a packed block holds at most %d tokens", i, kMaxPackedBlock); return FCP_ERR_UNSUPPORTED; }
-        blk = nb; covered = 0; segmented[nb] = 1;
+        blk = nb; covered = 0; segmented[nb] = 1; first_seg[nb] = i;
       }
       const fcp_segment& sg = p->segments[i];
       if (sg.tok_off != covered || sg.tok_len <= 0 || (int64_t)sg.tok_off + sg.tok_len > p->kv_blocks[blk].tok_len) {
@@ -91,13 +93,23 @@ int validate_problem(const fcp_problem* p) {
       covered += sg.tok_len;
     }
   }
-  int prev_q = -1;
+  // the rows of a packed query block are cut up once: its PACKED pairs must join KV blocks with the same members
+  auto same_members = [&](int32_t a, int32_t b) {
+    for (int32_t i = first_seg[a], j = first_seg[b]; a != b; i++, j++) {
+      const bool in_a = i < p->n_segments && p->segments[i].kv_blk == a, in_b = j < p->n_segments && p->segments[j].kv_blk == b;
+      if (!in_a || !in_b) return in_a == in_b;
+      if (p->segments[i].tok_len != p->segments[j].tok_len) return false;
+    }
+    return true;
+  };
+  int prev_q = -1, packed_kv = -1;
   int64_t pair_cursor = 0;
   for (int s = 0; s < p->n_slots; s++) {
     const fcp_slot& sl = p->slots[s];
     if (sl.q_blk < 0 || sl.q_blk >= p->n_q_blocks || sl.q_blk < prev_q) {
       set_error("slots[%d]: q_blk out of range or not ascending", s); return FCP_ERR_INVALID_ARG;
     }
+    if (sl.q_blk != prev_q) packed_kv = -1;
     prev_q = sl.q_blk;
     if (sl.pair_begin != pair_cursor || sl.n_pairs < 0 || pair_cursor + sl.n_pairs > p->n_pairs) {
       set_error("slots[%d]: pair range must continue where the previous slot ended", s);
@@ -129,6 +141,13 @@ int validate_problem(const fcp_problem* p) {
       }
       if ((pr.kind & 2) && sl.n_pairs != 1) {
         set_error("pairs[%lld]: a packed query block has one pair", (long long)i); return FCP_ERR_INVALID_ARG;
+      }
+      if (pr.kind & 2) {
+        if (packed_kv >= 0 && !same_members(packed_kv, pr.kv_blk)) {
+          set_error("pairs[%lld]: the PACKED pairs of a query block must join KV blocks with the same members", (long long)i);
+          return FCP_ERR_INVALID_ARG;
+        }
+        packed_kv = pr.kv_blk;
       }
     }
   }

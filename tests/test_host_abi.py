@@ -282,6 +282,24 @@ def test_packed_block_size_limit():
     assert fcp.fcp_workspace_bytes(fcp.Problem(ok, 2, 2, 64, 70000)) > 0
 
 
+def test_packed_pairs_of_a_query_block_agree_on_its_members():
+    """Two PACKED slots of one query block are accepted only if their KV blocks have the same members (their rows are cut
+    up once): two listings of one packed block are, blocks cut differently are refused, in either order."""
+    def problem(first, second):
+        segments, kv = [], []
+        for b, members in enumerate((first, second)):
+            kv.append((0, 0, 8 * b, 8))
+            segments += [(b, m, sum(members[:m]), n) for m, n in enumerate(members)]
+        plan = dict(kv_blocks=kv, q_blocks=[(0, 0, 0, 8)], pairs=[(0, 0, 3, 0), (0, 1, 3, 1)], slots=[(0, 0, 1, 0), (0, 1, 1, 8)],
+                    n_slot_rows=16, segments=segments)
+        return fcp.Problem({k: v if k == "n_slot_rows" else np.asarray(v, dtype=np.int32) for k, v in plan.items()}, 2, 2, 64, 8)
+    assert fcp.fcp_workspace_bytes(problem([3, 5], [3, 5])) > 0
+    for members in (([2, 2, 2, 2], [4, 4]), ([4, 4], [2, 2, 2, 2]), ([3, 5], [5, 3])):
+        with pytest.raises(fcp.FcpError) as e:
+            fcp.fcp_workspace_bytes(problem(*members))
+        assert e.value.code == binding.FCP_ERR_INVALID_ARG
+
+
 @pytest.mark.parametrize("packed", [False, True])
 def test_queue_tables_are_built_on_the_host_before_any_gpu_call(packed):
     """Without a GPU, fcp_queue_build still validates the problem, lays out the workspace and builds every table (work
