@@ -155,62 +155,92 @@ int validate_problem(const fcp_problem* p) {
   return FCP_OK;
 }
 
-void expand_problem(const fcp_problem* p, Expanded* x) {
-  // members of each packed KV block: segments are by (kv_blk, tok_off)
-  std::vector<int32_t> seg_begin(p->n_kv_blocks + 1, 0);
-  for (int i = 0; i < p->n_segments; i++) seg_begin[p->segments[i].kv_blk + 1]++;
-  for (int b = 0; b < p->n_kv_blocks; b++) seg_begin[b + 1] += seg_begin[b];
-  auto n_members = [&](int kb) { return seg_begin[kb + 1] - seg_begin[kb]; };
-  std::vector<int32_t> slot_begin(p->n_q_blocks + 1, 0);       // slots of a query block are consecutive
-  for (int s = 0; s < p->n_slots; s++) slot_begin[p->slots[s].q_blk + 1]++;
-  for (int b = 0; b < p->n_q_blocks; b++) slot_begin[b + 1] += slot_begin[b];
-  const bool spill = (p->flags & FCP_FLAG_BWD_SPILL_DS) != 0, direct = (p->flags & FCP_FLAG_DIRECT_SINGLE) != 0;
+namespace {
 
+// Rows of a block that the kernels treat as one segment: all of a plain block, or one member of a packed one.
+struct Run { int32_t off, len, seq; };
+struct Runs { std::vector<Run> run; std::vector<int32_t> begin; };   // of KV block b: begin[b] .. begin[b + 1]
+
+// Rows of a query-stationary item: one row tile of two heads when the group size is even, else two row tiles of one head.
+int item_rows(const fcp_problem* p) { return kFwdTileM * ((p->n_q_heads / p->n_kv_heads) % 2 == 0 ? 1 : 2); }
+
+Runs make_runs(const fcp_problem* p) {
+  Runs r;
+  r.run.reserve(p->n_kv_blocks);
+  for (int b = 0, i = 0; b < p->n_kv_blocks; b++) {
+    r.begin.push_back((int32_t)r.run.size());
+    if (i == p->n_segments || p->segments[i].kv_blk != b) r.run.push_back({0, p->kv_blocks[b].tok_len, p->kv_blocks[b].seq});
+    for (; i < p->n_segments && p->segments[i].kv_blk == b; i++) {
+      const fcp_segment& sg = p->segments[i];
+      r.run.push_back({sg.tok_off, sg.tok_len, sg.seq});
+    }
+  }
+  r.begin.push_back((int32_t)r.run.size());
+  return r;
+}
+
+// f(query block, its slots s0 .. s1, its runs, n_runs, packed): the runs of its PACKED pairs' KV blocks (which all have the
+// same members), or one run of all its rows.
+template <class F>
+void for_q_blocks(const fcp_problem* p, const Runs& runs, F f) {
+  for (int b = 0, s = 0; b < p->n_q_blocks; b++) {
+    const int s0 = s;
+    int kb = -1;
+    for (; s < p->n_slots && p->slots[s].q_blk == b; s++)
+      if (p->slots[s].n_pairs == 1 && (p->pairs[p->slots[s].pair_begin].kind & 2)) kb = p->pairs[p->slots[s].pair_begin].kv_blk;
+    const Run whole = {0, p->q_blocks[b].tok_len, p->q_blocks[b].seq};
+    if (kb < 0) f(b, s0, s, &whole, 1, false);
+    else f(b, s0, s, &runs.run[runs.begin[kb]], runs.begin[kb + 1] - runs.begin[kb], true);
+  }
+}
+
+bool packed_slot(const fcp_problem* p, const fcp_slot& sl) { return sl.n_pairs == 1 && (p->pairs[sl.pair_begin].kind & 2); }
+
+int64_t q_items_of(const fcp_problem* p, int rows) {
+  return ceil_div(rows, item_rows(p)) * ((p->n_q_heads / p->n_kv_heads) % 2 == 0 ? p->n_q_heads / 2 : p->n_q_heads);
+}
+
+}  // namespace
+
+void expand_problem(const fcp_problem* p, bool forward_only, Expanded* x) {
+  const Runs runs = make_runs(p);
+  const bool spill = (p->flags & FCP_FLAG_BWD_SPILL_DS) != 0, direct = (p->flags & FCP_FLAG_DIRECT_SINGLE) != 0;
+  for (int b = 0; b < p->n_kv_blocks; b++)
+    for (int i = runs.begin[b]; i < runs.begin[b + 1]; i++)
+      x->kv.push_back({p->kv_blocks[b].tok_start + runs.run[i].off, runs.run[i].len, runs.run[i].seq, 0, 0});
   // query side: pairs (with the query rows and the KV segment each joins), forward and dQ segments
   struct Join { int32_t q_start, q_len, kv_seg; };
   std::vector<Join> joins;
-  std::vector<int32_t> kv_seg_of(p->n_kv_blocks);              // first KV segment of a block
-  for (int b = 0; b < p->n_kv_blocks; b++) {
-    const fcp_block& kb = p->kv_blocks[b];
-    kv_seg_of[b] = (int32_t)x->kv.size();
-    if (n_members(b) == 0) x->kv.push_back({kb.tok_start, kb.tok_len, kb.seq, 0, 0});
-    for (int m = seg_begin[b]; m < seg_begin[b + 1]; m++)
-      x->kv.push_back({kb.tok_start + p->segments[m].tok_off, p->segments[m].tok_len, p->segments[m].seq, 0, 0});
-  }
   int64_t frag = kDsSinkFrags;
-  auto add_pair = [&](int q_start, int q_len, int kv_seg, int kind) {
-    const KvSeg& k = x->kv[kv_seg];
-    x->pairs.push_back({k.start, k.len, kind, spill ? (int32_t)frag : 0});
-    joins.push_back({q_start, q_len, kv_seg});
-    x->kv[kv_seg].n_deps++;
-    frag += p->n_q_heads * ds_frags_per_head(kind, q_len, k.len);
-  };
-  for (int b = 0; b < p->n_q_blocks; b++) {
+  for_q_blocks(p, runs, [&](int b, int s0, int s1, const Run* run, int n_runs, bool packed) {
     const fcp_block& qb = p->q_blocks[b];
-    const int s0 = slot_begin[b], s1 = slot_begin[b + 1];
     const int to_final = (direct && s1 - s0 == 1) ? 1 : 0;
-    int packed_kv = -1;                                        // the KV block of its PACKED pair
-    for (int s = s0; s < s1; s++)
-      for (int i = p->slots[s].pair_begin; i < p->slots[s].pair_begin + p->slots[s].n_pairs; i++)
-        if (p->pairs[i].kind & 2) packed_kv = p->pairs[i].kv_blk;
-    // one query segment per member, the whole block if it has none; the pairs of a segment are consecutive
-    for (int m = 0; m < (packed_kv < 0 ? 1 : n_members(packed_kv)); m++) {
-      const int32_t off = packed_kv < 0 ? 0 : p->segments[seg_begin[packed_kv] + m].tok_off;
-      const int32_t len = packed_kv < 0 ? qb.tok_len : p->segments[seg_begin[packed_kv] + m].tok_len;
-      const int32_t seq = packed_kv < 0 ? qb.seq : p->segments[seg_begin[packed_kv] + m].seq;
-      const int32_t q0 = qb.tok_start + off, p0 = (int32_t)x->pairs.size();
+    // the pairs of a run are consecutive, for dQ
+    for (int m = 0; m < n_runs; m++) {
+      const int32_t q0 = qb.tok_start + run[m].off, p0 = (int32_t)x->pairs.size();
       for (int s = s0; s < s1; s++) {
         const fcp_slot& sl = p->slots[s];
-        x->fwd.push_back({q0, len, sl.row_start + off, (int32_t)x->pairs.size(), sl.n_pairs, seq, to_final, s - s0});
+        // a packed query block may have slots of FULL pairs too: the forward walks them once, with all rows of the block
+        const bool whole = packed && !packed_slot(p, sl);
+        if (!whole || m == 0)
+          x->fwd.push_back({whole ? qb.tok_start : q0, whole ? qb.tok_len : run[m].len, sl.row_start + (whole ? 0 : run[m].off),
+                            (int32_t)x->pairs.size(), sl.n_pairs, whole ? qb.seq : run[m].seq, to_final, s - s0});
+        else if (forward_only) continue;
         for (int i = sl.pair_begin; i < sl.pair_begin + sl.n_pairs; i++) {
           const fcp_pair& pr = p->pairs[i];
-          add_pair(q0, len, kv_seg_of[pr.kv_blk] + ((pr.kind & 2) ? m : 0), pr.kind & 1);
+          const int32_t seg = runs.begin[pr.kv_blk] + ((pr.kind & 2) ? m : 0);
+          KvSeg& k = x->kv[seg];
+          const int kind = pr.kind & 1;
+          x->pairs.push_back({k.start, k.len, kind, spill ? (int32_t)frag : 0});
+          joins.push_back({q0, run[m].len, seg});
+          k.n_deps++;
+          frag += p->n_q_heads * ds_frags_per_head(kind, run[m].len, k.len);
         }
       }
-      x->dq.push_back({q0, len, q0, p0, (int32_t)x->pairs.size() - p0, seq, 0, 0});
+      x->dq.push_back({q0, run[m].len, q0, p0, (int32_t)x->pairs.size() - p0, run[m].seq, 0, 0});
     }
-  }
-  x->n_ds_frags = frag;
+  });
+  if (forward_only) return;
 
   // KV side: the dependencies of each KV segment, in query order, the DIAG one last: the tiles of one KV segment then
   // walk the FULL dependencies in lockstep (identical step sequences, same XCD), so the Q / dO stream they share stays
@@ -226,33 +256,34 @@ void expand_problem(const fcp_problem* p, Expanded* x) {
     std::stable_partition(x->deps.begin() + k.dep_begin, x->deps.begin() + k.dep_begin + k.n_deps, [](const BwdDep& e) { return !(e.kind & 1); });
 }
 
-// Query-stationary items of a segment: two query heads of a KV head share one when the group size is even, else two row tiles.
-static int64_t q_items_of(const QSeg& s, int n_q_heads, int G) {
-  const int64_t n_tiles = ceil_div(s.len, kFwdTileM);
-  return (G % 2 == 0) ? n_tiles * (n_q_heads / 2) : ceil_div(n_tiles, 2) * n_q_heads;
-}
-
 size_t static_plan_bytes(const fcp_problem* p) {
   int64_t items = 0;
-  for (int s = 0; s < p->n_slots; s++)
-    items += q_items_of(QSeg{0, p->q_blocks[p->slots[s].q_blk].tok_len, 0, 0, 0, 0, 0, 0}, p->n_q_heads, p->n_q_heads / p->n_kv_heads);
+  for (int s = 0; s < p->n_slots; s++) items += q_items_of(p, p->q_blocks[p->slots[s].q_blk].tok_len);
   auto align = [](size_t x) { return (x + 255) & ~(size_t)255; };
   return 1024 + align(16 * (size_t)std::max(1, p->n_pairs)) + align(72 * (size_t)std::max<int64_t>(1, items));
 }
 
-int compute_layout(const fcp_problem* p, WsLayout* L) {
-  Expanded x;
-  expand_problem(p, &x);
-  return compute_layout(p, x, L);
-}
-
-int compute_layout(const fcp_problem* p, const Expanded& x, WsLayout* L) {
+int compute_layout(const fcp_problem* p, bool forward_only, WsLayout* L) {
   std::memset(L, 0, sizeof(*L));
-  const int G = p->n_q_heads / p->n_kv_heads;
-  for (const QSeg& s : x.fwd) L->n_fwd_items += q_items_of(s, p->n_q_heads, G);
-  for (const QSeg& s : x.dq) L->n_dq_items += q_items_of(s, p->n_q_heads, G);
-  for (const KvSeg& k : x.kv) L->n_bwd_items += ceil_div(k.len, kBwdTileN) * p->n_kv_heads;
-  L->n_pairs = (int64_t)x.pairs.size();
+  const Runs runs = make_runs(p);
+  for (const Run& r : runs.run) L->n_bwd_items += ceil_div(r.len, kBwdTileN) * p->n_kv_heads;
+  int64_t frags = kDsSinkFrags;
+  for_q_blocks(p, runs, [&](int b, int s0, int s1, const Run* run, int n_runs, bool packed) {
+    int64_t items = 0;
+    for (int m = 0; m < n_runs; m++) items += q_items_of(p, run[m].len);
+    L->n_dq_items += items;
+    for (int s = s0; s < s1; s++) {
+      const bool whole = packed && !packed_slot(p, p->slots[s]);
+      L->n_fwd_items += whole ? q_items_of(p, p->q_blocks[b].tok_len) : items;
+      L->n_pairs += (int64_t)p->slots[s].n_pairs * (whole && forward_only ? 1 : n_runs);
+    }
+    if (!(p->flags & FCP_FLAG_BWD_SPILL_DS) || s0 == s1) return;
+    for (int i = p->slots[s0].pair_begin; i < p->slots[s1 - 1].pair_begin + p->slots[s1 - 1].n_pairs; i++) {
+      const fcp_pair& pr = p->pairs[i];
+      for (int m = 0; m < n_runs; m++)
+        frags += p->n_q_heads * ds_frags_per_head(pr.kind, run[m].len, runs.run[runs.begin[pr.kv_blk] + ((pr.kind & 2) ? m : 0)].len);
+    }
+  });
   std::vector<int32_t> slots_of(p->n_q_blocks, 0);
   for (int s = 0; s < p->n_slots; s++) slots_of[p->slots[s].q_blk]++;
   const bool direct = (p->flags & FCP_FLAG_DIRECT_SINGLE) != 0;
@@ -270,8 +301,8 @@ int compute_layout(const fcp_problem* p, const Expanded& x, WsLayout* L) {
     L->t_q += p->q_blocks[b].tok_len;
   }
   if (L->t_q * p->n_q_heads > INT32_MAX) { set_error("more than 2^31-1 (query row, head) entries"); return FCP_ERR_UNSUPPORTED; }
-  if (L->n_fwd_items > INT32_MAX || L->n_bwd_items > INT32_MAX || L->n_merge_items > INT32_MAX || L->n_dq_items > INT32_MAX) {
-    set_error("too many work items"); return FCP_ERR_UNSUPPORTED;
+  if (L->n_pairs > INT32_MAX || L->n_fwd_items > INT32_MAX || L->n_bwd_items > INT32_MAX || L->n_merge_items > INT32_MAX || L->n_dq_items > INT32_MAX) {
+    set_error("too many pairs or work items"); return FCP_ERR_UNSUPPORTED;
   }
   auto align = [](size_t x) { return (x + 255) & ~(size_t)255; };
   size_t off = align(sizeof(WsHeader));
@@ -287,7 +318,7 @@ int compute_layout(const fcp_problem* p, const Expanded& x, WsLayout* L) {
   L->off_lse2 = off;        off = align(off + sizeof(float) * (size_t)std::max<int64_t>(1, L->t_q * p->n_q_heads));
   L->off_ds = off;
   if (p->flags & FCP_FLAG_BWD_SPILL_DS) {
-    const int64_t frags = x.n_ds_frags + 1;   // the dQ kernel requests fragments in pairs: one past the last may be named (never used)
+    frags++;   // the dQ kernel requests the fragments of a whole tile in pairs: one past the last may be named (never used)
     if (frags > INT32_MAX) { set_error("FCP_FLAG_BWD_SPILL_DS: more than 2^31-1 dS fragments"); return FCP_ERR_UNSUPPORTED; }
     L->n_ds_frags = frags;
     off = align(off + (size_t)frags * kDsFragBytes);
@@ -336,7 +367,7 @@ int layout_for(const fcp_problem* p, const void* workspace, WsLayout* L) {
   }
   int rc = validate_problem(p);
   if (rc) return rc;
-  return compute_layout(p, L);
+  return compute_layout(p, false, L);
 }
 
 namespace {
@@ -775,7 +806,7 @@ extern "C" int fcp_workspace_bytes(const fcp_problem* p, size_t* bytes) {
   int rc = validate_problem(p);
   if (rc) return rc;
   WsLayout L;
-  rc = compute_layout(p, &L);
+  rc = compute_layout(p, false, &L);
   if (rc) return rc;
   *bytes = L.total;
   return FCP_OK;
@@ -792,6 +823,7 @@ int fcp::build_queue_image(const fcp_problem* p, const Expanded& x, const WsLayo
   WsHeader* hdr = reinterpret_cast<WsHeader*>(host.data());
   for (float& v : hdr->infs) v = INFINITY;
   auto put = [&](size_t off, const auto& v) { if (!v.empty()) std::memcpy(host.data() + off, v.data(), v.size() * sizeof(v[0])); };
+  if ((int64_t)x.pairs.size() != L.n_pairs) { set_error("internal: pair count mismatch"); return FCP_ERR_INVALID_ARG; }
   put(L.off_pairs, x.pairs);
   std::vector<QItem> flat;
   q_items(p, x.fwd, x.pairs, L.n_fwd_items, &flat, hdr->fwd_begin);
@@ -868,10 +900,8 @@ int fcp::build_queue_image(const fcp_problem* p, const Expanded& x, const WsLayo
 extern "C" int fcp_queue_build(const fcp_problem* p, void* workspace, size_t workspace_bytes, void* stream) {
   int rc = validate_problem(p);
   if (rc) return rc;
-  Expanded x;
-  expand_problem(p, &x);
   WsLayout L;
-  rc = compute_layout(p, x, &L);
+  rc = compute_layout(p, false, &L);
   if (rc) return rc;
   if (!workspace || ((uintptr_t)workspace & 255)) {
     set_error("fcp_queue_build: workspace is NULL or not 256-byte aligned"); return FCP_ERR_INVALID_ARG;
@@ -880,6 +910,8 @@ extern "C" int fcp_queue_build(const fcp_problem* p, void* workspace, size_t wor
     set_error("fcp_queue_build: workspace too small (%zu < %zu)", workspace_bytes, L.total);
     return FCP_ERR_BUFFER_TOO_SMALL;
   }
+  Expanded x;
+  expand_problem(p, false, &x);
   std::vector<unsigned char> host;
   rc = build_queue_image(p, x, L, false, &host);
   if (rc) return rc;

@@ -74,7 +74,7 @@ struct WsHeader {
 
 // Byte offsets of the workspace sections, a pure function of the problem's counts.
 struct WsLayout {
-  int64_t n_fwd_items, n_bwd_items, n_bwd_deps, n_merge_items, n_dq_items, n_pairs, t_q;
+  int64_t n_fwd_items, n_bwd_items, n_merge_items, n_dq_items, n_pairs, t_q;
   int merge_chunk;  // (row, head) entries per merge work item, chosen per problem
   int64_t n_ds_frags;   // fragments of the dS spill buffer, sinks and one fragment of slack included (0 without the flag)
   size_t off_pairs, off_fwd_items, off_bwd_deps, off_bwd_items, off_merge_items, off_slot_rh, off_dq_items, off_dls, off_lse2, off_ds, total;
@@ -89,12 +89,11 @@ struct Expanded {
   std::vector<QSeg> fwd, dq;       // per slot; per query block (all pairs of its slots)
   std::vector<KvSeg> kv;
   std::vector<BwdDep> deps;        // by KV segment
-  int64_t n_ds_frags;              // dS fragments of all pairs, sinks included
 };
-void expand_problem(const fcp_problem* p, Expanded* x);   // host; p has been validated
+// forward_only: for an image without backward tables (dq, kv, deps and their pairs stay out)
+void expand_problem(const fcp_problem* p, bool forward_only, Expanded* x);   // host; p has been validated
 int validate_problem(const fcp_problem* p);           // host; sets the error text
-int compute_layout(const fcp_problem* p, WsLayout* L); // host
-int compute_layout(const fcp_problem* p, const Expanded& x, WsLayout* L);
+int compute_layout(const fcp_problem* p, bool forward_only, WsLayout* L);   // host; counts only, p has been validated
 // the layout of a problem on a workspace: from the registry that fcp_queue_build fills, else validated and computed
 int layout_for(const fcp_problem* p, const void* workspace, WsLayout* L);   // host
 void remember_layout(const fcp_problem* p, const void* workspace, const WsLayout& L);

@@ -1896,11 +1896,11 @@ extern "C" int fcp_device_info(int32_t* n_compute_units, int32_t* fwd_grid, int3
   return FCP_OK;
 }
 
-static int launch_fwd(const char* who, const fcp_problem* p, const void* q, const void* k, const void* v,
+static int launch_fwd(const char* who, const fcp_problem* p, const WsLayout* layout, const void* q, const void* k, const void* v,
                       void* o_part, float* lse_part, void* o, float* lse, void* workspace, void* stream) {
   WsLayout L;
-  int rc = layout_for(p, workspace, &L);
-  if (rc) return rc;
+  if (layout) L = *layout;
+  else if (int rc = layout_for(p, workspace, &L)) return rc;
   if (L.n_fwd_items == 0) return FCP_OK;
   if (!q || !k || !v || !workspace || (p->n_slot_rows && !(p->flags & FCP_FLAG_RUNNING_MERGE) && (!o_part || !lse_part))) {
     set_error("%s: NULL pointer", who); return FCP_ERR_INVALID_ARG;
@@ -1943,7 +1943,7 @@ static int launch_fwd(const char* who, const fcp_problem* p, const void* q, cons
 
 extern "C" int fcp_block_attn_fwd(const fcp_problem* p, const void* q, const void* k, const void* v,
                                   void* o_part, float* lse_part, void* workspace, void* stream) {
-  return launch_fwd("fcp_block_attn_fwd", p, q, k, v, o_part, lse_part, nullptr, nullptr, workspace, stream);
+  return launch_fwd("fcp_block_attn_fwd", p, nullptr, q, k, v, o_part, lse_part, nullptr, nullptr, workspace, stream);
 }
 
 // ---- forward without any allocation: the queue tables live in a fixed device array ----
@@ -1983,10 +1983,8 @@ extern "C" int fcp_block_attn_fwd_static(const fcp_problem* p, const void* q, co
     set_error("fcp_block_attn_fwd_static: FCP_FLAG_DIRECT_SINGLE is not supported here (all slots go to the partial buffers)");
     return FCP_ERR_INVALID_ARG;
   }
-  Expanded x;
-  expand_problem(p, &x);
   WsLayout L;
-  rc = compute_layout(p, x, &L);
+  rc = compute_layout(p, true, &L);
   if (rc) return rc;
   const size_t plan_bytes = static_plan_bytes(p);
   if (plan_bytes > kStaticPlanBytes || L.off_bwd_deps > kStaticScratchBytes) {
@@ -2003,19 +2001,21 @@ extern "C" int fcp_block_attn_fwd_static(const fcp_problem* p, const void* q, co
   // The tables are rebuilt on every call (the array keeps the previous call's contents): header with
   // zeroed counters, resolved pairs, forward items.  Host memory only; one copy; the copy is waited for
   // because its source dies with this frame.
+  Expanded x;
+  expand_problem(p, true, &x);
   std::vector<unsigned char> image;
   rc = build_queue_image(p, x, L, true, &image);
   if (rc) return rc;
   hipError_t e = hipMemcpyAsync(ws, image.data(), image.size(), hipMemcpyHostToDevice, (hipStream_t)stream);
   if (e == hipSuccess) e = hipStreamSynchronize((hipStream_t)stream);
   if (e != hipSuccess) { set_error("fcp_block_attn_fwd_static: %s", hipGetErrorString(e)); return FCP_ERR_HIP; }
-  return launch_fwd("fcp_block_attn_fwd_static", p, q, k, v, o_part, lse_part, nullptr, nullptr, ws, stream);
+  return launch_fwd("fcp_block_attn_fwd_static", p, &L, q, k, v, o_part, lse_part, nullptr, nullptr, ws, stream);
 }
 
 extern "C" int fcp_block_attn_fwd_out(const fcp_problem* p, const void* q, const void* k, const void* v,
                                       void* o_part, float* lse_part, void* o, float* lse,
                                       void* workspace, void* stream) {
-  return launch_fwd("fcp_block_attn_fwd_out", p, q, k, v, o_part, lse_part, o, lse, workspace, stream);
+  return launch_fwd("fcp_block_attn_fwd_out", p, nullptr, q, k, v, o_part, lse_part, o, lse, workspace, stream);
 }
 
 extern "C" int fcp_merge_partials(const fcp_problem* p, const void* o_part, const float* lse_part,
