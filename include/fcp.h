@@ -245,13 +245,14 @@ int fcp_block_attn_fwd_out(const fcp_problem* p, const void* q, const void* k, c
  *
  * Same result as fcp_queue_build + fcp_block_attn_fwd, bit for bit, with no workspace argument: the
  * forward's queue tables (header with the queue counters, resolved pairs, forward work items) are built
- * on the host at every call and copied into a fixed array of 16 MiB inside the library's device image,
+ * on the host at every call and copied into a fixed array of 8 MiB inside the library's device image,
  * which every device the library runs on holds until the process ends.  The call allocates no device
  * memory (no hipMalloc / hipFree, no allocating library routine); it waits on `stream` for its table
  * copy, then enqueues the kernel and returns.
  * Limits and errors: FCP_ERR_BUFFER_TOO_SMALL if the plan's pairs (16 bytes each) and forward work items (72 bytes
- * each, a packed block counted as one block) need more than 2 MiB, or the tables with the members of packed blocks
- * as items of their own more than the array (about 28 000 work items: the packed 64K-token training batch fits, the 1M-token share does not);
+ * each, a packed block counted as one block) need more than 2 MiB (about 28 000 work items: the packed 64K-token
+ * training batch fits, the 1M-token share does not), or, with millions of query rows of few heads in packed blocks, if
+ * the member bounds (2 bytes a row) do not fit the array beside them;
  * FCP_ERR_INVALID_ARG with FCP_FLAG_DIRECT_SINGLE (every slot goes to the partial buffers here);
  * otherwise as fcp_block_attn_fwd.  All calls on one device share that device's array, counters
  * included: calls that overlap in time on one device race, whatever their streams.

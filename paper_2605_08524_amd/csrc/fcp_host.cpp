@@ -157,8 +157,9 @@ int validate_problem(const fcp_problem* p) {
 
 namespace {
 
-// Rows of a block that the kernels treat as one segment: all of a plain block, or one member of a packed one.
-struct Run { int32_t off, len, seq; };
+// Rows of a block that the kernels treat as one segment: all of a plain block, or whole members of a packed one
+// (segments seg_begin .. of the problem; more than one: joined).
+struct Run { int32_t off, len, seq, seg_begin, n_segs; };
 struct Runs { std::vector<Run> run; std::vector<int32_t> begin; };   // of KV block b: begin[b] .. begin[b + 1]
 
 // Rows of a query-stationary item: one row tile of two heads when the group size is even, else two row tiles of one head.
@@ -167,12 +168,18 @@ int item_rows(const fcp_problem* p) { return kFwdTileM * ((p->n_q_heads / p->n_k
 Runs make_runs(const fcp_problem* p) {
   Runs r;
   r.run.reserve(p->n_kv_blocks);
+  const int most = item_rows(p);
   for (int b = 0, i = 0; b < p->n_kv_blocks; b++) {
     r.begin.push_back((int32_t)r.run.size());
-    if (i == p->n_segments || p->segments[i].kv_blk != b) r.run.push_back({0, p->kv_blocks[b].tok_len, p->kv_blocks[b].seq});
+    if (i == p->n_segments || p->segments[i].kv_blk != b) r.run.push_back({0, p->kv_blocks[b].tok_len, p->kv_blocks[b].seq, i, 0});
     for (; i < p->n_segments && p->segments[i].kv_blk == b; i++) {
       const fcp_segment& sg = p->segments[i];
-      r.run.push_back({sg.tok_off, sg.tok_len, sg.seq});
+      if ((int32_t)r.run.size() > r.begin[b] && r.run.back().len + sg.tok_len <= most) {
+        r.run.back().len += sg.tok_len;
+        r.run.back().n_segs++;
+      } else {
+        r.run.push_back({sg.tok_off, sg.tok_len, sg.seq, i, 1});
+      }
     }
   }
   r.begin.push_back((int32_t)r.run.size());
@@ -188,7 +195,7 @@ void for_q_blocks(const fcp_problem* p, const Runs& runs, F f) {
     int kb = -1;
     for (; s < p->n_slots && p->slots[s].q_blk == b; s++)
       if (p->slots[s].n_pairs == 1 && (p->pairs[p->slots[s].pair_begin].kind & 2)) kb = p->pairs[p->slots[s].pair_begin].kv_blk;
-    const Run whole = {0, p->q_blocks[b].tok_len, p->q_blocks[b].seq};
+    const Run whole = {0, p->q_blocks[b].tok_len, p->q_blocks[b].seq, 0, 0};
     if (kb < 0) f(b, s0, s, &whole, 1, false);
     else f(b, s0, s, &runs.run[runs.begin[kb]], runs.begin[kb + 1] - runs.begin[kb], true);
   }
@@ -208,6 +215,11 @@ void expand_problem(const fcp_problem* p, bool forward_only, Expanded* x) {
   for (int b = 0; b < p->n_kv_blocks; b++)
     for (int i = runs.begin[b]; i < runs.begin[b + 1]; i++)
       x->kv.push_back({p->kv_blocks[b].tok_start + runs.run[i].off, runs.run[i].len, runs.run[i].seq, 0, 0});
+  if (p->n_segments) {
+    int64_t t_q = 0;
+    for (int b = 0; b < p->n_q_blocks; b++) t_q += p->q_blocks[b].tok_len;
+    x->q_seg.assign(t_q, 0);
+  }
   // query side: pairs (with the query rows and the KV segment each joins), forward and dQ segments
   struct Join { int32_t q_start, q_len, kv_seg; };
   std::vector<Join> joins;
@@ -230,7 +242,7 @@ void expand_problem(const fcp_problem* p, bool forward_only, Expanded* x) {
           const fcp_pair& pr = p->pairs[i];
           const int32_t seg = runs.begin[pr.kv_blk] + ((pr.kind & 2) ? m : 0);
           KvSeg& k = x->kv[seg];
-          const int kind = pr.kind & 1;
+          const int kind = (pr.kind & 2) && run[m].n_segs == 1 ? pr.kind & 1 : pr.kind;
           x->pairs.push_back({k.start, k.len, kind, spill ? (int32_t)frag : 0});
           joins.push_back({q0, run[m].len, seg});
           k.n_deps++;
@@ -238,6 +250,11 @@ void expand_problem(const fcp_problem* p, bool forward_only, Expanded* x) {
         }
       }
       x->dq.push_back({q0, run[m].len, q0, p0, (int32_t)x->pairs.size() - p0, run[m].seq, 0, 0});
+      if (run[m].n_segs > 1)
+        for (int i = run[m].seg_begin; i < run[m].seg_begin + run[m].n_segs; i++) {
+          const int lo = p->segments[i].tok_off - run[m].off, hi = lo + p->segments[i].tok_len;
+          std::fill(x->q_seg.begin() + q0 + lo, x->q_seg.begin() + q0 + hi, seg_word(lo, hi));
+        }
     }
   });
   if (forward_only) return;
@@ -308,6 +325,7 @@ int compute_layout(const fcp_problem* p, bool forward_only, WsLayout* L) {
   size_t off = align(sizeof(WsHeader));
   L->off_pairs = off;       off = align(off + sizeof(DevPair) * (size_t)std::max<int64_t>(1, L->n_pairs));
   L->off_fwd_items = off;   off = align(off + sizeof(QItem) * (size_t)std::max<int64_t>(1, L->n_fwd_items));
+  L->off_q_seg = off;       off = align(off + (p->n_segments ? sizeof(uint16_t) * (size_t)L->t_q : 0));
   L->off_bwd_deps = off;    off = align(off + sizeof(BwdDep) * (size_t)std::max<int64_t>(1, L->n_pairs));
   L->off_bwd_items = off;   off = align(off + sizeof(BwdItem) * (size_t)std::max<int64_t>(1, L->n_bwd_items));
   L->off_merge_items = off; off = align(off + sizeof(MergeItem) * (size_t)std::max<int64_t>(1, L->n_merge_items));
@@ -825,6 +843,7 @@ int fcp::build_queue_image(const fcp_problem* p, const Expanded& x, const WsLayo
   auto put = [&](size_t off, const auto& v) { if (!v.empty()) std::memcpy(host.data() + off, v.data(), v.size() * sizeof(v[0])); };
   if ((int64_t)x.pairs.size() != L.n_pairs) { set_error("internal: pair count mismatch"); return FCP_ERR_INVALID_ARG; }
   put(L.off_pairs, x.pairs);
+  put(L.off_q_seg, x.q_seg);
   std::vector<QItem> flat;
   q_items(p, x.fwd, x.pairs, L.n_fwd_items, &flat, hdr->fwd_begin);
   if ((int64_t)flat.size() != L.n_fwd_items) { set_error("internal: forward item count mismatch"); return FCP_ERR_INVALID_ARG; }

@@ -18,9 +18,12 @@ constexpr int kMergeChunk = 1024;   // most (row, head) entries per merge work i
 constexpr int kMergeMinItems = 2048;  // the merge aims at this many work items at least: 8 per compute unit
 
 // Device-side records (all int32 so the host can build them as plain arrays).
-// The kernels know no packed blocks: a packed block's pair with itself reaches them as one FULL or DIAG pair per
-// member sequence, its rows as one query (KV) segment per member, exactly as if each member were a block of its own
-// (expand_problem).  kind is therefore FCP_KIND_FULL or FCP_KIND_DIAG in every record below.
+// A packed block reaches the kernels cut into runs of whole members, each a query (KV) segment with one pair of its own
+// (expand_problem).  Neighbours join a run while it fits the rows of one query-stationary item; its pair keeps the PACKED
+// kind and the kernels mask by member (q_seg).  A member alone in its run is an ordinary segment: FULL or DIAG, no mask.
+// Forward, GQA 32/8, d = 128, 1024-token blocks, against one segment per member and against the block walked whole with the
+// union of its rows' key ranges: 2048 sequences of 8 tokens 105 us (815, 164); 49152 tokens in sequences of 16-256: 328 us
+// (354, 477).
 // ds_frag: first 32x32 dS fragment of the pair in the spill buffer (FCP_FLAG_BWD_SPILL_DS; else 0).
 struct DevPair { int32_t kv_start, kv_len, kind, ds_frag; };
 // Query-stationary item of two 128-row sub-tiles that walk the same pair list and share a KV head
@@ -36,18 +39,21 @@ struct BwdDep  { int32_t q_start, q_len, kind, ds_frag; };
 // n_iv: barrier intervals of the item: its 32-row steps (dependencies x query heads of the group; a DIAG dependency from the
 // tile's own rows on) plus two of pipeline fill, rounded up to even.  first: the first of its dependencies.
 struct BwdItem { int32_t kv_start, kv_rows, tile_off, dep_begin, n_deps, kv_head, kv_blk_len, n_iv; BwdDep first; };
-constexpr int kMaxPackedBlock = 65535;   // tokens of a packed block
+constexpr int kMaxPackedBlock = 65535;   // tokens of a packed block: what fcp_workspace_bytes and the calls on a problem accept
+// q_seg, per Q-buffer row of a joined run: first row of the row's member in the low byte, its last in the high byte, both
+// counted from the run's first row (the run's KV rows have the same bounds).  A run has at most 256 rows.
+inline uint16_t seg_word(int lo, int hi) { return (uint16_t)(lo | (hi - 1) << 8); }
 
 // The dS spill buffer (FCP_FLAG_BWD_SPILL_DS) is a sequence of 2 KB fragments, one per (pair, query head,
 // 32 query rows, 32 KV rows).  Fragments [0, kDsSinkFrags) take the stores of steps that have no fragment
 // (pipeline fill, tiles above the diagonal); a pair's fragments follow from its ds_frag, head-major, then by
 // 32-row query group; a FULL pair keeps ceil(kv_len / 32) fragments per query group, a DIAG pair only those at or
-// below the diagonal (query group i keeps i + 1).
+// below the diagonal (query group i keeps i + 1); a joined run keeps what FULL / DIAG keep, with zeros between members.
 constexpr int kDsFragBytes = 2048;
 constexpr int kDsSinkFrags = 256;
 inline int64_t ds_frags_per_head(int kind, int q_len, int kv_len) {
   const int64_t nq = (q_len + 31) / 32, nk = (kv_len + 31) / 32;
-  return (kind & 1) ? nq * (nq + 1) / 2 : nq * nk;   // DIAG: at or below the diagonal
+  return (kind & 1) ? nq * (nq + 1) / 2 : nq * nk;   // DIAG and PACKED_DIAG: at or below the diagonal
 }
 struct MergeItem { int32_t out_rh, n_rh, slot_begin, n_slots, rh_off, pad0, pad1, pad2; };
 
@@ -77,10 +83,10 @@ struct WsLayout {
   int64_t n_fwd_items, n_bwd_items, n_merge_items, n_dq_items, n_pairs, t_q;
   int merge_chunk;  // (row, head) entries per merge work item, chosen per problem
   int64_t n_ds_frags;   // fragments of the dS spill buffer, sinks and one fragment of slack included (0 without the flag)
-  size_t off_pairs, off_fwd_items, off_bwd_deps, off_bwd_items, off_merge_items, off_slot_rh, off_dq_items, off_dls, off_lse2, off_ds, total;
+  size_t off_pairs, off_fwd_items, off_q_seg, off_bwd_deps, off_bwd_items, off_merge_items, off_slot_rh, off_dq_items, off_dls, off_lse2, off_ds, total;
 };
 
-// The problem as the kernels see it.  Segment = rows that share a pair list: a query block (KV block), or one member of
+// The problem as the kernels see it.  Segment = rows that share a pair list: a query block (KV block), or one run of
 // a packed one.  ordinal: which slot of its query block a forward segment is (0 for dQ).
 struct QSeg { int32_t start, len, out_row, pair_begin, n_pairs, seq, to_final, ordinal; };   // rows in the Q buffer / partial buffers
 struct KvSeg { int32_t start, len, seq, dep_begin, n_deps; };
@@ -89,6 +95,7 @@ struct Expanded {
   std::vector<QSeg> fwd, dq;       // per slot; per query block (all pairs of its slots)
   std::vector<KvSeg> kv;
   std::vector<BwdDep> deps;        // by KV segment
+  std::vector<uint16_t> q_seg;     // per Q-buffer row (empty without packed blocks)
 };
 // forward_only: for an image without backward tables (dq, kv, deps and their pairs stay out)
 void expand_problem(const fcp_problem* p, bool forward_only, Expanded* x);   // host; p has been validated
@@ -97,7 +104,7 @@ int compute_layout(const fcp_problem* p, bool forward_only, WsLayout* L);   // h
 // the layout of a problem on a workspace: from the registry that fcp_queue_build fills, else validated and computed
 int layout_for(const fcp_problem* p, const void* workspace, WsLayout* L);   // host
 void remember_layout(const fcp_problem* p, const void* workspace, const WsLayout& L);
-// what limits fcp_block_attn_fwd_static: 1 KB, 16 bytes per pair and 72 per forward item of the plan's query blocks
+// what limits fcp_block_attn_fwd_static: 1 KB, 16 bytes per pair and 72 per forward item of the plan's query blocks as given
 size_t static_plan_bytes(const fcp_problem* p);
 void set_error(const char* fmt, ...);
 int build_queue_image(const fcp_problem* p, const Expanded& x, const WsLayout& L, bool forward_only, std::vector<unsigned char>* image);  // host

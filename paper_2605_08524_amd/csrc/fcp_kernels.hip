@@ -361,7 +361,7 @@ struct FwdArgs {
   void* o_part; float* lse_part; int32_t part_is_bf16;
   void* o; float* lse; int32_t o_is_f32;     // final outputs for query blocks with a single slot (or NULL)
   int32_t running;                            // fold every slot into the running (o, lse) in place (fp32 o)
-  WsHeader* hdr; const DevPair* pairs; const QItem* items;
+  WsHeader* hdr; const DevPair* pairs; const QItem* items; const uint16_t* q_seg;
   int32_t n_q_heads, n_kv_heads;
   float scale_log2;   // softmax scale * log2(e)
 };
@@ -405,6 +405,15 @@ struct TileIter {
 // A tile past the end of the item has len = 0: everything is masked.
 struct TileMeta { int c0, len, kind; };
 
+// The scores of a 64-column tile that a lane keeps if only columns < c count, one bit per score: score e = 16 rt + r of a lane
+// is column 8 (e / 4) + 4 g + e % 4.  A mask of bits costs a score two operations, as a compare with a bound does, but only
+// one register in all beside the scores, also where a row has two bounds (a joined run).
+__device__ __forceinline__ uint32_t keep_below(int c, int g) {
+  c = min(max(c, 0), kFwdTileN);
+  const int n = 4 * (c >> 3) + min(max((c & 7) - 4 * g, 0), 4);
+  return n < 32 ? (1u << n) - 1 : 0xffffffffu;
+}
+
 template <int D>
 __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
   constexpr int KC = D / 16;      // k-chunks of the QK^T contraction
@@ -421,6 +430,7 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
   __shared__ __attribute__((aligned(16))) int32_t s_rec[2][64];   // records of this item and the next
   __shared__ int s_next;
   __shared__ __attribute__((aligned(16))) unsigned char s_stage[8][kStageBytes];
+  __shared__ uint32_t s_mask[2 * kFwdTileM / kFwdTileN][512];   // joined run: scores that each lane keeps of each KV tile (written and read by that lane)
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform, kept in a scalar register
@@ -475,6 +485,18 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
     const int my_limit = tile_off_q + my_row;                // last visible column of a DIAG pair for this lane
     const uint16_t* kbase = a.k + (int64_t)kvh * D;
     const uint16_t* vbase = a.v + (int64_t)kvh * D;
+
+    if (it.first.kind & 2) {
+      // joined run: the columns of the row's member, up to the row itself under a causal mask; rows past the end: none
+      int lo = 0, hi = 0;
+      if (my_row < q_rows) {
+        const int sg = a.q_seg[(sub ? it.q_start[1] : it.q_start[0]) + my_row];
+        lo = sg & 0xff; hi = ((it.first.kind & 1) ? min(sg >> 8, my_limit) : sg >> 8) + 1;
+      }
+#pragma unroll
+      for (int t = 0; t < 2 * kFwdTileM / kFwdTileN; t++)
+        s_mask[t][tid] = keep_below(hi - t * kFwdTileN, g) & ~keep_below(lo - t * kFwdTileN, g);
+    }
 
     // Q^T fragments (B operand of S^T = K Q^T): lane = query row, 8 consecutive d per k-chunk.
     bf16x8 qf[KC];
@@ -638,15 +660,16 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
         // readfirstlane: the condition is wave-uniform, but the compiler does not know it and would
         // otherwise run the rare path on every tile as 64 compares and selects
         const int need_mask = __builtin_amdgcn_readfirstlane(
-            (int)(tm.len == 0 || tm.c0 + kFwdTileN > tm.len || ((tm.kind & 1) && tm.c0 + kFwdTileN - 1 > wave_row_lo)));
+            (int)(tm.len == 0 || tm.c0 + kFwdTileN > tm.len || (tm.kind & 2) || ((tm.kind & 1) && tm.c0 + kFwdTileN - 1 > wave_row_lo)));
         if (need_mask) {
-          // last visible column for this lane, relative to the tile's first column
-          const int limit = ((tm.kind & 1) ? min(tm.len - 1, my_limit) : tm.len - 1) - tm.c0 - 4 * g;
+          // one bit per score of this lane (see keep_below): columns up to the last visible one, or of the row's member
+          uint32_t keep = (tm.kind & 2) ? 0u : keep_below(((tm.kind & 1) ? min(tm.len, my_limit + 1) : tm.len) - tm.c0, g);
+          if (__builtin_amdgcn_readfirstlane(tm.kind & 2)) keep = s_mask[tm.c0 / kFwdTileN][tid];
 #pragma unroll
           for (int rt = 0; rt < 2; rt++)
 #pragma unroll
             for (int r = 0; r < 16; r++)
-              if (rt * 32 + 8 * (r >> 2) + (r & 3) > limit) sn[rt][r] = -INFINITY;
+              if (!(keep & (1u << (16 * rt + r)))) sn[rt][r] = -INFINITY;
         }
       }
       if constexpr (!LAST) {
@@ -976,7 +999,7 @@ struct BwdArgs {
   const void* o; const float* lse; int32_t o_is_f32; float* lse2_out; float* dls_out;
   void* dq; void* dk; void* dv;    // fp32, or bf16 in the GRAD_BF16 instances of the kernels
   unsigned char* ds;               // dS spill buffer (2 KB fragments), or NULL
-  WsHeader* hdr; const DevPair* pairs; const BwdDep* deps; const BwdItem* items; const QItem* dq_items;
+  WsHeader* hdr; const DevPair* pairs; const BwdDep* deps; const BwdItem* items; const QItem* dq_items; const uint16_t* q_seg;
   int64_t t_q;
   int32_t n_q_heads, n_kv_heads;
   float scale, scale_log2;
@@ -1017,7 +1040,10 @@ struct StepIter {
 constexpr int kDkdvBufs = 7;        // ring of LDS step buffers
 constexpr int kNoMask = 1 << 30;    // diagonal threshold of a step that needs no mask
 
-template <int D, bool GRAD_BF16, bool SPILL>
+// JOINED: the problem has packed blocks, so items may be joined runs.  Only that instance masks by member: compiled into the
+// other one, the third form of the interval took registers from the other two (8-worker share, d = 128, without SPILL: 5441 ->
+// 5607 us).
+template <int D, bool GRAD_BF16, bool SPILL, bool JOINED>
 __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
   constexpr int KC = D / 16;
   constexpr int DT = D / 32;
@@ -1034,6 +1060,7 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
   __shared__ __attribute__((aligned(256))) float lds_sc[NB][64];   // [LSE*log2e x 32 | D*scale x 32]
   __shared__ int s_next;
   __shared__ __attribute__((aligned(16))) int32_t s_rec[64];       // next item's record, as in fwd_kernel
+  __shared__ int s_klo[JOINED ? 256 : 1], s_khi[JOINED ? 256 : 1];   // joined run: the query rows of the member of each producer lane's KV row, minus 4g
   __shared__ __attribute__((aligned(16))) unsigned char s_stage[4][kStageBytes];   // producers at an item's start, consumers at its end
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -1225,6 +1252,14 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
     } else {
       // =============================== producer ===============================
       int kvg = it.tile_off + my_kv - 4 * g;       // masked iff kvg > q0 + 8*(r/4) + r%4 on a DIAG step
+      const bool joined = JOINED && (it.first.kind & 2);
+      if (joined) {
+        // Joined run: a KV row is seen by the query rows of its own member only, from the first of them on under a full mask,
+        // from the row itself under a causal one (as above).
+        const int sg = kv_ok ? a.q_seg[it.first.q_start + it.tile_off + my_kv] : 0;
+        s_klo[tid] = kv_ok ? (sg & 0xff) - 4 * g : 0x7fff0000;
+        s_khi[tid] = (sg >> 8) + 1 - 4 * g;
+      }
       // SPILL: the dS this wave forms also goes to memory, one 2 KB fragment per step, for the dQ pass.  There a
       // KV row past the ragged end of the tile must carry dS = 0 (here its column of dK^T / dV^T is simply never
       // stored): such lanes get a threshold nothing passes, and a ragged tile runs every step through the masked
@@ -1252,6 +1287,7 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
       for (int kc = 0; kc < KC; kc++) row_a[kc] = lds_addr(lds_t[0]) + b_p * BUF + tile_off<D>(l32, 2 * kc + g);
       uint32_t sc_a = lds_sc0 + b_s * 256 + 16 * g;      // scalars of step i+1: rows 8*q4 + 4g .. +3 at +32*q4, D*scale at +128
       int thr_t = thr_none;      // diagonal threshold of the step that B handles in this interval
+      bool causal_t = false;     // joined run: the mask of that step is causal
       f32x16 s_a, dp_a, s_b, dp_b;
 #pragma unroll
       for (int r = 0; r < 16; r++) { s_a[r] = 0.f; dp_a[r] = 0.f; s_b[r] = 0.f; dp_b[r] = 0.f; }
@@ -1265,8 +1301,13 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
 
       // One interval: MFMAs of A(i+2) into (sn, dpn); B(i+1) on (sc, dpc) between them.
       auto interval = [&](auto masked, f32x16& sc, f32x16& dpc, f32x16& sn, f32x16& dpn) {
-        constexpr bool MASK = decltype(masked)::value;    // diagonal / ragged end
+        constexpr int MASK = decltype(masked)::value;     // 0: no mask, 1: diagonal / ragged end, 2: joined run
         const int thr_s = __builtin_amdgcn_readfirstlane(thr_t);
+        int klo = kvg, hlim = 0;                          // joined run: rows 8*(r/4) + r%4 >= hlim of the step are past the member
+        if constexpr (MASK == 2) {
+          hlim = s_khi[tid] - thr_s;
+          if (!causal_t) klo = s_klo[tid];
+        }
         f32x4 lse_c = lse_n, dl_c = dl_n;      // scalars of rows 8*q4 + 4g .. +3, one group of four ahead
         uint32_t pk[16];           // [0..7] P pairs, [8..15] dS pairs: four B operands for the consumer
         float p_prev = 0.f, ds_prev = 0.f;
@@ -1318,7 +1359,8 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
               p_ahead = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[r + 1], a.scale_log2, -lse_q));
             }
             const float dl_r = dl_c[r & 3];
-            if constexpr (MASK) p = (kvg > thr_s + 8 * (r >> 2) + (r & 3)) ? 0.f : p;
+            if constexpr (MASK == 1) p = (kvg > thr_s + 8 * (r >> 2) + (r & 3)) ? 0.f : p;
+            if constexpr (MASK == 2) p = (klo > thr_s + 8 * (r >> 2) + (r & 3) || 8 * (r >> 2) + (r & 3) >= hlim) ? 0.f : p;
             const float ds = p * __builtin_fmaf(dpc[r], a.scale, -dl_r);
             if (r & 1) {
               pk[r >> 1] = pack_bf16(p_prev, p); pk[8 + (r >> 1)] = pack_bf16(ds_prev, ds);
@@ -1349,6 +1391,7 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
         if constexpr (SPILL) frag_t = sink;
         if (si.more) {
           if (si.cur.kind != FCP_KIND_FULL) thr_t = si.q0;
+          if constexpr (JOINED) causal_t = (si.cur.kind & 1) != 0;
           if constexpr (SPILL) {
             const int q32 = si.q0 >> 5, nq32 = (si.cur.q_len + 31) >> 5;
             const int head = it.kv_head * group + si.hh;
@@ -1365,11 +1408,20 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
         hb ^= 1;
       };
       // the first interval handles B(-1) (nothing) and A(0), the second B(0) and A(1), ...
-      const std::false_type no_mask;
-      const std::true_type with_mask;
-      for (int iv = 0; iv < n_iv; iv += 2) {
-        if (thr_t != kNoMask) interval(with_mask, s_a, dp_a, s_b, dp_b); else interval(no_mask, s_a, dp_a, s_b, dp_b);
-        if (thr_t != kNoMask) interval(with_mask, s_b, dp_b, s_a, dp_a); else interval(no_mask, s_b, dp_b, s_a, dp_a);
+      const std::integral_constant<int, 0> no_mask;
+      const std::integral_constant<int, 1> with_mask;
+      const std::integral_constant<int, 2> member_mask;
+      if (joined) {
+        // every step masked by member; outside the item's steps thr_t names no row at all, which masks everything
+        for (int iv = 0; iv < n_iv; iv += 2) {
+          interval(member_mask, s_a, dp_a, s_b, dp_b);
+          interval(member_mask, s_b, dp_b, s_a, dp_a);
+        }
+      } else {
+        for (int iv = 0; iv < n_iv; iv += 2) {
+          if (thr_t != kNoMask) interval(with_mask, s_a, dp_a, s_b, dp_b); else interval(no_mask, s_a, dp_a, s_b, dp_b);
+          if (thr_t != kNoMask) interval(with_mask, s_b, dp_b, s_a, dp_a); else interval(no_mask, s_b, dp_b, s_a, dp_a);
+        }
       }
     }
     __syncthreads();
@@ -1387,7 +1439,8 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
 // Columns past the diagonal or past a ragged end get P = 0.  Every dQ row has one writer: plain
 // stores, deterministic.
 // =====================================================================================
-template <int D, bool WITH_D, bool GRAD_BF16>
+// JOINED as in dkdv_kernel (8-worker share, d = 128: 3687 -> 3734 us with both masks in one instance).
+template <int D, bool WITH_D, bool GRAD_BF16, bool JOINED>
 __global__ void __launch_bounds__(512, 2) dq_kernel(BwdArgs a) {
   constexpr int KC = D / 16;
   constexpr int DT = D / 32;
@@ -1396,6 +1449,7 @@ __global__ void __launch_bounds__(512, 2) dq_kernel(BwdArgs a) {
   __shared__ __attribute__((aligned(16))) int32_t s_rec[64];   // next item's record, as in fwd_kernel
   __shared__ int s_next;
   __shared__ __attribute__((aligned(16))) unsigned char s_stage[8][kStageBytes];
+  __shared__ uint16_t s_seg[JOINED ? 512 : 1];   // joined run: member bounds of each lane's query row, as in fwd_kernel
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform, kept in a scalar register
@@ -1446,6 +1500,7 @@ __global__ void __launch_bounds__(512, 2) dq_kernel(BwdArgs a) {
     const uint16_t* kbase = a.k + (int64_t)kvh * D;
     const uint16_t* vbase = a.v + (int64_t)kvh * D;
 
+    if (JOINED) s_seg[tid] = row_ok ? a.q_seg[q_start + my_row] : (uint16_t)0;
     bf16x8 qf[KC], dof[KC];
     float lse_l = INFINITY, dl_l = 0.f;     // rows past the end: P = exp2(-inf) = 0
     {
@@ -1558,8 +1613,15 @@ __global__ void __launch_bounds__(512, 2) dq_kernel(BwdArgs a) {
           // wave-uniform: tiles that straddle the diagonal, and tiles that hold a ragged end (their K rows past
           // the end are zero in LDS, but S = 0 there still gives P = exp2(-LSE), which overflows for a row whose
           // logits are all strongly negative; inf * 0 would then poison the whole dQ row)
-          const bool need_mask = (diag && tc0 + kFwdTileN - 1 > wave_row_lo) || tc0 + kFwdTileN > tp.kv_len;
-          const int limit = diag ? tile_off_q + my_row : tp.kv_len - 1;      // last visible column for this lane
+          const bool joined = JOINED && (tp.kind & 2);
+          const bool need_mask = joined || (diag && tc0 + kFwdTileN - 1 > wave_row_lo) || tc0 + kFwdTileN > tp.kv_len;
+          int limit = diag ? tile_off_q + my_row : tp.kv_len - 1;            // last visible column for this lane
+          int first = 0;                                                     // first one (a joined run: of the row's member)
+          if (joined) {
+            const int sg = s_seg[tid];
+            first = sg & 0xff;
+            limit = min(limit, sg >> 8);
+          }
           // the two 32-row halves of the KV tile one after the other: half the live accumulators
 #pragma unroll
           for (int rt = 0; rt < 2; rt++) {
@@ -1591,7 +1653,7 @@ __global__ void __launch_bounds__(512, 2) dq_kernel(BwdArgs a) {
 #pragma unroll
               for (int r = 0; r < 16; r++) {
                 const int c = tc0 + rt * 32 + 8 * (r >> 2) + 4 * g + (r & 3);
-                if (c > limit) s[r] = 0.f;
+                if (c > limit || c < first) s[r] = 0.f;
               }
             }
 #pragma unroll
@@ -1933,6 +1995,7 @@ static int launch_fwd(const char* who, const fcp_problem* p, const WsLayout* lay
   a.hdr = reinterpret_cast<WsHeader*>(ws);
   a.pairs = reinterpret_cast<const DevPair*>(ws + L.off_pairs);
   a.items = reinterpret_cast<const QItem*>(ws + L.off_fwd_items);
+  a.q_seg = reinterpret_cast<const uint16_t*>(ws + L.off_q_seg);
   a.n_q_heads = p->n_q_heads; a.n_kv_heads = p->n_kv_heads;
   a.scale_log2 = resolve_scale(p) * kLog2e;
   const int grid = (int)std::min<int64_t>(L.n_fwd_items, (int64_t)cu_count() * kFwdWgPerCu);
@@ -1948,9 +2011,11 @@ extern "C" int fcp_block_attn_fwd(const fcp_problem* p, const void* q, const voi
 
 // ---- forward without any allocation: the queue tables live in a fixed device array ----
 namespace fcp {
-// A call is limited by the tables of its plan as given (static_plan_bytes, 2 MiB); the array is larger because a packed
-// block's members become items of their own (8 times the plan's tables covers members of 20 tokens and more).
-constexpr size_t kStaticPlanBytes = 2u << 20, kStaticScratchBytes = 16u << 20;
+// A call is limited by the tables of its plan as given (static_plan_bytes, 2 MiB).  The array holds whatever such a plan
+// becomes: two neighbouring runs of a packed block have more rows than one item, so a block of n items' rows has at
+// most 3 n items (members one row longer than an item between members of one row) and as many pairs, and 16 + 80 bytes for
+// each of 3 n are 4 times the 72 counted for each of n.  Only the member bounds (2 bytes per query row) can be more.
+constexpr size_t kStaticPlanBytes = 2u << 20, kStaticScratchBytes = (8u << 20) + (16u << 10);
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 // Device address of `scratch` on each device (the array's name is a host-side stand-in, not an
 // address a kernel can use; every device holds its own copy at its own address).
@@ -1988,10 +2053,8 @@ extern "C" int fcp_block_attn_fwd_static(const fcp_problem* p, const void* q, co
   if (rc) return rc;
   const size_t plan_bytes = static_plan_bytes(p);
   if (plan_bytes > kStaticPlanBytes || L.off_bwd_deps > kStaticScratchBytes) {
-    const bool plan = plan_bytes > kStaticPlanBytes;
-    set_error("fcp_block_attn_fwd_static: the forward's queue tables need %zu bytes, the fixed scratch array holds %zu "
-              "(use fcp_queue_build + fcp_block_attn_fwd with a workspace of your own)", plan ? plan_bytes : L.off_bwd_deps,
-              plan ? kStaticPlanBytes : kStaticScratchBytes);
+    set_error("fcp_block_attn_fwd_static: the forward's queue tables need %zu bytes, the limit is %zu "
+              "(use fcp_queue_build + fcp_block_attn_fwd with a workspace of your own)", plan_bytes, kStaticPlanBytes);
     return FCP_ERR_BUFFER_TOO_SMALL;
   }
   if (L.n_fwd_items == 0) return FCP_OK;
@@ -2068,11 +2131,20 @@ static int fill_bwd_args(const fcp_problem* p, WsLayout* L, BwdArgs* a, void* wo
   a->deps = reinterpret_cast<const BwdDep*>(ws + L->off_bwd_deps);
   a->items = reinterpret_cast<const BwdItem*>(ws + L->off_bwd_items);
   a->dq_items = reinterpret_cast<const QItem*>(ws + L->off_dq_items);
+  a->q_seg = reinterpret_cast<const uint16_t*>(ws + L->off_q_seg);
   a->n_q_heads = p->n_q_heads; a->n_kv_heads = p->n_kv_heads;
   a->scale = resolve_scale(p); a->scale_log2 = a->scale * kLog2e;
   a->dq = nullptr; a->dk = nullptr; a->dv = nullptr;
   a->o = nullptr; a->lse = nullptr; a->o_is_f32 = 0; a->lse2_out = nullptr; a->dls_out = nullptr; a->ds = nullptr;
   return FCP_OK;
+}
+
+template <bool J>
+static auto dkdv_instance(bool d128, bool gb, bool spill) -> void (*)(BwdArgs) {
+  if (d128) return spill ? (gb ? dkdv_kernel<128, true, true, J> : dkdv_kernel<128, false, true, J>)
+                         : (gb ? dkdv_kernel<128, true, false, J> : dkdv_kernel<128, false, false, J>);
+  return spill ? (gb ? dkdv_kernel<64, true, true, J> : dkdv_kernel<64, false, true, J>)
+               : (gb ? dkdv_kernel<64, true, false, J> : dkdv_kernel<64, false, false, J>);
 }
 
 extern "C" int fcp_block_attn_bwd_dkdv(const fcp_problem* p, const void* q, const void* k, const void* v,
@@ -2086,19 +2158,23 @@ extern "C" int fcp_block_attn_bwd_dkdv(const fcp_problem* p, const void* q, cons
   a.q = (const uint16_t*)q; a.k = (const uint16_t*)k; a.v = (const uint16_t*)v; a.d_o = (const uint16_t*)d_o;
   a.dk = dk; a.dv = dv;
   int grid = (int)std::min<int64_t>(L.n_bwd_items, (int64_t)cu_count() * kDkdvWgPerCu);
-  const bool gb = (p->flags & FCP_FLAG_GRAD_BF16) != 0;
+  const bool gb = (p->flags & FCP_FLAG_GRAD_BF16) != 0, d128 = p->head_dim == 128;
   const bool spill = (p->flags & FCP_FLAG_BWD_SPILL_DS) != 0;
   if (spill) a.ds = static_cast<unsigned char*>(workspace) + L.off_ds;
-  void (*kern)(BwdArgs) =
-      spill ? (p->head_dim == 128 ? (gb ? dkdv_kernel<128, true, true> : dkdv_kernel<128, false, true>)
-                                  : (gb ? dkdv_kernel<64, true, true> : dkdv_kernel<64, false, true>))
-            : (p->head_dim == 128 ? (gb ? dkdv_kernel<128, true, false> : dkdv_kernel<128, false, false>)
-                                  : (gb ? dkdv_kernel<64, true, false> : dkdv_kernel<64, false, false>));
+  void (*kern)(BwdArgs) = p->n_segments > 0 ? dkdv_instance<true>(d128, gb, spill) : dkdv_instance<false>(d128, gb, spill);
   hipLaunchKernelGGL(kern, dim3(grid), dim3(512), 0, (hipStream_t)stream, a);
   return check_launch("fcp_block_attn_bwd_dkdv");
 }
 
 // o / lse == NULL: the per-row scalars come from fcp_bwd_preprocess; else the kernel computes and publishes them.
+template <bool J>
+static auto dq_instance(bool d128, bool with_d, bool gb) -> void (*)(BwdArgs) {
+  if (d128) return with_d ? (gb ? dq_kernel<128, true, true, J> : dq_kernel<128, true, false, J>)
+                          : (gb ? dq_kernel<128, false, true, J> : dq_kernel<128, false, false, J>);
+  return with_d ? (gb ? dq_kernel<64, true, true, J> : dq_kernel<64, true, false, J>)
+                : (gb ? dq_kernel<64, false, true, J> : dq_kernel<64, false, false, J>);
+}
+
 static int launch_dq(const char* who, const fcp_problem* p, const void* q, const void* k, const void* v,
                      const void* o, const float* lse, const void* d_o, void* dq, void* workspace, void* stream) {
   WsLayout L;
@@ -2118,9 +2194,7 @@ static int launch_dq(const char* who, const fcp_problem* p, const void* q, const
     a.dls_out = reinterpret_cast<float*>(ws + L.off_dls);
     a.lse2_out = reinterpret_cast<float*>(ws + L.off_lse2);
   }
-  void (*kern)(BwdArgs) =
-      with_d ? (d128 ? (gb ? dq_kernel<128, true, true> : dq_kernel<128, true, false>) : (gb ? dq_kernel<64, true, true> : dq_kernel<64, true, false>))
-             : (d128 ? (gb ? dq_kernel<128, false, true> : dq_kernel<128, false, false>) : (gb ? dq_kernel<64, false, true> : dq_kernel<64, false, false>));
+  void (*kern)(BwdArgs) = p->n_segments > 0 ? dq_instance<true>(d128, with_d, gb) : dq_instance<false>(d128, with_d, gb);
   hipLaunchKernelGGL(kern, dim3(grid), dim3(512), 0, (hipStream_t)stream, a);
   return check_launch(who);
 }

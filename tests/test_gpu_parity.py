@@ -768,3 +768,106 @@ def test_query_blocks_without_slots(case, spill):
     _check("dq", got["dq"][row_kept], ref[0])
     _check("dk", got["dk"], ref[1])
     _check("dv", got["dv"], ref[2])
+
+
+RUNS = [
+    # member lengths of one packed block, Hq, Hkv, d, causal: where neighbours just fit a run (128 rows; 256 for an odd group) or do not
+    ([1, 129, 1, 127, 1, 128, 64, 64, 65, 63, 2, 3], 4, 2, 128, 1),
+    ([1] * 130 + [126, 2, 300, 5], 2, 1, 64, 1),
+    ([60, 70, 58, 128, 127, 2], 8, 2, 128, 0),
+    ([1, 257, 1, 255, 1, 256, 128, 128, 129, 3], 3, 1, 64, 1),
+    ([100, 100, 56, 40, 200, 57, 1], 2, 2, 128, 1),
+    ([90, 31, 120, 17, 250], 6, 2, 64, 0),
+]
+
+
+def _tables_by_definition(prob, q, k, v, d_o, causal_kinds=(1, 3)):
+    """Attention and its gradients straight from the tables of a problem in fp64: which KV rows a query row sees is read
+    off the pairs (and the members of packed blocks) entry by entry."""
+    see = np.zeros((prob.t_q, prob.t_kv), dtype=bool)
+    for q_blk, kv_blk, kind, _ in prob.pairs:
+        (_, _, q0, n), (_, _, k0, m) = prob.q_blocks[q_blk], prob.kv_blocks[kv_blk]
+        sub = np.ones((n, m), dtype=bool)
+        if kind in causal_kinds:
+            sub &= np.arange(m)[None, :] <= np.arange(n)[:, None]
+        if kind >= 2:
+            member = np.concatenate([np.full(ln, i) for i, (b, _, _, ln) in enumerate(prob.segments) if b == kv_blk])
+            sub &= member[None, :] == member[:, None]
+        see[q0:q0 + n, k0:k0 + m] |= sub
+    hq, hkv, d = prob.n_q_heads, prob.n_kv_heads, prob.head_dim
+    q, k, v, d_o = (orc.bf16_to_f64(x) for x in (q, k, v, d_o))
+    o, lse, dq, dk, dv = np.zeros(q.shape), np.full(q.shape[:2], -np.inf), np.zeros(q.shape), np.zeros(k.shape), np.zeros(v.shape)
+    for h in range(hq):
+        g = h // (hq // hkv)
+        s = np.where(see, q[:, h] @ k[:, g].T / np.sqrt(d), -np.inf)
+        lse[:, h] = np.logaddexp.reduce(s, axis=1)
+        p = np.exp(s - lse[:, h, None])
+        o[:, h] = p @ v[:, g]
+        ds = p * (d_o[:, h] @ v[:, g].T - np.sum(o[:, h] * d_o[:, h], axis=1)[:, None]) / np.sqrt(d)
+        dq[:, h] = ds @ k[:, g]
+        dk[:, g] += ds.T @ q[:, h]
+        dv[:, g] += p.T @ d_o[:, h]
+    return o, lse, dq, dk, dv
+
+
+def _check_tables(plan, hq, hkv, d, bs, seed, flags):
+    """Both forwards, merge and backward on the tables of a plan against their definition."""
+    from paper_2605_08524_amd import binding as B
+    from paper_2605_08524_amd.harness import to_dev_bf16
+    dev = torch.device("cuda:0")
+    prob = B.Problem(plan, hq, hkv, d, bs, 0.0, F32 | flags)
+    rng = np.random.default_rng(seed)
+    host = [workloads.bf16_bits(rng.standard_normal((n, h, d)).astype(np.float32))
+            for n, h in ((prob.t_q, hq), (prob.t_kv, hkv), (prob.t_kv, hkv), (prob.t_q, hq))]
+    q, k, v, d_o = (to_dev_bf16(x, dev) for x in host)
+    nbytes = B.fcp_workspace_bytes(prob)
+    ws = torch.full((nbytes + 256,), 0xFF, dtype=torch.uint8, device=dev)
+    ws_ptr = ws.data_ptr() + (-ws.data_ptr()) % 256
+    B.fcp_queue_build(prob, ws_ptr, nbytes)
+    nan = lambda *shape: torch.full(shape, float("nan"), dtype=torch.float32, device=dev)
+    o_part, lse_part = nan(max(1, prob.n_slot_rows), hq, d), nan(max(1, prob.n_slot_rows), hq)
+    o, lse, dq = nan(prob.t_q, hq, d), nan(prob.t_q, hq), nan(prob.t_q, hq, d)
+    dk, dv = nan(prob.t_kv, hkv, d), nan(prob.t_kv, hkv, d)
+    B.fcp_block_attn_fwd(prob, q, k, v, o_part, lse_part, ws_ptr)
+    B.fcp_merge_partials(prob, o_part, lse_part, o, lse, ws_ptr)
+    B.fcp_block_attn_bwd(prob, q, k, v, o, lse, d_o, dq, dk, dv, ws_ptr)
+    o_part2, lse_part2 = nan(*o_part.shape), nan(*lse_part.shape)
+    B.fcp_block_attn_fwd_static(prob, q, k, v, o_part2, lse_part2)
+    torch.cuda.synchronize(dev)
+    assert torch.equal(o_part, o_part2) and torch.equal(lse_part, lse_part2)
+    ref = _tables_by_definition(prob, *host)
+    _check("o", o.cpu().numpy(), ref[0])
+    _check_lse("lse", lse.cpu().numpy(), ref[1])
+    for name, got, want in zip(("dq", "dk", "dv"), (dq, dk, dv), ref[2:]):
+        _check(name, got.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("spill", [0, 16])
+@pytest.mark.parametrize("case", range(len(RUNS)))
+def test_members_joined_into_runs(case, spill):
+    """Members of a packed block at the edges of what joins a run, with a plain sequence beside them."""
+    from paper_2605_08524_amd import binding as B
+    members, hq, hkv, d, causal = RUNS[case]
+    _say(f"case runs{case} spill={spill}")
+    lens, bs = members + [70], sum(members) + 1
+    plan = B.fcp_plan_blocks_packed(lens, bs, causal, 0, None, [0] * len(members) + [1])
+    assert len(plan["segments"]) == len(members)
+    _check_tables(plan, hq, hkv, d, bs, 900 + case, spill)
+
+
+@pytest.mark.parametrize("spill", [0, 16])
+@pytest.mark.parametrize("hq,hkv,d", [(4, 2, 64), (3, 1, 128)])
+def test_packed_query_block_with_further_slots(hq, hkv, d, spill):
+    """Tables that only a caller builds: a packed query block whose members also see a shared prefix (a slot of a FULL pair)
+    and a second listing of the packed block (a slot of its own), and a second query block that pairs the listings with the
+    kinds the other way round."""
+    members = [30, 1, 97, 128, 5, 140, 20]
+    _say(f"case further slots {hq}/{hkv} d={d} spill={spill}")
+    n = sum(members)
+    off = np.concatenate([[0], np.cumsum(members)[:-1]])
+    kv = [(0, 0, 0, n), (0, 0, n, n), (1, 0, 2 * n, 150)]
+    segments = [(b, 10 + m, int(off[m]), ln) for b in (0, 1) for m, ln in enumerate(members)]
+    plan = dict(kv_blocks=kv, q_blocks=[(0, 0, 0, n), (0, 0, n, n)], pairs=[(0, 2, 0, 0), (0, 0, 3, 1), (0, 1, 2, 2), (1, 0, 2, 3), (1, 1, 3, 4)],
+                slots=[(0, 0, 1, 0), (0, 1, 1, n), (0, 2, 1, 2 * n), (1, 3, 1, 3 * n), (1, 4, 1, 4 * n)], n_slot_rows=5 * n, segments=segments)
+    plan = {key: x if key == "n_slot_rows" else np.asarray(x, dtype=np.int32) for key, x in plan.items()}
+    _check_tables(plan, hq, hkv, d, 512, 950, spill)

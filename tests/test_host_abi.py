@@ -322,6 +322,36 @@ def test_queue_tables_are_built_on_the_host_before_any_gpu_call(packed):
             assert e.value.code == -4, fcp.fcp_last_error()
 
 
+def test_static_forward_accepts_every_plan_within_its_limit():
+    """fcp_block_attn_fwd_static is limited by the plan as given (16 bytes a pair, 72 a forward item, 2 MiB); a plan within
+    that limit is never refused because its packed blocks become more items than that.  The size check comes before any
+    GPU call: without a GPU an accepted plan fails later, with FCP_ERR_HIP."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("needs a box without a GPU: here an accepted plan would be launched")
+    align = lambda x: (x + 255) // 256 * 256
+    bs, refused, taken = 1024, 0, 0
+    for hq, hkv in ((64, 64), (32, 8), (6, 2), (8, 4), (16, 1)):
+        for members in ([20] * 51, [1] * 1024, [8] * 128, [129, 1] * 7, [257, 1] * 3 + [129, 1], [700, 300]):
+            rows = hq // 2 * -(-sum(members) // 128) if hq // hkv % 2 == 0 else hq * -(-sum(members) // 256)
+            fit = (2 * 2 ** 20 - 1024 - 256) // (72 * rows + 16)           # about as many blocks as the limit allows
+            for n in (fit - 2, fit + 8):
+                if n * len(members) > 200000:
+                    continue
+                n_pairs, n_items = n, n * rows
+                over = 1024 + align(16 * n_pairs) + align(72 * n_items) > 2 * 2 ** 20
+                unit = np.repeat(np.arange(n), len(members)).astype(np.int32)
+                plan = fcp.fcp_plan_blocks_packed(members * n, bs + 1, 1, 0, None, unit)
+                assert len(plan["pairs"]) == n_pairs
+                p = fcp.Problem(plan, hq, hkv, 64, bs + 1)
+                with pytest.raises(fcp.FcpError) as e:
+                    fcp.fcp_block_attn_fwd_static(p, None, None, None, None, None)
+                assert e.value.code == (binding.FCP_ERR_BUFFER_TOO_SMALL if over else binding.FCP_ERR_HIP), (hq, hkv, members[:3], n)
+                refused += over
+                taken += not over
+    assert refused > 5 and taken > 5
+
+
 def test_layout_counts_without_building_the_tables():
     """A launch on a workspace that the layout registry does not know computes the layout anew, as fcp_workspace_bytes does:
     from counts, not by building what fcp_queue_build uploads (0.04 of its time here; 0.36 when it built the pair and
