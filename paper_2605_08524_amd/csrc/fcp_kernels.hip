@@ -1629,22 +1629,26 @@ __global__ void __launch_bounds__(512, 2) dq_kernel(BwdArgs a) {
 #pragma unroll
             for (int r = 0; r < 16; r++) { s[r] = 0.f; dp[r] = 0.f; }
             // K and V rows are requested PFQ k-chunks (2 PFQ MFMAs) before the MFMAs that use them; left to
-            // the compiler each read is issued one MFMA ahead and waited for in full (depths 1 .. 4 measured: 2)
+            // the compiler each read is issued one MFMA ahead and waited for in full (depths 1 .. 4 measured: 2).
+            // The first MFMA waits for one read: with the other chunks requested in front of it, too, d = 64 is 4 % slower.
             constexpr int PFQ = 2;
             u32x4 opk[PFQ], opv[PFQ];
-#pragma unroll
-            for (int i = 0; i < PFQ; i++) {
-              opk[i] = lds_read16(row_off[i] + rt * 32 * (D * 2));
-              opv[i] = lds_read16(row_off[i] + rt * 32 * (D * 2) + TB);
-            }
+            auto request = [&](int kc) {
+              opk[kc % PFQ] = lds_read16(row_off[kc] + rt * 32 * (D * 2));
+              opv[kc % PFQ] = lds_read16(row_off[kc] + rt * 32 * (D * 2) + TB);
+            };
+            request(0);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int kc = 0; kc < KC; kc++) {
               s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(opk[kc % PFQ]), qf[kc], s, 0, 0, 0);
-              dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(opv[kc % PFQ]), dof[kc], dp, 0, 0, 0);
-              if (kc + PFQ < KC) {
-                opk[kc % PFQ] = lds_read16(row_off[kc + PFQ] + rt * 32 * (D * 2));
-                opv[kc % PFQ] = lds_read16(row_off[kc + PFQ] + rt * 32 * (D * 2) + TB);
+              if (kc == 0) {
+                __builtin_amdgcn_sched_barrier(0);
+                request(1);
+                __builtin_amdgcn_sched_barrier(0);
               }
+              dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(opv[kc % PFQ]), dof[kc], dp, 0, 0, 0);
+              if (kc + PFQ < KC) request(kc + PFQ);
               __builtin_amdgcn_sched_barrier(0);
             }
 #pragma unroll
@@ -1653,7 +1657,7 @@ __global__ void __launch_bounds__(512, 2) dq_kernel(BwdArgs a) {
 #pragma unroll
               for (int r = 0; r < 16; r++) {
                 const int c = tc0 + rt * 32 + 8 * (r >> 2) + 4 * g + (r & 3);
-                if (c > limit || c < first) s[r] = 0.f;
+                if (c > limit || (JOINED && c < first)) s[r] = 0.f;
               }
             }
 #pragma unroll
