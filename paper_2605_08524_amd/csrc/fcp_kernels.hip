@@ -402,7 +402,7 @@ struct TileIter {
 };
 
 // What a wave needs to know about a tile when it masks it: first column, visible length, kind of its pair.
-// A tile past the end of the item has len = 0: everything is masked.
+// A tile past the end of the item has len = 0: everything is masked.  So has a tile of a joined run, which is always masked.
 struct TileMeta { int c0, len, kind; };
 
 // The scores of a 64-column tile that a lane keeps if only columns < c count, one bit per score: score e = 16 rt + r of a lane
@@ -533,7 +533,7 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
         d_v = reinterpret_cast<uint64_t>(vbase + row0);
         const int valid = min(kFwdTileN, ti.cur.kv_len - ti.c0);
         d_lim = (uint32_t)((valid - 1) * kv_row_stride * 2);
-        d_meta = TileMeta{ti.c0, ti.cur.kv_len, ti.cur.kind};
+        d_meta = TileMeta{ti.c0, (ti.cur.kind & 2) ? 0 : ti.cur.kv_len, ti.cur.kind};
         ti.advance();
       }
     };
@@ -660,7 +660,7 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
         // readfirstlane: the condition is wave-uniform, but the compiler does not know it and would
         // otherwise run the rare path on every tile as 64 compares and selects
         const int need_mask = __builtin_amdgcn_readfirstlane(
-            (int)(tm.len == 0 || tm.c0 + kFwdTileN > tm.len || (tm.kind & 2) || ((tm.kind & 1) && tm.c0 + kFwdTileN - 1 > wave_row_lo)));
+            (int)(tm.c0 + kFwdTileN > tm.len || ((tm.kind & 1) && tm.c0 + kFwdTileN - 1 > wave_row_lo)));
         if (need_mask) {
           // one bit per score of this lane (see keep_below): columns up to the last visible one, or of the row's member
           uint32_t keep = (tm.kind & 2) ? 0u : keep_below(((tm.kind & 1) ? min(tm.len, my_limit + 1) : tm.len) - tm.c0, g);
