@@ -650,8 +650,9 @@ def main():
     kernel_flops = {"fwd": 4 * unit, "bwd_dkdv": 8 * unit, "bwd_dq": (2 if spill else 6) * unit}
     kernel_name = {"fwd": "fwd_kernel", "bwd_dkdv": "dkdv_kernel", "bwd_dq": "dq_ds_kernel" if spill else "dq_kernel"}
     tf = "true" if spill else "false"
-    kernel_instance = {"fwd": f"fcp::fwd_kernel<{wl.head_dim}, {'true' if args.packed else 'false'}>", "bwd_dkdv": f"fcp::dkdv_kernel<{wl.head_dim}, false, {tf}>",
-                       "bwd_dq": f"fcp::dq_ds_kernel<{wl.head_dim}, false>" if spill else f"fcp::dq_kernel<{wl.head_dim}, true, false>"}
+    joined = "true" if len(dp.plan.get("segments", ())) else "false"        # the instances that mask by member
+    kernel_instance = {"fwd": f"fcp::fwd_kernel<{wl.head_dim}>", "bwd_dkdv": f"fcp::dkdv_kernel<{wl.head_dim}, false, {tf}, {joined}>",
+                       "bwd_dq": f"fcp::dq_ds_kernel<{wl.head_dim}, false>" if spill else f"fcp::dq_kernel<{wl.head_dim}, true, false, {joined}>"}
     cands = [k for k in kernel_flops if k in stage_ms]
     dom = max(cands, key=lambda k: stage_ms[k])
     achieved = kernel_flops[dom] / (stage_ms[dom] * 1e-3) / 1e12
@@ -680,7 +681,7 @@ def main():
             "n_kv_heads": wl.n_kv_heads, "head_dim": wl.head_dim, "n_seqs": int(len(wl.seq_lens)),
             "n_pairs": int(len(dp.plan["pairs"])), "n_slots": int(len(dp.plan["slots"])),
             "n_q_blocks": int(len(dp.plan["q_blocks"])), "packed_members": int(len(dp.plan.get("segments", ()))),
-            "fwd_items": int(sum(-(-int(dp.plan["q_blocks"][qb][3]) // 128) for qb in dp.plan["slots"][:, 0]) * (wl.n_q_heads // 2 if (wl.n_q_heads // wl.n_kv_heads) % 2 == 0 else wl.n_q_heads)),
+            "fwd_items": None if len(dp.plan.get("segments", ())) else int(sum(-(-int(dp.plan["q_blocks"][qb][3]) // 128) for qb in dp.plan["slots"][:, 0]) * (wl.n_q_heads // 2 if (wl.n_q_heads // wl.n_kv_heads) % 2 == 0 else wl.n_q_heads)),
             "nnz_per_head": nnz, "o_dtype": "f32" if backward else "bf16", "parallelism": "single-gpu",
             "backward": (args.bwd if backward else None), "workspace_bytes": dp.ws_bytes,
         },

@@ -596,7 +596,8 @@ def test_packed_blocks_fwd_bwd(case, flags):
 
 
 def test_packed_blocks_cut_work_items_and_tiles():
-    """Packing must shrink what the kernels are given: fewer query blocks, hence fewer forward work items."""
+    """Packing must shrink what the planner hands on (fewer query blocks, fewer pairs); neighbouring short members then share
+    work items."""
     from paper_2605_08524_amd import binding as B
     from paper_2605_08524_amd.harness import packed_plan
     wl = workloads.custom_workload([100, 156, 30, 70, 90, 64, 64, 64], 256, 1, 0, 4, 2, 128, seed=1, name="packed-count")
@@ -686,7 +687,7 @@ WAVE_EDGES = [
     ([100, 128, 130, 300, 1], 128, 1, 0, 3, 1, 64),             # odd group: items without a second sub-tile
     ([320, 384, 385, 448, 449, 512, 577], 1024, 1, 0, 2, 2, 128),   # items of 5 to 10 tiles: early and late ticket requests
     ([320, 385, 449, 513], 1024, 0, 0, 4, 2, 64),               # the same without a diagonal
-    ([17], 128, 1, 0, 2, 1, 128),                               # one item: every other workgroup finds the queues dry
+    ([17], 128, 1, 0, 2, 1, 128),                               # one item, one workgroup
     ([1500, 40], 128, 1, 2, 2, 1, 64),                          # one KV head: KV ranges, not sequences, go to the XCDs
     ([33] * 150, 128, 1, 0, 8, 4, 64),                          # more items than compute units, one tile each
 ]

@@ -271,8 +271,8 @@ def test_segment_tables_are_validated():
 
 
 def test_packed_block_size_limit():
-    """The kernels keep a token's member bounds in two 16-bit halves: a packed block above 65 535 tokens is refused
-    when the problem is validated (the planner itself has no such limit)."""
+    """A packed block above 65 535 tokens is refused when the problem is validated: a limit of the interface, which the
+    planner itself does not have."""
     plan = fcp.fcp_plan_blocks_packed([40000, 29000], 70000, 1, 0, None, [0, 0])
     assert plan["kv_blocks"].tolist() == [[0, 0, 0, 69000]] and len(plan["segments"]) == 2
     with pytest.raises(fcp.FcpError) as e:
@@ -303,7 +303,7 @@ def test_packed_pairs_of_a_query_block_agree_on_its_members():
 @pytest.mark.parametrize("packed", [False, True])
 def test_queue_tables_are_built_on_the_host_before_any_gpu_call(packed):
     """Without a GPU, fcp_queue_build still validates the problem, lays out the workspace and builds every table (work
-    items, dependency lists, member bounds of packed blocks) in host memory; only the upload fails, with FCP_ERR_HIP.
+    items, dependency lists, member bounds of joined runs) in host memory; only the upload fails, with FCP_ERR_HIP.
     This is how the queue builder runs under the host sanitizers."""
     import torch
     if torch.cuda.is_available():
