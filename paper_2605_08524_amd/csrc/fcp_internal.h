@@ -22,8 +22,8 @@ constexpr int kMergeMinItems = 2048;  // the merge aims at this many work items 
 // (expand_problem).  Neighbours join a run while it fits the rows of one query-stationary item; its pair keeps the PACKED
 // kind and the kernels mask by member (q_seg).  A member alone in its run is an ordinary segment: FULL or DIAG, no mask.
 // Forward, GQA 32/8, d = 128, 1024-token blocks, against one segment per member and against the block walked whole with the
-// union of its rows' key ranges: 2048 sequences of 8 tokens 105 us (815, 164); 49152 tokens in sequences of 16-256: 328 us
-// (354, 477).
+// union of its rows' key ranges: 2048 sequences of 8 tokens 105 us (821, 164); 49152 tokens in sequences of 16-256: 335 us
+// (365, 477).
 // ds_frag: first 32x32 dS fragment of the pair in the spill buffer (FCP_FLAG_BWD_SPILL_DS; else 0).
 struct DevPair { int32_t kv_start, kv_len, kind, ds_frag; };
 // Query-stationary item of two 128-row sub-tiles that walk the same pair list and share a KV head
