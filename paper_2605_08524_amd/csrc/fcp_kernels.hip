@@ -273,25 +273,28 @@ __device__ __forceinline__ void retire(int32_t* counter, int32_t* done) {
 // workgroup leaves its loop when all queues are dry.
 struct ItemStream {
   int32_t* counter; const int32_t* begin;
-  int ticket;
+  int ticket, bounds;      // bounds: lane 0 the home queue's begin, lane 1 its end
   bool dry;
+  // An increment that wraps at 2^32: of an add the compiler makes one add per wave and waits for its result on the spot (4000
+  // tokens, 4 heads, d = 64, forward: 19.6 us with adds, 19.1 so; training step of 2000 tokens: 53.2 and 52.5).
+  __device__ __forceinline__ static int draw(int32_t* c) { return (int)atomicInc(reinterpret_cast<unsigned*>(c), 0xffffffffu); }
   __device__ __forceinline__ static int home_queue() { return __builtin_amdgcn_s_getreg((3 << 11) | 20) & (kNumXcd - 1); }   // XCC_ID (id 20), bits [3:0]
   // The first item, or -1.  The queue's bounds (lane 0: its begin, lane 1: its end) are in flight beside the ticket: one
   // round trip to memory in front of the first record instead of two.
   __device__ __forceinline__ int start(int32_t* c, const int32_t* b, int lane) {
     counter = c; begin = b; ticket = 0; dry = false;
-    const int bounds = begin[home_queue() + (lane & 1)];
+    bounds = begin[home_queue() + (lane & 1)];
     request(lane);
     const int t = __builtin_amdgcn_readfirstlane(ticket), b0 = __builtin_amdgcn_readlane(bounds, 0);
     if (t < __builtin_amdgcn_readlane(bounds, 1) - b0) return b0 + t;
     dry = true;
     return steal(lane);
   }
-  __device__ __forceinline__ void request(int lane) { if (!dry && lane == 0) ticket = atomicAdd(&counter[home_queue() * kCounterStride], 1); }
+  __device__ __forceinline__ void request(int lane) { if (!dry && lane == 0) ticket = draw(&counter[home_queue() * kCounterStride]); }
   __device__ __forceinline__ int take(int lane) {
     if (!dry) {
-      const int home = home_queue(), b0 = begin[home], t = __builtin_amdgcn_readfirstlane(ticket);
-      if (t < begin[home + 1] - b0) return b0 + t;
+      const int t = __builtin_amdgcn_readfirstlane(ticket), b0 = __builtin_amdgcn_readlane(bounds, 0);
+      if (t < __builtin_amdgcn_readlane(bounds, 1) - b0) return b0 + t;
       dry = true;
     }
     return steal(lane);
@@ -307,7 +310,7 @@ struct ItemStream {
       left &= left - 1;
       const int ql = (home + l) % kNumXcd;
       int i = 0;
-      if (lane == 0) i = atomicAdd(&counter[ql * kCounterStride], 1);
+      if (lane == 0) i = draw(&counter[ql * kCounterStride]);
       i = __builtin_amdgcn_readfirstlane(i);
       if (i < __builtin_amdgcn_readlane(n, l)) return __builtin_amdgcn_readlane(b0, l) + i;
     }
