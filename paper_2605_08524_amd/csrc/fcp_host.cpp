@@ -234,27 +234,39 @@ void expand_problem(const fcp_problem* p, bool forward_only, Expanded* x) {
         const fcp_slot& sl = p->slots[s];
         // a packed query block may have slots of FULL pairs too: the forward walks them once, with all rows of the block
         const bool whole = packed && !packed_slot(p, sl);
-        if (!whole || m == 0)
-          x->fwd.push_back({whole ? qb.tok_start : q0, whole ? qb.tok_len : run[m].len, sl.row_start + (whole ? 0 : run[m].off),
-                            (int32_t)x->pairs.size(), sl.n_pairs, whole ? qb.seq : run[m].seq, to_final, s - s0});
-        else if (forward_only) continue;
+        const int32_t span0 = (int32_t)x->spans.size();
+        if (whole && m > 0 && forward_only) continue;
         for (int i = sl.pair_begin; i < sl.pair_begin + sl.n_pairs; i++) {
           const fcp_pair& pr = p->pairs[i];
           const int32_t seg = runs.begin[pr.kv_blk] + ((pr.kind & 2) ? m : 0);
           KvSeg& k = x->kv[seg];
           const int kind = (pr.kind & 2) && run[m].n_segs == 1 ? pr.kind & 1 : pr.kind;
+          if (!whole || m == 0) {
+            if ((int32_t)x->spans.size() > span0 && x->spans.back().kind == FCP_KIND_FULL && !(kind & 2) &&
+                x->spans.back().kv_start + x->spans.back().kv_len == k.start) {
+              DevPair& sp = x->spans.back();
+              if (kind == FCP_KIND_DIAG) { sp.kind = kind; sp.ext = sp.kv_len; }
+              sp.kv_len += k.len;
+            } else {
+              x->spans.push_back({k.start, k.len, kind, 0});
+            }
+          }
+          if (forward_only) continue;
           x->pairs.push_back({k.start, k.len, kind, spill ? (int32_t)frag : 0});
           joins.push_back({q0, run[m].len, seg});
           k.n_deps++;
           frag += p->n_q_heads * ds_frags_per_head(kind, run[m].len, k.len);
         }
+        if (!whole || m == 0)
+          x->fwd.push_back({whole ? qb.tok_start : q0, whole ? qb.tok_len : run[m].len, sl.row_start + (whole ? 0 : run[m].off),
+                            span0, (int32_t)x->spans.size() - span0, whole ? qb.seq : run[m].seq, to_final, s - s0});
       }
-      x->dq.push_back({q0, run[m].len, q0, p0, (int32_t)x->pairs.size() - p0, run[m].seq, 0, 0});
       if (run[m].n_segs > 1)
         for (int i = run[m].seg_begin; i < run[m].seg_begin + run[m].n_segs; i++) {
           const int lo = p->segments[i].tok_off - run[m].off, hi = lo + p->segments[i].tok_len;
           std::fill(x->q_seg.begin() + q0 + lo, x->q_seg.begin() + q0 + hi, seg_word(lo, hi));
         }
+      if (!forward_only) x->dq.push_back({q0, run[m].len, q0, p0, (int32_t)x->pairs.size() - p0, run[m].seq, 0, 0});
     }
   });
   if (forward_only) return;
@@ -267,7 +279,7 @@ void expand_problem(const fcp_problem* p, bool forward_only, Expanded* x) {
   x->deps.resize(x->pairs.size());
   for (size_t i = 0; i < joins.size(); i++) {
     KvSeg& k = x->kv[joins[i].kv_seg];
-    x->deps[k.dep_begin + k.n_deps++] = {joins[i].q_start, joins[i].q_len, x->pairs[i].kind, x->pairs[i].ds_frag};
+    x->deps[k.dep_begin + k.n_deps++] = {joins[i].q_start, joins[i].q_len, x->pairs[i].kind, x->pairs[i].ext};
   }
   for (const KvSeg& k : x->kv)
     std::stable_partition(x->deps.begin() + k.dep_begin, x->deps.begin() + k.dep_begin + k.n_deps, [](const BwdDep& e) { return !(e.kind & 1); });
@@ -292,7 +304,8 @@ int compute_layout(const fcp_problem* p, bool forward_only, WsLayout* L) {
     for (int s = s0; s < s1; s++) {
       const bool whole = packed && !packed_slot(p, p->slots[s]);
       L->n_fwd_items += whole ? q_items_of(p, p->q_blocks[b].tok_len) : items;
-      L->n_pairs += (int64_t)p->slots[s].n_pairs * (whole && forward_only ? 1 : n_runs);
+      L->n_spans += (int64_t)p->slots[s].n_pairs * (whole ? 1 : n_runs);
+      if (!forward_only) L->n_pairs += (int64_t)p->slots[s].n_pairs * n_runs;
     }
     if (!(p->flags & FCP_FLAG_BWD_SPILL_DS) || s0 == s1) return;
     for (int i = p->slots[s0].pair_begin; i < p->slots[s1 - 1].pair_begin + p->slots[s1 - 1].n_pairs; i++) {
@@ -318,12 +331,13 @@ int compute_layout(const fcp_problem* p, bool forward_only, WsLayout* L) {
     L->t_q += p->q_blocks[b].tok_len;
   }
   if (L->t_q * p->n_q_heads > INT32_MAX) { set_error("more than 2^31-1 (query row, head) entries"); return FCP_ERR_UNSUPPORTED; }
-  if (L->n_pairs > INT32_MAX || L->n_fwd_items > INT32_MAX || L->n_bwd_items > INT32_MAX || L->n_merge_items > INT32_MAX || L->n_dq_items > INT32_MAX) {
+  if (std::max(L->n_pairs, L->n_spans) > INT32_MAX || L->n_fwd_items > INT32_MAX || L->n_bwd_items > INT32_MAX || L->n_merge_items > INT32_MAX || L->n_dq_items > INT32_MAX) {
     set_error("too many pairs or work items"); return FCP_ERR_UNSUPPORTED;
   }
   auto align = [](size_t x) { return (x + 255) & ~(size_t)255; };
   size_t off = align(sizeof(WsHeader));
   L->off_pairs = off;       off = align(off + sizeof(DevPair) * (size_t)std::max<int64_t>(1, L->n_pairs));
+  L->off_spans = off;       off = align(off + sizeof(DevPair) * (size_t)std::max<int64_t>(1, L->n_spans));
   L->off_fwd_items = off;   off = align(off + sizeof(QItem) * (size_t)std::max<int64_t>(1, L->n_fwd_items));
   L->off_q_seg = off;       off = align(off + (p->n_segments ? sizeof(uint16_t) * (size_t)L->t_q : 0));
   L->off_bwd_deps = off;    off = align(off + sizeof(BwdDep) * (size_t)std::max<int64_t>(1, L->n_pairs));
@@ -390,17 +404,21 @@ int layout_for(const fcp_problem* p, const void* workspace, WsLayout* L) {
 
 namespace {
 
-// 64-row KV tiles that a query-stationary item visits: every pair in full, a DIAG pair up to the item's last row.
-void count_tiles(QItem* it, const std::vector<DevPair>& pairs) {
+// Column of a pair (not a span: 0) or span where its DIAG block starts.
+int diag_off(const DevPair& p, bool spans) { return spans ? p.ext : 0; }
+
+// 64-row KV tiles that a query-stationary item visits: every pair (span) in full, a DIAG one up to the item's last row.
+void count_tiles(QItem* it, const std::vector<DevPair>& pairs, bool spans) {
   const int row_hi = std::max(it->tile_off[0] + it->q_rows[0], it->tile_off[1] + it->q_rows[1]);
   int n = 0;
   for (int i = it->pair_begin; i < it->pair_begin + it->n_pairs; i++) {
-    const int nc = (pairs[i].kind & 1) ? std::min(pairs[i].kv_len, row_hi) : pairs[i].kv_len;
+    const int nc = (pairs[i].kind & 1) ? std::min(pairs[i].kv_len, diag_off(pairs[i], spans) + row_hi) : pairs[i].kv_len;
     n += (nc + kQTileN - 1) / kQTileN;
   }
   it->n_tiles = n;
   if (it->n_pairs > 0) it->first = pairs[it->pair_begin];
-  it->diag_last = it->n_pairs > 0 && (pairs[it->pair_begin + it->n_pairs - 1].kind & 1);
+  it->diag_last = -1;
+  if (it->n_pairs > 0 && (pairs[it->pair_begin + it->n_pairs - 1].kind & 1)) it->diag_last = diag_off(pairs[it->pair_begin + it->n_pairs - 1], spans);
 }
 
 // Work items in groups that stay together: the items of a unit (one per (segment, KV head)) are consecutive in `items`, a
@@ -476,7 +494,7 @@ struct ItemGroups {
 // The query-stationary items (forward, dQ) of a list of segments, one unit per (segment, KV head): its items share
 // K/V.  An item joins two sub-tiles: heads (2j, 2j+1) of the group on one row tile when G is even, else row tiles
 // (2j, 2j+1) of one head.
-void q_items(const fcp_problem* p, const std::vector<QSeg>& segs, const std::vector<DevPair>& pairs, int64_t n_items, std::vector<QItem>* flat,
+void q_items(const fcp_problem* p, const std::vector<QSeg>& segs, const std::vector<DevPair>& pairs, bool spans, int64_t n_items, std::vector<QItem>* flat,
              int32_t begin[kNumXcd + 1]) {
   const int G = p->n_q_heads / p->n_kv_heads, heads_per_item = G % 2 == 0 ? 2 : 1;
   ItemGroups<QItem> groups;
@@ -491,7 +509,7 @@ void q_items(const fcp_problem* p, const std::vector<QSeg>& segs, const std::vec
     for (int t = 0; t < n_tiles; t++) {
       const int off = t * kFwdTileM, n_rows = std::min(kFwdTileM, sg.len - off);
       for (int i = sg.pair_begin; i < sg.pair_begin + sg.n_pairs; i++)
-        tile_w[t] += (int64_t)n_rows * ((pairs[i].kind & 1) ? std::min(pairs[i].kv_len, off + n_rows) : pairs[i].kv_len);
+        tile_w[t] += (int64_t)n_rows * ((pairs[i].kind & 1) ? std::min(pairs[i].kv_len, diag_off(pairs[i], spans) + off + n_rows) : pairs[i].kv_len);
     }
     rows.clear();
     int64_t w = 0;                                // of the segment and one KV head
@@ -506,7 +524,7 @@ void q_items(const fcp_problem* p, const std::vector<QSeg>& segs, const std::vec
         it.out_row[k] = sg.out_row + off; it.tile_off[k] = off;
         if (!absent) w += tile_w[tile] * (G / heads_per_item);
       }
-      count_tiles(&it, pairs);
+      count_tiles(&it, pairs, spans);
       rows.push_back(it);
     }
     for (int g = 0; g < p->n_kv_heads; g++) {
@@ -842,15 +860,17 @@ int fcp::build_queue_image(const fcp_problem* p, const Expanded& x, const WsLayo
   for (float& v : hdr->infs) v = INFINITY;
   auto put = [&](size_t off, const auto& v) { if (!v.empty()) std::memcpy(host.data() + off, v.data(), v.size() * sizeof(v[0])); };
   if ((int64_t)x.pairs.size() != L.n_pairs) { set_error("internal: pair count mismatch"); return FCP_ERR_INVALID_ARG; }
+  if ((int64_t)x.spans.size() > L.n_spans) { set_error("internal: span count mismatch"); return FCP_ERR_INVALID_ARG; }
   put(L.off_pairs, x.pairs);
+  put(L.off_spans, x.spans);
   put(L.off_q_seg, x.q_seg);
   std::vector<QItem> flat;
-  q_items(p, x.fwd, x.pairs, L.n_fwd_items, &flat, hdr->fwd_begin);
+  q_items(p, x.fwd, x.spans, true, L.n_fwd_items, &flat, hdr->fwd_begin);
   if ((int64_t)flat.size() != L.n_fwd_items) { set_error("internal: forward item count mismatch"); return FCP_ERR_INVALID_ARG; }
   put(L.off_fwd_items, flat);
   if (forward_only) return FCP_OK;
   // ---- dQ: query-stationary items over all pairs of a query segment
-  q_items(p, x.dq, x.pairs, L.n_dq_items, &flat, hdr->dq_begin);
+  q_items(p, x.dq, x.pairs, false, L.n_dq_items, &flat, hdr->dq_begin);
   if ((int64_t)flat.size() != L.n_dq_items) { set_error("internal: dQ item count mismatch"); return FCP_ERR_INVALID_ARG; }
   put(L.off_dq_items, flat);
   // ---- dK / dV: dependency lists per KV segment, one group per (KV segment, KV head)

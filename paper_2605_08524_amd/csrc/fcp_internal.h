@@ -24,15 +24,20 @@ constexpr int kMergeMinItems = 2048;  // the merge aims at this many work items 
 // Forward, GQA 32/8, d = 128, 1024-token blocks, against one segment per member and against the block walked whole with the
 // union of its rows' key ranges: 2048 sequences of 8 tokens 105 us (821, 164); 49152 tokens in sequences of 16-256: 335 us
 // (365, 477).
-// ds_frag: first 32x32 dS fragment of the pair in the spill buffer (FCP_FLAG_BWD_SPILL_DS; else 0).
-struct DevPair { int32_t kv_start, kv_len, kind, ds_frag; };
+// ext: first 32x32 dS fragment of the pair in the spill buffer (FCP_FLAG_BWD_SPILL_DS; else 0).
+// The forward walks spans instead: neighbouring pairs of a slot whose KV rows follow each other, joined (FULL ones, and the DIAG
+// one that ends them).  Its tiles then run on across block borders, and what the walk looks up per pair is looked up once
+// per slot.  ext of a span: column where its DIAG block starts.
+struct DevPair { int32_t kv_start, kv_len, kind, ext; };
 // Query-stationary item of two 128-row sub-tiles that walk the same pair list and share a KV head
 // (two query heads of a group, or two neighbouring row tiles of one head; q_rows[1] = 0: none).
 // to_final != 0 (forward items only): the slot is the only one of its query block.
 // q_blk_len (dQ items only): rows of the whole query block (of the member, in a packed block).
 // n_tiles: 64-row KV tiles the item walks (a DIAG pair only up to the item's last query row).
+// pair_begin, n_pairs, first, diag_last: spans in forward items, pairs in dQ items.
 // first: the first of its pairs (in the record, so that an item's first tile needs no second table read).
-// diag_last: the last pair is DIAG (a wave whose rows end early need not compute the tiles past them).
+// diag_last: column of the last span where its DIAG block starts, -1 if it has none (a wave whose rows end early need not compute
+// the tiles past them).
 struct QItem { int32_t q_start[2], q_rows[2], out_row[2], tile_off[2], head[2], pair_begin, n_pairs, to_final, q_blk_len, n_tiles, diag_last; DevPair first; };
 constexpr int kQTileN = 64;         // KV rows per LDS tile of the query-stationary kernels
 struct BwdDep  { int32_t q_start, q_len, kind, ds_frag; };
@@ -80,10 +85,10 @@ struct WsHeader {
 
 // Byte offsets of the workspace sections, a pure function of the problem's counts.
 struct WsLayout {
-  int64_t n_fwd_items, n_bwd_items, n_merge_items, n_dq_items, n_pairs, t_q;
+  int64_t n_fwd_items, n_bwd_items, n_merge_items, n_dq_items, n_pairs, n_spans, t_q;   // n_spans: at most
   int merge_chunk;  // (row, head) entries per merge work item, chosen per problem
   int64_t n_ds_frags;   // fragments of the dS spill buffer, sinks and one fragment of slack included (0 without the flag)
-  size_t off_pairs, off_fwd_items, off_q_seg, off_bwd_deps, off_bwd_items, off_merge_items, off_slot_rh, off_dq_items, off_dls, off_lse2, off_ds, total;
+  size_t off_pairs, off_spans, off_fwd_items, off_q_seg, off_bwd_deps, off_bwd_items, off_merge_items, off_slot_rh, off_dq_items, off_dls, off_lse2, off_ds, total;
 };
 
 // The problem as the kernels see it.  Segment = rows that share a pair list: a query block (KV block), or one run of
@@ -91,13 +96,13 @@ struct WsLayout {
 struct QSeg { int32_t start, len, out_row, pair_begin, n_pairs, seq, to_final, ordinal; };   // rows in the Q buffer / partial buffers
 struct KvSeg { int32_t start, len, seq, dep_begin, n_deps; };
 struct Expanded {
-  std::vector<DevPair> pairs;
+  std::vector<DevPair> pairs, spans;
   std::vector<QSeg> fwd, dq;       // per slot; per query block (all pairs of its slots)
   std::vector<KvSeg> kv;
   std::vector<BwdDep> deps;        // by KV segment
   std::vector<uint16_t> q_seg;     // per Q-buffer row (empty without packed blocks)
 };
-// forward_only: for an image without backward tables (dq, kv, deps and their pairs stay out)
+// forward_only: for an image without backward tables (pairs, dq, deps stay out)
 void expand_problem(const fcp_problem* p, bool forward_only, Expanded* x);   // host; p has been validated
 int validate_problem(const fcp_problem* p);           // host; sets the error text
 int compute_layout(const fcp_problem* p, bool forward_only, WsLayout* L);   // host; counts only, p has been validated

@@ -58,6 +58,14 @@ __device__ __forceinline__ bf16x8 lds_tr_pair(const unsigned char* lo, const uns
 }
 
 __device__ __forceinline__ float xor32(float x) { return __shfl_xor(x, 32, 64); }
+// Maximum over a lane and its partner (lane ^ 32), without a trip through LDS: the swap leaves the lower half of x in both
+// halves of one result, the upper half in the other.  (__builtin_bit_cast of a vector element takes element 0: copies first.)
+__device__ __forceinline__ float max32(float x) {
+  const uint32_t a = __builtin_bit_cast(uint32_t, x);
+  const u32x2 r = __builtin_amdgcn_permlane32_swap(a, a, false, false);
+  const uint32_t lo = r[0], hi = r[1];
+  return fmaxf(__builtin_bit_cast(float, lo), __builtin_bit_cast(float, hi));
+}
 
 // LDS accesses through 32-bit LDS addresses kept in registers: a tile buffer switch is then one
 // add per address (in place) and row / tile offsets fold into the instruction's immediate field.
@@ -351,6 +359,13 @@ __device__ __forceinline__ Item read_item(const int32_t* rec) {
 // workgroup barrier per tile.  The first iteration of an item computes S of its first tile only
 // and the last one only adds the last tile to O, so the pipeline fill costs no MFMAs; all
 // iterations issue the same tile loads, and the ring runs on from item to item.
+// Between the last MFMA of an iteration and the first of the next lie the barrier, the row maximum and the walk to the next tile,
+// without an MFMA beside them in either wave of the SIMD (both have just passed the barrier): 1150 of 3650 cycles at d = 128,
+// 1050 of 2350 at d = 64 (timestamps).  What runs there is kept short: spans instead of pairs (DevPair) and a step of a few scalar
+// additions inside one, one word per tile that says from where on it is masked, buffer offsets as immediates, the maximum
+// over both halves without LDS, the row sums pinned into the exponential phase.  Forward, before and after: 4000 tokens, 4 heads,
+// d = 64 19.1 -> 16.4 us; 65536 lognormal tokens, GQA 32/8, d = 128 2357 -> 2211 (1010 -> 1040 TFLOP/s); 32768 rows of a
+// 262144-token sequence 64.2 -> 60.4 ms; short sequences in shared blocks 335 -> 309 us.
 // A wave computes only the tiles its own rows can see: past them (a diagonal, a ragged end, an item of one sub-tile) it
 // loads and waits.  65536 packed tokens (lognormal, GQA 32/8, d = 128): 2.66 -> 2.60 ms; sequences of 16-256 tokens:
 // 0.72 -> 0.66 ms.
@@ -364,7 +379,7 @@ struct FwdArgs {
   void* o_part; float* lse_part; int32_t part_is_bf16;
   void* o; float* lse; int32_t o_is_f32;     // final outputs for query blocks with a single slot (or NULL)
   int32_t running;                            // fold every slot into the running (o, lse) in place (fp32 o)
-  WsHeader* hdr; const DevPair* pairs; const QItem* items; const uint16_t* q_seg;
+  WsHeader* hdr; const DevPair* spans; const QItem* items; const uint16_t* q_seg;
   int32_t n_q_heads, n_kv_heads;
   float scale_log2;   // softmax scale * log2(e)
 };
@@ -376,23 +391,23 @@ struct TileIter {
   int pair, pair_end, c0, ncols, row_hi;   // row_hi = tile_off + q_rows (first row past the tile)
   DevPair cur;
   bool more;
-  __device__ __forceinline__ void set(int kv_start, int kv_len, int kind, int ds_frag) {
+  __device__ __forceinline__ void set(int kv_start, int kv_len, int kind, int ext) {
     // the pair index is wave-uniform; readfirstlane says so to the compiler, which then keeps the record (and
     // everything derived from it) in scalar registers and branches on it with scalar branches
     cur.kv_start = __builtin_amdgcn_readfirstlane(kv_start); cur.kv_len = __builtin_amdgcn_readfirstlane(kv_len);
-    cur.kind = __builtin_amdgcn_readfirstlane(kind); cur.ds_frag = __builtin_amdgcn_readfirstlane(ds_frag);
+    cur.kind = __builtin_amdgcn_readfirstlane(kind); cur.ext = __builtin_amdgcn_readfirstlane(ext);
     ncols = (cur.kind & 1) ? min(cur.kv_len, row_hi) : cur.kv_len;
   }
   __device__ __forceinline__ void load_pair() {
     const DevPair p = pairs[pair];
-    set(p.kv_start, p.kv_len, p.kind, p.ds_frag);
+    set(p.kv_start, p.kv_len, p.kind, p.ext);
   }
   __device__ __forceinline__ void init(const DevPair* p, const QItem& it) {
     pairs = p; pair = it.pair_begin; pair_end = it.pair_begin + it.n_pairs; c0 = 0; ncols = 0;
     row_hi = max(it.tile_off[0] + it.q_rows[0], it.tile_off[1] + it.q_rows[1]);
     cur = DevPair{0, 0, 0, 0};
     more = it.n_pairs > 0;
-    if (more) set(it.first.kv_start, it.first.kv_len, it.first.kind, it.first.ds_frag);
+    if (more) set(it.first.kv_start, it.first.kv_len, it.first.kind, it.first.ext);
   }
   __device__ __forceinline__ void advance() {
     c0 += kFwdTileN;
@@ -403,10 +418,6 @@ struct TileIter {
     }
   }
 };
-
-// What a wave needs to know about a tile when it masks it: first column, visible length, kind of its pair.
-// A tile past the end of the item has len = 0: everything is masked.  So has a tile of a joined run, which is always masked.
-struct TileMeta { int c0, len, kind; };
 
 // The scores of a 64-column tile that a lane keeps if only columns < c count, one bit per score: score e = 16 rt + r of a lane
 // is column 8 (e / 4) + 4 g + e % 4.  A mask of bits costs a score two operations, as a compare with a bound does, but only
@@ -452,19 +463,27 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
   const uint32_t dma_step = (uint32_t)(8 * RPI * kv_row_stride * 2);
   // transpose-read pattern inside a 16-lane group: row tr_row, 4 columns from tr_col
   const int tr_row = (lane & 15) >> 2, tr_col = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-  // Ring positions, advanced by one buffer per tile and kept across items: in iteration i the
-  // wave reads the K rows of tile i+1 (b_k), transposes V of tile i (b_v), and tile i+3 is requested (b_dma).
-  int b_k = 0, b_v = NB - 1, b_dma = 2;
-  // Per-lane LDS addresses into the current buffers (the swizzle has period 16 in the row, so
-  // rows +16 / +32 are plain immediate offsets), advanced in place.
+  // Tile t of an item is in buffer t % 4: in iteration i the wave reads the K rows of tile i+1, transposes V of tile i, and
+  // tile i+3 is requested.  Per-lane LDS addresses (the swizzle has period 16 in the row, so rows +16 / +32 are plain
+  // immediate offsets) of a pair of buffers: the second one is an immediate offset too, and the addresses change pairs
+  // every other tile.
+  static_assert(NB == 4 && BUF + 3 * 16 * D * 2 < 65536 && BUF + 32 * D * 2 < 65536, "two pairs of buffers, offsets of 16 bits");
   uint32_t tr_lo[DT], tr_hi[DT], kk_off[KC];
 #pragma unroll
   for (int dt = 0; dt < DT; dt++) {
-    tr_lo[dt] = lds_addr(lds_kv[b_v]) + TB + tile_off<D>(4 * g + tr_row, 4 * dt + (tr_col >> 3)) + (tr_col & 4) * 2;
-    tr_hi[dt] = lds_addr(lds_kv[b_v]) + TB + tile_off<D>(4 * g + tr_row + 8, 4 * dt + (tr_col >> 3)) + (tr_col & 4) * 2;
+    tr_lo[dt] = lds_addr(lds_kv[0]) + TB + tile_off<D>(4 * g + tr_row, 4 * dt + (tr_col >> 3)) + (tr_col & 4) * 2;
+    tr_hi[dt] = lds_addr(lds_kv[0]) + TB + tile_off<D>(4 * g + tr_row + 8, 4 * dt + (tr_col >> 3)) + (tr_col & 4) * 2;
   }
 #pragma unroll
-  for (int kc = 0; kc < KC; kc++) kk_off[kc] = lds_addr(lds_kv[b_k]) + tile_off<D>(l32, 2 * kc + g);
+  for (int kc = 0; kc < KC; kc++) kk_off[kc] = lds_addr(lds_kv[0]) + tile_off<D>(l32, 2 * kc + g);
+  auto move_k = [&](int by) {
+#pragma unroll
+    for (int kc = 0; kc < KC; kc++) kk_off[kc] += by;
+  };
+  auto move_v = [&](int by) {
+#pragma unroll
+    for (int dt = 0; dt < DT; dt++) { tr_lo[dt] += by; tr_hi[dt] += by; }
+  };
 
   ItemStream items;
   if (wave == 0) {
@@ -482,7 +501,7 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
     const int sub = wave >> 2, wq = sub ? 3 - (wave & 3) : wave & 3;
     // selects, not it.q_rows[sub]: a run-time index would put the whole item into private memory
     const int q_rows = (sub ? it.q_rows[1] : it.q_rows[0]), tile_off_q = (sub ? it.tile_off[1] : it.tile_off[0]), head = (sub ? it.head[1] : it.head[0]);
-    const int kvh = it.head[0] / group;
+    const int kvh = __builtin_amdgcn_readfirstlane(it.head[0] / group);     // the division runs on the vector unit
     const int my_row = wq * 32 + l32;                        // row inside the sub-tile
     const int wave_row_lo = tile_off_q + wq * 32;            // rows of this wave inside the block
     const int my_limit = tile_off_q + my_row;                // last visible column of a DIAG pair for this lane
@@ -512,52 +531,70 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
       for (int r = 0; r < 16; r++) o[dt][r] = 0.f;
     float m_run = -INFINITY, l_run = 0.f;
 
-    TileIter ti;                      // names the next tile to LOAD
-    ti.init(a.pairs, it);
-    // Tiles this wave computes: all of the item's, less the trailing ones of a last DIAG pair that start past its own
+    // Tiles this wave computes: all of the item's, less the trailing ones of a last DIAG span that start past its own
     // last row; none if its rows lie past the ragged end.  What remains it only loads and waits for.
     const int row_hi = max(it.tile_off[0] + it.q_rows[0], it.tile_off[1] + it.q_rows[1]);
     const int wave_row_hi = min(wave_row_lo + 32, tile_off_q + q_rows);
     const int n_tiles = it.n_tiles;
     const int n_vis = wq * 32 >= q_rows ? 0
-                    : it.diag_last ? n_tiles - ((row_hi + kFwdTileN - 1) / kFwdTileN - (wave_row_hi + kFwdTileN - 1) / kFwdTileN)
-                                   : n_tiles;
+                    : it.diag_last >= 0 ? n_tiles - ((it.diag_last + row_hi + kFwdTileN - 1) / kFwdTileN - (it.diag_last + wave_row_hi + kFwdTileN - 1) / kFwdTileN)
+                                        : n_tiles;
 
-    // The load of one tile in two parts.  describe(): scalar bookkeeping with branches, run at
-    // an iteration boundary.  issue(): branch-free, sits between the MFMAs.
+    // The load of one tile in two parts.  describe(): scalar bookkeeping, run at an iteration boundary, where no MFMA
+    // covers it: inside a span a handful of additions.  issue(): branch-free, sits between the MFMAs.
+    // A tile is masked for this wave from the column on where its first row sees nothing more (a DIAG span), the span ends, or at
+    // once (a joined run); see mask_word.
+    const uint32_t lim_whole = (uint32_t)((kFwdTileN - 1) * kv_row_stride * 2), tile_step = (uint32_t)(kFwdTileN * kv_row_stride * 2);
     uint64_t d_k = 0, d_v = 0;
-    uint32_t d_lim = 0;
-    TileMeta d_meta = {0, 0, 0};
+    uint32_t d_lim = 0, lim_last = 0;
+    int left = 0, span = 0;           // tiles of the span in hand not yet described, less one; its number
+    int d_word = 0;                   // 4 * (columns that need no mask - first column - 64) + kind: below zero needs a mask
+    auto open_span = [&](const DevPair& sp) {
+      // wave-uniform: readfirstlane says so to the compiler, which then keeps what follows in scalar registers
+      const int kv_start = __builtin_amdgcn_readfirstlane(sp.kv_start), kv_len = __builtin_amdgcn_readfirstlane(sp.kv_len);
+      const int kind = __builtin_amdgcn_readfirstlane(sp.kind), diag = __builtin_amdgcn_readfirstlane(sp.ext);
+      const int ncols = (kind & 1) ? min(kv_len, diag + row_hi) : kv_len;
+      left = (ncols - 1) / kFwdTileN;
+      lim_last = (uint32_t)((min(kFwdTileN, kv_len - left * kFwdTileN) - 1) * kv_row_stride * 2);
+      d_lim = left > 0 ? lim_whole : lim_last;
+      const int64_t row0 = (int64_t)kv_start * kv_row_stride;
+      d_k = reinterpret_cast<uint64_t>(kbase + row0);
+      d_v = reinterpret_cast<uint64_t>(vbase + row0);
+      const int open = (kind & 2) ? 0 : (kind & 1) ? diag + wave_row_lo + 1 : kv_len;
+      d_word = 4 * (open - kFwdTileN) + kind;
+      span++;
+    };
     auto describe = [&]() {
-      d_k = reinterpret_cast<uint64_t>(zeros); d_v = d_k; d_lim = 0; d_meta = TileMeta{0, 0, 0};
-      if (ti.more) {
-        const int64_t row0 = (int64_t)(ti.cur.kv_start + ti.c0) * kv_row_stride;
-        d_k = reinterpret_cast<uint64_t>(kbase + row0);
-        d_v = reinterpret_cast<uint64_t>(vbase + row0);
-        const int valid = min(kFwdTileN, ti.cur.kv_len - ti.c0);
-        d_lim = (uint32_t)((valid - 1) * kv_row_stride * 2);
-        d_meta = TileMeta{ti.c0, (ti.cur.kind & 2) ? 0 : ti.cur.kv_len, ti.cur.kind};
-        ti.advance();
+      if (__builtin_expect(left > 0, 1)) {
+        left--;
+        d_k += tile_step; d_v += tile_step;
+        d_word -= 4 * kFwdTileN;
+        d_lim = left > 0 ? lim_whole : lim_last;
+      } else if (span < it.n_pairs) {
+        open_span(a.spans[it.pair_begin + span]);
+      } else {
+        d_k = reinterpret_cast<uint64_t>(zeros); d_v = d_k; d_lim = 0;      // past the end
       }
     };
+    int dma_tile = 0;
     auto issue = [&]() {
-      const uint32_t lbase = lds_addr(lds_kv[0]) + b_dma * BUF;
+      const uint32_t lbase = lds_addr(lds_kv[0]) + (dma_tile & (NB - 1)) * BUF;
 #pragma unroll
       for (int n = 0; n < NDMA; n++) {
         const uint32_t voff = min(dma_row0 + n * dma_step, d_lim) + dma_chunk;
         lds_dma16_s(reinterpret_cast<const unsigned char*>(d_k), voff, lbase + (8 * n + wave) * 1024);
         lds_dma16_s(reinterpret_cast<const unsigned char*>(d_v), voff, lbase + TB + (8 * n + wave) * 1024);
       }
-      b_dma = (b_dma == NB - 1) ? 0 : b_dma + 1;
+      dma_tile++;
     };
     const bool short_item = n_vis < 7;         // too short to ask for the next ticket later than here
     if (wave == 0 && short_item) items.request(lane);
-    // prologue: tiles 0 and 1 into the two buffers before the next one to load
-    TileMeta meta[3];                 // tiles i+1, i+2, i+3 (shift register)
-    b_dma = (b_dma + NB - 2) % NB;
-    describe(); issue(); meta[0] = d_meta;
-    describe(); issue(); meta[1] = d_meta;
-    describe(); meta[2] = d_meta;     // tile 2, requested inside the first iteration
+    // prologue: tiles 0 and 1
+    int word[3];                      // d_word of tiles i+1, i+2, i+3 (shift register)
+    if (it.n_pairs > 0) open_span(it.first); else describe();
+    issue(); word[0] = d_word;
+    describe(); issue(); word[1] = d_word;
+    describe(); word[2] = d_word;     // tile 2, requested inside the first iteration
     dma_wait();
     __syncthreads();
 
@@ -567,29 +604,20 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
 #pragma unroll
       for (int r = 0; r < 16; r++) { s_a[rt][r] = -INFINITY; s_b[rt][r] = 0.f; }
 
-    auto rotate = [&]() {             // the ring, to the next tile
-      meta[0] = meta[1]; meta[1] = meta[2];
-      describe(); meta[2] = d_meta;
-      const int sk = (b_k == NB - 1) ? -(NB - 1) * BUF : BUF;
-#pragma unroll
-      for (int kc = 0; kc < KC; kc++) kk_off[kc] += sk;
-      b_k = (b_k == NB - 1) ? 0 : b_k + 1;
-      const int sv = (b_v == NB - 1) ? -(NB - 1) * BUF : BUF;
-#pragma unroll
-      for (int dt = 0; dt < DT; dt++) { tr_lo[dt] += sv; tr_hi[dt] += sv; }
-      b_v = (b_v == NB - 1) ? 0 : b_v + 1;
-    };
+    auto next_tile = [&]() { word[0] = word[1]; word[1] = word[2]; describe(); word[2] = d_word; };
+    int k_step = 2 * BUF, v_step = 2 * BUF;      // to the other pair of buffers
     // the tile two ahead has landed once at most one tile's loads are in flight
     auto tile_barrier = [&]() {
       __builtin_amdgcn_s_waitcnt(0x0F70 | (DMA_PER_TILE & 15) | ((DMA_PER_TILE >> 4) << 14));
       __syncthreads();
     };
     // One iteration.  sc = scores of tile i (masked, maximum already folded into m_run);
-    // sn receives S^T of tile i+1.
+    // sn receives S^T of tile i+1.  ODD: i is odd (the buffer of its pair that V of tile i is in; K of tile i+1: the other one).
     // FIRST: nothing to exponentiate or to add to O yet (S^T of tile 0 only); LAST: no next tile (O += V P of the
     // last tile only).  An item thus costs one iteration's worth of MFMAs per tile and nothing for the pipeline fill.
-    auto iteration = [&](auto first_t, auto last_t, f32x16 (&sc)[2], f32x16 (&sn)[2]) {
-      constexpr bool FIRST = decltype(first_t)::value, LAST = decltype(last_t)::value;
+    auto iteration = [&](auto first_t, auto last_t, auto odd_t, f32x16 (&sc)[2], f32x16 (&sn)[2]) {
+      constexpr bool FIRST = decltype(first_t)::value, LAST = decltype(last_t)::value, ODD = decltype(odd_t)::value;
+      constexpr uint32_t K_OFF = ODD ? 0 : BUF, V_OFF = ODD ? BUF : 0;
       const float m_use = (m_run == -INFINITY) ? 0.f : m_run;
       u32x4 pb[4];                    // P^T of tile i as four B operands (rt, j)
       float rs = 0.f;
@@ -605,8 +633,9 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
         rs += p;
         if (r & 1) {
           pb[e >> 3][(e >> 1) & 3] = pack_bf16(p_prev, p);
-          // keeps the vector work between the MFMAs it was written between
-          asm volatile("" :: "v"(pb[e >> 3][(e >> 1) & 3]));
+          // keeps the vector work between the MFMAs it was written between; without rs the 32 additions all sank behind the
+          // barrier, where no MFMA covers them, and held 32 registers until then
+          asm volatile("" : "+v"(rs) : "v"(pb[e >> 3][(e >> 1) & 3]));
         } else p_prev = p;
       };
       // ---- phase 1: S^T(i+1) = K Q^T (two 32-row halves); exponentials of tile i between the MFMAs
@@ -617,7 +646,7 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
       } else {
         u32x4 op[PF];
 #pragma unroll
-        for (int u = 0; u < PF; u++) op[u] = lds_read16(kk_off[u / 2] + (u & 1) * 32 * (D * 2));
+        for (int u = 0; u < PF; u++) op[u] = lds_read16(kk_off[u / 2] + K_OFF + (u & 1) * 32 * (D * 2));
 #pragma unroll
         for (int u = 0; u < NS1; u++) {
           const int kc = u / 2, rt = u & 1;
@@ -626,7 +655,7 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
             for (int r = 0; r < 16; r++) sn[rt][r] = 0.f;
           }
           sn[rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(op[u % PF]), qf[kc], sn[rt], 0, 0, 0);
-          if (u + PF < NS1) op[u % PF] = lds_read16(kk_off[(u + PF) / 2] + ((u + PF) & 1) * 32 * (D * 2));
+          if (u + PF < NS1) op[u % PF] = lds_read16(kk_off[(u + PF) / 2] + K_OFF + ((u + PF) & 1) * 32 * (D * 2));
           // 24 of the 32 elements in this phase
           if constexpr (!FIRST) {
 #pragma unroll
@@ -640,7 +669,7 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
       if constexpr (!FIRST) {
         u32x4 op[PF];
         auto fetch = [&](int u) {
-          const uint32_t rows = 16 * (u / DT) * (D * 2);
+          const uint32_t rows = V_OFF + 16 * (u / DT) * (D * 2);
           return __builtin_bit_cast(u32x4, lds_tr_pair_at(tr_lo[u % DT] + rows, tr_hi[u % DT] + rows));
         };
 #pragma unroll
@@ -659,15 +688,12 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
       // ---- mask of tile i+1 (only tiles that touch the diagonal or a ragged end, or lie past the
       // end of the item), then its maximum
       if constexpr (!LAST) {
-        const TileMeta tm = meta[0];
-        // readfirstlane: the condition is wave-uniform, but the compiler does not know it and would
-        // otherwise run the rare path on every tile as 64 compares and selects
-        const int need_mask = __builtin_amdgcn_readfirstlane(
-            (int)(tm.c0 + kFwdTileN > tm.len || ((tm.kind & 1) && tm.c0 + kFwdTileN - 1 > wave_row_lo)));
-        if (need_mask) {
+        const int w = __builtin_amdgcn_readfirstlane(word[0]);
+        if (__builtin_expect(w < 0, 0)) {
           // one bit per score of this lane (see keep_below): columns up to the last visible one, or of the row's member
-          uint32_t keep = (tm.kind & 2) ? 0u : keep_below(((tm.kind & 1) ? min(tm.len, my_limit + 1) : tm.len) - tm.c0, g);
-          if (__builtin_amdgcn_readfirstlane(tm.kind & 2)) keep = s_mask[tm.c0 / kFwdTileN][tid];
+          const int open = (w >> 2) + kFwdTileN;       // columns of the tile that the wave's first row sees
+          uint32_t keep = keep_below(open + ((w & 1) ? l32 : 0), g);
+          if (w & 2) keep = s_mask[-(w >> 2) / kFwdTileN - 1][tid];
 #pragma unroll
           for (int rt = 0; rt < 2; rt++)
 #pragma unroll
@@ -683,7 +709,7 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
         // m_run only moves when some row's maximum exceeds it by more than kRescaleSlack (a
         // wave-uniform decision): any reference gives the same O and LSE as long as exp2 stays in
         // range, and P <= 2^slack is harmless in bf16/fp32.  Most tiles skip the rescaling of O.
-        mx = fmaxf(mx, xor32(mx)) * a.scale_log2;
+        mx = max32(mx) * a.scale_log2;
         if (__builtin_amdgcn_ballot_w64(mx > m_run + kRescaleSlack) != 0) {
           const float m_new = fmaxf(m_run, mx);
           const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
@@ -696,7 +722,12 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
             for (int r = 0; r < 16; r++) o[dt][r] *= alpha;
         }
       }
-      rotate();
+      if constexpr (ODD && !FIRST) {
+        move_v(v_step); v_step = -v_step;
+      } else if constexpr (!LAST && !FIRST) {
+        move_k(k_step); k_step = -k_step;
+      }
+      next_tile();
     };
     const std::true_type yes;
     const std::false_type no;
@@ -710,31 +741,34 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
     };
     int idle = n_tiles - n_vis;
     if (n_vis > 0) {
-      iteration(yes, no, s_a, s_b);        // S^T of tile 0
+      iteration(yes, no, yes, s_a, s_b);   // S^T of tile 0 (i = -1)
       // iterations that do both phases; they alternate (s_b, s_a), (s_a, s_b)
       int rem = n_vis - 1;
-      for (int left = 4; left >= 0; left -= 2) {      // down to 4 (5) of them, to 2 (3), to 0 (1)
-        for (; rem >= left + 2; rem -= 2) {
-          iteration(no, no, s_b, s_a);
-          iteration(no, no, s_a, s_b);
+      for (int stop = 4; stop >= 0; stop -= 2) {      // down to 4 (5) of them, to 2 (3), to 0 (1)
+        for (; rem >= stop + 2; rem -= 2) {
+          iteration(no, no, no, s_b, s_a);
+          iteration(no, no, yes, s_a, s_b);
         }
         if (wave == 0) {
-          if (left == 4 && !short_item) items.request(lane);
-          if (left == 2) next_item();
+          if (stop == 4 && !short_item) items.request(lane);
+          if (stop == 2) next_item();
         }
       }
       if (rem) {
-        iteration(no, no, s_b, s_a);       // a tail, not a branch inside the loop (which costs dozens of spills)
+        iteration(no, no, no, s_b, s_a);   // a tail, not a branch inside the loop (which costs dozens of spills)
+        move_v(BUF);                       // V of the last tile is in the second buffer of its pair
       } else {
 #pragma unroll
         for (int rt = 0; rt < 2; rt++) s_a[rt] = s_b[rt];
       }
-      iteration(no, yes, s_a, s_b);        // O += V P of the last tile
+      iteration(no, yes, no, s_a, s_b);    // O += V P of the last tile
+      move_v((rem ? -BUF : 0) + (v_step < 0 ? -2 * BUF : 0));       // back to buffer 0 for the next item
+      move_k(k_step < 0 ? -2 * BUF : 0);
     } else {
-      issue(); tile_barrier(); rotate();
+      issue(); tile_barrier(); next_tile();
       if (wave == 0) next_item();
     }
-    for (; idle > 0; idle--) { issue(); tile_barrier(); rotate(); }
+    for (; idle > 0; idle--) { issue(); tile_barrier(); next_tile(); }
     if (n_tiles == 0) { dma_wait(); __syncthreads(); }      // an item without tiles has no barrier behind next_item()
     dma_wait();         // the look-ahead loads past the end of the item (zero tiles)
 
@@ -1824,10 +1858,10 @@ __global__ void __launch_bounds__(512, 2) dq_ds_kernel(BwdArgs a) {
         const int f0 = ti.c0 >> 5;
         int frag;
         if (ti.cur.kind & 1) {
-          frag = ti.cur.ds_frag + head * (nq32 * (nq32 + 1) / 2) + q32 * (q32 + 1) / 2 + min(f0, q32);
+          frag = ti.cur.ext + head * (nq32 * (nq32 + 1) / 2) + q32 * (q32 + 1) / 2 + min(f0, q32);
         } else {
           const int nkv32 = (ti.cur.kv_len + 31) >> 5;
-          frag = ti.cur.ds_frag + (head * nq32 + q32) * nkv32 + min(f0, nkv32 - 1);
+          frag = ti.cur.ext + (head * nq32 + q32) * nkv32 + min(f0, nkv32 - 1);
         }
         d_ds = reinterpret_cast<uint64_t>(a.ds + (int64_t)frag * kDsFragBytes);
         const int vis = (ti.cur.kind & 1) ? min(ti.cur.kv_len, wave_row_lo + 32) : ti.cur.kv_len;
@@ -2000,7 +2034,7 @@ static int launch_fwd(const char* who, const fcp_problem* p, const WsLayout* lay
   a.running = running ? 1 : 0;
   a.o_is_f32 = (p->flags & FCP_FLAG_O_F32) ? 1 : 0;
   a.hdr = reinterpret_cast<WsHeader*>(ws);
-  a.pairs = reinterpret_cast<const DevPair*>(ws + L.off_pairs);
+  a.spans = reinterpret_cast<const DevPair*>(ws + L.off_spans);
   a.items = reinterpret_cast<const QItem*>(ws + L.off_fwd_items);
   a.q_seg = reinterpret_cast<const uint16_t*>(ws + L.off_q_seg);
   a.n_q_heads = p->n_q_heads; a.n_kv_heads = p->n_kv_heads;

@@ -872,3 +872,47 @@ def test_packed_query_block_with_further_slots(hq, hkv, d, spill):
                 slots=[(0, 0, 1, 0), (0, 1, 1, n), (0, 2, 1, 2 * n), (1, 3, 1, 3 * n), (1, 4, 1, 4 * n)], n_slot_rows=5 * n, segments=segments)
     plan = {key: x if key == "n_slot_rows" else np.asarray(x, dtype=np.int32) for key, x in plan.items()}
     _check_tables(plan, hq, hkv, d, 512, 950, spill)
+
+
+SPANS = [
+    # seq_lens, block, causal, c, Hq, Hkv, d, n (of every slot's FULL pairs the n-th, 2n-th, .. is left out; 0: none)
+    ([700, 333], 40, 1, 0, 4, 4, 64, 0),            # one span per block of queries, tiles across block borders, block < tile
+    ([700, 333], 96, 1, 3, 6, 2, 128, 0),           # odd group, slots end inside the sequence
+    ([515, 64, 1], 130, 0, 2, 4, 2, 64, 0),         # full masks
+    ([900, 129], 100, 1, 0, 2, 1, 128, 3),          # gaps: several spans per slot, a DIAG block behind a gap
+    ([900, 129], 64, 1, 8, 8, 2, 64, 2),            # every span a tile
+]
+
+
+@pytest.mark.parametrize("case", range(len(SPANS)))
+def test_spans_of_neighbouring_and_distant_blocks(case):
+    """The forward joins neighbouring KV blocks of a slot; tables may also name blocks that are no neighbours.  Partials
+    against the oracle's for the same tables."""
+    from paper_2605_08524_amd import binding as B
+    from paper_2605_08524_amd.harness import to_dev_bf16
+    lens, bs, causal, c, hq, hkv, d, n = SPANS[case]
+    wl = workloads.custom_workload(lens, bs, causal, c, hq, hkv, d, seed=900 + case, name=f"spans{case}")
+    _say(f"case {wl.name}")
+    dev = torch.device("cuda:0")
+    plan = dict(B.fcp_plan_blocks(wl.seq_lens, bs, causal, c))
+    slots, pairs = [], []
+    for q_blk, pair_begin, n_pairs, row_start in plan["slots"]:
+        kept = [p for i, p in enumerate(plan["pairs"][pair_begin:pair_begin + n_pairs]) if p[2] != 0 or n == 0 or i % n != n - 1]
+        slots.append((q_blk, len(pairs), len(kept), row_start))
+        pairs += [(p[0], p[1], p[2], len(slots) - 1) for p in kept]
+    plan["slots"] = np.asarray(slots, dtype=np.int32).reshape(-1, 4)
+    plan["pairs"] = np.asarray(pairs, dtype=np.int32).reshape(-1, 4)
+    prob = B.Problem(plan, hq, hkv, d, bs, 0.0, 0)
+    nbytes = B.fcp_workspace_bytes(prob)
+    ws = torch.full((nbytes + 256,), 0xFF, dtype=torch.uint8, device=dev)
+    ws_ptr = ws.data_ptr() + (-ws.data_ptr()) % 256
+    B.fcp_queue_build(prob, ws_ptr, nbytes)
+    q, k, v = (to_dev_bf16(x, dev) for x in (wl.q(), wl.k(), wl.v()))
+    o_part = torch.full((prob.n_slot_rows, hq, d), float("nan"), dtype=torch.float32, device=dev)
+    lse_part = torch.full((prob.n_slot_rows, hq), float("nan"), dtype=torch.float32, device=dev)
+    op, lp = orc.partial_fwd(wl.q(), wl.k(), wl.v(), plan, bs, causal)
+    for _ in range(2):
+        B.fcp_block_attn_fwd(prob, q, k, v, o_part, lse_part, ws_ptr)
+        torch.cuda.synchronize(dev)
+        _check("o_part", o_part.cpu().numpy(), op)
+        _check_lse("lse_part", lse_part.cpu().numpy(), lp)
