@@ -1042,35 +1042,34 @@ struct BwdArgs {
   float scale, scale_log2;
 };
 
-// Iterator over the 32-row query steps of a backward item: rows, then the G query heads of
-// the group, then the dependent query blocks.  A DIAG dependency starts at the tile's own rows.
-struct StepIter {
+// Iterator over the runs of a backward item: the STEP-row query steps of one dependent query block and head, in order; the G
+// query heads of the group inside a dependency.  A DIAG dependency starts at the tile's own rows.  Inside a run a step is a
+// few additions; what a new run needs is worked out at its start (consumers spent 350-600 of an interval's 2000 cycles on a walk
+// with branches per step, no MFMA beside it; dK/dV of a training step, d = 128: 65536 lognormal tokens, 32/8 heads, dS kept 5183 ->
+// 5005 us; 32768 tokens, 64/8 heads 4368 -> 4035).
+template <int STEP>
+struct RunIter {
   const BwdDep* deps;
-  int dep, n_deps, hh, group, q0, first_diag;
+  int dep, n_deps, hh, group, first_diag;
+  int q0, left, last_rows;      // of the run: first row of its first step, steps not yet passed, rows of its last step
   BwdDep cur;
-  bool more;
-  __device__ __forceinline__ int first_q0() const { return (cur.kind & 1) ? first_diag : 0; }
   __device__ __forceinline__ void init(const BwdDep* d, const BwdItem& it, int group_) {
-    deps = d + it.dep_begin; dep = 0; n_deps = it.n_deps; hh = 0; group = group_; first_diag = it.tile_off & ~31; q0 = 0;
+    deps = d + it.dep_begin; dep = 0; n_deps = it.n_deps; hh = -1; group = group_; first_diag = it.tile_off & ~31;
     cur = it.first;
-    more = n_deps > 0;
-    if (more) {
-      q0 = first_q0();
-      more = q0 < cur.q_len;
-    }
+    q0 = 0; left = 0; last_rows = 0;
   }
-  __device__ __forceinline__ void advance() {
-    q0 += 32;
-    if (q0 >= cur.q_len) {
-      hh++;
-      if (hh < group) {
-        q0 = first_q0();
-      } else {
-        hh = 0;
-        dep++;
-        if (dep < n_deps) { cur = deps[dep]; q0 = first_q0(); } else { more = false; }
-      }
+  // the next run, or false behind the last one
+  __device__ __forceinline__ bool next() {
+    left = 0;
+    if (++hh == group) {
+      hh = 0;
+      if (++dep < n_deps) cur = deps[dep];
     }
+    if (dep >= n_deps) { hh = group - 1; return false; }
+    q0 = (cur.kind & 1) ? first_diag : 0;
+    left = (cur.q_len - q0 + STEP - 1) / STEP;
+    last_rows = cur.q_len - q0 - STEP * (left - 1);
+    return true;
   }
 };
 
@@ -1139,8 +1138,8 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
     const int my_kv = sub * 32 + l32;                  // KV row inside the tile
     const bool kv_ok = my_kv < it.kv_rows;
     const int n_iv = it.n_iv;                          // barrier intervals of the item
-    StepIter si;
-    si.init(a.deps, it, group);
+    RunIter<32> run;                                   // consumer: the step to load; producer: the step of the next B
+    run.init(a.deps, it, group);
 
     if (consumer) {
       // =============================== consumer ===============================
@@ -1173,32 +1172,31 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
 
       // The load of one step in two parts.  describe(): scalar bookkeeping with branches, run at a
       // step boundary.  issue(): branch-free, sits between the MFMAs of the step.
-      uint64_t d_q = 0, d_do = 0;          // tile sources (row q0 of the head)
+      uint64_t d_q = 0, d_do = 0;          // tile sources (first row of the step)
       uint32_t d_lim = 0;                  // byte offset of the last valid row
       int d_valid = 0;
       int64_t d_sc = 0;                    // element offset of the step's first row in the head-major scalars
-      const uint32_t row_bytes = (uint32_t)(q_row_stride * 2);
-      int run_dep = -1, run_hh = -1;       // the run (dependency, head) of the step described last
+      const uint32_t row_bytes = (uint32_t)(q_row_stride * 2), lim_whole = 31 * row_bytes;
+      uint32_t lim_last = 0;
       auto describe = [&]() {
-        if (!si.more) {
-          d_q = reinterpret_cast<uint64_t>(zeros); d_do = d_q; d_lim = 0; d_valid = 0; d_sc = 0;
-          run_dep = -1;
-          return;
-        }
-        if (si.dep == run_dep && si.hh == run_hh) {
-          // the next 32 rows of the same run: advance the pointers instead of recomputing them
+        if (__builtin_expect(run.left > 1, 1)) {
+          // the next 32 rows of the same run: only its last step may be ragged
+          run.left--;
           d_q += 32 * (uint64_t)row_bytes; d_do += 32 * (uint64_t)row_bytes; d_sc += 32;
-        } else {
-          const int head = it.kv_head * group + si.hh;
-          const int64_t row = (int64_t)(si.cur.q_start + si.q0);
+          d_valid = run.left > 1 ? 32 : run.last_rows;
+          d_lim = run.left > 1 ? lim_whole : lim_last;
+        } else if (run.next()) {
+          const int head = it.kv_head * group + run.hh;
+          const int64_t row = (int64_t)(run.cur.q_start + run.q0);
           d_q = reinterpret_cast<uint64_t>(a.q + row * q_row_stride + (int64_t)head * D);
           d_do = reinterpret_cast<uint64_t>(a.d_o + row * q_row_stride + (int64_t)head * D);
           d_sc = (int64_t)head * a.t_q + row;
-          run_dep = si.dep; run_hh = si.hh;
+          lim_last = (uint32_t)(run.last_rows - 1) * row_bytes;
+          d_valid = run.left > 1 ? 32 : run.last_rows;
+          d_lim = run.left > 1 ? lim_whole : lim_last;
+        } else {
+          d_q = reinterpret_cast<uint64_t>(zeros); d_do = d_q; d_lim = 0; d_valid = 0; d_sc = 0;
         }
-        d_valid = min(32, si.cur.q_len - si.q0);
-        d_lim = (uint32_t)(d_valid - 1) * row_bytes;
-        si.advance();
       };
       auto issue = [&]() {
         const uint32_t lbase = lds_addr(lds_t[0]) + b_dma * BUF;
@@ -1306,9 +1304,12 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
       // memory, and the rotation makes the transposing LDS reads of the dQ pass bank-conflict free.
       if constexpr (SPILL) { if (!kv_ok) kvg = 0x7fff0000; }
       const int thr_none = (SPILL && it.kv_rows < kBwdTileN) ? kNoMask - 1 : kNoMask;
-      const int nkv32 = (it.kv_blk_len + 31) >> 5, my_kv32 = (it.tile_off >> 5) + sub;
+      // a step whose first query row is below this one is masked: the diagonal rows that this wave's last KV row does not reach
+      // need none
+      const int mask_below = (SPILL && it.kv_rows < kBwdTileN) ? kNoMask : it.tile_off + sub * 32 + 31;
+      const int kv0 = it.tile_off + sub * 32;              // the wave's first KV row inside the segment
       const int sink = (int)(blockIdx.x & (kDsSinkFrags - 1));
-      int frag_t = sink;         // fragment of the step that B handles in this interval
+      int frag_t = sink, d_frag = 0, dd_frag = 0;   // fragment of the step that B handles in this interval; increments inside a run
       uint32_t sp_off[2];
 #pragma unroll
       for (int j = 0; j < 2; j++) sp_off[j] = 1024 * j + 512 * g + 16 * ((l32 + 8 * j + 4 * g) & 31);
@@ -1323,7 +1324,7 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
 #pragma unroll
       for (int kc = 0; kc < KC; kc++) row_a[kc] = lds_addr(lds_t[0]) + b_p * BUF + tile_off<D>(l32, 2 * kc + g);
       uint32_t sc_a = lds_sc0 + b_s * 256 + 16 * g;      // scalars of step i+1: rows 8*q4 + 4g .. +3 at +32*q4, D*scale at +128
-      int thr_t = thr_none;      // diagonal threshold of the step that B handles in this interval
+      int thr_t = thr_none, d_thr = 0;     // diagonal threshold of the step that B handles in this interval
       bool causal_t = false;     // joined run: the mask of that step is causal
       f32x16 s_a, dp_a, s_b, dp_b;
 #pragma unroll
@@ -1350,7 +1351,8 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
         float p_prev = 0.f, ds_prev = 0.f;
         const uint32_t hdst = lds_h0 + (hb ^ 1) * (4 * 4096);
         unsigned char* fptr = nullptr;
-        if constexpr (SPILL) fptr = a.ds + (int64_t)__builtin_amdgcn_readfirstlane(frag_t) * kDsFragBytes;
+        // no fragment: KV rows past the tile's end, above the diagonal
+        if constexpr (SPILL) fptr = a.ds + (int64_t)__builtin_amdgcn_readfirstlane(sub * 32 < it.kv_rows && (thr_t >= kv0 || (JOINED && !causal_t)) ? frag_t : sink) * kDsFragBytes;
         float p_ahead = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[0], a.scale_log2, -lse_c[0]));
 #pragma unroll
         for (int k = 0; k < NS; k++) {
@@ -1424,23 +1426,24 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
           __syncthreads();
         }
         // the step that B handles next
-        thr_t = thr_none;
-        if constexpr (SPILL) frag_t = sink;
-        if (si.more) {
-          if (si.cur.kind != FCP_KIND_FULL) thr_t = si.q0;
-          if constexpr (JOINED) causal_t = (si.cur.kind & 1) != 0;
+        if (__builtin_expect(run.left > 1, 1)) {
+          run.left--;
+          thr_t += d_thr;
+          if constexpr (SPILL) { frag_t += d_frag; d_frag += dd_frag; }
+        } else if (run.next()) {
+          const bool diag = (run.cur.kind & 1) != 0;
+          thr_t = run.cur.kind != FCP_KIND_FULL ? run.q0 : thr_none;
+          d_thr = run.cur.kind != FCP_KIND_FULL ? 32 : 0;
+          if constexpr (JOINED) causal_t = diag;
           if constexpr (SPILL) {
-            const int q32 = si.q0 >> 5, nq32 = (si.cur.q_len + 31) >> 5;
-            const int head = it.kv_head * group + si.hh;
-            if (sub * 32 < it.kv_rows) {
-              if (si.cur.kind & 1) {
-                if (my_kv32 <= q32) frag_t = si.cur.ds_frag + head * (nq32 * (nq32 + 1) / 2) + q32 * (q32 + 1) / 2 + my_kv32;
-              } else {
-                frag_t = si.cur.ds_frag + (head * nq32 + q32) * nkv32 + my_kv32;
-              }
-            }
+            const int q32 = run.q0 >> 5, nq32 = (run.cur.q_len + 31) >> 5, nkv32 = (it.kv_blk_len + 31) >> 5, head = it.kv_head * group + run.hh;
+            frag_t = run.cur.ds_frag + (kv0 >> 5) + (diag ? head * (nq32 * (nq32 + 1) / 2) + q32 * (q32 + 1) / 2 : (head * nq32 + q32) * nkv32);
+            d_frag = diag ? q32 + 1 : nkv32;
+            dd_frag = diag ? 1 : 0;
           }
-          si.advance();
+        } else {
+          thr_t = thr_none; d_thr = 0;
+          frag_t = sink; d_frag = 0; dd_frag = 0;
         }
         hb ^= 1;
       };
@@ -1456,8 +1459,8 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
         }
       } else {
         for (int iv = 0; iv < n_iv; iv += 2) {
-          if (thr_t != kNoMask) interval(with_mask, s_a, dp_a, s_b, dp_b); else interval(no_mask, s_a, dp_a, s_b, dp_b);
-          if (thr_t != kNoMask) interval(with_mask, s_b, dp_b, s_a, dp_a); else interval(no_mask, s_b, dp_b, s_a, dp_a);
+          if (thr_t < mask_below) interval(with_mask, s_a, dp_a, s_b, dp_b); else interval(no_mask, s_a, dp_a, s_b, dp_b);
+          if (thr_t < mask_below) interval(with_mask, s_b, dp_b, s_a, dp_a); else interval(no_mask, s_b, dp_b, s_a, dp_a);
         }
       }
     }
