@@ -207,6 +207,21 @@ int64_t q_items_of(const fcp_problem* p, int rows) {
   return ceil_div(rows, item_rows(p)) * ((p->n_q_heads / p->n_kv_heads) % 2 == 0 ? p->n_q_heads / 2 : p->n_q_heads);
 }
 
+// Append the KV rows of a pair to the spans of a slot (those from span0 on): to the last one where they follow it.  A block
+// larger than kMaxSpan is several spans; a DIAG one is not cut (its contractions would take hours).
+void add_spans(std::vector<DevPair>* spans, int32_t span0, const KvSeg& k, int kind) {
+  for (int32_t off = 0, n; off < k.len; off += n) {
+    n = kind == FCP_KIND_FULL ? std::min(k.len - off, kMaxSpan) : k.len;
+    DevPair* last = (int32_t)spans->size() > span0 ? &spans->back() : nullptr;
+    if (last && last->kind == FCP_KIND_FULL && !(kind & 2) && last->kv_start + last->kv_len == k.start + off && (int64_t)last->kv_len + n <= kMaxSpan) {
+      if (kind == FCP_KIND_DIAG) { last->kind = kind; last->ext = last->kv_len; }
+      last->kv_len += n;
+    } else {
+      spans->push_back({k.start + off, n, kind, 0});
+    }
+  }
+}
+
 }  // namespace
 
 void expand_problem(const fcp_problem* p, bool forward_only, Expanded* x) {
@@ -241,16 +256,7 @@ void expand_problem(const fcp_problem* p, bool forward_only, Expanded* x) {
           const int32_t seg = runs.begin[pr.kv_blk] + ((pr.kind & 2) ? m : 0);
           KvSeg& k = x->kv[seg];
           const int kind = (pr.kind & 2) && run[m].n_segs == 1 ? pr.kind & 1 : pr.kind;
-          if (!whole || m == 0) {
-            if ((int32_t)x->spans.size() > span0 && x->spans.back().kind == FCP_KIND_FULL && !(kind & 2) &&
-                x->spans.back().kv_start + x->spans.back().kv_len == k.start) {
-              DevPair& sp = x->spans.back();
-              if (kind == FCP_KIND_DIAG) { sp.kind = kind; sp.ext = sp.kv_len; }
-              sp.kv_len += k.len;
-            } else {
-              x->spans.push_back({k.start, k.len, kind, 0});
-            }
-          }
+          if (!whole || m == 0) add_spans(&x->spans, span0, k, kind);
           if (forward_only) continue;
           x->pairs.push_back({k.start, k.len, kind, spill ? (int32_t)frag : 0});
           joins.push_back({q0, run[m].len, seg});
@@ -304,7 +310,8 @@ int compute_layout(const fcp_problem* p, bool forward_only, WsLayout* L) {
     for (int s = s0; s < s1; s++) {
       const bool whole = packed && !packed_slot(p, p->slots[s]);
       L->n_fwd_items += whole ? q_items_of(p, p->q_blocks[b].tok_len) : items;
-      L->n_spans += (int64_t)p->slots[s].n_pairs * (whole ? 1 : n_runs);
+      for (int i = p->slots[s].pair_begin; i < p->slots[s].pair_begin + p->slots[s].n_pairs; i++)
+        L->n_spans += ceil_div(p->kv_blocks[p->pairs[i].kv_blk].tok_len, kMaxSpan) * (whole ? 1 : n_runs);
       if (!forward_only) L->n_pairs += (int64_t)p->slots[s].n_pairs * n_runs;
     }
     if (!(p->flags & FCP_FLAG_BWD_SPILL_DS) || s0 == s1) return;
