@@ -1668,31 +1668,35 @@ __global__ void __launch_bounds__(512, 2) dq_kernel(BwdArgs a) {
             f32x16 s, dp;
 #pragma unroll
             for (int r = 0; r < 16; r++) { s[r] = 0.f; dp[r] = 0.f; }
-            // K and V rows are requested PFQ k-chunks (2 PFQ MFMAs) before the MFMAs that use them; left to
-            // the compiler each read is issued one MFMA ahead and waited for in full (depths 1 .. 4 measured: 2).
-            // The first MFMA waits for one read: with the other chunks requested in front of it, too, d = 64 is 4 % slower.
-            constexpr int PFQ = 2;
-            u32x4 opk[PFQ], opv[PFQ];
-            auto request = [&](int kc) {
-              opk[kc % PFQ] = lds_read16(row_off[kc] + rt * 32 * (D * 2));
-              opv[kc % PFQ] = lds_read16(row_off[kc] + rt * 32 * (D * 2) + TB);
-            };
+            // All MFMAs of S, then those of dP with the exponentials of S between them, then those of dQ: the second half of dS
+            // is formed between the MFMAs of the first.  S and dP in turn, as the operands come, left all 88 issue slots of
+            // vector work without an MFMA of the same wave beside them; the other wave of the SIMD covered most of that, and power
+            // bounds the rest: training step of 32768 tokens, 64/8 heads, d = 128 8899 -> 8827 us, 8-worker share 11941 -> 11877.
+            // Operands: row chunks of K, then of V, four in flight (the first MFMA waits for one read: with the others requested
+            // in front of it, too, d = 64 is 4 % slower).
+            constexpr int PFQ = 4;
+            u32x4 op[PFQ];
+            auto request = [&](int u) { op[u % PFQ] = lds_read16(row_off[u % KC] + rt * 32 * (D * 2) + (u < KC ? 0 : TB)); };
             request(0);
+            request(1);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int kc = 0; kc < KC; kc++) {
-              s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(opk[kc % PFQ]), qf[kc], s, 0, 0, 0);
-              if (kc == 0) {
-                __builtin_amdgcn_sched_barrier(0);
-                request(1);
-                __builtin_amdgcn_sched_barrier(0);
+            for (int u = 0; u < 2 * KC; u++) {
+              if (u < KC) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(op[u % PFQ]), qf[u], s, 0, 0, 0);
+              else dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(op[u % PFQ]), dof[u % KC], dp, 0, 0, 0);
+              if (u == 0) { request(2); request(3); }
+              if (u + PFQ < 2 * KC) request(u + PFQ);
+              // from the second MFMA of dP on: the first one covers the wait for S
+              if (u > KC) {
+#pragma unroll
+                for (int r = (u - KC - 1) * 16 / (KC - 1); r < (u - KC) * 16 / (KC - 1); r++) {
+                  float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], a.scale_log2, -lse_l));
+                  asm volatile("" : "+v"(p));        // keeps it between the MFMAs it was written between
+                  s[r] = p;
+                }
               }
-              dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(opv[kc % PFQ]), dof[kc], dp, 0, 0, 0);
-              if (kc + PFQ < KC) request(kc + PFQ);
               __builtin_amdgcn_sched_barrier(0);
             }
-#pragma unroll
-            for (int r = 0; r < 16; r++) s[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], a.scale_log2, -lse_l));
             if (need_mask) {                    // wave-uniform: only tiles that straddle the diagonal
 #pragma unroll
               for (int r = 0; r < 16; r++) {
@@ -1700,19 +1704,32 @@ __global__ void __launch_bounds__(512, 2) dq_kernel(BwdArgs a) {
                 if (c > limit || (JOINED && c < first)) s[r] = 0.f;
               }
             }
+            constexpr int PFT = 2;
+            bf16x8 kt[PFT];
+            u32x4 db[2];                        // dS^T as two B operands
+            auto fetch = [&](int u) {
+              const uint32_t rows = (rt * 32 + 16 * (u / DT)) * (D * 2);
+              kt[u % PFT] = lds_tr_pair_at(tr_lo[u % DT] + rows, tr_hi[u % DT] + rows);
+            };
+            auto ds_pair = [&](int i) {
+              const float x = s[2 * i] * __builtin_fmaf(dp[2 * i], a.scale, -dl_l), y = s[2 * i + 1] * __builtin_fmaf(dp[2 * i + 1], a.scale, -dl_l);
+              db[i >> 2][i & 3] = pack_bf16(x, y);
+              asm volatile("" :: "v"(db[i >> 2][i & 3]));
+            };
 #pragma unroll
-            for (int r = 0; r < 16; r++) s[r] *= __builtin_fmaf(dp[r], a.scale, -dl_l);
+            for (int u = 0; u < PFT; u++) fetch(u);
 #pragma unroll
-            for (int j = 0; j < 2; j++) {
-              u32x4 db;
+            for (int i = 0; i < 4; i++) ds_pair(i);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-              for (int i = 0; i < 4; i++) db[i] = pack_bf16(s[8 * j + 2 * i], s[8 * j + 2 * i + 1]);
-              const uint32_t rows = (rt * 32 + 16 * j) * (D * 2);
+            for (int u = 0; u < 2 * DT; u++) {
+              acc[u % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kt[u % PFT], as_bf16x8(db[u / DT]), acc[u % DT], 0, 0, 0);
+              if (u + PFT < 2 * DT) fetch(u + PFT);
+              if (u < DT) {
 #pragma unroll
-              for (int dt = 0; dt < DT; dt++) {
-                const bf16x8 kt = lds_tr_pair_at(tr_lo[dt] + rows, tr_hi[dt] + rows);
-                acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kt, as_bf16x8(db), acc[dt], 0, 0, 0);
+                for (int i = 4 + u * 4 / DT; i < 4 + (u + 1) * 4 / DT; i++) ds_pair(i);
               }
+              __builtin_amdgcn_sched_barrier(0);
             }
           }
         }
