@@ -201,25 +201,35 @@ void for_q_blocks(const fcp_problem* p, const Runs& runs, F f) {
   }
 }
 
+// a member alone in its run is an ordinary segment
+int kind_in_run(int kind, const Run& run) { return (kind & 2) && run.n_segs == 1 ? kind & 1 : kind; }
+
 bool packed_slot(const fcp_problem* p, const fcp_slot& sl) { return sl.n_pairs == 1 && (p->pairs[sl.pair_begin].kind & 2); }
 
 int64_t q_items_of(const fcp_problem* p, int rows) {
   return ceil_div(rows, item_rows(p)) * ((p->n_q_heads / p->n_kv_heads) % 2 == 0 ? p->n_q_heads / 2 : p->n_q_heads);
 }
 
-// Append the KV rows of a pair to the spans of a slot (those from span0 on): to the last one where they follow it.  A block
-// larger than kMaxSpan is several spans; a DIAG one is not cut (its contractions would take hours).
-void add_spans(std::vector<DevPair>* spans, int32_t span0, const KvSeg& k, int kind) {
-  for (int32_t off = 0, n; off < k.len; off += n) {
-    n = kind == FCP_KIND_FULL ? std::min(k.len - off, kMaxSpan) : k.len;
-    DevPair* last = (int32_t)spans->size() > span0 ? &spans->back() : nullptr;
-    if (last && last->kind == FCP_KIND_FULL && !(kind & 2) && last->kv_start + last->kv_len == k.start + off && (int64_t)last->kv_len + n <= kMaxSpan) {
-      if (kind == FCP_KIND_DIAG) { last->kind = kind; last->ext = last->kv_len; }
-      last->kv_len += n;
-    } else {
-      spans->push_back({k.start + off, n, kind, 0});
-    }
+// Append KV rows to the spans of a forward segment (those from span0 on): to the last one where they follow it.
+void append_span(std::vector<DevPair>* spans, int32_t span0, int32_t start, int32_t len, int kind) {
+  DevPair* last = (int32_t)spans->size() > span0 ? &spans->back() : nullptr;
+  if (last && last->kind == FCP_KIND_FULL && !(kind & 2) && last->kv_start + last->kv_len == start && (int64_t)last->kv_len + len <= kMaxSpan) {
+    if (kind == FCP_KIND_DIAG) { last->kind = kind; last->ext = last->kv_len; }
+    last->kv_len += len;
+  } else {
+    spans->push_back({start, len, kind, 0});
   }
+}
+
+// The spans of a pair for rows [row0, row0 + rows) of its query block: no more than kMaxSpan rows each.  Under a DIAG pair those
+// rows see the columns before them in full.
+void add_spans(std::vector<DevPair>* spans, int32_t span0, const KvSeg& k, int kind, int32_t row0, int32_t rows) {
+  const int32_t full = kind == FCP_KIND_FULL ? k.len : kind == FCP_KIND_DIAG ? row0 : 0;
+  for (int32_t off = 0, n; off < full; off += n) {
+    n = std::min(full - off, kMaxSpan);
+    append_span(spans, span0, k.start + off, n, FCP_KIND_FULL);
+  }
+  if (kind != FCP_KIND_FULL) append_span(spans, span0, k.start + full, kind == FCP_KIND_DIAG ? rows : k.len, kind);
 }
 
 }  // namespace
@@ -249,23 +259,30 @@ void expand_problem(const fcp_problem* p, bool forward_only, Expanded* x) {
         const fcp_slot& sl = p->slots[s];
         // a packed query block may have slots of FULL pairs too: the forward walks them once, with all rows of the block
         const bool whole = packed && !packed_slot(p, sl);
-        const int32_t span0 = (int32_t)x->spans.size();
-        if (whole && m > 0 && forward_only) continue;
+        if (!whole || m == 0) {
+          // the forward's rows: a segment of at most kMaxSpan rows each
+          const int32_t first = whole ? qb.tok_start : q0, out = sl.row_start + (whole ? 0 : run[m].off), len = whole ? qb.tok_len : run[m].len;
+          for (int32_t row = 0, n; row < len; row += n) {
+            n = std::min(len - row, kMaxSpan);
+            const int32_t span0 = (int32_t)x->spans.size();
+            for (int i = sl.pair_begin; i < sl.pair_begin + sl.n_pairs; i++) {
+              const fcp_pair& pr = p->pairs[i];
+              add_spans(&x->spans, span0, x->kv[runs.begin[pr.kv_blk] + ((pr.kind & 2) ? m : 0)], kind_in_run(pr.kind, run[m]), row, n);
+            }
+            x->fwd.push_back({first + row, n, out + row, span0, (int32_t)x->spans.size() - span0, whole ? qb.seq : run[m].seq, to_final, s - s0});
+          }
+        }
+        if (forward_only) continue;
         for (int i = sl.pair_begin; i < sl.pair_begin + sl.n_pairs; i++) {
           const fcp_pair& pr = p->pairs[i];
           const int32_t seg = runs.begin[pr.kv_blk] + ((pr.kind & 2) ? m : 0);
           KvSeg& k = x->kv[seg];
-          const int kind = (pr.kind & 2) && run[m].n_segs == 1 ? pr.kind & 1 : pr.kind;
-          if (!whole || m == 0) add_spans(&x->spans, span0, k, kind);
-          if (forward_only) continue;
+          const int kind = kind_in_run(pr.kind, run[m]);
           x->pairs.push_back({k.start, k.len, kind, spill ? (int32_t)frag : 0});
           joins.push_back({q0, run[m].len, seg});
           k.n_deps++;
           frag += p->n_q_heads * ds_frags_per_head(kind, run[m].len, k.len);
         }
-        if (!whole || m == 0)
-          x->fwd.push_back({whole ? qb.tok_start : q0, whole ? qb.tok_len : run[m].len, sl.row_start + (whole ? 0 : run[m].off),
-                            span0, (int32_t)x->spans.size() - span0, whole ? qb.seq : run[m].seq, to_final, s - s0});
       }
       if (run[m].n_segs > 1)
         for (int i = run[m].seg_begin; i < run[m].seg_begin + run[m].n_segs; i++) {
@@ -311,7 +328,7 @@ int compute_layout(const fcp_problem* p, bool forward_only, WsLayout* L) {
       const bool whole = packed && !packed_slot(p, p->slots[s]);
       L->n_fwd_items += whole ? q_items_of(p, p->q_blocks[b].tok_len) : items;
       for (int i = p->slots[s].pair_begin; i < p->slots[s].pair_begin + p->slots[s].n_pairs; i++)
-        L->n_spans += ceil_div(p->kv_blocks[p->pairs[i].kv_blk].tok_len, kMaxSpan) * (whole ? 1 : n_runs);
+        L->n_spans += ceil_div(p->kv_blocks[p->pairs[i].kv_blk].tok_len, kMaxSpan) * ceil_div(p->q_blocks[b].tok_len, kMaxSpan) * (whole ? 1 : n_runs);
       if (!forward_only) L->n_pairs += (int64_t)p->slots[s].n_pairs * n_runs;
     }
     if (!(p->flags & FCP_FLAG_BWD_SPILL_DS) || s0 == s1) return;

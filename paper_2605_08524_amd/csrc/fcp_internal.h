@@ -29,7 +29,9 @@ constexpr int kMergeMinItems = 2048;  // the merge aims at this many work items 
 // one that ends them).  Its tiles then run on across block borders, and what the walk looks up per pair is looked up once
 // per slot.  ext of a span: column where its DIAG block starts.
 struct DevPair { int32_t kv_start, kv_len, kind, ext; };
-constexpr int32_t kMaxSpan = 1 << 28;   // rows of a span: the forward holds 4 * (columns of it) in 32 bits (whole tiles)
+// Rows of a span, and of a forward segment (QSeg): the forward holds 4 * (columns of a span) in 32 bits.  Whole items.
+constexpr int32_t kMaxSpan = 1 << 28;
+static_assert(kMaxSpan % (2 * kFwdTileM) == 0, "a query block in segments has as many items as in one");
 // Query-stationary item of two 128-row sub-tiles that walk the same pair list and share a KV head
 // (two query heads of a group, or two neighbouring row tiles of one head; q_rows[1] = 0: none).
 // to_final != 0 (forward items only): the slot is the only one of its query block.

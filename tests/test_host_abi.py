@@ -374,3 +374,61 @@ def test_layout_counts_without_building_the_tables():
             fcp.fcp_queue_build(p, 256, need, None)
         build.append(time.perf_counter() - t)
     assert min(layout) < 0.15 * min(build)
+
+
+def _forward_rows(prob):
+    """The forward's segments and spans as the host hands them to the queue builder: fcp::expand_problem of the same library
+    fills seven std::vectors (begin, end, capacity; zeroed memory is an empty one).  Segments (start, len, out_row, first span,
+    spans), spans (kv_start, kv_len, kind, column where a DIAG block starts)."""
+    vectors = (ctypes.c_void_p * 21)()
+    binding._lib._ZN3fcp14expand_problemEPK11fcp_problembPNS_8ExpandedE(ctypes.byref(prob.c), ctypes.c_bool(True), ctypes.byref(vectors))
+
+    def table(i, width):
+        begin, end = vectors[3 * i] or 0, vectors[3 * i + 1] or 0
+        return np.frombuffer(ctypes.string_at(begin, end - begin), dtype=np.int32).reshape(-1, width)
+    return table(2, 8)[:, :5], table(1, 4)
+
+
+M = 1 << 28            # most rows of a span
+
+
+@pytest.mark.parametrize("kv_lens,q_len,pairs", [
+    ([5 * M + 77], 70, [(0, 0)]),                                    # a FULL block longer than a span
+    ([M - 5, 3, 2, 1, M], 9, [(0, 0), (1, 0), (2, 0), (3, 0), (4, 0)]),   # joined up to the limit, not past it
+    ([M, 640], 640, [(0, 0), (1, 1)]),                               # DIAG behind a whole span
+    ([M - 640, 640], 640, [(0, 0), (1, 1)]),                         # DIAG that ends one
+    ([M - 639, 640], 640, [(0, 0), (1, 1)]),
+    ([64, 3 * M + 77], 3 * M + 77, [(0, 0), (1, 1)]),                # DIAG blocks longer than a span
+    ([2 * M], 2 * M, [(0, 1)]),
+    ([M], M, [(0, 1)]),
+    ([2 * M + 1, 500], 2 * M + 1, [(0, 1), (1, 0)]),                 # ... and a FULL block behind one
+])
+def test_spans_of_very_long_blocks(kv_lens, q_len, pairs):
+    """The forward's mask word is 4 * (columns of a span that a wave's first row sees - 64) + 2 bits in a signed 32-bit register.
+    Spans and segments keep it in range whatever a block's length, and every row still sees what its pairs say."""
+    kv = [(0, i, sum(kv_lens[:i]), n) for i, n in enumerate(kv_lens)]
+    diag = [b for b, kind in pairs if kind]
+    plan = dict(kv_blocks=kv, q_blocks=[(0, diag[0] if diag else 99, 0, q_len)], pairs=[(0, b, kind, 0) for b, kind in pairs],
+                slots=[(0, 0, len(pairs), 0)], n_slot_rows=q_len)
+    plan = {k: v if k == "n_slot_rows" else np.asarray(v, dtype=np.int32) for k, v in plan.items()}
+    prob = fcp.Problem(plan, 1, 1, 64, max(kv_lens + [q_len]))
+    assert fcp.fcp_workspace_bytes(prob) > 0
+    segments, spans = _forward_rows(prob)
+    assert np.array_equal(np.cumsum(segments[:, 1]) - segments[:, 1], segments[:, 0]) and segments[:, 1].sum() == q_len
+    assert np.array_equal(segments[:, 2], segments[:, 0])
+    for start, n, _, first, count in segments.astype(np.int64):
+        mine = spans[first:first + count].astype(np.int64)
+        opens = np.where(mine[:, 2] & 1, mine[:, 3] + n, mine[:, 1])             # of the last row; the first row's is less
+        assert (4 * opens + 3 < 2 ** 31).all() and (opens <= mine[:, 1]).all()
+        for row in sorted({0, min(63, n - 1), n // 2, n - 1}):
+            def joined(parts):
+                out = []
+                for lo, hi in parts:
+                    if out and out[-1][1] == lo:
+                        out[-1][1] = hi
+                    elif hi > lo:
+                        out.append([lo, hi])
+                return out
+            got = joined((s, s + (min(length, ext + row + 1) if kind & 1 else length)) for s, length, kind, ext in mine)
+            want = joined((kv[b][2], kv[b][2] + (start + row + 1 if kind else kv[b][3])) for b, kind in pairs)
+            assert got == want
