@@ -544,7 +544,8 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
     // covers it: inside a span a handful of additions.  issue(): branch-free, sits between the MFMAs.
     // A tile is masked for this wave from the column on where its first row sees nothing more (a DIAG span), the span ends, or at
     // once (a joined run); see mask_word.
-    const uint32_t lim_whole = (uint32_t)((kFwdTileN - 1) * kv_row_stride * 2), tile_step = (uint32_t)(kFwdTileN * kv_row_stride * 2);
+    const uint32_t lim_whole = (uint32_t)((kFwdTileN - 1) * kv_row_stride * 2);
+    const uint64_t tile_step = (uint64_t)(kFwdTileN * kv_row_stride * 2);        // from 2^18 KV heads on more than 32 bits
     uint64_t d_k = 0, d_v = 0;
     uint32_t d_lim = 0, lim_last = 0;
     int left = 0, span = 0;           // tiles of the span in hand not yet described, less one; its number

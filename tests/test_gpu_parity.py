@@ -916,3 +916,31 @@ def test_spans_of_neighbouring_and_distant_blocks(case):
         torch.cuda.synchronize(dev)
         _check("o_part", o_part.cpu().numpy(), op)
         _check_lse("lse_part", lse_part.cpu().numpy(), lp)
+
+
+def test_kv_tile_of_4_gib():
+    """262144 KV heads of d = 128: one 64-row tile of K spans 4 GiB, the step from it to the next is no 32-bit number.  A query row
+    against two tiles, sampled heads against the softmax in fp64."""
+    from paper_2605_08524_amd import binding as B
+    heads, rows, d = 1 << 18, 65, 128
+    _say(f"case {heads} heads, {rows} rows")
+    dev = torch.device("cuda:0")
+    plan = dict(kv_blocks=[(0, 0, 0, rows)], q_blocks=[(1, 0, 0, 1)], pairs=[(0, 0, 0, 0)], slots=[(0, 0, 1, 0)], n_slot_rows=1)
+    plan = {key: x if key == "n_slot_rows" else np.asarray(x, dtype=np.int32) for key, x in plan.items()}
+    prob = B.Problem(plan, heads, heads, d, rows, 0.0, 0)
+    nbytes = B.fcp_workspace_bytes(prob)
+    ws = torch.full((nbytes + 256,), 0xFF, dtype=torch.uint8, device=dev)
+    ws_ptr = ws.data_ptr() + (-ws.data_ptr()) % 256
+    B.fcp_queue_build(prob, ws_ptr, nbytes)
+    g = torch.Generator(device=dev).manual_seed(5)
+    q, k, v = (torch.empty((n, heads, d), dtype=torch.bfloat16, device=dev).normal_(generator=g) for n in (1, rows, rows))
+    o_part = torch.full((1, heads, d), float("nan"), device=dev)
+    lse_part = torch.full((1, heads), float("nan"), device=dev)
+    B.fcp_block_attn_fwd(prob, q, k, v, o_part, lse_part, ws_ptr)
+    torch.cuda.synchronize(dev)
+    sample = torch.tensor([0, 1, 77777, heads // 2, heads - 2, heads - 1], device=dev)
+    qs, ks, vs = (x[:, sample].float().cpu().numpy().astype(np.float64) for x in (q, k, v))
+    s = np.einsum("hd,rhd->hr", qs[0], ks) / np.sqrt(d)
+    p = np.exp(s - s.max(axis=1, keepdims=True))
+    _check("o_part", o_part[:, sample].cpu().numpy(), (np.einsum("hr,rhd->hd", p, vs) / p.sum(axis=1, keepdims=True))[None])
+    _check_lse("lse_part", lse_part[:, sample].cpu().numpy(), (s.max(axis=1) + np.log(p.sum(axis=1)))[None])
