@@ -360,7 +360,7 @@ int compute_layout(const fcp_problem* p, bool forward_only, WsLayout* L) {
   }
   auto align = [](size_t x) { return (x + 255) & ~(size_t)255; };
   size_t off = align(sizeof(WsHeader));
-  L->off_pairs = off;       off = align(off + sizeof(DevPair) * (size_t)std::max<int64_t>(1, L->n_pairs));
+  L->off_pairs = off;       if (!forward_only) off = align(off + sizeof(DevPair) * (size_t)std::max<int64_t>(1, L->n_pairs));
   L->off_spans = off;       off = align(off + sizeof(DevPair) * (size_t)std::max<int64_t>(1, L->n_spans));
   L->off_fwd_items = off;   off = align(off + sizeof(QItem) * (size_t)std::max<int64_t>(1, L->n_fwd_items));
   L->off_q_seg = off;       off = align(off + (p->n_segments ? sizeof(uint16_t) * (size_t)L->t_q : 0));

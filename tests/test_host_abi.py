@@ -352,6 +352,27 @@ def test_static_forward_accepts_every_plan_within_its_limit():
     assert refused > 5 and taken > 5
 
 
+def test_static_forward_fills_its_array_to_the_last_byte():
+    """Packed blocks of many rows and few heads reach the end of the device array (8 MiB + 16 KiB) before the limit of the plan:
+    header, spans (16 bytes), forward items (80 bytes) and member bounds (2 bytes a row) that end exactly there are accepted,
+    256 bytes more are not."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("needs a box without a GPU: here an accepted plan would be launched")
+    align = lambda x: (x + 255) // 256 * 256
+    limit, header = 8 * 2 ** 20 + 16 * 2 ** 10, 4352
+    blocks = 3453                                                   # of four members of 256 tokens: four spans, four items
+    for last, want in ((769, binding.FCP_ERR_HIP), (897, binding.FCP_ERR_BUFFER_TOO_SMALL)):      # ... and one of 256 and `last`
+        spans, items, rows = 4 * blocks + 2, 4 * blocks + 1 + 4, 1024 * blocks + 256 + last
+        size = header + align(16 * spans) + align(80 * items) + align(2 * rows)
+        assert size - limit == (0 if want == binding.FCP_ERR_HIP else 256)
+        unit = np.repeat(np.arange(blocks + 1), [4] * blocks + [2]).astype(np.int32)
+        plan = fcp.fcp_plan_blocks_packed([256] * (4 * blocks + 1) + [last], 1281, 1, 0, None, unit)
+        with pytest.raises(fcp.FcpError) as e:
+            fcp.fcp_block_attn_fwd_static(fcp.Problem(plan, 1, 1, 64, 1281), None, None, None, None, None)
+        assert e.value.code == want, last
+
+
 def test_layout_counts_without_building_the_tables():
     """A launch on a workspace that the layout registry does not know computes the layout anew, as fcp_workspace_bytes does:
     from counts, not by building what fcp_queue_build uploads (0.04 of its time here; 0.36 when it built the pair and
