@@ -1043,34 +1043,42 @@ struct BwdArgs {
   float scale, scale_log2;
 };
 
-// Iterator over the runs of a backward item: the STEP-row query steps of one dependent query block and head, in order; the G
+// Iterator over the runs of a backward item: the 32-row query steps of one dependent query block and head, in order; the G
 // query heads of the group inside a dependency.  A DIAG dependency starts at the tile's own rows.  Inside a run a step is a
 // few additions; what a new run needs is worked out at its start (consumers spent 350-600 of an interval's 2000 cycles on a walk
 // with branches per step, no MFMA beside it; dK/dV of a training step, d = 128: 65536 lognormal tokens, 32/8 heads, dS kept 5183 ->
 // 5005 us; 32768 tokens, 64/8 heads 4368 -> 4035).
-template <int STEP>
+// A dependency's record comes by a scalar load, requested when the one before it is done with, one step or more before its use: a
+// vector load requested on use waited for the tile loads in flight too, and runs of one step were slower than in that walk
+// (8192 tokens in 32-token blocks, 16 heads, d = 64, dS kept: that walk 326 us, a vector load on use 365, so 319; recomputing 283,
+// 304, 276; packed blocks of 16-256 tokens, d = 64: 309, 317, 304).
 struct RunIter {
   const BwdDep* deps;
   int dep, n_deps, hh, group, first_diag;
   int q0, left, last_rows;      // of the run: first row of its first step, steps not yet passed, rows of its last step
   BwdDep cur;
   __device__ __forceinline__ void init(const BwdDep* d, const BwdItem& it, int group_) {
-    deps = d + it.dep_begin; dep = 0; n_deps = it.n_deps; hh = -1; group = group_; first_diag = it.tile_off & ~31;
+    deps = d + it.dep_begin; dep = 0; n_deps = it.n_deps; hh = 0; group = group_; first_diag = it.tile_off & ~31;
     cur = it.first;
     q0 = 0; left = 0; last_rows = 0;
   }
-  // the next run, or false behind the last one
+  // The next run (cur, head hh of the group), or false behind the last one.  ahead() follows once cur and hh have been used.
   __device__ __forceinline__ bool next() {
     left = 0;
-    if (++hh == group) {
-      hh = 0;
-      if (++dep < n_deps) cur = deps[dep];
-    }
-    if (dep >= n_deps) { hh = group - 1; return false; }
+    if (dep >= n_deps) return false;
     q0 = (cur.kind & 1) ? first_diag : 0;
-    left = (cur.q_len - q0 + STEP - 1) / STEP;
-    last_rows = cur.q_len - q0 - STEP * (left - 1);
+    left = (cur.q_len - q0 + 31) / 32;
+    last_rows = cur.q_len - q0 - 32 * (left - 1);
     return true;
+  }
+  __device__ __forceinline__ void ahead() {
+    if (++hh < group) return;
+    hh = 0;
+    if (++dep < n_deps) {
+      // the constant address space makes the load a scalar one: no kernel writes the table
+      const u32x4 r = *(const __attribute__((address_space(4))) u32x4*)(uintptr_t)(deps + dep);
+      cur = BwdDep{(int)r[0], (int)r[1], (int)r[2], (int)r[3]};
+    }
   }
 };
 
@@ -1139,7 +1147,7 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
     const int my_kv = sub * 32 + l32;                  // KV row inside the tile
     const bool kv_ok = my_kv < it.kv_rows;
     const int n_iv = it.n_iv;                          // barrier intervals of the item
-    RunIter<32> run;                                   // consumer: the step to load; producer: the step of the next B
+    RunIter run;                                       // consumer: the step to load; producer: the step of the next B
     run.init(a.deps, it, group);
 
     if (consumer) {
@@ -1195,6 +1203,7 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
           lim_last = (uint32_t)(run.last_rows - 1) * row_bytes;
           d_valid = run.left > 1 ? 32 : run.last_rows;
           d_lim = run.left > 1 ? lim_whole : lim_last;
+          run.ahead();
         } else {
           d_q = reinterpret_cast<uint64_t>(zeros); d_do = d_q; d_lim = 0; d_valid = 0; d_sc = 0;
         }
@@ -1257,7 +1266,9 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
             else acc_k[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(aop[jw]), as_bf16x8(bop[u % PFC]), acc_k[n], 0, 0, 0);
             if (u + PFC < NS) bop[u % PFC] = fetch_b(u + PFC);
             if (n == NN - 1) aop[jw] = fetch_a(jw);
-            if (u == NS / 2) issue();
+            // Early in the interval: dK/dV of an 8-worker share (32/8 heads, d = 128) takes 5700 us with the loads behind the 9th of
+            // the 16 MFMAs, 5640 behind the 7th, 5564 the 5th, 5578 the 3rd, 5510 the 2nd.
+            if (u == 1) issue();
             __builtin_amdgcn_sched_barrier(0);
           }
           next_tile();
@@ -1309,8 +1320,9 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
       // need none
       const int mask_below = (SPILL && it.kv_rows < kBwdTileN) ? kNoMask : it.tile_off + sub * 32 + 31;
       const int kv0 = it.tile_off + sub * 32;              // the wave's first KV row inside the segment
+      const int frag_from = sub * 32 < it.kv_rows ? kv0 : 0x7fffffff;   // first query row whose step has a fragment under a causal mask
       const int sink = (int)(blockIdx.x & (kDsSinkFrags - 1));
-      int frag_t = sink, d_frag = 0, dd_frag = 0;   // fragment of the step that B handles in this interval; increments inside a run
+      int frag_t = sink, d_frag = 0;   // fragment of the step that B handles in this interval; its increment inside a run
       uint32_t sp_off[2];
 #pragma unroll
       for (int j = 0; j < 2; j++) sp_off[j] = 1024 * j + 512 * g + 16 * ((l32 + 8 * j + 4 * g) & 31);
@@ -1326,7 +1338,7 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
       for (int kc = 0; kc < KC; kc++) row_a[kc] = lds_addr(lds_t[0]) + b_p * BUF + tile_off<D>(l32, 2 * kc + g);
       uint32_t sc_a = lds_sc0 + b_s * 256 + 16 * g;      // scalars of step i+1: rows 8*q4 + 4g .. +3 at +32*q4, D*scale at +128
       int thr_t = thr_none, d_thr = 0;     // diagonal threshold of the step that B handles in this interval
-      bool causal_t = false;     // joined run: the mask of that step is causal
+      int causal_t = 0;          // 1: the run of that step is causal (a row group then keeps one fragment more than the one before it)
       f32x16 s_a, dp_a, s_b, dp_b;
 #pragma unroll
       for (int r = 0; r < 16; r++) { s_a[r] = 0.f; dp_a[r] = 0.f; s_b[r] = 0.f; dp_b[r] = 0.f; }
@@ -1353,7 +1365,7 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
         const uint32_t hdst = lds_h0 + (hb ^ 1) * (4 * 4096);
         unsigned char* fptr = nullptr;
         // no fragment: KV rows past the tile's end, above the diagonal
-        if constexpr (SPILL) fptr = a.ds + (int64_t)__builtin_amdgcn_readfirstlane(sub * 32 < it.kv_rows && (thr_t >= kv0 || (JOINED && !causal_t)) ? frag_t : sink) * kDsFragBytes;
+        if constexpr (SPILL) fptr = a.ds + (int64_t)__builtin_amdgcn_readfirstlane((JOINED && !causal_t ? kNoMask : thr_t) >= frag_from ? frag_t : sink) * kDsFragBytes;
         float p_ahead = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[0], a.scale_log2, -lse_c[0]));
 #pragma unroll
         for (int k = 0; k < NS; k++) {
@@ -1430,21 +1442,20 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
         if (__builtin_expect(run.left > 1, 1)) {
           run.left--;
           thr_t += d_thr;
-          if constexpr (SPILL) { frag_t += d_frag; d_frag += dd_frag; }
+          if constexpr (SPILL) { frag_t += d_frag; d_frag += causal_t; }
         } else if (run.next()) {
-          const bool diag = (run.cur.kind & 1) != 0;
           thr_t = run.cur.kind != FCP_KIND_FULL ? run.q0 : thr_none;
           d_thr = run.cur.kind != FCP_KIND_FULL ? 32 : 0;
-          if constexpr (JOINED) causal_t = diag;
+          if constexpr (SPILL || JOINED) causal_t = run.cur.kind & 1;
           if constexpr (SPILL) {
             const int q32 = run.q0 >> 5, nq32 = (run.cur.q_len + 31) >> 5, nkv32 = (it.kv_blk_len + 31) >> 5, head = it.kv_head * group + run.hh;
-            frag_t = run.cur.ds_frag + (kv0 >> 5) + (diag ? head * (nq32 * (nq32 + 1) / 2) + q32 * (q32 + 1) / 2 : (head * nq32 + q32) * nkv32);
-            d_frag = diag ? q32 + 1 : nkv32;
-            dd_frag = diag ? 1 : 0;
+            frag_t = run.cur.ds_frag + (kv0 >> 5) + (causal_t ? head * (nq32 * (nq32 + 1) / 2) + q32 * (q32 + 1) / 2 : (head * nq32 + q32) * nkv32);
+            d_frag = causal_t ? q32 + 1 : nkv32;
           }
+          run.ahead();
         } else {
           thr_t = thr_none; d_thr = 0;
-          frag_t = sink; d_frag = 0; dd_frag = 0;
+          frag_t = sink; d_frag = 0; causal_t = 0;
         }
         hb ^= 1;
       };

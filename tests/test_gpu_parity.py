@@ -918,6 +918,26 @@ def test_spans_of_neighbouring_and_distant_blocks(case):
         _check_lse("lse_part", lse_part.cpu().numpy(), lp)
 
 
+SHORT_RUNS = [
+    # seq_lens, block, causal, c, Hq, Hkv, d: every run of the dK/dV walk one step, one and a ragged one, one of few rows
+    ([230, 33, 5], 32, 1, 0, 6, 2, 64),
+    ([230, 33, 5], 33, 1, 2, 2, 2, 128),
+    ([90, 8], 7, 0, 0, 4, 1, 128),
+    ([300, 64], 64, 0, 3, 4, 4, 64),
+    ([300, 65, 1], 65, 1, 0, 8, 2, 128),
+]
+
+
+@pytest.mark.parametrize("spill", [0, 16])
+@pytest.mark.parametrize("case", range(len(SHORT_RUNS)))
+def test_bwd_short_runs(case, spill):
+    """dK/dV walks runs (the steps of one dependent query block and head) and requests the next dependency's record ahead:
+    items of many runs of one or two steps, with and without the dS of every step going to memory."""
+    lens, bs, causal, c, hq, hkv, d = SHORT_RUNS[case]
+    wl = workloads.custom_workload(lens, bs, causal, c, hq, hkv, d, seed=970 + case, name=f"runs{case}-{spill}")
+    _full_parity(wl, backward=True, flags=F32 | spill, partials=False)
+
+
 def test_kv_tile_of_4_gib():
     """262144 KV heads of d = 128: one 64-row tile of K spans 4 GiB, the step from it to the next is no 32-bit number.  A query row
     against two tiles, sampled heads against the softmax in fp64."""
