@@ -1050,7 +1050,7 @@ struct BwdArgs {
 // 5005 us; 32768 tokens, 64/8 heads 4368 -> 4035).
 // A dependency's record comes by a scalar load, requested when the one before it is done with, one step or more before its use: a
 // vector load requested on use waited for the tile loads in flight too, and runs of one step were slower than in that walk
-// (8192 tokens in 32-token blocks, 16 heads, d = 64, dS kept: that walk 326 us, a vector load on use 365, so 319; recomputing 283,
+// (8192 tokens in 32-token blocks, 16 heads, d = 64, dS kept: that walk 326 us, a vector load on use 365, so 313; recomputing 283,
 // 304, 276; packed blocks of 16-256 tokens, d = 64: 309, 317, 304).
 struct RunIter {
   const BwdDep* deps;
@@ -1309,16 +1309,15 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
       }
       // SPILL: the dS this wave forms also goes to memory, one 2 KB fragment per step, for the dQ pass.  There a
       // KV row past the ragged end of the tile must carry dS = 0 (here its column of dK^T / dV^T is simply never
-      // stored): such lanes get a threshold nothing passes, and a ragged tile runs every step through the masked
+      // stored): such lanes get a KV row that no threshold lets pass, and a ragged tile runs every step through the masked
       // variant.  Fragment layout, shared with dq_ds_kernel: the 16 bytes that lane (KV row r = lane % 32,
       // g = lane / 32) holds for j = 0, 1 (query rows 16j + 4g + {0..3} and 16j + 8 + 4g + {0..3} of the step)
       // sit at byte 1024 j + 512 g + 16 ((r + 8 j + 4 g) % 32): every store instruction writes 1 KB of consecutive
       // memory, and the rotation makes the transposing LDS reads of the dQ pass bank-conflict free.
       if constexpr (SPILL) { if (!kv_ok) kvg = 0x7fff0000; }
-      const int thr_none = (SPILL && it.kv_rows < kBwdTileN) ? kNoMask - 1 : kNoMask;
       // a step whose first query row is below this one is masked: the diagonal rows that this wave's last KV row does not reach
       // need none
-      const int mask_below = (SPILL && it.kv_rows < kBwdTileN) ? kNoMask : it.tile_off + sub * 32 + 31;
+      const int mask_below = (SPILL && it.kv_rows < kBwdTileN) ? kNoMask + 1 : it.tile_off + sub * 32 + 31;
       const int kv0 = it.tile_off + sub * 32;              // the wave's first KV row inside the segment
       const int frag_from = sub * 32 < it.kv_rows ? kv0 : 0x7fffffff;   // first query row whose step has a fragment under a causal mask
       const int sink = (int)(blockIdx.x & (kDsSinkFrags - 1));
@@ -1337,7 +1336,7 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
 #pragma unroll
       for (int kc = 0; kc < KC; kc++) row_a[kc] = lds_addr(lds_t[0]) + b_p * BUF + tile_off<D>(l32, 2 * kc + g);
       uint32_t sc_a = lds_sc0 + b_s * 256 + 16 * g;      // scalars of step i+1: rows 8*q4 + 4g .. +3 at +32*q4, D*scale at +128
-      int thr_t = thr_none, d_thr = 0;     // diagonal threshold of the step that B handles in this interval
+      int thr_t = kNoMask, d_thr = 0;     // diagonal threshold of the step that B handles in this interval
       int causal_t = 0;          // 1: the run of that step is causal (a row group then keeps one fragment more than the one before it)
       f32x16 s_a, dp_a, s_b, dp_b;
 #pragma unroll
@@ -1444,7 +1443,7 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
           thr_t += d_thr;
           if constexpr (SPILL) { frag_t += d_frag; d_frag += causal_t; }
         } else if (run.next()) {
-          thr_t = run.cur.kind != FCP_KIND_FULL ? run.q0 : thr_none;
+          thr_t = run.cur.kind != FCP_KIND_FULL ? run.q0 : kNoMask;
           d_thr = run.cur.kind != FCP_KIND_FULL ? 32 : 0;
           if constexpr (SPILL || JOINED) causal_t = run.cur.kind & 1;
           if constexpr (SPILL) {
@@ -1454,7 +1453,7 @@ __global__ void __launch_bounds__(512, 2) dkdv_kernel(BwdArgs a) {
           }
           run.ahead();
         } else {
-          thr_t = thr_none; d_thr = 0;
+          thr_t = kNoMask; d_thr = 0;
           frag_t = sink; d_frag = 0; causal_t = 0;
         }
         hb ^= 1;
