@@ -248,6 +248,10 @@ void expand_problem(const fcp_problem* p, bool forward_only, Expanded* x) {
   // query side: pairs (with the query rows and the KV segment each joins), forward and dQ segments
   struct Join { int32_t q_start, q_len, kv_seg; };
   std::vector<Join> joins;
+  // what tables without packed blocks become at most: grown by push_back the lists took 5-20 % of the queue builder's time
+  x->fwd.reserve(p->n_slots);
+  x->spans.reserve(p->n_pairs);
+  if (!forward_only) { x->pairs.reserve(p->n_pairs); joins.reserve(p->n_pairs); x->dq.reserve(p->n_q_blocks); }
   int64_t frag = kDsSinkFrags;
   for_q_blocks(p, runs, [&](int b, int s0, int s1, const Run* run, int n_runs, bool packed) {
     const fcp_block& qb = p->q_blocks[b];
@@ -327,9 +331,14 @@ int compute_layout(const fcp_problem* p, bool forward_only, WsLayout* L) {
     for (int s = s0; s < s1; s++) {
       const bool whole = packed && !packed_slot(p, p->slots[s]);
       L->n_fwd_items += whole ? q_items_of(p, p->q_blocks[b].tok_len) : items;
+      const int64_t n_pairs = (int64_t)p->slots[s].n_pairs * n_runs;
+      if (!forward_only) L->n_pairs += n_pairs;
+      if (p->block_size <= kMaxSpan) {
+        L->n_spans += whole ? p->slots[s].n_pairs : n_pairs;
+        continue;
+      }
       for (int i = p->slots[s].pair_begin; i < p->slots[s].pair_begin + p->slots[s].n_pairs; i++)
         L->n_spans += ceil_div(p->kv_blocks[p->pairs[i].kv_blk].tok_len, kMaxSpan) * ceil_div(p->q_blocks[b].tok_len, kMaxSpan) * (whole ? 1 : n_runs);
-      if (!forward_only) L->n_pairs += (int64_t)p->slots[s].n_pairs * n_runs;
     }
     if (!(p->flags & FCP_FLAG_BWD_SPILL_DS) || s0 == s1) return;
     for (int i = p->slots[s0].pair_begin; i < p->slots[s1 - 1].pair_begin + p->slots[s1 - 1].n_pairs; i++) {
@@ -489,8 +498,8 @@ struct ItemGroups {
     order.swap(order2); group_end.swap(end2); weight.swap(w2); key.swap(key2);
   }
   // Longest-processing-time assignment of weighted groups to the XCD queues: groups in
-  // descending weight, each to the currently lightest queue.  Ties resolve to the lower index.
-  void spread_over_xcds(std::vector<Item>* out, int32_t begin[kNumXcd + 1]) const {
+  // descending weight, each to the currently lightest queue.  Ties resolve to the lower index.  out: room for all items.
+  void spread_over_xcds(Item* out, int32_t begin[kNumXcd + 1]) const {
     std::vector<int> by_weight(weight.size());
     std::iota(by_weight.begin(), by_weight.end(), 0);
     std::stable_sort(by_weight.begin(), by_weight.end(), [&](int a, int b) { return weight[a] > weight[b]; });
@@ -501,24 +510,23 @@ struct ItemGroups {
       per_xcd[best].push_back(g);
       load[best] += weight[g];
     }
-    out->clear();
-    out->reserve(items.size());
+    Item* const first = out;
     for (int x = 0; x < kNumXcd; x++) {
-      begin[x] = (int32_t)out->size();
+      begin[x] = (int32_t)(out - first);
       for (int g : per_xcd[x])
         for (int32_t u = g ? group_end[g - 1] : 0; u < group_end[g]; u++) {
           const int32_t unit = order[u];
-          out->insert(out->end(), items.begin() + (unit ? unit_end[unit - 1] : 0), items.begin() + unit_end[unit]);
+          out = std::copy(items.begin() + (unit ? unit_end[unit - 1] : 0), items.begin() + unit_end[unit], out);
         }
     }
-    begin[kNumXcd] = (int32_t)out->size();
+    begin[kNumXcd] = (int32_t)(out - first);
   }
 };
 
 // The query-stationary items (forward, dQ) of a list of segments, one unit per (segment, KV head): its items share
 // K/V.  An item joins two sub-tiles: heads (2j, 2j+1) of the group on one row tile when G is even, else row tiles
-// (2j, 2j+1) of one head.
-void q_items(const fcp_problem* p, const std::vector<QSeg>& segs, const std::vector<DevPair>& pairs, bool spans, int64_t n_items, std::vector<QItem>* flat,
+// (2j, 2j+1) of one head.  out: n_items of them; false if there would be another number.
+bool q_items(const fcp_problem* p, const std::vector<QSeg>& segs, const std::vector<DevPair>& pairs, bool spans, int64_t n_items, QItem* out,
              int32_t begin[kNumXcd + 1]) {
   const int G = p->n_q_heads / p->n_kv_heads, heads_per_item = G % 2 == 0 ? 2 : 1;
   ItemGroups<QItem> groups;
@@ -564,9 +572,11 @@ void q_items(const fcp_problem* p, const std::vector<QSeg>& segs, const std::vec
   // whole sequence: the workgroups of an XCD then walk one KV range at a time, which stays in that XCD's L2, instead of
   // as many ranges as a query block has slots (forward of 13000 rows at the end of a 200000-token sequence, 16 KV heads,
   // slots of 4096 columns, plus 118000 tokens of short sequences: 11.2 -> 9.7 ms).
+  if ((int64_t)groups.items.size() != n_items) return false;
   groups.merge(1);
   groups.merge(n_ord);
-  groups.spread_over_xcds(flat, begin);
+  groups.spread_over_xcds(out, begin);
+  return true;
 }
 
 }  // namespace
@@ -888,15 +898,14 @@ int fcp::build_queue_image(const fcp_problem* p, const Expanded& x, const WsLayo
   put(L.off_pairs, x.pairs);
   put(L.off_spans, x.spans);
   put(L.off_q_seg, x.q_seg);
-  std::vector<QItem> flat;
-  q_items(p, x.fwd, x.spans, true, L.n_fwd_items, &flat, hdr->fwd_begin);
-  if ((int64_t)flat.size() != L.n_fwd_items) { set_error("internal: forward item count mismatch"); return FCP_ERR_INVALID_ARG; }
-  put(L.off_fwd_items, flat);
+  if (!q_items(p, x.fwd, x.spans, true, L.n_fwd_items, reinterpret_cast<QItem*>(host.data() + L.off_fwd_items), hdr->fwd_begin)) {
+    set_error("internal: forward item count mismatch"); return FCP_ERR_INVALID_ARG;
+  }
   if (forward_only) return FCP_OK;
   // ---- dQ: query-stationary items over all pairs of a query segment
-  q_items(p, x.dq, x.pairs, false, L.n_dq_items, &flat, hdr->dq_begin);
-  if ((int64_t)flat.size() != L.n_dq_items) { set_error("internal: dQ item count mismatch"); return FCP_ERR_INVALID_ARG; }
-  put(L.off_dq_items, flat);
+  if (!q_items(p, x.dq, x.pairs, false, L.n_dq_items, reinterpret_cast<QItem*>(host.data() + L.off_dq_items), hdr->dq_begin)) {
+    set_error("internal: dQ item count mismatch"); return FCP_ERR_INVALID_ARG;
+  }
   // ---- dK / dV: dependency lists per KV segment, one group per (KV segment, KV head)
   {
     const int G = p->n_q_heads / p->n_kv_heads;
@@ -928,10 +937,8 @@ int fcp::build_queue_image(const fcp_problem* p, const Expanded& x, const WsLayo
       }
     }
     groups.merge(1);
-    std::vector<BwdItem> bwd;
-    groups.spread_over_xcds(&bwd, hdr->bwd_begin);
-    if ((int64_t)bwd.size() != L.n_bwd_items) { set_error("internal: backward item count mismatch"); return FCP_ERR_INVALID_ARG; }
-    put(L.off_bwd_items, bwd);
+    if ((int64_t)groups.items.size() != L.n_bwd_items) { set_error("internal: backward item count mismatch"); return FCP_ERR_INVALID_ARG; }
+    groups.spread_over_xcds(reinterpret_cast<BwdItem*>(host.data() + L.off_bwd_items), hdr->bwd_begin);
   }
   // ---- merge: row-head chunks per query block; slots of a query block are consecutive.
   {
