@@ -908,14 +908,70 @@ def test_spans_of_neighbouring_and_distant_blocks(case):
     ws_ptr = ws.data_ptr() + (-ws.data_ptr()) % 256
     B.fcp_queue_build(prob, ws_ptr, nbytes)
     q, k, v = (to_dev_bf16(x, dev) for x in (wl.q(), wl.k(), wl.v()))
-    o_part = torch.full((prob.n_slot_rows, hq, d), float("nan"), dtype=torch.float32, device=dev)
-    lse_part = torch.full((prob.n_slot_rows, hq), float("nan"), dtype=torch.float32, device=dev)
     op, lp = orc.partial_fwd(wl.q(), wl.k(), wl.v(), plan, bs, causal)
     for _ in range(2):
+        o_part = torch.full((prob.n_slot_rows, hq, d), float("nan"), dtype=torch.float32, device=dev)
+        lse_part = torch.full((prob.n_slot_rows, hq), float("nan"), dtype=torch.float32, device=dev)
         B.fcp_block_attn_fwd(prob, q, k, v, o_part, lse_part, ws_ptr)
         torch.cuda.synchronize(dev)
         _check("o_part", o_part.cpu().numpy(), op)
         _check_lse("lse_part", lse_part.cpu().numpy(), lp)
+
+
+TURNED = [
+    # seq_lens, block, causal, c, Hq, Hkv, d, gap as in SPANS, turn (the pairs of a slot, rotated by so many)
+    ([700, 333], 96, 1, 0, 3, 1, 128, 3, 2),        # odd group: the two row tiles of an item end in different tiles of several spans
+    ([700, 333], 40, 1, 4, 6, 2, 64, 2, 1),
+    ([640, 190], 128, 1, 2, 4, 4, 64, 0, 1),        # FULL behind DIAG: no span ends in a diagonal, or the second one of two does
+    ([515, 300], 100, 0, 0, 4, 2, 128, 4, 3),       # full masks
+]
+
+
+@pytest.mark.parametrize("spill", [0, 16])
+@pytest.mark.parametrize("case", range(len(TURNED)))
+def test_tables_with_gaps_and_turned_slots(case, spill):
+    """Slots with gaps and with pairs in another order than by column, on every route: partials and merge, static, backward,
+    results written directly, and a running result over the stages."""
+    from paper_2605_08524_amd import binding as B
+    from paper_2605_08524_amd.harness import to_dev_bf16
+    lens, bs, causal, c, hq, hkv, d, n, turn = TURNED[case]
+    _say(f"case turned{case} spill={spill}")
+    plan = dict(B.fcp_plan_blocks(lens, bs, causal, c))
+    slots, pairs = [], []
+    for q_blk, pair_begin, n_pairs, row_start in plan["slots"]:
+        kept = [p for i, p in enumerate(plan["pairs"][pair_begin:pair_begin + n_pairs]) if p[2] != 0 or n == 0 or i % n != n - 1]
+        kept = kept[turn % len(kept):] + kept[:turn % len(kept)] if kept else kept
+        slots.append((q_blk, len(pairs), len(kept), row_start))
+        pairs += [(p[0], p[1], p[2], len(slots) - 1) for p in kept]
+    plan["slots"] = np.asarray(slots, dtype=np.int32).reshape(-1, 4)
+    plan["pairs"] = np.asarray(pairs, dtype=np.int32).reshape(-1, 4)
+    _check_tables(plan, hq, hkv, d, bs, 980 + case, spill)
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(990 + case)
+    stages = [B.fcp_stage_tables(plan, k)[0] for k in range(B.fcp_stage_tables(plan, 0)[1])]
+    direct = B.Problem(plan, hq, hkv, d, bs, 0.0, F32 | DIRECT | spill)
+    host = [workloads.bf16_bits(rng.standard_normal((m, h, d)).astype(np.float32))
+            for m, h in ((direct.t_q, hq), (direct.t_kv, hkv), (direct.t_kv, hkv), (direct.t_q, hq))]
+    q, k, v = (to_dev_bf16(x, dev) for x in host[:3])
+    ref = _tables_by_definition(direct, *host)
+    problems = [direct] + [B.Problem(stage, hq, hkv, d, bs, 0.0, F32 | B.FCP_FLAG_RUNNING_MERGE) for stage in stages]
+    spaces = []
+    for prob in problems:
+        nbytes = B.fcp_workspace_bytes(prob)
+        ws = torch.full((nbytes + 256,), 0xFF, dtype=torch.uint8, device=dev)
+        spaces.append((ws, ws.data_ptr() + (-ws.data_ptr()) % 256))
+        B.fcp_queue_build(prob, spaces[-1][1], nbytes)
+    nan = lambda *shape: torch.full(shape, float("nan"), dtype=torch.float32, device=dev)
+    o, lse, o_part, lse_part = nan(direct.t_q, hq, d), nan(direct.t_q, hq), nan(direct.n_slot_rows, hq, d), nan(direct.n_slot_rows, hq)
+    B.fcp_block_attn_fwd_out(direct, q, k, v, o_part, lse_part, o, lse, spaces[0][1])
+    B.fcp_merge_partials(direct, o_part, lse_part, o, lse, spaces[0][1])
+    running, running_lse = nan(direct.t_q, hq, d), torch.full((direct.t_q, hq), float("-inf"), device=dev)
+    for prob, (_, ws_ptr) in zip(problems[1:], spaces[1:]):
+        B.fcp_block_attn_fwd_out(prob, q, k, v, None, None, running, running_lse, ws_ptr)
+    torch.cuda.synchronize(dev)
+    for name, got, got_lse in (("direct", o, lse), ("running", running, running_lse)):
+        _check(name, got.cpu().numpy(), ref[0])
+        _check_lse(name, got_lse.cpu().numpy(), ref[1])
 
 
 SHORT_RUNS = [
