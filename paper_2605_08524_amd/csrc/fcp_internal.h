@@ -21,9 +21,9 @@ constexpr int kMergeMinItems = 2048;  // the merge aims at this many work items 
 // A packed block reaches the kernels cut into runs of whole members, each a query (KV) segment with one pair of its own
 // (expand_problem).  Neighbours join a run while it fits the rows of one query-stationary item; its pair keeps the PACKED
 // kind and the kernels mask by member (q_seg).  A member alone in its run is an ordinary segment: FULL or DIAG, no mask.
-// Forward, GQA 32/8, d = 128, 1024-token blocks, against one segment per member and against the block walked whole with the
-// union of its rows' key ranges: 2048 sequences of 8 tokens 105 us (821, 164); 49152 tokens in sequences of 16-256: 307 us
-// (365, 477).
+// Forward, GQA 32/8, d = 128, 1024-token blocks, when runs replaced one segment per member, against that and against the block
+// walked whole with the union of its rows' key ranges, on one box: 2048 sequences of 8 tokens 105 us (821, 164); 49152 tokens in
+// sequences of 16-256: 335 us (365, 477).
 // ext: first 32x32 dS fragment of the pair in the spill buffer (FCP_FLAG_BWD_SPILL_DS; else 0).
 // The forward walks spans instead: neighbouring pairs of a slot whose KV rows follow each other, joined (FULL ones, and the DIAG
 // one that ends them).  Its tiles then run on across block borders, and what the walk looks up per pair is looked up once

@@ -358,13 +358,15 @@ __device__ __forceinline__ Item read_item(const int32_t* rec) {
 // four LDS buffers filled by LDS-DMA three tiles ahead (all 8 waves share one stream); one
 // workgroup barrier per tile.  The first iteration of an item computes S of its first tile only
 // and the last one only adds the last tile to O, so the pipeline fill costs no MFMAs; all
-// iterations issue the same tile loads, and the ring runs on from item to item.
+// iterations issue the same tile loads.  Every item starts at buffer 0, without a barrier of its own: no wave reads the ring
+// behind the last tile barrier, and a wave fills the same rows of every buffer, so the look-ahead loads that could still land in
+// the next item's first tiles are its own, and it waits for them at the item's end.
 // Between the last MFMA of an iteration and the first of the next lie the barrier, the row maximum and the walk to the next tile,
 // without an MFMA beside them in either wave of the SIMD (both have just passed the barrier): 1150 of 3650 cycles at d = 128,
 // 1050 of 2350 at d = 64 (timestamps).  What runs there is kept short: spans instead of pairs (DevPair) and a step of a few scalar
 // additions inside one, one word per tile that says from where on it is masked, buffer offsets as immediates, the maximum
 // over both halves without LDS, the row sums pinned into the exponential phase.  Forward, before and after: 4000 tokens, 4 heads,
-// d = 64 19.1 -> 16.4 us; 65536 lognormal tokens, GQA 32/8, d = 128 2357 -> 2211 (1010 -> 1040 TFLOP/s); 32768 rows of a
+// d = 64 19.1 -> 16.4 us; 65536 lognormal tokens, GQA 32/8, d = 128 2357 -> 2211 (977 -> 1042 algorithmic TFLOP/s); 32768 rows of a
 // 262144-token sequence 64.2 -> 60.4 ms; short sequences in shared blocks 335 -> 309 us.
 // A wave computes only the tiles its own rows can see: past them (a diagonal, a ragged end, an item of one sub-tile) it
 // loads and waits.  65536 packed tokens (lognormal, GQA 32/8, d = 128): 2.66 -> 2.60 ms; sequences of 16-256 tokens:
@@ -543,7 +545,7 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
     // The load of one tile in two parts.  describe(): scalar bookkeeping, run at an iteration boundary, where no MFMA
     // covers it: inside a span a handful of additions.  issue(): branch-free, sits between the MFMAs.
     // A tile is masked for this wave from the column on where its first row sees nothing more (a DIAG span), the span ends, or at
-    // once (a joined run); see mask_word.
+    // once (a joined run): d_word, and word[] of the tiles described ahead.
     const uint32_t lim_whole = (uint32_t)((kFwdTileN - 1) * kv_row_stride * 2);
     const uint64_t tile_step = (uint64_t)(kFwdTileN * kv_row_stride * 2);        // from 2^18 KV heads on more than 32 bits
     uint64_t d_k = 0, d_v = 0;
@@ -1683,8 +1685,8 @@ __global__ void __launch_bounds__(512, 2) dq_kernel(BwdArgs a) {
             // is formed between the MFMAs of the first.  S and dP in turn, as the operands come, left all 88 issue slots of
             // vector work without an MFMA of the same wave beside them; the other wave of the SIMD covered most of that, and power
             // bounds the rest: training step of 32768 tokens, 64/8 heads, d = 128 8899 -> 8827 us, 8-worker share 11941 -> 11877.
-            // Operands: row chunks of K, then of V, four in flight (the first MFMA waits for one read: with the others requested
-            // in front of it, too, d = 64 is 4 % slower).
+            // Operands: row chunks of K, then of V, four in flight; two of them are requested in front of the first MFMA, which
+            // waits for one (with all four in front of it d = 64 is 4 % slower).
             constexpr int PFQ = 4;
             u32x4 op[PFQ];
             auto request = [&](int u) { op[u % PFQ] = lds_read16(row_off[u % KC] + rt * 32 * (D * 2) + (u < KC ? 0 : TB)); };
