@@ -370,14 +370,18 @@ int compute_layout(const fcp_problem* p, bool forward_only, WsLayout* L) {
   auto align = [](size_t x) { return (x + 255) & ~(size_t)255; };
   size_t off = align(sizeof(WsHeader));
   L->off_pairs = off;       if (!forward_only) off = align(off + sizeof(DevPair) * (size_t)std::max<int64_t>(1, L->n_pairs));
-  L->off_spans = off;       off = align(off + sizeof(DevPair) * (size_t)std::max<int64_t>(1, L->n_spans));
   L->off_fwd_items = off;   off = align(off + sizeof(QItem) * (size_t)std::max<int64_t>(1, L->n_fwd_items));
   L->off_q_seg = off;       off = align(off + (p->n_segments ? sizeof(uint16_t) * (size_t)L->t_q : 0));
-  L->off_bwd_deps = off;    off = align(off + sizeof(BwdDep) * (size_t)std::max<int64_t>(1, L->n_pairs));
-  L->off_bwd_items = off;   off = align(off + sizeof(BwdItem) * (size_t)std::max<int64_t>(1, L->n_bwd_items));
-  L->off_merge_items = off; off = align(off + sizeof(MergeItem) * (size_t)std::max<int64_t>(1, L->n_merge_items));
-  L->off_slot_rh = off;     off = align(off + sizeof(int32_t) * (size_t)std::max(1, p->n_slots));
-  L->off_dq_items = off;    off = align(off + sizeof(QItem) * (size_t)std::max<int64_t>(1, L->n_dq_items));
+  if (!forward_only) {
+    L->off_bwd_deps = off;    off = align(off + sizeof(BwdDep) * (size_t)std::max<int64_t>(1, L->n_pairs));
+    L->off_bwd_items = off;   off = align(off + sizeof(BwdItem) * (size_t)std::max<int64_t>(1, L->n_bwd_items));
+    L->off_merge_items = off; off = align(off + sizeof(MergeItem) * (size_t)std::max<int64_t>(1, L->n_merge_items));
+    L->off_slot_rh = off;     off = align(off + sizeof(int32_t) * (size_t)std::max(1, p->n_slots));
+    L->off_dq_items = off;    off = align(off + sizeof(QItem) * (size_t)std::max<int64_t>(1, L->n_dq_items));
+  }
+  // last of the tables: there are usually far fewer spans than the layout has room for, and only those are uploaded (4142 pairs,
+  // 257 spans, 16 heads: queue builder 406 us with all of the room, 387 so; forward without a workspace 163 and 151)
+  L->off_spans = off;       off = align(off + sizeof(DevPair) * (size_t)std::max<int64_t>(1, L->n_spans));
   // backward scratch, head-major [Hq][T_q] fp32: D * scale, then LSE * log2(e)
   L->off_dls = off;         off = align(off + sizeof(float) * (size_t)std::max<int64_t>(1, L->t_q * p->n_q_heads));
   L->off_lse2 = off;        off = align(off + sizeof(float) * (size_t)std::max<int64_t>(1, L->t_q * p->n_q_heads));
@@ -884,17 +888,15 @@ extern "C" int fcp_workspace_bytes(const fcp_problem* p, size_t* bytes) {
 
 // The host image of the workspace sections that the kernels read: header (zeroed counters, queue
 // ranges, zero / +inf pages), resolved pairs, forward items and, unless forward_only, the backward,
-// dQ and merge tables.  `host` is resized to the image (everything before the backward scratch
-// region, or before the backward dependency lists when forward_only).
+// dQ and merge tables.  `image` is resized to what there is of them: up to the last span.
 int fcp::build_queue_image(const fcp_problem* p, const Expanded& x, const WsLayout& L, bool forward_only, std::vector<unsigned char>* image) {
-  const size_t upload = forward_only ? L.off_bwd_deps : L.off_dls;
-  image->assign(upload, 0);
+  if ((int64_t)x.spans.size() > L.n_spans) { set_error("internal: span count mismatch"); return FCP_ERR_INVALID_ARG; }
+  image->assign(L.off_spans + x.spans.size() * sizeof(DevPair), 0);
   std::vector<unsigned char>& host = *image;
   WsHeader* hdr = reinterpret_cast<WsHeader*>(host.data());
   for (float& v : hdr->infs) v = INFINITY;
   auto put = [&](size_t off, const auto& v) { if (!v.empty()) std::memcpy(host.data() + off, v.data(), v.size() * sizeof(v[0])); };
   if ((int64_t)x.pairs.size() != L.n_pairs) { set_error("internal: pair count mismatch"); return FCP_ERR_INVALID_ARG; }
-  if ((int64_t)x.spans.size() > L.n_spans) { set_error("internal: span count mismatch"); return FCP_ERR_INVALID_ARG; }
   put(L.off_pairs, x.pairs);
   put(L.off_spans, x.spans);
   put(L.off_q_seg, x.q_seg);

@@ -2126,7 +2126,7 @@ extern "C" int fcp_block_attn_fwd_static(const fcp_problem* p, const void* q, co
   rc = compute_layout(p, true, &L);
   if (rc) return rc;
   const size_t plan_bytes = static_plan_bytes(p);
-  if (plan_bytes > kStaticPlanBytes || L.off_bwd_deps > kStaticScratchBytes) {
+  if (plan_bytes > kStaticPlanBytes || L.off_dls > kStaticScratchBytes) {
     set_error("fcp_block_attn_fwd_static: the forward's queue tables need %zu bytes, the limit is %zu "
               "(use fcp_queue_build + fcp_block_attn_fwd with a workspace of your own)", plan_bytes, kStaticPlanBytes);
     return FCP_ERR_BUFFER_TOO_SMALL;
