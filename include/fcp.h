@@ -244,7 +244,7 @@ int fcp_block_attn_fwd_out(const fcp_problem* p, const void* q, const void* k, c
  * workspace (code under HIP graph capture set-up, tight serving loops, harnesses that forbid hipMalloc).
  *
  * Same result as fcp_queue_build + fcp_block_attn_fwd, bit for bit, with no workspace argument: the
- * forward's queue tables (header with the queue counters, resolved pairs, forward work items) are built
+ * forward's queue tables (header with the queue counters, spans of KV rows, forward work items) are built
  * on the host at every call and copied into a fixed array of 8 MiB inside the library's device image,
  * which every device the library runs on holds until the process ends.  The call allocates no device
  * memory (no hipMalloc / hipFree, no allocating library routine); it waits on `stream` for its table

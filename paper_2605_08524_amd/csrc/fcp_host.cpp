@@ -248,7 +248,7 @@ void expand_problem(const fcp_problem* p, bool forward_only, Expanded* x) {
   // query side: pairs (with the query rows and the KV segment each joins), forward and dQ segments
   struct Join { int32_t q_start, q_len, kv_seg; };
   std::vector<Join> joins;
-  // what tables without packed blocks become at most: grown by push_back the lists took 5-20 % of the queue builder's time
+  // what tables without packed blocks become at most (18749 pairs: queue builder 10.6 ms with lists grown as they fill, 6.0 so)
   x->fwd.reserve(p->n_slots);
   x->spans.reserve(p->n_pairs);
   if (!forward_only) { x->pairs.reserve(p->n_pairs); joins.reserve(p->n_pairs); x->dq.reserve(p->n_q_blocks); }
@@ -887,7 +887,7 @@ extern "C" int fcp_workspace_bytes(const fcp_problem* p, size_t* bytes) {
 }
 
 // The host image of the workspace sections that the kernels read: header (zeroed counters, queue
-// ranges, zero / +inf pages), resolved pairs, forward items and, unless forward_only, the backward,
+// ranges, zero / +inf pages), spans, forward items and, unless forward_only, the pairs, the backward,
 // dQ and merge tables.  `image` is resized to what there is of them: up to the last span.
 int fcp::build_queue_image(const fcp_problem* p, const Expanded& x, const WsLayout& L, bool forward_only, std::vector<unsigned char>* image) {
   if ((int64_t)x.spans.size() > L.n_spans) { set_error("internal: span count mismatch"); return FCP_ERR_INVALID_ARG; }

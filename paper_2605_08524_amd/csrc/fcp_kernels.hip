@@ -2136,7 +2136,7 @@ extern "C" int fcp_block_attn_fwd_static(const fcp_problem* p, const void* q, co
   rc = static_scratch(&ws);
   if (rc) return rc;
   // The tables are rebuilt on every call (the array keeps the previous call's contents): header with
-  // zeroed counters, resolved pairs, forward items.  Host memory only; one copy; the copy is waited for
+  // zeroed counters, spans, forward items.  Host memory only; one copy; the copy is waited for
   // because its source dies with this frame.
   Expanded x;
   expand_problem(p, true, &x);
