@@ -291,7 +291,8 @@ int fcp_block_attn_bwd(const fcp_problem* p, const void* q, const void* k, const
 
 /*
  * The stages of the backward as separate calls, so that a caller can time or overlap them.  fcp_block_attn_bwd
- * itself runs fcp_block_attn_bwd_dq_d (below) followed by fcp_block_attn_bwd_dkdv.
+ * itself runs fcp_block_attn_bwd_dq_d (below) followed by fcp_block_attn_bwd_dkdv (a small problem: D, then both in one launch,
+ * with the same bits).
  * fcp_bwd_preprocess:      computes D = rowsum(dO o O) and leaves scale*D and log2(e)*LSE
  *                          ([Hq,T_q] fp32 each) in the workspace.
  * fcp_block_attn_bwd_dkdv: KV-stationary kernel, writes dk and dv.
@@ -311,7 +312,7 @@ int fcp_block_attn_bwd_dq(const fcp_problem* p, const void* q, const void* k, co
  * fcp_block_attn_bwd_dq_d -- fcp_block_attn_bwd_dq that needs no fcp_bwd_preprocess: the kernel computes
  * D = rowsum(dO o O) for the rows of each work item itself (it holds their dO already) and leaves scale*D and
  * log2(e)*LSE in the workspace, where a later fcp_block_attn_bwd_dkdv on the same workspace finds them.
- * fcp_block_attn_bwd = this call followed by fcp_block_attn_bwd_dkdv.
+ * fcp_block_attn_bwd = this call followed by fcp_block_attn_bwd_dkdv, bit for bit.
  * o / lse: the forward's final outputs, as for fcp_block_attn_bwd.
  */
 int fcp_block_attn_bwd_dq_d(const fcp_problem* p, const void* q, const void* k, const void* v,

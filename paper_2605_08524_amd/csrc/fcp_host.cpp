@@ -396,6 +396,105 @@ int compute_layout(const fcp_problem* p, bool forward_only, WsLayout* L) {
   return FCP_OK;
 }
 
+namespace {
+
+// What a launch takes, in microseconds on 256 compute units, whole (one workgroup walks an item's tiles or steps one after the
+// other) and split (fwd_split_kernel, bwd_split_kernel): least-squares fits to 58 shapes (1000 to 40000 tokens, 1 to 32 heads, chains
+// of 1 to 512 tiles, full and causal, uniform and lognormal), which they meet within 15 % nearly everywhere.
+// A whole launch ends with its longest item or when all are through; a split one costs a fixed time per workgroup (unit) as well, but
+// its chains are an eighth.
+struct LaunchCost { double whole, whole_tile, whole_item, split, split_tile, split_unit, split_chain; };
+constexpr LaunchCost kLaunchCost[2][3] = {      // [d = 128][forward, dQ, dK/dV]
+    {{6.9, 0.92, 2.6, 5.0, 1.33, 11.3, 0.095}, {6.3, 1.27, 3.6, 5.0, 1.68, 12.8, 0.122}, {6.7, 0.537, 5.5, 5.0, 0.509, 7.7, 0.149}},
+    {{7.0, 1.25, 5.4, 4.8, 2.60, 35.6, 0.147}, {6.6, 1.87, 7.2, 4.6, 3.44, 40.3, 0.226}, {7.2, 0.702, 10.1, 4.3, 1.06, 31.3, 0.202}}};
+constexpr double kSplitGain = 1.15;      // split only what gains clearly: more than the fit is off by
+constexpr int kSplitMaxItems = 512;      // two to a compute unit: the fits reach no further, and walking larger tables would cost
+
+// The items of one kernel: tiles (steps) of the longest, of all; `units`: their 32-row units as fractions of a full item's.
+struct LaunchLoad {
+  int64_t longest = 0, tiles = 0, items = 0;
+  double unit_tiles = 0, units = 0;
+  void add(int64_t n, int64_t count, double share) {
+    longest = std::max(longest, n); tiles += n * count; items += count;
+    unit_tiles += n * count * share; units += count * share;
+  }
+  bool split(const LaunchCost& c) const {
+    constexpr double cus = 256;
+    const double whole = c.whole + c.whole_tile * std::max<double>(longest, tiles / cus) + c.whole_item * items / cus;
+    return whole > kSplitGain * (c.split + c.split_tile * unit_tiles / cus + c.split_unit * units / cus + c.split_chain * longest);
+  }
+};
+
+}  // namespace
+
+void choose_split(const fcp_problem* p, bool forward_only, WsLayout* L) {
+  const LaunchCost* cost = kLaunchCost[p->head_dim == 128];
+  const int G = p->n_q_heads / p->n_kv_heads, heads = G % 2 == 0 ? p->n_q_heads / 2 : p->n_q_heads, rows_of_item = item_rows(p);
+  const bool query = L->n_fwd_items <= kSplitMaxItems || (!forward_only && L->n_dq_items <= kSplitMaxItems), keys = !forward_only && L->n_bwd_items <= kSplitMaxItems;
+  if (!query && !keys) return;
+  LaunchLoad fwd, dq, dkdv;
+  bool complete = true;      // every slot holds all KV blocks that its rows see
+  auto seq_of = [&](int kv_blk) { return kv_blk >= 0 && kv_blk < p->n_kv_blocks ? p->kv_blocks[kv_blk].seq : -1; };
+  const Runs runs = make_runs(p);
+  std::vector<int64_t> steps(keys ? runs.run.size() : 0, 0);     // of a KV segment's dependencies that it sees in full
+  std::vector<char> diag(keys ? runs.run.size() : 0, 0);         // it has one that it sees from its own rows on
+  int max_q = 0, max_kv = 0;
+  auto segment = [&](LaunchLoad* l, int64_t full, int64_t diag_cols, int len) {
+    max_q = std::max(max_q, len);
+    for (int row = 0; row < len; row += rows_of_item) {
+      const int n = std::min(rows_of_item, len - row);
+      const int64_t tiles = ceil_div(full + std::min<int64_t>(diag_cols, row + n), kQTileN);
+      l->add(tiles, heads, (double)ceil_div(n, 32) * 32 / rows_of_item);
+    }
+  };
+  for_q_blocks(p, runs, [&](int b, int s0, int s1, const Run* run, int n_runs, bool packed) {
+    for (int m = 0; m < n_runs; m++) {
+      int64_t dq_full = 0, dq_diag = 0;
+      for (int s = s0; s < s1; s++) {
+        const fcp_slot& sl = p->slots[s];
+        const bool whole = packed && !packed_slot(p, sl);
+        int64_t full = 0, diag_cols = 0;
+        if (sl.n_pairs > 0) {
+          const fcp_pair &first = p->pairs[sl.pair_begin], &last = p->pairs[sl.pair_begin + sl.n_pairs - 1];
+          if (seq_of(first.kv_blk - 1) == seq_of(first.kv_blk) || (!(last.kind & 1) && seq_of(last.kv_blk + 1) == seq_of(last.kv_blk))) complete = false;
+        }
+        for (int i = sl.pair_begin; i < sl.pair_begin + sl.n_pairs; i++) {
+          const fcp_pair& pr = p->pairs[i];
+          const int seg = runs.begin[pr.kv_blk] + ((pr.kind & 2) ? m : 0);
+          ((pr.kind & 1) ? diag_cols : full) += runs.run[seg].len;
+          if (!keys) continue;
+          if (pr.kind & 1) diag[seg] = 1; else steps[seg] += ceil_div(run[m].len, 32) * G;
+        }
+        if (!whole || m == 0) segment(&fwd, full, diag_cols, whole ? p->q_blocks[b].tok_len : run[m].len);
+        dq_full += full; dq_diag += diag_cols;
+      }
+      segment(&dq, dq_full, dq_diag, run[m].len);
+    }
+  });
+  L->split_fwd = L->n_fwd_items > 0 && L->n_fwd_items <= kSplitMaxItems && fwd.split(cost[0]);
+  if (!complete) {
+    // The two kernels round P to bf16 against different references, so the stages of a plan and its one-pass forward agree to fp32
+    // rounding only where all of them take the same one.  What they have in common are the blocks: units if every KV block of a query
+    // block's sequence were a slot of its own.  At 2.5 (1) units to a compute unit a launch of the shortest slots takes what a whole one does.
+    std::unordered_map<int32_t, int64_t> blocks_of;
+    for (int i = 0; i < p->n_kv_blocks; i++) blocks_of[p->kv_blocks[i].seq]++;
+    int64_t units = 0;
+    for (int b = 0; b < p->n_q_blocks; b++) units += ceil_div(p->q_blocks[b].tok_len, 32) * p->n_q_heads * blocks_of[p->q_blocks[b].seq];
+    L->split_fwd = L->n_fwd_items > 0 && units <= (p->head_dim == 128 ? 256 : 640);
+  }
+  L->split_dq = !forward_only && L->n_dq_items > 0 && L->n_dq_items <= kSplitMaxItems && dq.split(cost[1]);
+  L->split_q_per_tile = (int)ceil_div(std::min(max_q, kFwdTileM), 32);
+  L->split_q_units = L->split_q_per_tile * (G % 2 == 0 || max_q > kFwdTileM ? 2 : 1);
+  for (size_t k = 0; k < steps.size(); k++)
+    for (int off = 0, len = runs.run[k].len; off < len; off += kBwdTileN) {
+      const int n = std::min(kBwdTileN, len - off);
+      max_kv = std::max(max_kv, n);
+      dkdv.add(steps[k] + (diag[k] ? ceil_div(len - off, 32) * G : 0), p->n_kv_heads, (double)ceil_div(n, 32) * 32 / kBwdTileN);
+    }
+  L->split_dkdv = keys && L->n_bwd_items > 0 && dkdv.split(cost[2]);
+  L->split_kv_units = (int)ceil_div(max_kv, 32);
+}
+
 // Layouts validated by fcp_queue_build, keyed by the workspace they were built into.  A launch on that
 // workspace with the same descriptor scalars reuses the layout instead of walking every table again: the
 // kernels read the device copy of the tables that fcp_queue_build made, so the host tables matter to a
@@ -436,7 +535,9 @@ int layout_for(const fcp_problem* p, const void* workspace, WsLayout* L) {
   }
   int rc = validate_problem(p);
   if (rc) return rc;
-  return compute_layout(p, false, L);
+  rc = compute_layout(p, false, L);
+  if (rc == FCP_OK) choose_split(p, false, L);
+  return rc;
 }
 
 namespace {
@@ -990,6 +1091,7 @@ extern "C" int fcp_queue_build(const fcp_problem* p, void* workspace, size_t wor
   hipError_t e = hipMemcpyAsync(workspace, host.data(), host.size(), hipMemcpyHostToDevice, (hipStream_t)stream);
   if (e == hipSuccess) e = hipStreamSynchronize((hipStream_t)stream);
   if (e != hipSuccess) { set_error("fcp_queue_build: %s", hipGetErrorString(e)); return FCP_ERR_HIP; }
+  choose_split(p, false, &L);
   remember_layout(p, workspace, L);
   return FCP_OK;
 }

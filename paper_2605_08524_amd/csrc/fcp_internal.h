@@ -90,6 +90,9 @@ struct WsHeader {
 struct WsLayout {
   int64_t n_fwd_items, n_bwd_items, n_merge_items, n_dq_items, n_pairs, n_spans, t_q;   // n_spans: at most
   int merge_chunk;  // (row, head) entries per merge work item, chosen per problem
+  // choose_split: which launches go to the split kernels, and the 32-row units that an item has there at most (of a sub-tile)
+  bool split_fwd, split_dq, split_dkdv;
+  int split_q_units, split_q_per_tile, split_kv_units;
   int64_t n_ds_frags;   // fragments of the dS spill buffer, sinks and one fragment of slack included (0 without the flag)
   size_t off_pairs, off_spans, off_fwd_items, off_q_seg, off_bwd_deps, off_bwd_items, off_merge_items, off_slot_rh, off_dq_items, off_dls, off_lse2, off_ds, total;
 };
@@ -109,6 +112,7 @@ struct Expanded {
 void expand_problem(const fcp_problem* p, bool forward_only, Expanded* x);   // host; p has been validated
 int validate_problem(const fcp_problem* p);           // host; sets the error text
 int compute_layout(const fcp_problem* p, bool forward_only, WsLayout* L);   // host; counts only, p has been validated
+void choose_split(const fcp_problem* p, bool forward_only, WsLayout* L);    // host; after compute_layout
 // the layout of a problem on a workspace: from the registry that fcp_queue_build fills, else validated and computed
 int layout_for(const fcp_problem* p, const void* workspace, WsLayout* L);   // host
 void remember_layout(const fcp_problem* p, const void* workspace, const WsLayout& L);

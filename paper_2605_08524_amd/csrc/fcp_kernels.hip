@@ -834,6 +834,299 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
 }
 
 // =====================================================================================
+// Launches that leave most of the chip idle.  An item of the kernels above is 256 query rows (128 KV rows) and a serial chain of
+// tiles; with few items the chain of the longest one is the launch (4000 tokens, 4 heads, d = 64: 140 items, 16 tiles of 1 us).
+// Here a workgroup owns 32 rows, a quarter of a sub-tile (KV tile), and its eight waves share what those rows stream: wave w
+// takes the 32-row tiles w, w + 8, .. of it through LDS of its own (LDS-DMA, waited for by count, no barrier in the loop), and
+// the eight results meet in LDS at the end.  A chain is a sixteenth as long, and there are eight (four) times the workgroups.  Same
+// items, same tables, no queues: a workgroup's place in the grid names its rows.  Where there is room two workgroups share a
+// compute unit (d = 64); nothing is scheduled by hand, the other waves cover the waits.
+// The price: 32 rows read every K / V (Q / dO) row of theirs by themselves, where an item reads them once for 256, and each
+// workgroup pays for its start and its reduction; choose_split weighs both.  Before / after, us: forward of 4000 tokens, 4 heads,
+// d = 64 16.6 / 10.8, of one 8192-token sequence 129 / 34 (4 heads: 131 / 63; d = 128: 167 / 49 and 169 / 119); backward of 2000
+// tokens, 4/2 heads, d = 64 35 / 14, of 8192 tokens 315 / 74 (4/1 heads: 730 / 267; d = 128: 424 / 110 and 952 / 376).
+// Four waves instead of eight: up to 25 % faster where the chip is full, 30-40 % slower where it is not.
+// =====================================================================================
+constexpr int kSplitRows = 32, kSplitWaves = 8;
+
+// A workgroup's item and which 32 rows of it: the units of an item follow each other on one XCD (apart, they read what they
+// share from further away: 2048-token sequences, 8 heads, d = 64, forward 68 -> 143 us).
+struct SplitPlace {
+  int item, unit;
+  __device__ __forceinline__ SplitPlace(int b, int units) { const int j = b / kNumXcd; unit = j % units; item = j / units * kNumXcd + b % kNumXcd; }
+};
+
+// A table record by scalar loads (wave-uniform address; no kernel writes the tables).
+template <class Item>
+__device__ __forceinline__ Item load_record(const Item* p) {
+  union { Item it; u32x4 w[sizeof(Item) / 16]; } u;
+#pragma unroll
+  for (int i = 0; i < (int)(sizeof(Item) / 16); i++) {
+    const u32x4 v = ((const __attribute__((address_space(4))) u32x4*)(uintptr_t)p)[i];
+#pragma unroll
+    for (int j = 0; j < 4; j++) u.w[i][j] = (uint32_t)__builtin_amdgcn_readfirstlane((int)v[j]);
+  }
+  return u.it;
+}
+
+// Records of 16 bytes (pairs, spans, dependencies), 64 at a time in a wave's registers: the walk to a wave's next tile passes
+// several of them and would wait for each.  The first one comes with the item.
+template <class Rec>
+struct RecordWindow {
+  const Rec* table;
+  int n, from;                  // records; number of the first one in the window, -1: nothing loaded yet
+  Rec head;
+  u32x4 w;
+  __device__ __forceinline__ void init(const Rec* t, int n_, const Rec& first) { table = t; n = n_; from = -1; head = first; w = u32x4{0, 0, 0, 0}; }
+  __device__ __forceinline__ Rec get(int i, int lane) {       // i: wave-uniform, below n
+    if (i == 0) return head;
+    if (from < 0 || i >= from + 64) { from = i; w = *reinterpret_cast<const u32x4*>(table + min(from + lane, n - 1)); }
+    const int l = i - from;
+    return Rec{__builtin_amdgcn_readlane((int)w[0], l), __builtin_amdgcn_readlane((int)w[1], l), __builtin_amdgcn_readlane((int)w[2], l), __builtin_amdgcn_readlane((int)w[3], l)};
+  }
+};
+
+// 32 rows of a [rows x D] slab into the wave's own LDS, rows past `valid` as repeats of the last valid one.
+template <int D>
+__device__ __forceinline__ void wave_tile_dma(uint32_t lds, const uint16_t* src, uint32_t row_bytes, int valid, int lane) {
+  constexpr int CPR = D / 8, RPI = 64 / CPR;
+  asm volatile("" : "+v"(lane));       // the offsets are formed here, not kept in registers through the caller's loop
+  const uint32_t lim = (uint32_t)(valid - 1) * row_bytes, own = (uint32_t)(lane / CPR) * row_bytes;
+#pragma unroll
+  for (int n = 0; n < kSplitRows / RPI; n++)
+    lds_dma16_s(reinterpret_cast<const unsigned char*>(src), min(own + n * RPI * row_bytes, lim) + (((lane % CPR) ^ swz<D>(n * RPI + lane / CPR)) << 4), lds + n * 1024);
+}
+// The same by the waves of a workgroup, one instruction each: the rows that stay.
+template <int D>
+__device__ __forceinline__ void group_tile_dma(uint32_t lds, const uint16_t* src, uint32_t row_bytes, int valid, int piece, int lane) {
+  constexpr int CPR = D / 8, RPI = 64 / CPR;
+  static_assert(kSplitRows / RPI <= kSplitWaves, "one instruction a wave");
+  if (piece >= kSplitRows / RPI) return;
+  const int r = piece * RPI + lane / CPR;
+  lds_dma16_s(reinterpret_cast<const unsigned char*>(src), (uint32_t)min(r, valid - 1) * row_bytes + (((lane % CPR) ^ swz<D>(r)) << 4), lds + piece * 1024);
+}
+// Waits in the loops of the split kernels; the memory clobber keeps LDS accesses on their side.
+__device__ __forceinline__ void lds_reads_done() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+template <int N>
+__device__ __forceinline__ void loads_left() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
+
+// A wave's [D x 32] accumulators as 32 rows of D floats in its LDS region (32 * D * 4 bytes, what its two tiles take); 16-byte
+// chunk c of row r at c ^ (r & 15): conflict free by row and by chunk.
+template <int D>
+__device__ __forceinline__ void put_result(unsigned char* region, const f32x16 (&acc)[D / 32], int lane) {
+  asm volatile("" : "+v"(lane));
+  const int l32 = lane & 31, g = lane >> 5;
+#pragma unroll
+  for (int dt = 0; dt < D / 32; dt++)
+#pragma unroll
+    for (int q4 = 0; q4 < 4; q4++)
+      *reinterpret_cast<f32x4*>(region + l32 * (D * 4) + (((8 * dt + 2 * q4 + g) ^ (l32 & 15)) << 4)) =
+          f32x4{acc[dt][4 * q4], acc[dt][4 * q4 + 1], acc[dt][4 * q4 + 2], acc[dt][4 * q4 + 3]};
+}
+template <int D>
+__device__ __forceinline__ f32x4 get_result(const unsigned char* region, int row, int chunk) {
+  return *reinterpret_cast<const f32x4*>(region + row * (D * 4) + ((chunk ^ (row & 15)) << 4));
+}
+// Four neighbouring columns of a row, in fp32 or rounded to bf16.
+__device__ __forceinline__ void store4(void* base, int64_t at, const f32x4& x, bool bf16) {
+  if (bf16) *reinterpret_cast<u32x2*>(reinterpret_cast<uint16_t*>(base) + at) = u32x2{pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3])};
+  else *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(base) + at) = x;
+}
+
+// What a query-stationary workgroup (forward, dQ) is about: the 32 rows of unit u of an item, per_tile units to a sub-tile.
+struct SplitQ {
+  int q_start, rows, tile_off, head, out_row;    // the unit's first row in the Q buffer, its rows (32, fewer at the end), its first row in the segment
+  __device__ __forceinline__ SplitQ(const QItem& it, int u, int per_tile) {
+    const int off = u % per_tile * kSplitRows, second = -(u / per_tile);
+    // by mask: a select becomes an index into the record, which then lives in memory
+    auto of = [&](const int32_t (&v)[2]) { return v[0] ^ ((v[0] ^ v[1]) & second); };
+    q_start = of(it.q_start) + off;
+    rows = min(of(it.q_rows) - off, kSplitRows);
+    tile_off = of(it.tile_off) + off;
+    head = of(it.head);
+    out_row = of(it.out_row) + off;
+  }
+};
+// The 32-column tiles of an item's pairs (spans) that one wave takes: every eighth.
+struct SplitTiles {
+  RecordWindow<DevPair> rec;
+  int pair, t, row_hi;          // the wave's tile t of pair `pair`; first row past the unit's
+  bool spans, have;
+  DevPair cur;
+  __device__ __forceinline__ void init(const DevPair* table, const QItem& it, bool spans_, int row_hi_, int wave, int lane) {
+    rec.init(table + it.pair_begin, it.n_pairs, it.first);
+    spans = spans_; row_hi = row_hi_; pair = -1; t = wave;
+    cur = it.first; have = it.n_pairs > 0;
+    if (have) { pair = 0; seek(lane); }
+  }
+  __device__ __forceinline__ int tiles() const {
+    return ((cur.kind & 1 ? min(cur.kv_len, (spans ? cur.ext : 0) + row_hi) : cur.kv_len) + kSplitRows - 1) / kSplitRows;
+  }
+  __device__ __forceinline__ void seek(int lane) {
+    for (int n = tiles(); t >= n; n = tiles()) {
+      t -= n;
+      if (++pair >= rec.n) { have = false; return; }
+      cur = rec.get(pair, lane);
+    }
+  }
+  __device__ __forceinline__ void next(int lane) { t += kSplitWaves; seek(lane); }
+};
+
+// Forward, 32 query rows of one head.
+template <int D>
+__global__ void __launch_bounds__(64 * kSplitWaves, D == 64 ? 4 : 2) fwd_split_kernel(FwdArgs a, int n_items, int units, int per_tile) {
+  constexpr int KC = D / 16, DT = D / 32, T = tile_bytes<D>(kSplitRows), NI = T / 1024;
+  __shared__ __attribute__((aligned(1024))) unsigned char lds_kv[kSplitWaves][2 * T];    // [K tile | V tile], at the end the wave's O
+  __shared__ __attribute__((aligned(1024))) unsigned char lds_q[T];
+  __shared__ float s_m[kSplitWaves][kSplitRows], s_l[kSplitWaves][kSplitRows];
+  __shared__ int s_act[kSplitWaves];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, g = lane >> 5;
+  const SplitPlace place(blockIdx.x, units);
+  if (place.item >= n_items) return;
+  const QItem it = load_record(a.items + place.item);
+  const SplitQ u(it, place.unit, per_tile);
+  if (u.rows <= 0) return;
+  const int group = a.n_q_heads / a.n_kv_heads, kvh = __builtin_amdgcn_readfirstlane(u.head / group);
+  const int64_t q_row_stride = (int64_t)a.n_q_heads * D, kv_row_stride = (int64_t)a.n_kv_heads * D;
+  const uint32_t kv_row_bytes = (uint32_t)(kv_row_stride * 2);
+  const uint16_t* kbase = a.k + (int64_t)kvh * D;
+  const uint16_t* vbase = a.v + (int64_t)kvh * D;
+  const uint32_t lk = lds_addr(lds_kv[wave]), lv = lk + T;
+
+  SplitTiles tiles;
+  tiles.init(a.spans, it, true, u.tile_off + u.rows, wave, lane);
+  auto issue = [&](const uint16_t* base, uint32_t lds) {
+    const int c0 = tiles.t * kSplitRows;
+    wave_tile_dma<D>(lds, base + (int64_t)(tiles.cur.kv_start + c0) * kv_row_stride, kv_row_bytes, min(kSplitRows, tiles.cur.kv_len - c0), lane);
+  };
+  group_tile_dma<D>(lds_addr(lds_q), a.q + (int64_t)u.q_start * q_row_stride + (int64_t)u.head * D, (uint32_t)(q_row_stride * 2), u.rows, wave, lane);
+  const bool active = tiles.have;
+  if (active) { issue(kbase, lk); issue(vbase, lv); }
+  int seg_lo = 0, seg_hi = 0;          // joined run: the columns of this lane's member
+  const int my_limit = u.tile_off + l32;
+  if (it.first.kind & 2) {
+    const int sg = l32 < u.rows ? a.q_seg[u.q_start + l32] : 0;
+    seg_lo = sg & 0xff; seg_hi = (sg >> 8) + 1;
+    if (l32 >= u.rows) seg_hi = 0;
+  }
+  loads_left<0>();
+  __syncthreads();
+
+  f32x16 o[DT];
+#pragma unroll
+  for (int dt = 0; dt < DT; dt++)
+#pragma unroll
+    for (int r = 0; r < 16; r++) o[dt][r] = 0.f;
+  float m_run = -INFINITY, l_run = 0.f;
+  bf16x8 qf[KC];
+#pragma unroll
+  for (int kc = 0; kc < KC; kc++) qf[kc] = as_bf16x8(lds_read16(lds_addr(lds_q) + tile_off<D>(l32, 2 * kc + g)));
+  const int tr_row = (lane & 15) >> 2, tr_col = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+
+  while (tiles.have) {
+    const DevPair cur = tiles.cur;
+    const int c0 = tiles.t * kSplitRows;
+    tiles.next(lane);
+    const bool more = tiles.have;
+    f32x16 s;
+#pragma unroll
+    for (int r = 0; r < 16; r++) s[r] = 0.f;
+#pragma unroll
+    for (int kc = 0; kc < KC; kc++)
+      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(lds_read16(lk + tile_off<D>(l32, 2 * kc + g))), qf[kc], s, 0, 0, 0);
+    lds_reads_done();
+    if (more) issue(kbase, lk);
+    // first column that this lane does not see / that some lane of the wave does not see
+    int lo = 0, hi = (cur.kind & 1) ? min(cur.kv_len, cur.ext + my_limit + 1) : cur.kv_len;
+    const int open = (cur.kind & 2) ? 0 : (cur.kind & 1) ? min(cur.kv_len, cur.ext + u.tile_off + 1) : cur.kv_len;
+    if (c0 + kSplitRows > open) {
+      if (cur.kind & 2) { lo = seg_lo; hi = min(seg_hi, hi); }
+#pragma unroll
+      for (int r = 0; r < 16; r++) {
+        const int c = c0 + 8 * (r >> 2) + 4 * g + (r & 3);
+        if (c < lo || c >= hi) s[r] = -INFINITY;
+      }
+    }
+    float mx = s[0];
+#pragma unroll
+    for (int r = 1; r < 16; r++) mx = fmaxf(mx, s[r]);
+    mx = max32(mx) * a.scale_log2;
+    if (__builtin_amdgcn_ballot_w64(mx > m_run + kRescaleSlack) != 0) {       // as in fwd_kernel
+      const float m_new = fmaxf(m_run, mx), m_safe = (m_new == -INFINITY) ? 0.f : m_new;
+      const float alpha = __builtin_amdgcn_exp2f(m_run - m_safe);
+      m_run = m_new;
+      l_run *= alpha;
+#pragma unroll
+      for (int dt = 0; dt < DT; dt++)
+#pragma unroll
+        for (int r = 0; r < 16; r++) o[dt][r] *= alpha;
+    }
+    const float m_use = (m_run == -INFINITY) ? 0.f : m_run;
+    u32x4 pb[2];
+#pragma unroll
+    for (int r = 0; r < 16; r += 2) {
+      const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], a.scale_log2, -m_use)), p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r + 1], a.scale_log2, -m_use));
+      l_run += p0 + p1;
+      pb[r >> 3][(r >> 1) & 3] = pack_bf16(p0, p1);
+    }
+    if (more) loads_left<NI>(); else loads_left<0>();        // V has landed once only the next K is in flight
+#pragma unroll
+    for (int j = 0; j < 2; j++)
+#pragma unroll
+      for (int dt = 0; dt < DT; dt++) {
+        const int c = 4 * dt + (tr_col >> 3);
+        const bf16x8 vt = lds_tr_pair_at(lv + tile_off<D>(16 * j + 4 * g + tr_row, c) + (tr_col & 4) * 2, lv + tile_off<D>(16 * j + 4 * g + tr_row + 8, c) + (tr_col & 4) * 2);
+        o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vt, as_bf16x8(pb[j]), o[dt], 0, 0, 0);
+      }
+    lds_reads_done();
+    if (more) { issue(vbase, lv); loads_left<NI>(); }        // the next K has landed once only the next V is in flight
+  }
+  if (active) put_result<D>(lds_kv[wave], o, lane);
+  const float l_tot = l_run + xor32(l_run);
+  if (g == 0) { s_m[wave][l32] = m_run; s_l[wave][l32] = l_tot; }
+  if (lane == 0) s_act[wave] = active;
+  __syncthreads();
+
+  // the waves' results, D / 4 lanes to a row
+  const bool to_final = it.to_final != 0;
+#pragma unroll
+  for (int pass = 0; pass < D * 8 / (64 * kSplitWaves); pass++) {
+    const int row = (tid + 64 * kSplitWaves * pass) / (D / 4), chunk = tid % (D / 4);
+    float m = -INFINITY, l = 0.f;
+#pragma unroll
+    for (int w = 0; w < kSplitWaves; w++) m = fmaxf(m, s_m[w][row]);
+    f32x4 x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < kSplitWaves; w++) {
+      if (!s_act[w]) break;              // waves without a tile are the last ones
+      const float mw = s_m[w][row], f = mw == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(mw - m);      // nothing seen: O and l are zero
+      l += f * s_l[w][row];
+      x += f * get_result<D>(lds_kv[w], row, chunk);
+    }
+    if (row >= u.rows) continue;
+    const float inv = l > 0.f ? 1.0f / l : 0.f;
+    const float lse = l > 0.f ? (m + __builtin_amdgcn_logf(l)) * kLn2 : -INFINITY;
+    if (a.running) {
+      // as in fwd_kernel
+      const int64_t r = u.q_start + row;
+      float* op = reinterpret_cast<float*>(a.o) + r * q_row_stride + (int64_t)u.head * D + 4 * chunk;
+      float* lp = a.lse + r * a.n_q_heads + u.head;
+      const float lse_o = *lp, top = fmaxf(lse_o, lse);
+      const float w_o = lse_o == -INFINITY ? 0.f : __expf(lse_o - top), w_s = lse == -INFINITY ? 0.f : __expf(lse - top), tot = w_o + w_s;
+      const float c_o = tot > 0.f ? w_o / tot : 0.f, c_s = tot > 0.f ? w_s / tot * inv : 0.f;
+      f32x4 old = *reinterpret_cast<f32x4*>(op);
+      if (lse_o == -INFINITY) old = f32x4{0.f, 0.f, 0.f, 0.f};
+      *reinterpret_cast<f32x4*>(op) = old * c_o + x * c_s;
+      if (chunk == 0) *lp = tot > 0.f ? top + __logf(tot) : -INFINITY;
+    } else {
+      const int64_t r = (to_final ? u.q_start : u.out_row) + row;
+      store4(to_final ? a.o : a.o_part, r * q_row_stride + (int64_t)u.head * D + 4 * chunk, x * inv, to_final ? !a.o_is_f32 : a.part_is_bf16);
+      if (chunk == 0) (to_final ? a.lse : a.lse_part)[r * a.n_q_heads + u.head] = lse;
+    }
+  }
+}
+
+// =====================================================================================
 // Merge: LSE-weighted reduction of the partials of each query block.  HBM-bound.
 // One group of D/4 lanes owns one (row, head) entry: a float4 of the head vector per lane.
 // =====================================================================================
@@ -1992,6 +2285,345 @@ __global__ void __launch_bounds__(512, 2) dq_ds_kernel(BwdArgs a) {
 }
 
 // =====================================================================================
+// Backward for launches that leave most of the chip idle (see fwd_split_kernel).  dQ and dK / dV in one launch: they only share
+// D and LSE, which a launch of delta_kernel leaves for both (2000 tokens, 4/2 heads, d = 64, us: one after the other, D inside dQ,
+// 8.8 + 8.9; so 3.4 + 10.3).
+// dQ: 32 query rows of one head, the waves share their KV tiles.
+// =====================================================================================
+// LDS of both: the waves' streams, the rows that stay, 64 scalars a wave, the waves that had a tile.
+template <int D> constexpr int split_lds() { return (kSplitWaves + 1) * 2 * tile_bytes<D>(kSplitRows) + kSplitWaves * 256 + kSplitWaves * 4; }
+
+template <int D, bool WITH_D, bool GRAD_BF16>
+__device__ __forceinline__ void dq_split(const BwdArgs& a, int block, int n_items, int units, int per_tile, bool members, unsigned char* lds) {
+  constexpr int KC = D / 16, DT = D / 32, T = tile_bytes<D>(kSplitRows);
+  unsigned char* const lds_kv = lds;                                  // a wave's [K tile | V tile], at the end its dQ
+  unsigned char* const lds_q = lds + kSplitWaves * 2 * T;             // Q, dO
+  float* const s_lse = reinterpret_cast<float*>(lds_q + 2 * T);
+  float* const s_dl = s_lse + kSplitRows;
+  int* const s_act = reinterpret_cast<int*>(lds_q + 2 * T + kSplitWaves * 256);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, g = lane >> 5;
+  const SplitPlace place(block, units);
+  if (place.item >= n_items) return;
+  const QItem it = load_record(a.dq_items + place.item);
+  const SplitQ u(it, place.unit, per_tile);
+  if (u.rows <= 0) return;
+  const int group = a.n_q_heads / a.n_kv_heads, kvh = __builtin_amdgcn_readfirstlane(u.head / group);
+  const int64_t q_row_stride = (int64_t)a.n_q_heads * D, kv_row_stride = (int64_t)a.n_kv_heads * D;
+  const uint32_t kv_row_bytes = (uint32_t)(kv_row_stride * 2);
+  const int64_t row0 = (int64_t)u.q_start * q_row_stride + (int64_t)u.head * D;
+  const uint16_t* kbase = a.k + (int64_t)kvh * D;
+  const uint16_t* vbase = a.v + (int64_t)kvh * D;
+  const uint32_t lk = lds_addr(lds_kv) + wave * 2 * T, lv = lk + T;
+
+  SplitTiles tiles;
+  tiles.init(a.pairs, it, false, u.tile_off + u.rows, wave, lane);
+  auto issue = [&](const uint16_t* base, uint32_t lds) {
+    const int c0 = tiles.t * kSplitRows;
+    wave_tile_dma<D>(lds, base + (int64_t)(tiles.cur.kv_start + c0) * kv_row_stride, kv_row_bytes, min(kSplitRows, tiles.cur.kv_len - c0), lane);
+  };
+  group_tile_dma<D>(lds_addr(lds_q), a.q + row0, (uint32_t)(q_row_stride * 2), u.rows, wave, lane);
+  group_tile_dma<D>(lds_addr(lds_q) + T, a.d_o + row0, (uint32_t)(q_row_stride * 2), u.rows, kSplitWaves - 1 - wave, lane);
+  const bool active = tiles.have;
+  if (active) { issue(kbase, lk); issue(vbase, lv); }
+  int seg_lo = 0, seg_hi = 0;          // joined run: first and last column of this lane's member
+  if (members) {                       // some of its pairs may be joined, not only the first
+    const int sg = l32 < u.rows ? a.q_seg[u.q_start + l32] : 0;
+    seg_lo = sg & 0xff; seg_hi = sg >> 8;
+  }
+  if constexpr (WITH_D) {
+    // D = rowsum(dO o O), D / 8 lanes to a row
+    constexpr int LPR = D / 8;
+    static_assert(kSplitRows * LPR <= 64 * kSplitWaves, "one row a thread");
+    const int r = tid / LPR, c = 8 * (tid % LPR);
+    float d = 0.f;
+    if (r < u.rows) {
+      const int64_t at = row0 + r * q_row_stride + c;
+      const u32x4 dv = *reinterpret_cast<const u32x4*>(a.d_o + at);
+      float ov[8];
+      if (a.o_is_f32) {
+        const f32x4 x0 = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(a.o) + at), x1 = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(a.o) + at + 4);
+#pragma unroll
+        for (int i = 0; i < 4; i++) { ov[i] = x0[i]; ov[4 + i] = x1[i]; }
+      } else {
+        const u32x4 x = *reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(a.o) + at);
+#pragma unroll
+        for (int i = 0; i < 4; i++) { ov[2 * i] = __uint_as_float(x[i] << 16); ov[2 * i + 1] = __uint_as_float(x[i] & 0xffff0000u); }
+      }
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        d += __uint_as_float(dv[i] << 16) * ov[2 * i];
+        d += __uint_as_float(dv[i] & 0xffff0000u) * ov[2 * i + 1];
+      }
+    }
+    for (int off = LPR / 2; off > 0; off >>= 1) d += __shfl_xor(d, off, 64);
+    if (r < kSplitRows && c == 0) {
+      float lse2 = INFINITY, dl = 0.f;
+      if (r < u.rows) {
+        const float l = a.lse[(int64_t)(u.q_start + r) * a.n_q_heads + u.head];
+        lse2 = (l == -INFINITY) ? INFINITY : l * kLog2e;
+        dl = d * a.scale;
+        const int64_t hr = (int64_t)u.head * a.t_q + u.q_start + r;
+        a.lse2_out[hr] = lse2;
+        a.dls_out[hr] = dl;
+      }
+      s_lse[r] = lse2; s_dl[r] = dl;
+    }
+  } else if (tid < kSplitRows) {
+    const int64_t hr = (int64_t)u.head * a.t_q + u.q_start + min(tid, u.rows - 1);
+    s_lse[tid] = tid < u.rows ? a.lse2[hr] : INFINITY;
+    s_dl[tid] = a.dls[hr];
+  }
+  loads_left<0>();
+  __syncthreads();
+
+  f32x16 acc[DT];
+#pragma unroll
+  for (int dt = 0; dt < DT; dt++)
+#pragma unroll
+    for (int r = 0; r < 16; r++) acc[dt][r] = 0.f;
+  bf16x8 qf[KC], dof[KC];
+#pragma unroll
+  for (int kc = 0; kc < KC; kc++) {
+    qf[kc] = as_bf16x8(lds_read16(lds_addr(lds_q) + tile_off<D>(l32, 2 * kc + g)));
+    dof[kc] = as_bf16x8(lds_read16(lds_addr(lds_q) + T + tile_off<D>(l32, 2 * kc + g)));
+  }
+  const float lse_l = s_lse[l32], dl_l = s_dl[l32];
+
+  while (tiles.have) {
+    int ln = lane;
+    asm volatile("" : "+v"(ln));       // as in dkdv_split
+    const int l32 = ln & 31, g = ln >> 5, tr_row = (ln & 15) >> 2, tr_col = 16 * ((ln >> 4) & 1) + 4 * (ln & 3);
+    const DevPair cur = tiles.cur;
+    const int c0 = tiles.t * kSplitRows;
+    tiles.next(lane);
+    const bool more = tiles.have;
+    f32x16 s, dp;
+#pragma unroll
+    for (int r = 0; r < 16; r++) { s[r] = 0.f; dp[r] = 0.f; }
+#pragma unroll
+    for (int kc = 0; kc < KC; kc++)
+      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(lds_read16(lk + tile_off<D>(l32, 2 * kc + g))), qf[kc], s, 0, 0, 0);
+#pragma unroll
+    for (int kc = 0; kc < KC; kc++)
+      dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(lds_read16(lv + tile_off<D>(l32, 2 * kc + g))), dof[kc], dp, 0, 0, 0);
+    lds_reads_done();
+    if (more) issue(vbase, lv);
+#pragma unroll
+    for (int r = 0; r < 16; r++) s[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], a.scale_log2, -lse_l));
+    const int open = (cur.kind & 2) ? 0 : (cur.kind & 1) ? min(cur.kv_len, u.tile_off + 1) : cur.kv_len;
+    if (c0 + kSplitRows > open) {
+      int first = 0, last = (cur.kind & 1) ? min(cur.kv_len - 1, u.tile_off + l32) : cur.kv_len - 1;
+      if (cur.kind & 2) { first = seg_lo; last = min(last, seg_hi); }
+#pragma unroll
+      for (int r = 0; r < 16; r++) {
+        const int c = c0 + 8 * (r >> 2) + 4 * g + (r & 3);
+        if (c < first || c > last) s[r] = 0.f;
+      }
+    }
+    u32x4 db[2];
+#pragma unroll
+    for (int r = 0; r < 16; r += 2)
+      db[r >> 3][(r >> 1) & 3] = pack_bf16(s[r] * __builtin_fmaf(dp[r], a.scale, -dl_l), s[r + 1] * __builtin_fmaf(dp[r + 1], a.scale, -dl_l));
+#pragma unroll
+    for (int j = 0; j < 2; j++)
+#pragma unroll
+      for (int dt = 0; dt < DT; dt++) {
+        const int c = 4 * dt + (tr_col >> 3);
+        const bf16x8 kt = lds_tr_pair_at(lk + tile_off<D>(16 * j + 4 * g + tr_row, c) + (tr_col & 4) * 2, lk + tile_off<D>(16 * j + 4 * g + tr_row + 8, c) + (tr_col & 4) * 2);
+        acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kt, as_bf16x8(db[j]), acc[dt], 0, 0, 0);
+      }
+    lds_reads_done();
+    if (more) { issue(kbase, lk); loads_left<0>(); }
+  }
+  if (active) put_result<D>(lds_kv + wave * 2 * T, acc, lane);
+  if (lane == 0) s_act[wave] = active;
+  __syncthreads();
+#pragma unroll
+  for (int pass = 0; pass < D * 8 / (64 * kSplitWaves); pass++) {
+    const int row = (tid + 64 * kSplitWaves * pass) / (D / 4), chunk = tid % (D / 4);
+    f32x4 x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < kSplitWaves; w++) {
+      if (!s_act[w]) break;
+      x += get_result<D>(lds_kv + w * 2 * T, row, chunk);
+    }
+    if (row < u.rows) store4(a.dq, row0 + row * q_row_stride + 4 * chunk, x, GRAD_BF16);
+  }
+}
+
+// dK, dV: 32 KV rows of one KV head, the waves share the 32-row query steps of their dependencies and query heads.
+template <int D, bool GRAD_BF16>
+__device__ __forceinline__ void dkdv_split(const BwdArgs& a, int block, int n_items, int units, unsigned char* lds) {
+  constexpr int KC = D / 16, DT = D / 32, T = tile_bytes<D>(kSplitRows);
+  unsigned char* const lds_t = lds;                                   // a wave's [Q tile | dO tile], at the end its dK, then its dV
+  unsigned char* const lds_kv = lds + kSplitWaves * 2 * T;            // K, V
+  unsigned char* const lds_sc = lds_kv + 2 * T;                       // a wave's [LSE*log2e x 32 | D*scale x 32]
+  int* const s_act = reinterpret_cast<int*>(lds_sc + kSplitWaves * 256);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, g = lane >> 5;
+  const SplitPlace place(block, units);
+  const int off = place.unit * kSplitRows;
+  if (place.item >= n_items) return;
+  const BwdItem it = load_record(a.items + place.item);
+  const int rows = min(it.kv_rows - off, kSplitRows);
+  if (rows <= 0) return;
+  const int kv0 = it.tile_off + off;                     // first of the rows inside the segment
+  const int group = a.n_q_heads / a.n_kv_heads;
+  const int64_t q_row_stride = (int64_t)a.n_q_heads * D, kv_row_stride = (int64_t)a.n_kv_heads * D;
+  const int64_t kv_at = (int64_t)(it.kv_start + off) * kv_row_stride + (int64_t)it.kv_head * D;
+  const uint32_t lq = lds_addr(lds_t) + wave * 2 * T, lo = lq + T, lsc = lds_addr(lds_sc) + wave * 256;
+
+  // The wave's steps: every eighth of (dependency, head of the group, 32 query rows); a DIAG dependency from the rows' own on.
+  RecordWindow<BwdDep> rec;
+  rec.init(a.deps + it.dep_begin, it.n_deps, it.first);
+  BwdDep cur = it.first;
+  int dep = 0, t = wave, per_head = 0;
+  bool have = it.n_deps > 0;
+  auto first_row = [&]() { return (cur.kind & 1) ? kv0 : 0; };
+  auto seek = [&]() {
+    for (;;) {
+      per_head = (cur.q_len - first_row() + kSplitRows - 1) / kSplitRows;
+      if (t < per_head * group) return;
+      t -= per_head * group;
+      if (++dep >= it.n_deps) { have = false; return; }
+      cur = rec.get(dep, lane);
+    }
+  };
+  int q0 = 0;                                            // first query row of the step inside its segment
+  auto issue = [&]() {
+    const int hh = __builtin_amdgcn_readfirstlane(t / per_head), head = it.kv_head * group + hh;
+    q0 = first_row() + (t - hh * per_head) * kSplitRows;
+    const int valid = min(kSplitRows, cur.q_len - q0);
+    const int64_t row = cur.q_start + q0, at = row * q_row_stride + (int64_t)head * D;
+    wave_tile_dma<D>(lq, a.q + at, (uint32_t)(q_row_stride * 2), valid, lane);
+    wave_tile_dma<D>(lo, a.d_o + at, (uint32_t)(q_row_stride * 2), valid, lane);
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+    const float* in_range = (ln >> 5 ? a.dls : a.lse2) + (int64_t)head * a.t_q + row;
+    const float* past_end = ln >> 5 ? reinterpret_cast<const float*>(a.hdr->zeros) : a.hdr->infs;
+    lds_dma4(((ln & 31) < valid ? in_range : past_end) + (ln & 31), lsc);
+  };
+  if (have) seek();
+  group_tile_dma<D>(lds_addr(lds_kv), a.k + kv_at, (uint32_t)(kv_row_stride * 2), rows, wave, lane);
+  group_tile_dma<D>(lds_addr(lds_kv) + T, a.v + kv_at, (uint32_t)(kv_row_stride * 2), rows, kSplitWaves - 1 - wave, lane);
+  const bool active = have;
+  if (active) issue();
+  // query rows (of the segment) that see this lane's KV row: a joined run's of its own member, a diagonal's from the row itself on
+  int seg_lo = 0, seg_hi = 0x7fffffff;
+  if (it.first.kind & 2) {
+    const int sg = l32 < rows ? a.q_seg[it.first.q_start + kv0 + l32] : 0;
+    seg_lo = sg & 0xff; seg_hi = sg >> 8;
+  }
+  loads_left<0>();
+  __syncthreads();
+
+  f32x16 acc_k[DT], acc_v[DT];
+#pragma unroll
+  for (int dt = 0; dt < DT; dt++)
+#pragma unroll
+    for (int r = 0; r < 16; r++) { acc_k[dt][r] = 0.f; acc_v[dt][r] = 0.f; }
+
+  while (have) {
+    const int kind = cur.kind, first_q = q0;
+    int ln = lane;
+    asm volatile("" : "+v"(ln));       // the LDS addresses are formed in every step: held through the loop they cost d = 64 two dozen spills
+    const int l32 = ln & 31, g = ln >> 5, tr_row = (ln & 15) >> 2, tr_col = 16 * ((ln >> 4) & 1) + 4 * (ln & 3);
+    f32x16 s, dp;
+#pragma unroll
+    for (int r = 0; r < 16; r++) { s[r] = 0.f; dp[r] = 0.f; }
+#pragma unroll
+    for (int kc = 0; kc < KC; kc++) {
+      const uint32_t at = tile_off<D>(l32, 2 * kc + g);
+      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(lds_read16(lq + at)), as_bf16x8(lds_read16(lds_addr(lds_kv) + at)), s, 0, 0, 0);
+      if (kc & 1) __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int kc = 0; kc < KC; kc++) {
+      const uint32_t at = tile_off<D>(l32, 2 * kc + g);
+      dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(lds_read16(lo + at)), as_bf16x8(lds_read16(lds_addr(lds_kv) + T + at)), dp, 0, 0, 0);
+      if (kc & 1) __builtin_amdgcn_sched_barrier(0);
+    }
+    // scalars of rows 8 q4 + 4 g .. +3 of the step; the barriers keep the operands of one phase out of the next (d = 64: 128 registers)
+#pragma unroll
+    for (int q4 = 0; q4 < 4; q4++) {
+      const f32x4 lse4 = __builtin_bit_cast(f32x4, lds_read16(lsc + 32 * q4 + 16 * g));
+#pragma unroll
+      for (int i = 0; i < 4; i++) s[4 * q4 + i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[4 * q4 + i], a.scale_log2, -lse4[i]));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if ((kind & 2) || ((kind & 1) && first_q < kv0 + kSplitRows - 1)) {
+      int lo_q = (kind & 1) ? kv0 + l32 : 0, hi_q = 0x7fffffff;
+      if (kind & 2) { lo_q = max(lo_q, seg_lo); hi_q = seg_hi; }
+#pragma unroll
+      for (int r = 0; r < 16; r++) {
+        const int q = first_q + 8 * (r >> 2) + 4 * g + (r & 3);
+        if (q < lo_q || q > hi_q) s[r] = 0.f;
+      }
+    }
+    u32x4 pb[2], db[2];
+#pragma unroll
+    for (int q4 = 0; q4 < 4; q4++) {
+      const f32x4 dl4 = __builtin_bit_cast(f32x4, lds_read16(lsc + 32 * q4 + 16 * g + 128));
+#pragma unroll
+      for (int i = 0; i < 4; i += 2) {
+        const int r = 4 * q4 + i;
+        pb[q4 >> 1][(r >> 1) & 3] = pack_bf16(s[r], s[r + 1]);
+        db[q4 >> 1][(r >> 1) & 3] = pack_bf16(s[r] * __builtin_fmaf(dp[r], a.scale, -dl4[i]), s[r + 1] * __builtin_fmaf(dp[r + 1], a.scale, -dl4[i + 1]));
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < 2; j++)
+#pragma unroll
+      for (int dt = 0; dt < DT; dt++) {
+        const int c = 4 * dt + (tr_col >> 3);
+        const uint32_t lo16 = tile_off<D>(16 * j + 4 * g + tr_row, c) + (tr_col & 4) * 2, hi16 = tile_off<D>(16 * j + 4 * g + tr_row + 8, c) + (tr_col & 4) * 2;
+        acc_v[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_tr_pair_at(lo + lo16, lo + hi16), as_bf16x8(pb[j]), acc_v[dt], 0, 0, 0);
+        acc_k[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_tr_pair_at(lq + lo16, lq + hi16), as_bf16x8(db[j]), acc_k[dt], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    t += kSplitWaves;
+    seek();
+    lds_reads_done();
+    if (have) { issue(); loads_left<0>(); }
+  }
+  if (lane == 0) s_act[wave] = active;
+#pragma unroll
+  for (int o = 0; o < 2; o++) {
+    if (o) __syncthreads();          // dK has been read
+    if (active) put_result<D>(lds_t + wave * 2 * T, o ? acc_v : acc_k, lane);
+    __syncthreads();
+#pragma unroll
+    for (int pass = 0; pass < D * 8 / (64 * kSplitWaves); pass++) {
+      const int row = (tid + 64 * kSplitWaves * pass) / (D / 4), chunk = tid % (D / 4);
+      f32x4 x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int w = 0; w < kSplitWaves; w++) {
+        if (!s_act[w]) break;
+        x += get_result<D>(lds_t + w * 2 * T, row, chunk);
+      }
+      if (row < rows) store4(o ? a.dv : a.dk, kv_at + row * kv_row_stride + 4 * chunk, x, GRAD_BF16);
+    }
+  }
+}
+
+// Items of each kind and the workgroups of an item (of them in a sub-tile).  Items in eights: one to an XCD.
+struct SplitGrid {
+  int n_kv, kv_units, n_q, q_units, q_per_tile;
+  bool members;                 // the problem has packed blocks
+  __host__ __device__ int kv_blocks() const { return (n_kv + kNumXcd - 1) / kNumXcd * kNumXcd * kv_units; }
+  __host__ __device__ int q_blocks() const { return (n_q + kNumXcd - 1) / kNumXcd * kNumXcd * q_units; }
+};
+
+// Both in one launch, or either: dK / dV take the first workgroups of the grid, dQ the rest.
+template <int D, bool WITH_D, bool GRAD_BF16>
+__global__ void __launch_bounds__(64 * kSplitWaves, D == 64 ? 4 : 2) bwd_split_kernel(BwdArgs a, SplitGrid grid) {
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[split_lds<D>()];
+  const int kv = grid.kv_blocks();
+  if ((int)blockIdx.x < kv) dkdv_split<D, GRAD_BF16>(a, blockIdx.x, grid.n_kv, grid.kv_units, lds);
+  else dq_split<D, WITH_D, GRAD_BF16>(a, blockIdx.x - kv, grid.n_q, grid.q_units, grid.q_per_tile, grid.members, lds);
+}
+
+// =====================================================================================
 // Launchers
 // =====================================================================================
 static int cu_count() {
@@ -2019,6 +2651,7 @@ static float resolve_scale(const fcp_problem* p) {
 constexpr int kFwdWgPerCu = 1;   // 8 waves, two per SIMD
 constexpr int kDkdvWgPerCu = 1;   // 8 waves, two per SIMD
 constexpr int kDqWgPerCu = 1;   // 8 waves, two per SIMD
+
 
 }  // namespace fcp
 
@@ -2072,6 +2705,12 @@ static int launch_fwd(const char* who, const fcp_problem* p, const WsLayout* lay
   a.q_seg = reinterpret_cast<const uint16_t*>(ws + L.off_q_seg);
   a.n_q_heads = p->n_q_heads; a.n_kv_heads = p->n_kv_heads;
   a.scale_log2 = resolve_scale(p) * kLog2e;
+  if (L.split_fwd) {
+    const SplitGrid g = {0, 0, (int)L.n_fwd_items, L.split_q_units, L.split_q_per_tile, false};
+    void (*kern)(FwdArgs, int, int, int) = p->head_dim == 128 ? fwd_split_kernel<128> : fwd_split_kernel<64>;
+    hipLaunchKernelGGL(kern, dim3(g.q_blocks()), dim3(64 * kSplitWaves), 0, (hipStream_t)stream, a, g.n_q, g.q_units, g.q_per_tile);
+    return check_launch(who);
+  }
   const int grid = (int)std::min<int64_t>(L.n_fwd_items, (int64_t)cu_count() * kFwdWgPerCu);
   if (p->head_dim == 128) hipLaunchKernelGGL(fwd_kernel<128>, dim3(grid), dim3(512), 0, (hipStream_t)stream, a);
   else hipLaunchKernelGGL(fwd_kernel<64>, dim3(grid), dim3(512), 0, (hipStream_t)stream, a);
@@ -2125,6 +2764,7 @@ extern "C" int fcp_block_attn_fwd_static(const fcp_problem* p, const void* q, co
   WsLayout L;
   rc = compute_layout(p, true, &L);
   if (rc) return rc;
+  choose_split(p, true, &L);
   const size_t plan_bytes = static_plan_bytes(p);
   if (plan_bytes > kStaticPlanBytes || L.off_dls > kStaticScratchBytes) {
     set_error("fcp_block_attn_fwd_static: the forward's queue tables need %zu bytes, the limit is %zu "
@@ -2213,6 +2853,21 @@ static int fill_bwd_args(const fcp_problem* p, WsLayout* L, BwdArgs* a, void* wo
   return FCP_OK;
 }
 
+static auto bwd_split_instance(bool d128, bool with_d, bool gb) -> void (*)(BwdArgs, SplitGrid) {
+  if (d128) return with_d ? (gb ? bwd_split_kernel<128, true, true> : bwd_split_kernel<128, true, false>)
+                          : (gb ? bwd_split_kernel<128, false, true> : bwd_split_kernel<128, false, false>);
+  return with_d ? (gb ? bwd_split_kernel<64, true, true> : bwd_split_kernel<64, true, false>)
+                : (gb ? bwd_split_kernel<64, false, true> : bwd_split_kernel<64, false, false>);
+}
+
+// dK / dV, dQ, or both
+static int launch_bwd_split(const char* who, const fcp_problem* p, const WsLayout& L, const BwdArgs& a, bool kv, bool q, bool with_d, void* stream) {
+  void (*kern)(BwdArgs, SplitGrid) = bwd_split_instance(p->head_dim == 128, with_d, (p->flags & FCP_FLAG_GRAD_BF16) != 0);
+  const SplitGrid g = {kv ? (int)L.n_bwd_items : 0, L.split_kv_units, q ? (int)L.n_dq_items : 0, L.split_q_units, L.split_q_per_tile, p->n_segments > 0};
+  hipLaunchKernelGGL(kern, dim3(g.kv_blocks() + g.q_blocks()), dim3(64 * kSplitWaves), 0, (hipStream_t)stream, a, g);
+  return check_launch(who);
+}
+
 template <bool J>
 static auto dkdv_instance(bool d128, bool gb, bool spill) -> void (*)(BwdArgs) {
   if (d128) return spill ? (gb ? dkdv_kernel<128, true, true, J> : dkdv_kernel<128, false, true, J>)
@@ -2235,6 +2890,7 @@ extern "C" int fcp_block_attn_bwd_dkdv(const fcp_problem* p, const void* q, cons
   const bool gb = (p->flags & FCP_FLAG_GRAD_BF16) != 0, d128 = p->head_dim == 128;
   const bool spill = (p->flags & FCP_FLAG_BWD_SPILL_DS) != 0;
   if (spill) a.ds = static_cast<unsigned char*>(workspace) + L.off_ds;
+  if (!spill && L.split_dkdv) return launch_bwd_split("fcp_block_attn_bwd_dkdv", p, L, a, true, false, false, stream);
   void (*kern)(BwdArgs) = p->n_segments > 0 ? dkdv_instance<true>(d128, gb, spill) : dkdv_instance<false>(d128, gb, spill);
   hipLaunchKernelGGL(kern, dim3(grid), dim3(512), 0, (hipStream_t)stream, a);
   return check_launch("fcp_block_attn_bwd_dkdv");
@@ -2268,6 +2924,7 @@ static int launch_dq(const char* who, const fcp_problem* p, const void* q, const
     a.dls_out = reinterpret_cast<float*>(ws + L.off_dls);
     a.lse2_out = reinterpret_cast<float*>(ws + L.off_lse2);
   }
+  if (L.split_dq) return launch_bwd_split(who, p, L, a, false, true, with_d, stream);
   void (*kern)(BwdArgs) = p->n_segments > 0 ? dq_instance<true>(d128, with_d, gb) : dq_instance<false>(d128, with_d, gb);
   hipLaunchKernelGGL(kern, dim3(grid), dim3(512), 0, (hipStream_t)stream, a);
   return check_launch(who);
@@ -2328,6 +2985,16 @@ extern "C" int fcp_block_attn_bwd(const fcp_problem* p, const void* q, const voi
     rc = fcp_block_attn_bwd_dkdv(p, q, k, v, d_o, dk, dv, workspace, stream);
     if (rc) return rc;
     return fcp_block_attn_bwd_dq_ds(p, k, dq, workspace, stream);
+  }
+  WsLayout L;
+  BwdArgs a;
+  if (int rc = fill_bwd_args(p, &L, &a, workspace)) return rc;
+  if (L.split_dq && L.split_dkdv) {
+    // D by a launch of its own, then dK / dV and dQ side by side
+    if (int rc = fcp_bwd_preprocess(p, o, lse, d_o, workspace, stream)) return rc;
+    a.q = (const uint16_t*)q; a.k = (const uint16_t*)k; a.v = (const uint16_t*)v; a.d_o = (const uint16_t*)d_o;
+    a.dq = dq; a.dk = dk; a.dv = dv;
+    return launch_bwd_split("fcp_block_attn_bwd", p, L, a, true, true, false, stream);
   }
   // dQ first: its kernel also leaves the per-row scalars (D * scale, LSE * log2 e) that dK/dV needs
   int rc = fcp_block_attn_bwd_dq_d(p, q, k, v, o, lse, d_o, dq, workspace, stream);

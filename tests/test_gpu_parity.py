@@ -1020,3 +1020,33 @@ def test_kv_tile_of_4_gib():
     p = np.exp(s - s.max(axis=1, keepdims=True))
     _check("o_part", o_part[:, sample].cpu().numpy(), (np.einsum("hr,rhd->hd", p, vs) / p.sum(axis=1, keepdims=True))[None])
     _check_lse("lse_part", lse_part[:, sample].cpu().numpy(), (s.max(axis=1) + np.log(p.sum(axis=1)))[None])
+
+
+# Launches of a few short chains, which take the kernels that split a chain over the waves of a workgroup: 1 row, the edges of the
+# 32-row tiles, fewer tiles than waves and many more, tables longer than the 64 records a wave holds, one and several slots.
+SPLIT = [
+    ([1], 128, 1, 0, 1, 1, 64), ([31, 33], 128, 1, 0, 2, 1, 128), ([32, 64, 256, 257], 512, 0, 0, 3, 3, 64), ([255, 129], 1024, 1, 0, 4, 2, 128),
+    ([2600], 32, 1, 0, 1, 1, 64), ([2300, 5], 32, 0, 0, 2, 1, 128), ([1500], 777, 1, 16, 6, 2, 128), ([3000, 40], 1024, 1, 16, 8, 1, 64),
+    ([200, 150, 90], 128, 1, 1, 4, 2, 64),
+]
+
+
+@pytest.mark.parametrize("case", range(len(SPLIT)))
+def test_few_items_split_over_waves(case):
+    """Against the oracle; dq_d then dkdv, called one by one, give what fcp_block_attn_bwd does in one launch, bit for bit (D is summed in
+    one order everywhere, and each kernel's arithmetic does not depend on who runs beside it)."""
+    from paper_2605_08524_amd.harness import DevicePath
+    lens, bs, causal, c, hq, hkv, d = SPLIT[case]
+    wl = workloads.custom_workload(lens, bs, causal, c, hq, hkv, d, seed=700 + case, name=f"split{case}")
+    _full_parity(wl, backward=True, flags=F32)
+    dev = torch.device("cuda:0")
+    dp = DevicePath(wl, dev, flags=F32 | 8, backward=True)
+    dp.fwd(); dp.merge(); dp.bwd()
+    torch.cuda.synchronize(dev)
+    want = [t.clone() for t in (dp.dq, dp.dk, dp.dv)]
+    for t in (dp.dq, dp.dk, dp.dv):
+        t.fill_(float("nan"))
+    dp.bwd_dq_d(); dp.bwd_dkdv()
+    torch.cuda.synchronize(dev)
+    for w, t in zip(want, (dp.dq, dp.dk, dp.dv)):
+        assert torch.equal(w.view(torch.int16), t.view(torch.int16))
