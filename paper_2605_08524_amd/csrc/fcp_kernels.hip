@@ -2452,7 +2452,8 @@ __device__ __forceinline__ void dq_split(const BwdArgs& a, int block, int n_item
 }
 
 // dK, dV: 32 KV rows of one KV head, the waves share the 32-row query steps of their dependencies and query heads.
-template <int D, bool GRAD_BF16>
+// SPILL: dS goes to memory too, as dkdv_kernel leaves it.
+template <int D, bool GRAD_BF16, bool SPILL>
 __device__ __forceinline__ void dkdv_split(const BwdArgs& a, int block, int n_items, int units, unsigned char* lds) {
   constexpr int KC = D / 16, DT = D / 32, T = tile_bytes<D>(kSplitRows);
   unsigned char* const lds_t = lds;                                   // a wave's [Q tile | dO tile], at the end its dK, then its dV
@@ -2489,9 +2490,14 @@ __device__ __forceinline__ void dkdv_split(const BwdArgs& a, int block, int n_it
     }
   };
   int q0 = 0;                                            // first query row of the step inside its segment
+  int frag = 0;                                          // its dS fragment
   auto issue = [&]() {
     const int hh = __builtin_amdgcn_readfirstlane(t / per_head), head = it.kv_head * group + hh;
     q0 = first_row() + (t - hh * per_head) * kSplitRows;
+    if constexpr (SPILL) {
+      const int q32 = q0 >> 5, nq32 = (cur.q_len + 31) >> 5;
+      frag = cur.ds_frag + (kv0 >> 5) + ((cur.kind & 1) ? head * (nq32 * (nq32 + 1) / 2) + q32 * (q32 + 1) / 2 : (head * nq32 + q32) * ((it.kv_blk_len + 31) >> 5));
+    }
     const int valid = min(kSplitRows, cur.q_len - q0);
     const int64_t row = cur.q_start + q0, at = row * q_row_stride + (int64_t)head * D;
     wave_tile_dma<D>(lq, a.q + at, (uint32_t)(q_row_stride * 2), valid, lane);
@@ -2523,7 +2529,7 @@ __device__ __forceinline__ void dkdv_split(const BwdArgs& a, int block, int n_it
     for (int r = 0; r < 16; r++) { acc_k[dt][r] = 0.f; acc_v[dt][r] = 0.f; }
 
   while (have) {
-    const int kind = cur.kind, first_q = q0;
+    const int kind = cur.kind, first_q = q0, frag_now = frag;
     int ln = lane;
     asm volatile("" : "+v"(ln));       // the LDS addresses are formed in every step: held through the loop they cost d = 64 two dozen spills
     const int l32 = ln & 31, g = ln >> 5, tr_row = (ln & 15) >> 2, tr_col = 16 * ((ln >> 4) & 1) + 4 * (ln & 3);
@@ -2550,9 +2556,10 @@ __device__ __forceinline__ void dkdv_split(const BwdArgs& a, int block, int n_it
       for (int i = 0; i < 4; i++) s[4 * q4 + i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[4 * q4 + i], a.scale_log2, -lse4[i]));
     }
     __builtin_amdgcn_sched_barrier(0);
-    if ((kind & 2) || ((kind & 1) && first_q < kv0 + kSplitRows - 1)) {
+    if ((kind & 2) || ((kind & 1) && first_q < kv0 + kSplitRows - 1) || (SPILL && rows < kSplitRows)) {
       int lo_q = (kind & 1) ? kv0 + l32 : 0, hi_q = 0x7fffffff;
       if (kind & 2) { lo_q = max(lo_q, seg_lo); hi_q = seg_hi; }
+      if (SPILL && l32 >= rows) lo_q = 0x7fffffff;       // the dQ pass multiplies a row past the end with whatever K sits there
 #pragma unroll
       for (int r = 0; r < 16; r++) {
         const int q = first_q + 8 * (r >> 2) + 4 * g + (r & 3);
@@ -2569,6 +2576,11 @@ __device__ __forceinline__ void dkdv_split(const BwdArgs& a, int block, int n_it
         pb[q4 >> 1][(r >> 1) & 3] = pack_bf16(s[r], s[r + 1]);
         db[q4 >> 1][(r >> 1) & 3] = pack_bf16(s[r] * __builtin_fmaf(dp[r], a.scale, -dl4[i]), s[r + 1] * __builtin_fmaf(dp[r + 1], a.scale, -dl4[i + 1]));
       }
+    }
+    if constexpr (SPILL) {
+#pragma unroll
+      for (int j = 0; j < 2; j++)
+        *reinterpret_cast<u32x4*>(a.ds + (int64_t)__builtin_amdgcn_readfirstlane(frag_now) * kDsFragBytes + 1024 * j + 512 * g + 16 * ((l32 + 8 * j + 4 * g) & 31)) = db[j];
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -2615,11 +2627,11 @@ struct SplitGrid {
 };
 
 // Both in one launch, or either: dK / dV take the first workgroups of the grid, dQ the rest.
-template <int D, bool WITH_D, bool GRAD_BF16>
+template <int D, bool WITH_D, bool GRAD_BF16, bool SPILL>
 __global__ void __launch_bounds__(64 * kSplitWaves, D == 64 ? 4 : 2) bwd_split_kernel(BwdArgs a, SplitGrid grid) {
   __shared__ __attribute__((aligned(1024))) unsigned char lds[split_lds<D>()];
   const int kv = grid.kv_blocks();
-  if ((int)blockIdx.x < kv) dkdv_split<D, GRAD_BF16>(a, blockIdx.x, grid.n_kv, grid.kv_units, lds);
+  if ((int)blockIdx.x < kv) dkdv_split<D, GRAD_BF16, SPILL>(a, blockIdx.x, grid.n_kv, grid.kv_units, lds);
   else dq_split<D, WITH_D, GRAD_BF16>(a, blockIdx.x - kv, grid.n_q, grid.q_units, grid.q_per_tile, grid.members, lds);
 }
 
@@ -2853,16 +2865,17 @@ static int fill_bwd_args(const fcp_problem* p, WsLayout* L, BwdArgs* a, void* wo
   return FCP_OK;
 }
 
-static auto bwd_split_instance(bool d128, bool with_d, bool gb) -> void (*)(BwdArgs, SplitGrid) {
-  if (d128) return with_d ? (gb ? bwd_split_kernel<128, true, true> : bwd_split_kernel<128, true, false>)
-                          : (gb ? bwd_split_kernel<128, false, true> : bwd_split_kernel<128, false, false>);
-  return with_d ? (gb ? bwd_split_kernel<64, true, true> : bwd_split_kernel<64, true, false>)
-                : (gb ? bwd_split_kernel<64, false, true> : bwd_split_kernel<64, false, false>);
+template <int D>
+static auto bwd_split_instance(bool with_d, bool gb, bool spill) -> void (*)(BwdArgs, SplitGrid) {
+  if (spill) return gb ? bwd_split_kernel<D, false, true, true> : bwd_split_kernel<D, false, false, true>;
+  return with_d ? (gb ? bwd_split_kernel<D, true, true, false> : bwd_split_kernel<D, true, false, false>)
+                : (gb ? bwd_split_kernel<D, false, true, false> : bwd_split_kernel<D, false, false, false>);
 }
 
 // dK / dV, dQ, or both
 static int launch_bwd_split(const char* who, const fcp_problem* p, const WsLayout& L, const BwdArgs& a, bool kv, bool q, bool with_d, void* stream) {
-  void (*kern)(BwdArgs, SplitGrid) = bwd_split_instance(p->head_dim == 128, with_d, (p->flags & FCP_FLAG_GRAD_BF16) != 0);
+  const bool gb = (p->flags & FCP_FLAG_GRAD_BF16) != 0, spill = a.ds != nullptr;
+  void (*kern)(BwdArgs, SplitGrid) = p->head_dim == 128 ? bwd_split_instance<128>(with_d, gb, spill) : bwd_split_instance<64>(with_d, gb, spill);
   const SplitGrid g = {kv ? (int)L.n_bwd_items : 0, L.split_kv_units, q ? (int)L.n_dq_items : 0, L.split_q_units, L.split_q_per_tile, p->n_segments > 0};
   hipLaunchKernelGGL(kern, dim3(g.kv_blocks() + g.q_blocks()), dim3(64 * kSplitWaves), 0, (hipStream_t)stream, a, g);
   return check_launch(who);
@@ -2876,24 +2889,28 @@ static auto dkdv_instance(bool d128, bool gb, bool spill) -> void (*)(BwdArgs) {
                : (gb ? dkdv_kernel<64, true, false, J> : dkdv_kernel<64, false, false, J>);
 }
 
-extern "C" int fcp_block_attn_bwd_dkdv(const fcp_problem* p, const void* q, const void* k, const void* v,
-                                       const void* d_o, void* dk, void* dv, void* workspace, void* stream) {
+static int launch_dkdv(const char* who, const fcp_problem* p, const void* q, const void* k, const void* v,
+                       const void* d_o, void* dk, void* dv, bool spill, void* workspace, void* stream) {
   WsLayout L;
   BwdArgs a;
   int rc = fill_bwd_args(p, &L, &a, workspace);
   if (rc) return rc;
   if (L.n_bwd_items == 0) return FCP_OK;
-  if (!q || !k || !v || !d_o || !dk || !dv || !workspace) { set_error("fcp_block_attn_bwd_dkdv: NULL pointer"); return FCP_ERR_INVALID_ARG; }
+  if (!q || !k || !v || !d_o || !dk || !dv || !workspace) { set_error("%s: NULL pointer", who); return FCP_ERR_INVALID_ARG; }
   a.q = (const uint16_t*)q; a.k = (const uint16_t*)k; a.v = (const uint16_t*)v; a.d_o = (const uint16_t*)d_o;
   a.dk = dk; a.dv = dv;
   int grid = (int)std::min<int64_t>(L.n_bwd_items, (int64_t)cu_count() * kDkdvWgPerCu);
   const bool gb = (p->flags & FCP_FLAG_GRAD_BF16) != 0, d128 = p->head_dim == 128;
-  const bool spill = (p->flags & FCP_FLAG_BWD_SPILL_DS) != 0;
   if (spill) a.ds = static_cast<unsigned char*>(workspace) + L.off_ds;
-  if (!spill && L.split_dkdv) return launch_bwd_split("fcp_block_attn_bwd_dkdv", p, L, a, true, false, false, stream);
+  if (L.split_dkdv) return launch_bwd_split(who, p, L, a, true, false, false, stream);
   void (*kern)(BwdArgs) = p->n_segments > 0 ? dkdv_instance<true>(d128, gb, spill) : dkdv_instance<false>(d128, gb, spill);
   hipLaunchKernelGGL(kern, dim3(grid), dim3(512), 0, (hipStream_t)stream, a);
-  return check_launch("fcp_block_attn_bwd_dkdv");
+  return check_launch(who);
+}
+
+extern "C" int fcp_block_attn_bwd_dkdv(const fcp_problem* p, const void* q, const void* k, const void* v,
+                                       const void* d_o, void* dk, void* dv, void* workspace, void* stream) {
+  return launch_dkdv("fcp_block_attn_bwd_dkdv", p, q, k, v, d_o, dk, dv, p && (p->flags & FCP_FLAG_BWD_SPILL_DS), workspace, stream);
 }
 
 // o / lse == NULL: the per-row scalars come from fcp_bwd_preprocess; else the kernel computes and publishes them.
@@ -2978,7 +2995,10 @@ extern "C" int fcp_block_attn_bwd(const fcp_problem* p, const void* q, const voi
     set_error("fcp_block_attn_bwd: NULL pointer");
     return FCP_ERR_INVALID_ARG;
   }
-  if (p && (p->flags & FCP_FLAG_BWD_SPILL_DS)) {
+  WsLayout L;
+  BwdArgs a;
+  if (int rc = fill_bwd_args(p, &L, &a, workspace)) return rc;
+  if ((p->flags & FCP_FLAG_BWD_SPILL_DS) && !L.recompute) {
     // D first (a pass of its own), then dK/dV, which also writes dS, then dQ from that dS
     int rc = fcp_bwd_preprocess(p, o, lse, d_o, workspace, stream);
     if (rc) return rc;
@@ -2986,9 +3006,6 @@ extern "C" int fcp_block_attn_bwd(const fcp_problem* p, const void* q, const voi
     if (rc) return rc;
     return fcp_block_attn_bwd_dq_ds(p, k, dq, workspace, stream);
   }
-  WsLayout L;
-  BwdArgs a;
-  if (int rc = fill_bwd_args(p, &L, &a, workspace)) return rc;
   if (L.split_dq && L.split_dkdv) {
     // D by a launch of its own, then dK / dV and dQ side by side
     if (int rc = fcp_bwd_preprocess(p, o, lse, d_o, workspace, stream)) return rc;
@@ -2999,6 +3016,6 @@ extern "C" int fcp_block_attn_bwd(const fcp_problem* p, const void* q, const voi
   // dQ first: its kernel also leaves the per-row scalars (D * scale, LSE * log2 e) that dK/dV needs
   int rc = fcp_block_attn_bwd_dq_d(p, q, k, v, o, lse, d_o, dq, workspace, stream);
   if (rc) return rc;
-  return fcp_block_attn_bwd_dkdv(p, q, k, v, d_o, dk, dv, workspace, stream);
+  return launch_dkdv("fcp_block_attn_bwd", p, q, k, v, d_o, dk, dv, false, workspace, stream);
 }
 
