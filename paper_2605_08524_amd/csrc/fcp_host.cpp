@@ -206,8 +206,13 @@ int kind_in_run(int kind, const Run& run) { return (kind & 2) && run.n_segs == 1
 
 bool packed_slot(const fcp_problem* p, const fcp_slot& sl) { return sl.n_pairs == 1 && (p->pairs[sl.pair_begin].kind & 2); }
 
+// A row tile of at most 64 rows takes four heads of a group of 4, 8, ..: all eight waves of the workgroup have rows then.
+bool four_heads(const fcp_problem* p, int rows) { return rows <= kFwdTileM / 2 && (p->n_q_heads / p->n_kv_heads) % 4 == 0; }
+
 int64_t q_items_of(const fcp_problem* p, int rows) {
-  return ceil_div(rows, item_rows(p)) * ((p->n_q_heads / p->n_kv_heads) % 2 == 0 ? p->n_q_heads / 2 : p->n_q_heads);
+  const int64_t tiles = ceil_div(rows, item_rows(p));
+  if ((p->n_q_heads / p->n_kv_heads) % 2 != 0) return tiles * p->n_q_heads;
+  return tiles * (p->n_q_heads / 2) - (four_heads(p, rows - (int)(tiles - 1) * kFwdTileM) ? p->n_q_heads / 4 : 0);
 }
 
 // Append KV rows to the spans of a forward segment (those from span0 on): to the last one where they follow it.
@@ -314,7 +319,9 @@ void expand_problem(const fcp_problem* p, bool forward_only, Expanded* x) {
 
 size_t static_plan_bytes(const fcp_problem* p) {
   int64_t items = 0;
-  for (int s = 0; s < p->n_slots; s++) items += q_items_of(p, p->q_blocks[p->slots[s].q_blk].tok_len);
+  // items of two sub-tiles, whether four heads share some or not
+  const int64_t heads = (p->n_q_heads / p->n_kv_heads) % 2 == 0 ? p->n_q_heads / 2 : p->n_q_heads;
+  for (int s = 0; s < p->n_slots; s++) items += ceil_div(p->q_blocks[p->slots[s].q_blk].tok_len, item_rows(p)) * heads;
   auto align = [](size_t x) { return (x + 255) & ~(size_t)255; };
   return 1024 + align(16 * (size_t)std::max(1, p->n_pairs)) + align(72 * (size_t)std::max<int64_t>(1, items));
 }
@@ -449,7 +456,8 @@ void choose_split(const fcp_problem* p, bool forward_only, WsLayout* L) {
     for (int row = 0; row < len; row += rows_of_item) {
       const int n = std::min(rows_of_item, len - row);
       const int64_t tiles = ceil_div(full + std::min<int64_t>(diag_cols, row + n), kQTileN);
-      l->add(tiles, heads, (double)ceil_div(n, 32) * 32 / rows_of_item);
+      const int four = four_heads(p, n) ? 2 : 1;
+      l->add(tiles, heads / four, (double)ceil_div(n, 32) * 32 * four / rows_of_item);
     }
   };
   for_q_blocks(p, runs, [&](int b, int s0, int s1, const Run* run, int n_runs, bool packed) {
@@ -490,6 +498,10 @@ void choose_split(const fcp_problem* p, bool forward_only, WsLayout* L) {
   L->split_dq = !forward_only && L->n_dq_items > 0 && L->n_dq_items <= kSplitMaxItems && dq.split(cost[1]);
   L->split_q_per_tile = (int)ceil_div(std::min(max_q, kFwdTileM), 32);
   L->split_q_units = L->split_q_per_tile * (G % 2 == 0 || max_q > kFwdTileM ? 2 : 1);
+  if (G % 4 == 0) {                                        // items of four heads have two units a head, or one
+    if (max_q > kFwdTileM / 2) L->split_q_per_tile = 4;
+    L->split_q_units = max_q > kFwdTileM / 2 ? 8 : 4 * L->split_q_per_tile;
+  }
   for (size_t k = 0; k < steps.size(); k++)
     for (int off = 0, len = runs.run[k].len; off < len; off += kBwdTileN) {
       const int n = std::min(kBwdTileN, len - off);
@@ -635,7 +647,7 @@ struct ItemGroups {
 
 // The query-stationary items (forward, dQ) of a list of segments, one unit per (segment, KV head): its items share
 // K/V.  An item joins two sub-tiles: heads (2j, 2j+1) of the group on one row tile when G is even, else row tiles
-// (2j, 2j+1) of one head.  out: n_items of them; false if there would be another number.
+// (2j, 2j+1) of one head; of a row tile of at most 64 rows heads 4j .. 4j + 3 when G is a multiple of 4.  out: n_items of them; false if there would be another number.
 bool q_items(const fcp_problem* p, const std::vector<QSeg>& segs, const std::vector<DevPair>& pairs, bool spans, int64_t n_items, QItem* out,
              int32_t begin[kNumXcd + 1]) {
   const int G = p->n_q_heads / p->n_kv_heads, heads_per_item = G % 2 == 0 ? 2 : 1;
@@ -670,11 +682,13 @@ bool q_items(const fcp_problem* p, const std::vector<QSeg>& segs, const std::vec
       rows.push_back(it);
     }
     for (int g = 0; g < p->n_kv_heads; g++) {
-      for (const QItem& r : rows)
-        for (int hh = 0; hh < G; hh += heads_per_item) {
+      for (const QItem& r : rows) {
+        const int heads = four_heads(p, r.q_rows[0]) ? 4 : heads_per_item;
+        for (int hh = 0; hh < G; hh += heads) {
           groups.items.push_back(r);
-          groups.items.back().head[0] = g * G + hh; groups.items.back().head[1] = g * G + hh + heads_per_item - 1;
+          groups.items.back().head[0] = g * G + hh; groups.items.back().head[1] = g * G + hh + heads - 1;
         }
+      }
       groups.close_unit(w, ((int64_t)sg.seq * p->n_kv_heads + g) * n_ord + sg.ordinal);
     }
   }

@@ -500,9 +500,11 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
     const QItem it = read_item<QItem>(s_rec[par]);
     // Sub-item, 32-row group inside it.  The groups of sub-item 1 run backwards over the waves: waves w and w + 4 share a
     // SIMD, so the group that sees least of a diagonal (or nothing, past a ragged end) sits next to one that sees most.
-    const int sub = wave >> 2, wq = sub ? 3 - (wave & 3) : wave & 3;
+    // Four heads on 64 rows: two waves a head, both groups on every pair of SIMDs.
+    const bool four = it.head[1] - it.head[0] == 3;
+    const int sub = wave >> 2, wq = four ? (wave & 1) ^ sub : sub ? 3 - (wave & 3) : wave & 3;
     // selects, not it.q_rows[sub]: a run-time index would put the whole item into private memory
-    const int q_rows = (sub ? it.q_rows[1] : it.q_rows[0]), tile_off_q = (sub ? it.tile_off[1] : it.tile_off[0]), head = (sub ? it.head[1] : it.head[0]);
+    const int q_rows = (sub ? it.q_rows[1] : it.q_rows[0]), tile_off_q = (sub ? it.tile_off[1] : it.tile_off[0]), head = four ? it.head[0] + (wave >> 1) : (sub ? it.head[1] : it.head[0]);
     const int kvh = __builtin_amdgcn_readfirstlane(it.head[0] / group);     // the division runs on the vector unit
     const int my_row = wq * 32 + l32;                        // row inside the sub-tile
     const int wave_row_lo = tile_off_q + wq * 32;            // rows of this wave inside the block
@@ -777,7 +779,7 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
 
     // ---- epilogue (the record is read again, not kept in registers through the tile loop): normalise, write the partial (fp32) and its LSE
     const QItem e = read_item<QItem>(s_rec[par]);
-    const int e_row = wq * 32 + l32, e_head = sub ? e.head[1] : e.head[0];
+    const int e_row = wq * 32 + l32, e_head = e.head[1] - e.head[0] == 3 ? e.head[0] + (wave >> 1) : sub ? e.head[1] : e.head[0];
     const bool e_ok = e_row < (sub ? e.q_rows[1] : e.q_rows[0]);
     const int64_t e_q_row = (int64_t)((sub ? e.q_start[1] : e.q_start[0]) + e_row);
     const float l_tot = l_run + xor32(l_run);
@@ -937,13 +939,15 @@ __device__ __forceinline__ void store4(void* base, int64_t at, const f32x4& x, b
 struct SplitQ {
   int q_start, rows, tile_off, head, out_row;    // the unit's first row in the Q buffer, its rows (32, fewer at the end), its first row in the segment
   __device__ __forceinline__ SplitQ(const QItem& it, int u, int per_tile) {
-    const int off = u % per_tile * kSplitRows, second = -(u / per_tile);
+    const bool four = it.head[1] - it.head[0] == 3;      // four heads, two units each at most
+    if (four) per_tile = min(per_tile, 2);
+    const int off = u % per_tile * kSplitRows, part = u / per_tile, second = four ? 0 : -part;
     // by mask: a select becomes an index into the record, which then lives in memory
     auto of = [&](const int32_t (&v)[2]) { return v[0] ^ ((v[0] ^ v[1]) & second); };
     q_start = of(it.q_start) + off;
     rows = min(of(it.q_rows) - off, kSplitRows);
     tile_off = of(it.tile_off) + off;
-    head = of(it.head);
+    head = four ? it.head[0] + part : of(it.head);
     out_row = of(it.out_row) + off;
   }
 };
@@ -1799,7 +1803,7 @@ __global__ void __launch_bounds__(512, 2) dq_kernel(BwdArgs a) {
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform, kept in a scalar register
-  const int sub = wave >> 2, wq = sub ? 3 - (wave & 3) : wave & 3;   // sub-item, 32-row group inside it (order: see fwd_kernel)
+  const int sub = wave >> 2;
   const int l32 = lane & 31, g = lane >> 5;
   const int group = a.n_q_heads / a.n_kv_heads;
   const int64_t q_row_stride = (int64_t)a.n_q_heads * D;
@@ -1837,7 +1841,9 @@ __global__ void __launch_bounds__(512, 2) dq_kernel(BwdArgs a) {
   int item_idx = __builtin_amdgcn_readfirstlane(s_next);   // wave-uniform
   while (item_idx >= 0) {
     const QItem it = read_item<QItem>(s_rec);
-    const int q_start = (sub ? it.q_start[1] : it.q_start[0]), q_rows = (sub ? it.q_rows[1] : it.q_rows[0]), tile_off_q = (sub ? it.tile_off[1] : it.tile_off[0]), head = (sub ? it.head[1] : it.head[0]);
+    const bool four = it.head[1] - it.head[0] == 3;
+    const int wq = four ? (wave & 1) ^ sub : sub ? 3 - (wave & 3) : wave & 3;      // 32-row group inside the sub-item (order: see fwd_kernel)
+    const int q_start = (sub ? it.q_start[1] : it.q_start[0]), q_rows = (sub ? it.q_rows[1] : it.q_rows[0]), tile_off_q = (sub ? it.tile_off[1] : it.tile_off[0]), head = four ? it.head[0] + (wave >> 1) : (sub ? it.head[1] : it.head[0]);
     const int kvh = it.head[0] / group;
     const int my_row = wq * 32 + l32;
     const bool row_ok = my_row < q_rows;
@@ -2091,7 +2097,7 @@ __global__ void __launch_bounds__(512, 2) dq_ds_kernel(BwdArgs a) {
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int sub = wave >> 2, wq = wave & 3;
+  const int sub = wave >> 2;
   const int l32 = lane & 31, g = lane >> 5;
   const int group = a.n_q_heads / a.n_kv_heads;
   const int64_t q_row_stride = (int64_t)a.n_q_heads * D;
@@ -2146,7 +2152,9 @@ __global__ void __launch_bounds__(512, 2) dq_ds_kernel(BwdArgs a) {
   int item_idx = __builtin_amdgcn_readfirstlane(s_next);   // wave-uniform
   while (item_idx >= 0) {
     const QItem it = read_item<QItem>(s_rec);
-    const int q_start = (sub ? it.q_start[1] : it.q_start[0]), q_rows = (sub ? it.q_rows[1] : it.q_rows[0]), tile_off_q = (sub ? it.tile_off[1] : it.tile_off[0]), head = (sub ? it.head[1] : it.head[0]);
+    const bool four = it.head[1] - it.head[0] == 3;
+    const int wq = four ? wave & 1 : wave & 3;
+    const int q_start = (sub ? it.q_start[1] : it.q_start[0]), q_rows = (sub ? it.q_rows[1] : it.q_rows[0]), tile_off_q = (sub ? it.tile_off[1] : it.tile_off[0]), head = four ? it.head[0] + (wave >> 1) : (sub ? it.head[1] : it.head[0]);
     const int kvh = it.head[0] / group;
     const int my_row = wq * 32 + l32;
     const bool row_ok = my_row < q_rows;
