@@ -412,9 +412,9 @@ namespace {
 // its chains are an eighth.
 struct LaunchCost { double whole, whole_tile, whole_item, split, split_tile, split_unit, split_chain; };
 constexpr LaunchCost kLaunchCost[2][3] = {      // [d = 128][forward, dQ, dK/dV]
-    {{6.9, 0.92, 2.6, 5.0, 1.33, 11.3, 0.095}, {6.3, 1.27, 3.6, 5.0, 1.68, 12.8, 0.122}, {6.7, 0.537, 5.5, 5.0, 0.509, 7.7, 0.149}},
-    {{7.0, 1.25, 5.4, 4.8, 2.60, 35.6, 0.147}, {6.6, 1.87, 7.2, 4.6, 3.44, 40.3, 0.226}, {7.2, 0.702, 10.1, 4.3, 1.06, 31.3, 0.202}}};
-constexpr double kSplitGain = 1.25;      // split only what gains clearly: a shape that the fit gives 1.2 was 3 % slower
+    {{5.0, 0.93, 4.5, 5.2, 1.14, 10.7, 0.095}, {6.8, 1.25, 3.4, 4.9, 1.46, 12.8, 0.127}, {6.4, 0.538, 5.8, 5.1, 0.470, 5.8, 0.143}},
+    {{6.6, 1.25, 5.8, 4.7, 2.48, 32.5, 0.141}, {7.2, 1.83, 8.5, 4.4, 3.24, 38.8, 0.209}, {7.2, 0.703, 10.0, 4.6, 0.948, 25.7, 0.194}}};
+constexpr double kSplitGain = 1.15;      // split only what gains clearly: every shape that the fit gives 1.11 and more did gain, 3 % at least
 constexpr int kSplitMaxItems = 512;      // two to a compute unit: the fits reach no further, and walking larger tables would cost
 
 // The items of one kernel: tiles (steps) of the longest, of all; `units`: their 32-row units as fractions of a full item's.
@@ -576,6 +576,9 @@ void count_tiles(QItem* it, const std::vector<DevPair>& pairs, bool spans) {
   if (it->n_pairs > 0 && (pairs[it->pair_begin + it->n_pairs - 1].kind & 1)) it->diag_last = diag_off(pairs[it->pair_begin + it->n_pairs - 1], spans);
 }
 
+int32_t chain_of(const QItem& it) { return it.n_tiles; }
+int32_t chain_of(const BwdItem& it) { return it.n_iv; }
+
 // Work items in groups that stay together: the items of a unit (one per (segment, KV head)) are consecutive in `items`, a
 // group is a run of units in `order`.
 template <class Item>
@@ -621,7 +624,9 @@ struct ItemGroups {
   }
   // Longest-processing-time assignment of weighted groups to the XCD queues: groups in
   // descending weight, each to the currently lightest queue.  Ties resolve to the lower index.  out: room for all items.
-  void spread_over_xcds(Item* out, int32_t begin[kNumXcd + 1]) const {
+  // split: for a split kernel, which has no queues (workgroup b runs on XCD b % 8): the longest chains first, by turns on the XCDs
+  // (the last workgroups of 4000 tokens, 4 heads, d = 64 started 4.7 of 10.5 us late, whole chains before them; forward 10.8 -> 9.2 us).
+  void spread_over_xcds(Item* out, int32_t begin[kNumXcd + 1], bool split) const {
     std::vector<int> by_weight(weight.size());
     std::iota(by_weight.begin(), by_weight.end(), 0);
     std::stable_sort(by_weight.begin(), by_weight.end(), [&](int a, int b) { return weight[a] > weight[b]; });
@@ -642,13 +647,14 @@ struct ItemGroups {
         }
     }
     begin[kNumXcd] = (int32_t)(out - first);
+    if (split) std::stable_sort(first, out, [](const Item& a, const Item& b) { return chain_of(a) > chain_of(b); });
   }
 };
 
 // The query-stationary items (forward, dQ) of a list of segments, one unit per (segment, KV head): its items share
 // K/V.  An item joins two sub-tiles: heads (2j, 2j+1) of the group on one row tile when G is even, else row tiles
 // (2j, 2j+1) of one head; of a row tile of at most 64 rows heads 4j .. 4j + 3 when G is a multiple of 4.  out: n_items of them; false if there would be another number.
-bool q_items(const fcp_problem* p, const std::vector<QSeg>& segs, const std::vector<DevPair>& pairs, bool spans, int64_t n_items, QItem* out,
+bool q_items(const fcp_problem* p, const std::vector<QSeg>& segs, const std::vector<DevPair>& pairs, bool spans, bool split, int64_t n_items, QItem* out,
              int32_t begin[kNumXcd + 1]) {
   const int G = p->n_q_heads / p->n_kv_heads, heads_per_item = G % 2 == 0 ? 2 : 1;
   ItemGroups<QItem> groups;
@@ -699,7 +705,7 @@ bool q_items(const fcp_problem* p, const std::vector<QSeg>& segs, const std::vec
   if ((int64_t)groups.items.size() != n_items) return false;
   groups.merge(1);
   groups.merge(n_ord);
-  groups.spread_over_xcds(out, begin);
+  groups.spread_over_xcds(out, begin, split);
   return true;
 }
 
@@ -1020,12 +1026,12 @@ int fcp::build_queue_image(const fcp_problem* p, const Expanded& x, const WsLayo
   put(L.off_pairs, x.pairs);
   put(L.off_spans, x.spans);
   put(L.off_q_seg, x.q_seg);
-  if (!q_items(p, x.fwd, x.spans, true, L.n_fwd_items, reinterpret_cast<QItem*>(host.data() + L.off_fwd_items), hdr->fwd_begin)) {
+  if (!q_items(p, x.fwd, x.spans, true, L.split_fwd, L.n_fwd_items, reinterpret_cast<QItem*>(host.data() + L.off_fwd_items), hdr->fwd_begin)) {
     set_error("internal: forward item count mismatch"); return FCP_ERR_INVALID_ARG;
   }
   if (forward_only) return FCP_OK;
   // ---- dQ: query-stationary items over all pairs of a query segment
-  if (!q_items(p, x.dq, x.pairs, false, L.n_dq_items, reinterpret_cast<QItem*>(host.data() + L.off_dq_items), hdr->dq_begin)) {
+  if (!q_items(p, x.dq, x.pairs, false, L.split_dq, L.n_dq_items, reinterpret_cast<QItem*>(host.data() + L.off_dq_items), hdr->dq_begin)) {
     set_error("internal: dQ item count mismatch"); return FCP_ERR_INVALID_ARG;
   }
   // ---- dK / dV: dependency lists per KV segment, one group per (KV segment, KV head)
@@ -1060,7 +1066,7 @@ int fcp::build_queue_image(const fcp_problem* p, const Expanded& x, const WsLayo
     }
     groups.merge(1);
     if ((int64_t)groups.items.size() != L.n_bwd_items) { set_error("internal: backward item count mismatch"); return FCP_ERR_INVALID_ARG; }
-    groups.spread_over_xcds(reinterpret_cast<BwdItem*>(host.data() + L.off_bwd_items), hdr->bwd_begin);
+    groups.spread_over_xcds(reinterpret_cast<BwdItem*>(host.data() + L.off_bwd_items), hdr->bwd_begin, L.split_dkdv);
   }
   // ---- merge: row-head chunks per query block; slots of a query block are consecutive.
   {
@@ -1102,6 +1108,7 @@ extern "C" int fcp_queue_build(const fcp_problem* p, void* workspace, size_t wor
     set_error("fcp_queue_build: workspace too small (%zu < %zu)", workspace_bytes, L.total);
     return FCP_ERR_BUFFER_TOO_SMALL;
   }
+  choose_split(p, false, &L);
   Expanded x;
   expand_problem(p, false, &x);
   std::vector<unsigned char> host;
@@ -1110,7 +1117,6 @@ extern "C" int fcp_queue_build(const fcp_problem* p, void* workspace, size_t wor
   hipError_t e = hipMemcpyAsync(workspace, host.data(), host.size(), hipMemcpyHostToDevice, (hipStream_t)stream);
   if (e == hipSuccess) e = hipStreamSynchronize((hipStream_t)stream);
   if (e != hipSuccess) { set_error("fcp_queue_build: %s", hipGetErrorString(e)); return FCP_ERR_HIP; }
-  choose_split(p, false, &L);
   remember_layout(p, workspace, L);
   return FCP_OK;
 }
