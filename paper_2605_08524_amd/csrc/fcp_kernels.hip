@@ -845,9 +845,10 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
 // compute unit (d = 64); nothing is scheduled by hand, the other waves cover the waits.
 // The price: 32 rows read every K / V (Q / dO) row of theirs by themselves, where an item reads them once for 256, and each
 // workgroup pays for its start and its reduction; choose_split weighs both.  Before / after, us: forward of 4000 tokens, 4 heads,
-// d = 64 16.6 / 10.8, of one 8192-token sequence 129 / 34 (4 heads: 131 / 63; d = 128: 167 / 49 and 169 / 119); backward of 2000
-// tokens, 4/2 heads, d = 64 35 / 14, of 8192 tokens 315 / 74 (4/1 heads: 730 / 267; d = 128: 424 / 110 and 952 / 376).
-// Four waves instead of eight: up to 25 % faster where the chip is full, 30-40 % slower where it is not.
+// d = 64 16.6 / 9.2, of one 8192-token sequence 129 / 34 (4 heads: 131 / 62; d = 128: 167 / 49 and 169 / 118); backward of 2000
+// tokens, 4/2 heads, d = 64 35 / 14, of 8192 tokens 315 / 75 (4/1 heads: 730 / 268; d = 128: 424 / 111 and 952 / 378).
+// Four waves instead of eight: up to 25 % faster where the chip is full, 30-40 % slower where it is not; at d = 128, two such
+// workgroups to a compute unit where there are more than units, 0.6 to 1.2 times as fast.
 // =====================================================================================
 constexpr int kSplitRows = 32, kSplitWaves = 8;
 
