@@ -75,8 +75,8 @@ enum {
                                     backward's seven executed contractions for that much HBM traffic each way.  Set it
                                     before fcp_workspace_bytes / fcp_queue_build and keep it for every call on the
                                     workspace.  Shares whose dS does not fit in memory leave it unset.
-                                    At head_dim 64 fcp_block_attn_bwd recomputes all the same where that is faster (rows that
-                                    see about 80 columns and more) and then leaves no dS; the stage calls do as the flag says. */
+                                    At head_dim 64 the backward without the flag is the faster one where rows see about 80
+                                    columns and more, and needs none of that memory. */
   FCP_FLAG_RUNNING_MERGE = 32,   /* fcp_block_attn_fwd_out folds the result of every slot into the running (o, lse) in place instead of
                                     writing a partial: (O, LSE) <- merge((O, LSE), slot result), the two-way form of the reduction that
                                     fcp_merge_partials does in one go.  One launch handles ONE stage: the problem may hold at most one
@@ -330,8 +330,8 @@ int fcp_block_attn_bwd_dq_d(const fcp_problem* p, const void* q, const void* k, 
  * have run on the same workspace with the flag set (same stream, or ordered after it).  k: device bf16 [T_kv,Hkv,d];
  * dq: device [T_q,Hq,d] fp32 (bf16 with FCP_FLAG_GRAD_BF16), fully overwritten, one writer per row.
  * Errors: FCP_ERR_INVALID_ARG when the flag is not set or a pointer is NULL; otherwise as fcp_block_attn_bwd.
- * With the flag, fcp_block_attn_bwd = fcp_bwd_preprocess, fcp_block_attn_bwd_dkdv, then this call (head_dim 64: or what it is
- * without the flag, see there).
+ * With the flag, fcp_block_attn_bwd = fcp_bwd_preprocess, fcp_block_attn_bwd_dkdv, then this call, bit for bit: the dS that it
+ * leaves in the workspace serves this call as well.
  */
 int fcp_block_attn_bwd_dq_ds(const fcp_problem* p, const void* k, void* dq, void* workspace, void* stream);
 

@@ -438,11 +438,6 @@ struct LaunchLoad {
 void choose_split(const fcp_problem* p, bool forward_only, WsLayout* L) {
   const LaunchCost* cost = kLaunchCost[p->head_dim == 128];
   const int G = p->n_q_heads / p->n_kv_heads, heads = G % 2 == 0 ? p->n_q_heads / 2 : p->n_q_heads, rows_of_item = item_rows(p);
-  // At d = 64 the round trip of dS costs more than recomputing S and dP (2 d FLOPs for 2 bytes are half of what they are at d = 128),
-  // unless the rows see so little that the recomputing kernel's start of an item counts.  Backward, us, dS kept / recomputed: 16384
-  // tokens in 256-2048, 16 heads, full 503 / 416; 65536 lognormal, 9/3 heads 1548 / 1350; sequences of 16-256, 32/8 heads (2.8 tiles of 32
-  // columns a row) 808 / 785, of 16-64 (1.3 tiles) 1007 / 1272; d = 128: 7134 / 7296, 1207 / 1251.
-  L->recompute = p->head_dim == 64 && !forward_only && 2 * (L->n_ds_frags - kDsSinkFrags) >= 5 * ceil_div(L->t_q, 32) * p->n_q_heads;
   const bool query = L->n_fwd_items <= kSplitMaxItems || (!forward_only && L->n_dq_items <= kSplitMaxItems), keys = !forward_only && L->n_bwd_items <= kSplitMaxItems;
   if (!query && !keys) return;
   LaunchLoad fwd, dq, dkdv;

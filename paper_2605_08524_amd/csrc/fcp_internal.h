@@ -95,7 +95,6 @@ struct WsLayout {
   // choose_split: which launches go to the split kernels, and the 32-row units that an item has there at most (of a sub-tile)
   bool split_fwd, split_dq, split_dkdv;
   int split_q_units, split_q_per_tile, split_kv_units;
-  bool recompute;   // FCP_FLAG_BWD_SPILL_DS: fcp_block_attn_bwd recomputes S and dP for dQ all the same, because that is faster
   int64_t n_ds_frags;   // fragments of the dS spill buffer, sinks and one fragment of slack included (0 without the flag)
   size_t off_pairs, off_spans, off_fwd_items, off_q_seg, off_bwd_deps, off_bwd_items, off_merge_items, off_slot_rh, off_dq_items, off_dls, off_lse2, off_ds, total;
 };

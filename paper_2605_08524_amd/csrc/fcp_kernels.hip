@@ -2898,28 +2898,24 @@ static auto dkdv_instance(bool d128, bool gb, bool spill) -> void (*)(BwdArgs) {
                : (gb ? dkdv_kernel<64, true, false, J> : dkdv_kernel<64, false, false, J>);
 }
 
-static int launch_dkdv(const char* who, const fcp_problem* p, const void* q, const void* k, const void* v,
-                       const void* d_o, void* dk, void* dv, bool spill, void* workspace, void* stream) {
+extern "C" int fcp_block_attn_bwd_dkdv(const fcp_problem* p, const void* q, const void* k, const void* v,
+                                       const void* d_o, void* dk, void* dv, void* workspace, void* stream) {
   WsLayout L;
   BwdArgs a;
   int rc = fill_bwd_args(p, &L, &a, workspace);
   if (rc) return rc;
   if (L.n_bwd_items == 0) return FCP_OK;
-  if (!q || !k || !v || !d_o || !dk || !dv || !workspace) { set_error("%s: NULL pointer", who); return FCP_ERR_INVALID_ARG; }
+  if (!q || !k || !v || !d_o || !dk || !dv || !workspace) { set_error("fcp_block_attn_bwd_dkdv: NULL pointer"); return FCP_ERR_INVALID_ARG; }
   a.q = (const uint16_t*)q; a.k = (const uint16_t*)k; a.v = (const uint16_t*)v; a.d_o = (const uint16_t*)d_o;
   a.dk = dk; a.dv = dv;
   int grid = (int)std::min<int64_t>(L.n_bwd_items, (int64_t)cu_count() * kDkdvWgPerCu);
   const bool gb = (p->flags & FCP_FLAG_GRAD_BF16) != 0, d128 = p->head_dim == 128;
+  const bool spill = (p->flags & FCP_FLAG_BWD_SPILL_DS) != 0;
   if (spill) a.ds = static_cast<unsigned char*>(workspace) + L.off_ds;
-  if (L.split_dkdv) return launch_bwd_split(who, p, L, a, true, false, false, stream);
+  if (L.split_dkdv) return launch_bwd_split("fcp_block_attn_bwd_dkdv", p, L, a, true, false, false, stream);
   void (*kern)(BwdArgs) = p->n_segments > 0 ? dkdv_instance<true>(d128, gb, spill) : dkdv_instance<false>(d128, gb, spill);
   hipLaunchKernelGGL(kern, dim3(grid), dim3(512), 0, (hipStream_t)stream, a);
-  return check_launch(who);
-}
-
-extern "C" int fcp_block_attn_bwd_dkdv(const fcp_problem* p, const void* q, const void* k, const void* v,
-                                       const void* d_o, void* dk, void* dv, void* workspace, void* stream) {
-  return launch_dkdv("fcp_block_attn_bwd_dkdv", p, q, k, v, d_o, dk, dv, p && (p->flags & FCP_FLAG_BWD_SPILL_DS), workspace, stream);
+  return check_launch("fcp_block_attn_bwd_dkdv");
 }
 
 // o / lse == NULL: the per-row scalars come from fcp_bwd_preprocess; else the kernel computes and publishes them.
@@ -3007,7 +3003,7 @@ extern "C" int fcp_block_attn_bwd(const fcp_problem* p, const void* q, const voi
   WsLayout L;
   BwdArgs a;
   if (int rc = fill_bwd_args(p, &L, &a, workspace)) return rc;
-  if ((p->flags & FCP_FLAG_BWD_SPILL_DS) && !L.recompute) {
+  if (p->flags & FCP_FLAG_BWD_SPILL_DS) {
     // D first (a pass of its own), then dK/dV, which also writes dS, then dQ from that dS
     int rc = fcp_bwd_preprocess(p, o, lse, d_o, workspace, stream);
     if (rc) return rc;
@@ -3025,6 +3021,6 @@ extern "C" int fcp_block_attn_bwd(const fcp_problem* p, const void* q, const voi
   // dQ first: its kernel also leaves the per-row scalars (D * scale, LSE * log2 e) that dK/dV needs
   int rc = fcp_block_attn_bwd_dq_d(p, q, k, v, o, lse, d_o, dq, workspace, stream);
   if (rc) return rc;
-  return launch_dkdv("fcp_block_attn_bwd", p, q, k, v, d_o, dk, dv, false, workspace, stream);
+  return fcp_block_attn_bwd_dkdv(p, q, k, v, d_o, dk, dv, workspace, stream);
 }
 
