@@ -14,6 +14,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "fcp.h"
+
 #ifdef __cplusplus
 extern "C" {
 #endif
@@ -64,6 +66,16 @@ int fcp_lds_probe(int32_t mode, int32_t n_waves, int32_t iters, const void* src,
  * (n_rows >= 2048, row_stride >= 256), accumulated into.
  */
 int fcp_atomic_probe(float* buf, int64_t n_rows, int32_t row_stride, int32_t iters, int32_t workgroups_per_cu, void* stream);
+
+/*
+ * fcp_launch_probe -- which kernels the launches of a problem take (host, integer only).
+ * info[0..2]: 1 where the forward / dQ (recomputing) / dK, dV kernel is the split one (32 rows a workgroup, a chain over its waves).
+ * info[3..5]: work items of the forward / dQ / dK, dV.
+ * info[6], [7]: 0.
+ * info[8..15]: KV tiles in each of the eight queue ranges of the dQ items (0 with forward_only).
+ * forward_only: as fcp_block_attn_fwd_static lays the problem out, else as fcp_queue_build does.
+ */
+int fcp_launch_probe(const fcp_problem* p, int32_t forward_only, int32_t info[16]);
 
 #ifdef __cplusplus
 }

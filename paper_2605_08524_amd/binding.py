@@ -35,7 +35,7 @@ EXPORTS = (
     "fcp_plan_blocks", "fcp_plan_blocks_packed", "fcp_stage_tables", "fcp_workspace_bytes", "fcp_queue_build", "fcp_block_attn_fwd", "fcp_block_attn_fwd_out",
     "fcp_merge_partials", "fcp_block_attn_bwd", "fcp_bwd_preprocess", "fcp_block_attn_bwd_dkdv", "fcp_block_attn_bwd_dq",
     "fcp_block_attn_bwd_dq_d", "fcp_block_attn_bwd_dq_ds", "fcp_block_attn_fwd_static",
-    "fcp_last_error", "fcp_device_info", "fcp_mfma_probe", "fcp_mfma_valu_probe", "fcp_lds_probe", "fcp_atomic_probe",
+    "fcp_last_error", "fcp_device_info", "fcp_mfma_probe", "fcp_mfma_valu_probe", "fcp_lds_probe", "fcp_atomic_probe", "fcp_launch_probe",
     "fcp_block_costs", "fcp_assign_blocks", "fcp_worker_blocks", "fcp_comm_edges", "fcp_solve_matchings",
     "fcp_coalesce_stages", "fcp_pack_units",
 )
@@ -103,6 +103,7 @@ def _load():
     lib.fcp_device_info.argtypes = [i32p, i32p, i32p]
     lib.fcp_mfma_probe.argtypes = [C.c_int32, C.c_int32, C.c_void_p, C.c_void_p]
     lib.fcp_mfma_valu_probe.argtypes = [C.c_int32, C.c_int32, C.c_int32, C.c_void_p, C.c_void_p]
+    lib.fcp_launch_probe.argtypes = [C.POINTER(_Problem), C.c_int32, i32p]
     lib.fcp_lds_probe.argtypes = [C.c_int32, C.c_int32, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p]
     lib.fcp_atomic_probe.argtypes = [C.c_void_p, C.c_int64, C.c_int32, C.c_int32, C.c_int32, C.c_void_p]
     for name in EXPORTS:
@@ -300,6 +301,12 @@ def fcp_mfma_probe(operand_kind: int, iters: int, out, stream=None):
 
 def fcp_mfma_valu_probe(operand_kind: int, valu_per_mfma: int, iters: int, out, stream=None):
     _check(_lib.fcp_mfma_valu_probe(int(operand_kind), int(valu_per_mfma), int(iters), _ptr(out), _stream(stream)))
+
+
+def fcp_launch_probe(problem: Problem, forward_only: bool = False) -> dict:
+    info = (C.c_int32 * 16)()
+    _check(_lib.fcp_launch_probe(problem.ref, int(forward_only), info))
+    return {"split": tuple(bool(x) for x in info[0:3]), "items": tuple(info[3:6]), "dq_queue_tiles": tuple(info[8:16])}
 
 
 def fcp_lds_probe(mode: int, n_waves: int, iters: int, src, out, stream=None):

@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "fcp_internal.h"
+#include "fcp_probe.h"
 
 namespace fcp {
 
@@ -1116,5 +1117,28 @@ extern "C" int fcp_queue_build(const fcp_problem* p, void* workspace, size_t wor
   if (e == hipSuccess) e = hipStreamSynchronize((hipStream_t)stream);
   if (e != hipSuccess) { set_error("fcp_queue_build: %s", hipGetErrorString(e)); return FCP_ERR_HIP; }
   remember_layout(p, workspace, L);
+  return FCP_OK;
+}
+
+extern "C" int fcp_launch_probe(const fcp_problem* p, int32_t forward_only, int32_t info[16]) {
+  if (!info) { set_error("fcp_launch_probe: info is NULL"); return FCP_ERR_INVALID_ARG; }
+  int rc = validate_problem(p);
+  if (rc) return rc;
+  WsLayout L;
+  rc = compute_layout(p, forward_only != 0, &L);
+  if (rc) return rc;
+  choose_split(p, forward_only != 0, &L);
+  const int32_t head[8] = {L.split_fwd, L.split_dq, L.split_dkdv, (int32_t)L.n_fwd_items, (int32_t)L.n_dq_items, (int32_t)L.n_bwd_items, 0, 0};
+  std::fill(std::copy(head, head + 8, info), info + 16, 0);
+  if (forward_only) return FCP_OK;
+  Expanded x;
+  expand_problem(p, false, &x);
+  std::vector<unsigned char> image;
+  rc = build_queue_image(p, x, L, false, &image);
+  if (rc) return rc;
+  const WsHeader* hdr = reinterpret_cast<const WsHeader*>(image.data());
+  const QItem* items = reinterpret_cast<const QItem*>(image.data() + L.off_dq_items);
+  for (int q = 0; q < kNumXcd; q++)
+    for (int32_t i = hdr->dq_begin[q]; i < hdr->dq_begin[q + 1]; i++) info[8 + q] += items[i].n_tiles;
   return FCP_OK;
 }
