@@ -84,8 +84,7 @@ enum {
                                     stages go to one stream, and before the first one the caller fills lse with -inf (o is then
                                     ignored).  Needs FCP_FLAG_O_F32; the partial buffers are not touched and may be NULL; no merge call
                                     follows.  The worker then holds no partials at all, at the price of reading and writing the
-                                    running result once per stage.  Agrees with the one-pass result to fp32 rounding, or, where slots
-                                    of 4096 columns and more are few, to the rounding of P. */
+                                    running result once per stage.  Agrees with the one-pass result to fp32 rounding. */
   FCP_FLAG_DIRECT_SINGLE = 2     /* a query block with ONE slot needs no reduction: fcp_block_attn_fwd_out writes its
                                     result straight to the final o / lse and fcp_merge_partials leaves it alone.
                                     Set it before fcp_workspace_bytes / fcp_queue_build and keep it for every call

@@ -416,7 +416,6 @@ constexpr LaunchCost kLaunchCost[2][3] = {      // [d = 128][forward, dQ, dK/dV]
     {{5.0, 0.93, 4.5, 5.2, 1.14, 10.7, 0.095}, {6.8, 1.25, 3.4, 4.9, 1.46, 12.8, 0.127}, {6.4, 0.538, 5.8, 5.1, 0.470, 5.8, 0.143}},
     {{6.6, 1.25, 5.8, 4.7, 2.48, 32.5, 0.141}, {7.2, 1.83, 8.5, 4.4, 3.24, 38.8, 0.209}, {7.2, 0.703, 10.0, 4.6, 0.948, 25.7, 0.194}}};
 constexpr double kSplitGain = 1.15;      // split only what gains clearly: every shape that the fit gives 1.11 and more did gain, 3 % at least
-constexpr int kSplitLongSlot = 64;       // tiles (4096 columns)
 constexpr int kSplitMaxItems = 512;      // two to a compute unit: the fits reach no further, and walking larger tables would cost
 
 // The items of one kernel: tiles (steps) of the longest, of all; `units`: their 32-row units as fractions of a full item's.
@@ -482,12 +481,10 @@ void choose_split(const fcp_problem* p, bool forward_only, WsLayout* L) {
     }
   });
   L->split_fwd = L->n_fwd_items > 0 && L->n_fwd_items <= kSplitMaxItems && fwd.split(cost[0]);
-  if (!complete && fwd.longest < kSplitLongSlot) {
+  if (!complete) {
     // The two kernels round P to bf16 against different references, so the stages of a plan and its one-pass forward agree to fp32
-    // rounding only where all of them take the same one.  With shorter slots they do: by what they have in common, the blocks (with
-    // longer ones too much is at stake: 2048 rows of a 65536-token sequence, 4 heads, d = 64, slots of 16384 columns 257 us, split 119; a
-    // stage and the one-pass forward may then differ by the rounding of P).  Units if every KV block of a query block's sequence were a slot of its own; at 2.5 (1) units to a compute
-    // unit a launch of the shortest slots takes what a whole one does.
+    // rounding only where all of them take the same one.  What they have in common are the blocks: units if every KV block of a query
+    // block's sequence were a slot of its own.  At 2.5 (1) units to a compute unit a launch of the shortest slots takes what a whole one does.
     std::unordered_map<int32_t, int64_t> blocks_of;
     for (int i = 0; i < p->n_kv_blocks; i++) blocks_of[p->kv_blocks[i].seq]++;
     int64_t units = 0;

@@ -24,3 +24,18 @@ def test_few_long_chains_are_split_and_full_launches_are_not():
 def test_probe_validates():
     with pytest.raises(fcp.FcpError):
         fcp.fcp_launch_probe(_problem([100], 64, 1, 0, 4, 4, 96))
+
+
+def _forward_choices(lens, bs, causal, c, hq, hkv, d, owned=None):
+    """The forward's kernel of the one pass and of every stage of a plan."""
+    plan = fcp.fcp_plan_blocks(lens, bs, causal, c, None if owned is None else np.asarray(owned, dtype=np.int32))
+    tables = [plan] + [fcp.fcp_stage_tables(plan, k)[0] for k in range(fcp.fcp_stage_tables(plan, 0)[1])]
+    return [fcp.fcp_launch_probe(fcp.Problem(t, hq, hkv, d, bs, 0.0, F32))["split"][0] for t in tables]
+
+
+@pytest.mark.parametrize("case", [([65536], 1024, 1, 16, 4, 4, 64, [(0, 62), (0, 63)]), ([65536], 1024, 1, 16, 4, 4, 128, [(0, 62), (0, 63)]),
+                                  ([20000], 1024, 1, 5, 1, 1, 64, None), ([9000, 5000], 512, 0, 9, 2, 1, 128, None)])
+def test_stages_of_long_slots_take_the_kernel_of_the_one_pass(case):
+    """The two kernels round P against different references: only where all launches take the same one does a running result agree
+    with the one-pass forward to fp32 rounding."""
+    assert len(set(_forward_choices(*case))) == 1
