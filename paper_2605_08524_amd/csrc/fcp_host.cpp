@@ -435,14 +435,48 @@ struct LaunchLoad {
 
 }  // namespace
 
+namespace {
+
+// Every slot holds all KV blocks that its rows see: no query block's result is merged from several.
+bool slots_complete(const fcp_problem* p) {
+  auto seq_of = [&](int kv_blk) { return kv_blk >= 0 && kv_blk < p->n_kv_blocks ? p->kv_blocks[kv_blk].seq : -1; };
+  for (int s = 0; s < p->n_slots; s++) {
+    const fcp_slot& sl = p->slots[s];
+    if (sl.n_pairs == 0) continue;
+    const fcp_pair &first = p->pairs[sl.pair_begin], &last = p->pairs[sl.pair_begin + sl.n_pairs - 1];
+    if (seq_of(first.kv_blk - 1) == seq_of(first.kv_blk) || (!(last.kind & 1) && seq_of(last.kv_blk + 1) == seq_of(last.kv_blk))) return false;
+  }
+  return true;
+}
+
+// 32-row units of the forward if every KV block of a query block's sequence were a slot of its own.
+int64_t units_by_blocks(const fcp_problem* p) {
+  std::unordered_map<int32_t, int64_t> blocks_of;
+  for (int i = 0; i < p->n_kv_blocks; i++) blocks_of[p->kv_blocks[i].seq]++;
+  int64_t units = 0;
+  for (int b = 0; b < p->n_q_blocks; b++) units += ceil_div(p->q_blocks[b].tok_len, 32) * p->n_q_heads * blocks_of[p->q_blocks[b].seq];
+  return units;
+}
+
+}  // namespace
+
 void choose_split(const fcp_problem* p, bool forward_only, WsLayout* L) {
   const LaunchCost* cost = kLaunchCost[p->head_dim == 128];
   const int G = p->n_q_heads / p->n_kv_heads, heads = G % 2 == 0 ? p->n_q_heads / 2 : p->n_q_heads, rows_of_item = item_rows(p);
-  const bool query = L->n_fwd_items <= kSplitMaxItems || (!forward_only && L->n_dq_items <= kSplitMaxItems), keys = !forward_only && L->n_bwd_items <= kSplitMaxItems;
-  if (!query && !keys) return;
+  // The forward is chosen from its own tables alone, so that fcp_block_attn_fwd_static and a workspace choose alike.  Partial slots go
+  // further: the two kernels round P to bf16 against different references, so the stages of a plan and its one-pass forward agree to fp32
+  // rounding only where all of them take the same one.  What they have in common are the blocks, not the items of one launch.  At 2.5 (1)
+  // units to a compute unit a launch of the shortest slots takes what a whole one does.
+  const int64_t most_units = p->head_dim == 128 ? 256 : 640;
+  const bool few_fwd = L->n_fwd_items > 0 && L->n_fwd_items <= kSplitMaxItems;
+  bool fit_fwd = false;
+  if (L->n_fwd_items > 0 && (few_fwd || ceil_div(L->t_q * p->n_q_heads, 32) <= most_units)) {       // else the choice is neither's
+    if (!slots_complete(p)) L->split_fwd = units_by_blocks(p) <= most_units;
+    else fit_fwd = few_fwd;
+  }
+  const bool query = !forward_only && L->n_dq_items <= kSplitMaxItems, keys = !forward_only && L->n_bwd_items <= kSplitMaxItems;
+  if (!L->split_fwd && !fit_fwd && !query && !keys) return;
   LaunchLoad fwd, dq, dkdv;
-  bool complete = true;      // every slot holds all KV blocks that its rows see
-  auto seq_of = [&](int kv_blk) { return kv_blk >= 0 && kv_blk < p->n_kv_blocks ? p->kv_blocks[kv_blk].seq : -1; };
   const Runs runs = make_runs(p);
   std::vector<int64_t> steps(keys ? runs.run.size() : 0, 0);     // of a KV segment's dependencies that it sees in full
   std::vector<char> diag(keys ? runs.run.size() : 0, 0);         // it has one that it sees from its own rows on
@@ -463,10 +497,6 @@ void choose_split(const fcp_problem* p, bool forward_only, WsLayout* L) {
         const fcp_slot& sl = p->slots[s];
         const bool whole = packed && !packed_slot(p, sl);
         int64_t full = 0, diag_cols = 0;
-        if (sl.n_pairs > 0) {
-          const fcp_pair &first = p->pairs[sl.pair_begin], &last = p->pairs[sl.pair_begin + sl.n_pairs - 1];
-          if (seq_of(first.kv_blk - 1) == seq_of(first.kv_blk) || (!(last.kind & 1) && seq_of(last.kv_blk + 1) == seq_of(last.kv_blk))) complete = false;
-        }
         for (int i = sl.pair_begin; i < sl.pair_begin + sl.n_pairs; i++) {
           const fcp_pair& pr = p->pairs[i];
           const int seg = runs.begin[pr.kv_blk] + ((pr.kind & 2) ? m : 0);
@@ -480,17 +510,7 @@ void choose_split(const fcp_problem* p, bool forward_only, WsLayout* L) {
       segment(&dq, dq_full, dq_diag, run[m].len);
     }
   });
-  L->split_fwd = L->n_fwd_items > 0 && L->n_fwd_items <= kSplitMaxItems && fwd.split(cost[0]);
-  if (!complete) {
-    // The two kernels round P to bf16 against different references, so the stages of a plan and its one-pass forward agree to fp32
-    // rounding only where all of them take the same one.  What they have in common are the blocks: units if every KV block of a query
-    // block's sequence were a slot of its own.  At 2.5 (1) units to a compute unit a launch of the shortest slots takes what a whole one does.
-    std::unordered_map<int32_t, int64_t> blocks_of;
-    for (int i = 0; i < p->n_kv_blocks; i++) blocks_of[p->kv_blocks[i].seq]++;
-    int64_t units = 0;
-    for (int b = 0; b < p->n_q_blocks; b++) units += ceil_div(p->q_blocks[b].tok_len, 32) * p->n_q_heads * blocks_of[p->q_blocks[b].seq];
-    L->split_fwd = L->n_fwd_items > 0 && units <= (p->head_dim == 128 ? 256 : 640);
-  }
+  if (fit_fwd) L->split_fwd = fwd.split(cost[0]);
   L->split_dq = !forward_only && L->n_dq_items > 0 && L->n_dq_items <= kSplitMaxItems && dq.split(cost[1]);
   L->split_q_per_tile = (int)ceil_div(std::min(max_q, kFwdTileM), 32);
   L->split_q_units = L->split_q_per_tile * (G % 2 == 0 || max_q > kFwdTileM ? 2 : 1);

@@ -1100,3 +1100,19 @@ def test_row_tiles_of_at_most_64_rows_take_four_heads(hq, hkv, d, flags, packed)
             ref = orc.worker_bwd(wl.q(), wl.k(), wl.v(), wl.d_o(), wl.seq_lens, wl.block_size, wl.causal)
             for name, r in zip(("dq", "dk", "dv"), ref):
                 _check(name, res[name], r, tol_abs=TOL_ABS * (1.0 if name == "dq" else np.sqrt(2.0)))
+
+
+@pytest.mark.parametrize("case", [([800], 32, 0, 1, 1, 1, 64, None), ([1280], 32, 1, 1, 16, 16, 64, [(0, 39)]), ([1100, 300], 128, 1, 2, 4, 2, 128, None)])
+def test_forward_without_a_workspace_is_bit_equal_whatever_the_backward_has(case):
+    """625 and 640 forward items beside few of dQ; a small problem."""
+    from paper_2605_08524_amd import binding as B
+    from paper_2605_08524_amd.harness import DevicePath
+    lens, bs, causal, c, hq, hkv, d, owned = case
+    wl = workloads.custom_workload(lens, bs, causal, c, hq, hkv, d, q_owned=None if owned is None else np.asarray(owned, dtype=np.int32), seed=83, name="static")
+    dev = torch.device("cuda:0")
+    dp = DevicePath(wl, dev, flags=F32)
+    dp.fwd()
+    o, lse = torch.full_like(dp.o_part, float("nan")), torch.full_like(dp.lse_part, float("nan"))
+    B.fcp_block_attn_fwd_static(dp.problem, dp.q, dp.k, dp.v, o, lse, dp.stream)
+    torch.cuda.synchronize(dev)
+    assert torch.equal(o, dp.o_part) and torch.equal(lse, dp.lse_part)

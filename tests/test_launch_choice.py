@@ -39,3 +39,34 @@ def test_stages_of_long_slots_take_the_kernel_of_the_one_pass(case):
     """The two kernels round P against different references: only where all launches take the same one does a running result agree
     with the one-pass forward to fp32 rounding."""
     assert len(set(_forward_choices(*case))) == 1
+
+
+def test_forward_without_a_workspace_takes_the_kernel_of_the_one_with():
+    """fcp_block_attn_fwd_static gives the bits of fcp_queue_build + fcp_block_attn_fwd: many forward items beside few dQ or dK/dV items, and
+    the other way round."""
+    cases = [([800], 32, 0, 1, 1, 1, 64, None), ([1280], 32, 1, 1, 16, 16, 64, [(0, 39)]), ([640], 32, 1, 1, 32, 32, 64, [(0, 19)]),
+             ([1280], 32, 1, 1, 15, 5, 64, [(0, 39)])]
+    rng = np.random.default_rng(5)
+    for _ in range(150):
+        g = int(rng.choice([1, 2, 3, 4]))
+        hkv = int(rng.choice([1, 2, 5, 16]))
+        lens = [int(n) for n in rng.integers(1, 3000, size=rng.integers(1, 8))]
+        bs = int(rng.choice([32, 100, 128, 512]))
+        owned = None
+        if rng.random() < 0.5:
+            blocks = [(s, i) for s, n in enumerate(lens) for i in range(-(-n // bs))]
+            owned = [b for b in blocks if rng.random() < 0.2] or [blocks[-1]]
+        cases.append((lens, bs, int(rng.integers(0, 2)), int(rng.choice([0, 1, 2, 7])), g * hkv, hkv, int(rng.choice([64, 128])), owned))
+    chosen = []
+    for case in cases:
+        p = _problem(*case)
+        with_ws, without = (fcp.fcp_launch_probe(p, forward_only)["split"][0] for forward_only in (False, True))
+        assert with_ws == without, case
+        chosen.append(with_ws)
+    assert 10 < sum(chosen) < len(chosen) - 10      # both kernels were chosen
+
+
+@pytest.mark.parametrize("case", [([32] * 560 + [64], 32, 1, 1, 1, 1, 64), ([32] * 540 + [512], 256, 1, 1, 1, 1, 64), ([200] * 80 + [512], 256, 1, 1, 1, 1, 64)])
+def test_stages_of_many_items_take_the_kernel_of_the_one_pass(case):
+    """More than 512 items in the one pass and the first stage, one in the second."""
+    assert len(set(_forward_choices(*case))) == 1
