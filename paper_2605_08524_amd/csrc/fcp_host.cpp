@@ -483,8 +483,8 @@ void choose_split(const fcp_problem* p, bool forward_only, WsLayout* L) {
   int max_q = 0, max_kv = 0;
   auto segment = [&](LaunchLoad* l, int64_t full, int64_t diag_cols, int len) {
     max_q = std::max(max_q, len);
-    for (int row = 0; row < len; row += rows_of_item) {
-      const int n = std::min(rows_of_item, len - row);
+    for (int64_t row = 0; row < len; row += rows_of_item) {          // len: up to 2^31 - 1
+      const int n = (int)std::min<int64_t>(rows_of_item, len - row);
       const int64_t tiles = ceil_div(full + std::min<int64_t>(diag_cols, row + n), kQTileN);
       const int four = four_heads(p, n) ? 2 : 1;
       l->add(tiles, heads / four, (double)ceil_div(n, 32) * 32 * four / rows_of_item);
@@ -519,8 +519,8 @@ void choose_split(const fcp_problem* p, bool forward_only, WsLayout* L) {
     L->split_q_units = max_q > kFwdTileM / 2 ? 8 : 4 * L->split_q_per_tile;
   }
   for (size_t k = 0; k < steps.size(); k++)
-    for (int off = 0, len = runs.run[k].len; off < len; off += kBwdTileN) {
-      const int n = std::min(kBwdTileN, len - off);
+    for (int64_t off = 0, len = runs.run[k].len; off < len; off += kBwdTileN) {
+      const int n = (int)std::min<int64_t>(kBwdTileN, len - off);
       max_kv = std::max(max_kv, n);
       dkdv.add(steps[k] + (diag[k] ? ceil_div(len - off, 32) * G : 0), p->n_kv_heads, (double)ceil_div(n, 32) * 32 / kBwdTileN);
     }

@@ -1,4 +1,8 @@
 """Which kernels the launches of a problem take (fcp_launch_probe): host integer work, no GPU."""
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 
@@ -70,3 +74,25 @@ def test_forward_without_a_workspace_takes_the_kernel_of_the_one_with():
 def test_stages_of_many_items_take_the_kernel_of_the_one_pass(case):
     """More than 512 items in the one pass and the first stage, one in the second."""
     assert len(set(_forward_choices(*case))) == 1
+
+
+def test_a_block_of_all_rows_that_32_bits_hold():
+    """2^31 - 1 query rows beside one KV block: the walk over their items must end (it is the host's, before the NULL pointers are looked at)."""
+    code = """
+import os
+import subprocess
+import sys
+
+import numpy as np
+import paper_2605_08524_amd as fcp
+n = 2**31 - 1
+t = lambda *row: np.array([row], dtype=np.int32)
+plan = dict(kv_blocks=t(0, 0, 0, 64), q_blocks=t(0, 0, 0, n), pairs=t(0, 0, 0, 0), slots=t(0, 0, 1, 0), n_slot_rows=n)
+try:
+    fcp.fcp_bwd_preprocess(fcp.Problem(plan, 1, 1, 64, n, 0.0, 1), None, None, None, None)
+except fcp.FcpError as e:
+    assert "NULL pointer" in str(e)
+    print("refused")
+"""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    assert subprocess.run([sys.executable, "-c", code], cwd=root, timeout=60, capture_output=True, text=True).stdout == "refused\n"
