@@ -468,11 +468,11 @@ void choose_split(const fcp_problem* p, bool forward_only, WsLayout* L) {
   // rounding only where all of them take the same one.  What they have in common are the blocks, not the items of one launch.  At 2.5 (1)
   // units to a compute unit a launch of the shortest slots takes what a whole one does.
   const int64_t most_units = p->head_dim == 128 ? 256 : 640;
-  const bool few_fwd = L->n_fwd_items > 0 && L->n_fwd_items <= kSplitMaxItems;
   bool fit_fwd = false;
-  if (L->n_fwd_items > 0 && (few_fwd || ceil_div(L->t_q * p->n_q_heads, 32) <= most_units)) {       // else the choice is neither's
-    if (!slots_complete(p)) L->split_fwd = units_by_blocks(p) <= most_units;
-    else fit_fwd = few_fwd;
+  if (L->n_fwd_items > 0 && L->n_fwd_items <= std::max<int64_t>(kSplitMaxItems, most_units)) {
+    // a planned block has no more slots than its sequence has KV blocks, so items are no more than units; others may have any number
+    if (!slots_complete(p)) L->split_fwd = L->n_fwd_items <= most_units && units_by_blocks(p) <= most_units;
+    else fit_fwd = L->n_fwd_items <= kSplitMaxItems;
   }
   const bool query = !forward_only && L->n_dq_items <= kSplitMaxItems, keys = !forward_only && L->n_bwd_items <= kSplitMaxItems;
   if (!L->split_fwd && !fit_fwd && !query && !keys) return;

@@ -96,3 +96,14 @@ except fcp.FcpError as e:
 """
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     assert subprocess.run([sys.executable, "-c", code], cwd=root, timeout=60, capture_output=True, text=True).stdout == "refused\n"
+
+
+def test_slots_beyond_the_kv_blocks_do_not_grow_a_split_launch():
+    """Two slots of one KV block each and any number without pairs: the split forward's grid is items times units."""
+    def info(n_empty):
+        slots = np.array([[0, 0, 1, 0], [0, 1, 1, 64]] + [[0, 2, 0, 128]] * n_empty, dtype=np.int32)
+        plan = dict(kv_blocks=np.array([[0, 0, 0, 64], [0, 1, 64, 64]], dtype=np.int32), q_blocks=np.array([[0, 1, 0, 64]], dtype=np.int32),
+                    pairs=np.array([[0, 0, 0, 0], [0, 1, 1, 1]], dtype=np.int32), slots=slots, n_slot_rows=192)
+        return fcp.fcp_launch_probe(fcp.Problem(plan, 2, 2, 64, 64, 0.0, F32))
+    assert info(1)["split"][0]
+    assert info(1000)["items"][0] == 2004 and not info(1000)["split"][0]
