@@ -1046,8 +1046,8 @@ int fcp::build_queue_image(const fcp_problem* p, const Expanded& x, const WsLayo
     set_error("internal: forward item count mismatch"); return FCP_ERR_INVALID_ARG;
   }
   if (forward_only) return FCP_OK;
-  // ---- dQ: query-stationary items over all pairs of a query segment
-  if (!q_items(p, x.dq, x.pairs, false, L.split_dq, L.n_dq_items, reinterpret_cast<QItem*>(host.data() + L.off_dq_items), hdr->dq_begin)) {
+  // ---- dQ: query-stationary items over all pairs of a query segment; with dS kept dq_ds_kernel draws them from the queues, whatever dQ alone would take
+  if (!q_items(p, x.dq, x.pairs, false, L.split_dq && !(p->flags & FCP_FLAG_BWD_SPILL_DS), L.n_dq_items, reinterpret_cast<QItem*>(host.data() + L.off_dq_items), hdr->dq_begin)) {
     set_error("internal: dQ item count mismatch"); return FCP_ERR_INVALID_ARG;
   }
   // ---- dK / dV: dependency lists per KV segment, one group per (KV segment, KV head)

@@ -107,3 +107,15 @@ def test_slots_beyond_the_kv_blocks_do_not_grow_a_split_launch():
         return fcp.fcp_launch_probe(fcp.Problem(plan, 2, 2, 64, 64, 0.0, F32))
     assert info(1)["split"][0]
     assert info(1000)["items"][0] == 2004 and not info(1000)["split"][0]
+
+
+@pytest.mark.parametrize("lens,hq,hkv,d", [([900, 50, 1300, 333], 8, 2, 128), ([4096], 8, 8, 128), ([4096], 8, 8, 64)])
+def test_dq_from_ds_keeps_the_queue_order(lens, hq, hkv, d):
+    """With dS kept the dQ items are drawn from eight queues, which have to hold the same work; without it the split dQ, which has no
+    queues, takes the longest chains first."""
+    spill = fcp.fcp_launch_probe(_problem(lens, 1024, 1, 0, hq, hkv, d, flags=F32 | fcp.FCP_FLAG_BWD_SPILL_DS))
+    plain = fcp.fcp_launch_probe(_problem(lens, 1024, 1, 0, hq, hkv, d))
+    assert plain["split"][1] and plain["dq_queue_tiles"][0] == max(plain["dq_queue_tiles"])
+    tiles, total = spill["dq_queue_tiles"], sum(plain["dq_queue_tiles"])
+    assert sum(tiles) == total
+    assert max(tiles) <= total / 4 and max(tiles) < 0.6 * plain["dq_queue_tiles"][0]
