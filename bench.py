@@ -29,16 +29,6 @@ PEAK_HBM_GBS = 8000.0
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "cfg5_training_step_hbm_traffic.txt")
 
 
-def forward_items(plan, wl):
-    """Work items of the forward kernel: a 128-row tile of two heads (a tile of at most 64 rows: of four), of one head where the group is odd."""
-    group, items = wl.n_q_heads // wl.n_kv_heads, 0
-    for qb in plan["slots"][:, 0]:
-        rows = int(plan["q_blocks"][qb][3])
-        tiles, tail = -(-rows // 128), (rows - 1) % 128 + 1
-        items += tiles * (wl.n_q_heads // 2 if group % 2 == 0 else wl.n_q_heads) - (wl.n_q_heads // 4 if group % 4 == 0 and tail <= 64 else 0)
-    return items
-
-
 def measured_traffic(workload, kernel_instance):
     """HBM bytes per launch of `kernel_instance` (its full name, template arguments included) as recorded in the
     tracked rocprofv3 summary of the training step (FETCH_SIZE / WRITE_SIZE runs of this script, scaled by a plain copy
@@ -691,7 +681,7 @@ def main():
             "n_kv_heads": wl.n_kv_heads, "head_dim": wl.head_dim, "n_seqs": int(len(wl.seq_lens)),
             "n_pairs": int(len(dp.plan["pairs"])), "n_slots": int(len(dp.plan["slots"])),
             "n_q_blocks": int(len(dp.plan["q_blocks"])), "packed_members": int(len(dp.plan.get("segments", ()))),
-            "fwd_items": None if len(dp.plan.get("segments", ())) else forward_items(dp.plan, wl),
+            "fwd_items": None if len(dp.plan.get("segments", ())) else fcp.fcp_launch_probe(dp.problem, forward_only=True)["items"][0],
             "nnz_per_head": nnz, "o_dtype": "f32" if backward else "bf16", "parallelism": "single-gpu",
             "backward": (args.bwd if backward else None), "workspace_bytes": dp.ws_bytes,
         },

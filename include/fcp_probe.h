@@ -71,7 +71,7 @@ int fcp_atomic_probe(float* buf, int64_t n_rows, int32_t row_stride, int32_t ite
  * fcp_launch_probe -- which kernels the launches of a problem take (host, integer only).
  * info[0..2]: 1 where the forward / dQ (recomputing) / dK, dV kernel is the split one (32 rows a workgroup, a chain over its waves).
  * info[3..5]: work items of the forward / dQ / dK, dV.
- * info[6], [7]: 0.
+ * info[6], [7]: 1 where row tiles of at most 64 rows of the forward / dQ take four heads to an item.
  * info[8..15]: KV tiles in each of the eight queue ranges of the dQ items (0 with forward_only).
  * forward_only: as fcp_block_attn_fwd_static lays the problem out, else as fcp_queue_build does.
  */

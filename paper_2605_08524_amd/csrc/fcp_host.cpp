@@ -7,8 +7,10 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <functional>
 #include <mutex>
 #include <numeric>
+#include <queue>
 #include <unordered_map>
 #include <utility>
 #include <vector>
@@ -207,14 +209,18 @@ int kind_in_run(int kind, const Run& run) { return (kind & 2) && run.n_segs == 1
 
 bool packed_slot(const fcp_problem* p, const fcp_slot& sl) { return sl.n_pairs == 1 && (p->pairs[sl.pair_begin].kind & 2); }
 
-// A row tile of at most 64 rows takes four heads of a group of 4, 8, ..: all eight waves of the workgroup have rows then.
+// Items of two sub-tiles.
+int64_t q_items_of(const fcp_problem* p, int rows) {
+  return ceil_div(rows, item_rows(p)) * ((p->n_q_heads / p->n_kv_heads) % 2 == 0 ? p->n_q_heads / 2 : p->n_q_heads);
+}
+
+// A row tile of at most 64 rows may take four heads of a group of 4, 8, ..: all eight waves of the workgroup have rows then.
 bool four_heads(const fcp_problem* p, int rows) { return rows <= kFwdTileM / 2 && (p->n_q_heads / p->n_kv_heads) % 4 == 0; }
 
-int64_t q_items_of(const fcp_problem* p, int rows) {
-  const int64_t tiles = ceil_div(rows, item_rows(p));
-  if ((p->n_q_heads / p->n_kv_heads) % 2 != 0) return tiles * p->n_q_heads;
-  return tiles * (p->n_q_heads / 2) - (four_heads(p, rows - (int)(tiles - 1) * kFwdTileM) ? p->n_q_heads / 4 : 0);
-}
+// How many fewer items `rows` rows are then.
+int64_t four_heads_save(const fcp_problem* p, int rows) { return four_heads(p, (rows - 1) % kFwdTileM + 1) ? p->n_q_heads / 4 : 0; }
+
+constexpr int kFourHeadsItems = 512;     // of two heads: beyond, four always pay (see kTwoHeadsTile)
 
 // Append KV rows to the spans of a forward segment (those from span0 on): to the last one where they follow it.
 void append_span(std::vector<DevPair>* spans, int32_t span0, int32_t start, int32_t len, int kind) {
@@ -320,9 +326,7 @@ void expand_problem(const fcp_problem* p, bool forward_only, Expanded* x) {
 
 size_t static_plan_bytes(const fcp_problem* p) {
   int64_t items = 0;
-  // items of two sub-tiles, whether four heads share some or not
-  const int64_t heads = (p->n_q_heads / p->n_kv_heads) % 2 == 0 ? p->n_q_heads / 2 : p->n_q_heads;
-  for (int s = 0; s < p->n_slots; s++) items += ceil_div(p->q_blocks[p->slots[s].q_blk].tok_len, item_rows(p)) * heads;
+  for (int s = 0; s < p->n_slots; s++) items += q_items_of(p, p->q_blocks[p->slots[s].q_blk].tok_len);
   auto align = [](size_t x) { return (x + 255) & ~(size_t)255; };
   return 1024 + align(16 * (size_t)std::max(1, p->n_pairs)) + align(72 * (size_t)std::max<int64_t>(1, items));
 }
@@ -331,14 +335,16 @@ int compute_layout(const fcp_problem* p, bool forward_only, WsLayout* L) {
   std::memset(L, 0, sizeof(*L));
   const Runs runs = make_runs(p);
   for (const Run& r : runs.run) L->n_bwd_items += ceil_div(r.len, kBwdTileN) * p->n_kv_heads;
-  int64_t frags = kDsSinkFrags;
+  int64_t frags = kDsSinkFrags, fwd_save = 0, dq_save = 0;
   for_q_blocks(p, runs, [&](int b, int s0, int s1, const Run* run, int n_runs, bool packed) {
-    int64_t items = 0;
-    for (int m = 0; m < n_runs; m++) items += q_items_of(p, run[m].len);
+    int64_t items = 0, save = 0;
+    for (int m = 0; m < n_runs; m++) { items += q_items_of(p, run[m].len); save += four_heads_save(p, run[m].len); }
     L->n_dq_items += items;
+    dq_save += save;
     for (int s = s0; s < s1; s++) {
       const bool whole = packed && !packed_slot(p, p->slots[s]);
       L->n_fwd_items += whole ? q_items_of(p, p->q_blocks[b].tok_len) : items;
+      fwd_save += whole ? four_heads_save(p, p->q_blocks[b].tok_len) : save;
       const int64_t n_pairs = (int64_t)p->slots[s].n_pairs * n_runs;
       if (!forward_only) L->n_pairs += n_pairs;
       if (p->block_size <= kMaxSpan) {
@@ -355,6 +361,12 @@ int compute_layout(const fcp_problem* p, bool forward_only, WsLayout* L) {
         frags += p->n_q_heads * ds_frags_per_head(pr.kind, run[m].len, runs.run[runs.begin[pr.kv_blk] + ((pr.kind & 2) ? m : 0)].len);
     }
   });
+  L->fwd_four_save = fwd_save;
+  L->dq_four_save = dq_save;
+  const bool few_fwd = fwd_save > 0 && L->n_fwd_items <= kFourHeadsItems, few_dq = !forward_only && dq_save > 0 && L->n_dq_items <= kFourHeadsItems;
+  L->n_fwd_items -= fwd_save;
+  L->n_dq_items -= dq_save;
+  if (few_fwd || few_dq) choose_split(p, forward_only, L);      // may go back to two heads, so before anything is laid out
   std::vector<int32_t> slots_of(p->n_q_blocks, 0);
   for (int s = 0; s < p->n_slots; s++) slots_of[p->slots[s].q_blk]++;
   const bool direct = (p->flags & FCP_FLAG_DIRECT_SINGLE) != 0;
@@ -418,14 +430,47 @@ constexpr LaunchCost kLaunchCost[2][3] = {      // [d = 128][forward, dQ, dK/dV]
 constexpr double kSplitGain = 1.15;      // split only what gains clearly: every shape that the fit gives 1.11 and more did gain, 3 % at least
 constexpr int kSplitMaxItems = 512;      // two to a compute unit: the fits reach no further, and walking larger tables would cost
 
+// A row tile of at most 64 rows: four heads to an item make half as many items, whose tiles take longer, since all eight waves have rows
+// instead of four.  With that many items of two heads and more it always pays; below, it depends on how the items come out on the compute
+// units.  Two heads / four, us: 176 items of 48 tiles (the last 64 rows of 65600 tokens, 16/4 heads, d = 128) 51 / 71, 320 of 32 tiles 47 / 52,
+// dQ of 256 items of 65 tiles 127 / 138; 320 of one tile (sequences of 64) 18.2 / 13.7, 160 of one 11.5 / 11.1.
+constexpr double kTwoHeadsTile = 0.74;         // a tile of two heads on 64 rows against one of a full item, or of four heads
+constexpr double kFourHeadsGain = 1.02;        // else two: where both come out even, two were up to 7 % the faster
+constexpr double kForwardGroup = 0.012;        // what each workgroup adds to the start of a forward, us
+
 // The items of one kernel: tiles (steps) of the longest, of all; `units`: their 32-row units as fractions of a full item's.
 struct LaunchLoad {
   int64_t longest = 0, tiles = 0, items = 0;
   double unit_tiles = 0, units = 0;
+  struct Chains { int64_t tiles, count; bool four; };
+  std::vector<Chains> chains;     // kept where four heads may go back to two
   void add(int64_t n, int64_t count, double share) {
     longest = std::max(longest, n); tiles += n * count; items += count;
     unit_tiles += n * count * share; units += count * share;
   }
+  // The whole launch with items of four heads, or with two items of two for each: the longest chains first, each to the compute unit that is free first.
+  double makespan(const LaunchCost& c, bool four, double per_group) const {
+    constexpr int64_t cus = 256;
+    auto times = [&](const Chains& k) { return k.four && !four ? 2 * k.count : k.count; };
+    auto cost = [&](const Chains& k) { return c.whole_item + c.whole_tile * k.tiles * (k.four && !four ? kTwoHeadsTile : 1.0); };
+    int64_t n = 0;
+    double last = 0;
+    for (const Chains& k : chains) { n += times(k); last = std::max(last, cost(k)); }
+    if (n > cus) {
+      std::vector<double> x;
+      for (const Chains& k : chains) x.insert(x.end(), times(k), cost(k));
+      std::sort(x.begin(), x.end(), std::greater<double>());
+      std::priority_queue<double, std::vector<double>, std::greater<double>> free_at(std::greater<double>(), std::vector<double>(x.begin(), x.begin() + cus));
+      for (int64_t i = cus; i < n; i++) {
+        const double t = free_at.top() + x[i];
+        free_at.pop();
+        free_at.push(t);
+        last = std::max(last, t);
+      }
+    }
+    return c.whole + last + per_group * (double)std::min(n, cus);
+  }
+  bool four_pays(const LaunchCost& c, double per_group) const { return makespan(c, false, per_group) > kFourHeadsGain * makespan(c, true, per_group); }
   bool split(const LaunchCost& c) const {
     constexpr double cus = 256;
     const double whole = c.whole + c.whole_tile * std::max<double>(longest, tiles / cus) + c.whole_item * items / cus;
@@ -468,6 +513,7 @@ void choose_split(const fcp_problem* p, bool forward_only, WsLayout* L) {
   // rounding only where all of them take the same one.  What they have in common are the blocks, not the items of one launch.  At 2.5 (1)
   // units to a compute unit a launch of the shortest slots takes what a whole one does.
   const int64_t most_units = p->head_dim == 128 ? 256 : 640;
+  const bool spill = (p->flags & FCP_FLAG_BWD_SPILL_DS) != 0;
   bool fit_fwd = false;
   if (L->n_fwd_items > 0 && L->n_fwd_items <= std::max<int64_t>(kSplitMaxItems, most_units)) {
     // a planned block has no more slots than its sequence has KV blocks, so items are no more than units; others may have any number
@@ -475,19 +521,23 @@ void choose_split(const fcp_problem* p, bool forward_only, WsLayout* L) {
     else fit_fwd = L->n_fwd_items <= kSplitMaxItems;
   }
   const bool query = !forward_only && L->n_dq_items <= kSplitMaxItems, keys = !forward_only && L->n_bwd_items <= kSplitMaxItems;
-  if (!L->split_fwd && !fit_fwd && !query && !keys) return;
+  const bool may_two_fwd = !L->four_settled && L->four_fwd() && L->n_fwd_items + L->fwd_four_save <= kFourHeadsItems;
+  const bool may_two_dq = !L->four_settled && !forward_only && L->four_dq() && L->n_dq_items + L->dq_four_save <= kFourHeadsItems;
+  L->four_settled = true;
+  if (!L->split_fwd && !fit_fwd && !query && !keys && !may_two_fwd) return;
   LaunchLoad fwd, dq, dkdv;
   const Runs runs = make_runs(p);
   std::vector<int64_t> steps(keys ? runs.run.size() : 0, 0);     // of a KV segment's dependencies that it sees in full
   std::vector<char> diag(keys ? runs.run.size() : 0, 0);         // it has one that it sees from its own rows on
-  int max_q = 0, max_kv = 0;
-  auto segment = [&](LaunchLoad* l, int64_t full, int64_t diag_cols, int len) {
-    max_q = std::max(max_q, len);
+  int max_fwd = 0, max_dq = 0, max_kv = 0;
+  auto segment = [&](LaunchLoad* l, bool four_on, bool keep, int* most, int64_t full, int64_t diag_cols, int len) {
+    *most = std::max(*most, len);
     for (int64_t row = 0; row < len; row += rows_of_item) {          // len: up to 2^31 - 1
       const int n = (int)std::min<int64_t>(rows_of_item, len - row);
       const int64_t tiles = ceil_div(full + std::min<int64_t>(diag_cols, row + n), kQTileN);
-      const int four = four_heads(p, n) ? 2 : 1;
+      const int four = four_on && four_heads(p, n) ? 2 : 1;
       l->add(tiles, heads / four, (double)ceil_div(n, 32) * 32 * four / rows_of_item);
+      if (keep) l->chains.push_back({tiles, heads / four, four == 2});
     }
   };
   for_q_blocks(p, runs, [&](int b, int s0, int s1, const Run* run, int n_runs, bool packed) {
@@ -504,20 +554,22 @@ void choose_split(const fcp_problem* p, bool forward_only, WsLayout* L) {
           if (!keys) continue;
           if (pr.kind & 1) diag[seg] = 1; else steps[seg] += ceil_div(run[m].len, 32) * G;
         }
-        if (!whole || m == 0) segment(&fwd, full, diag_cols, whole ? p->q_blocks[b].tok_len : run[m].len);
+        if (!whole || m == 0) segment(&fwd, L->four_fwd(), may_two_fwd, &max_fwd, full, diag_cols, whole ? p->q_blocks[b].tok_len : run[m].len);
         dq_full += full; dq_diag += diag_cols;
       }
-      segment(&dq, dq_full, dq_diag, run[m].len);
+      segment(&dq, L->four_dq(), may_two_dq, &max_dq, dq_full, dq_diag, run[m].len);
     }
   });
   if (fit_fwd) L->split_fwd = fwd.split(cost[0]);
   L->split_dq = !forward_only && L->n_dq_items > 0 && L->n_dq_items <= kSplitMaxItems && dq.split(cost[1]);
-  L->split_q_per_tile = (int)ceil_div(std::min(max_q, kFwdTileM), 32);
-  L->split_q_units = L->split_q_per_tile * (G % 2 == 0 || max_q > kFwdTileM ? 2 : 1);
-  if (G % 4 == 0) {                                        // items of four heads have two units a head, or one
-    if (max_q > kFwdTileM / 2) L->split_q_per_tile = 4;
-    L->split_q_units = max_q > kFwdTileM / 2 ? 8 : 4 * L->split_q_per_tile;
-  }
+  // units of a sub-tile, and of an item: two sub-tiles (one, where odd groups have no second row tile), or four heads of two units or one
+  auto units_of = [&](bool four, int most) {
+    const int per_tile = (int)ceil_div(std::min(most, kFwdTileM), 32);
+    if (four) return most > kFwdTileM / 2 ? SplitUnits{8, 4} : SplitUnits{4 * per_tile, per_tile};
+    return SplitUnits{per_tile * (G % 2 == 0 || most > kFwdTileM ? 2 : 1), per_tile};
+  };
+  L->fwd_units = units_of(L->four_fwd(), max_fwd);
+  L->dq_units = units_of(L->four_dq(), max_dq);
   for (size_t k = 0; k < steps.size(); k++)
     for (int64_t off = 0, len = runs.run[k].len; off < len; off += kBwdTileN) {
       const int n = (int)std::min<int64_t>(kBwdTileN, len - off);
@@ -526,6 +578,9 @@ void choose_split(const fcp_problem* p, bool forward_only, WsLayout* L) {
     }
   L->split_dkdv = keys && L->n_bwd_items > 0 && dkdv.split(cost[2]);
   L->split_kv_units = (int)ceil_div(max_kv, 32);
+  // Split launches keep items of four heads: the units are the same, their neighbours on an XCD share more (dQ of 256 items, d = 64 84 -> 80 us).
+  if (may_two_fwd && !L->split_fwd && !fwd.four_pays(cost[0], kForwardGroup)) { L->n_fwd_items += L->fwd_four_save; L->fwd_four_save = 0; }
+  if (may_two_dq && (!L->split_dq || spill) && !dq.four_pays(cost[1], 0)) { L->n_dq_items += L->dq_four_save; L->dq_four_save = 0; }
 }
 
 // Layouts validated by fcp_queue_build, keyed by the workspace they were built into.  A launch on that
@@ -669,8 +724,8 @@ struct ItemGroups {
 
 // The query-stationary items (forward, dQ) of a list of segments, one unit per (segment, KV head): its items share
 // K/V.  An item joins two sub-tiles: heads (2j, 2j+1) of the group on one row tile when G is even, else row tiles
-// (2j, 2j+1) of one head; of a row tile of at most 64 rows heads 4j .. 4j + 3 when G is a multiple of 4.  out: n_items of them; false if there would be another number.
-bool q_items(const fcp_problem* p, const std::vector<QSeg>& segs, const std::vector<DevPair>& pairs, bool spans, bool split, int64_t n_items, QItem* out,
+// (2j, 2j+1) of one head; with `four`, of a row tile of at most 64 rows heads 4j .. 4j + 3 when G is a multiple of 4.  out: n_items of them; false if there would be another number.
+bool q_items(const fcp_problem* p, const std::vector<QSeg>& segs, const std::vector<DevPair>& pairs, bool spans, bool four, bool split, int64_t n_items, QItem* out,
              int32_t begin[kNumXcd + 1]) {
   const int G = p->n_q_heads / p->n_kv_heads, heads_per_item = G % 2 == 0 ? 2 : 1;
   ItemGroups<QItem> groups;
@@ -705,7 +760,7 @@ bool q_items(const fcp_problem* p, const std::vector<QSeg>& segs, const std::vec
     }
     for (int g = 0; g < p->n_kv_heads; g++) {
       for (const QItem& r : rows) {
-        const int heads = four_heads(p, r.q_rows[0]) ? 4 : heads_per_item;
+        const int heads = four && four_heads(p, r.q_rows[0]) ? 4 : heads_per_item;
         for (int hh = 0; hh < G; hh += heads) {
           groups.items.push_back(r);
           groups.items.back().head[0] = g * G + hh; groups.items.back().head[1] = g * G + hh + heads - 1;
@@ -1042,12 +1097,12 @@ int fcp::build_queue_image(const fcp_problem* p, const Expanded& x, const WsLayo
   put(L.off_pairs, x.pairs);
   put(L.off_spans, x.spans);
   put(L.off_q_seg, x.q_seg);
-  if (!q_items(p, x.fwd, x.spans, true, L.split_fwd, L.n_fwd_items, reinterpret_cast<QItem*>(host.data() + L.off_fwd_items), hdr->fwd_begin)) {
+  if (!q_items(p, x.fwd, x.spans, true, L.four_fwd(), L.split_fwd, L.n_fwd_items, reinterpret_cast<QItem*>(host.data() + L.off_fwd_items), hdr->fwd_begin)) {
     set_error("internal: forward item count mismatch"); return FCP_ERR_INVALID_ARG;
   }
   if (forward_only) return FCP_OK;
   // ---- dQ: query-stationary items over all pairs of a query segment; with dS kept dq_ds_kernel draws them from the queues, whatever dQ alone would take
-  if (!q_items(p, x.dq, x.pairs, false, L.split_dq && !(p->flags & FCP_FLAG_BWD_SPILL_DS), L.n_dq_items, reinterpret_cast<QItem*>(host.data() + L.off_dq_items), hdr->dq_begin)) {
+  if (!q_items(p, x.dq, x.pairs, false, L.four_dq(), L.split_dq && !(p->flags & FCP_FLAG_BWD_SPILL_DS), L.n_dq_items, reinterpret_cast<QItem*>(host.data() + L.off_dq_items), hdr->dq_begin)) {
     set_error("internal: dQ item count mismatch"); return FCP_ERR_INVALID_ARG;
   }
   // ---- dK / dV: dependency lists per KV segment, one group per (KV segment, KV head)
@@ -1145,7 +1200,7 @@ extern "C" int fcp_launch_probe(const fcp_problem* p, int32_t forward_only, int3
   rc = compute_layout(p, forward_only != 0, &L);
   if (rc) return rc;
   choose_split(p, forward_only != 0, &L);
-  const int32_t head[8] = {L.split_fwd, L.split_dq, L.split_dkdv, (int32_t)L.n_fwd_items, (int32_t)L.n_dq_items, (int32_t)L.n_bwd_items, 0, 0};
+  const int32_t head[8] = {L.split_fwd, L.split_dq, L.split_dkdv, (int32_t)L.n_fwd_items, (int32_t)L.n_dq_items, (int32_t)L.n_bwd_items, L.four_fwd(), L.four_dq()};
   std::fill(std::copy(head, head + 8, info), info + 16, 0);
   if (forward_only) return FCP_OK;
   Expanded x;

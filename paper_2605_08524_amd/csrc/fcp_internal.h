@@ -88,13 +88,21 @@ struct WsHeader {
   float infs[64];                   // +inf page: LSE of query rows past a ragged end (their P is 0)
 };
 
+// Workgroups of an item in a split launch at most (32 rows each), and of a sub-tile.
+struct SplitUnits { int units, per_tile; };
+
 // Byte offsets of the workspace sections, a pure function of the problem's counts.
 struct WsLayout {
   int64_t n_fwd_items, n_bwd_items, n_merge_items, n_dq_items, n_pairs, n_spans, t_q;   // n_spans: at most
   int merge_chunk;  // (row, head) entries per merge work item, chosen per problem
-  // choose_split: which launches go to the split kernels, and the 32-row units that an item has there at most (of a sub-tile)
+  int64_t fwd_four_save, dq_four_save;   // how many fewer items there are because row tiles of at most 64 rows take four heads; 0: they take two
+  bool four_settled;        // a choice already made stands: the sections are laid out for it
+  bool four_fwd() const { return fwd_four_save > 0; }
+  bool four_dq() const { return dq_four_save > 0; }
+  // choose_split: which launches go to the split kernels, and the 32-row units that an item has there at most
   bool split_fwd, split_dq, split_dkdv;
-  int split_q_units, split_q_per_tile, split_kv_units;
+  SplitUnits fwd_units, dq_units;
+  int split_kv_units;
   int64_t n_ds_frags;   // fragments of the dS spill buffer, sinks and one fragment of slack included (0 without the flag)
   size_t off_pairs, off_spans, off_fwd_items, off_q_seg, off_bwd_deps, off_bwd_items, off_merge_items, off_slot_rh, off_dq_items, off_dls, off_lse2, off_ds, total;
 };

@@ -2727,7 +2727,7 @@ static int launch_fwd(const char* who, const fcp_problem* p, const WsLayout* lay
   a.n_q_heads = p->n_q_heads; a.n_kv_heads = p->n_kv_heads;
   a.scale_log2 = resolve_scale(p) * kLog2e;
   if (L.split_fwd) {
-    const SplitGrid g = {0, 0, (int)L.n_fwd_items, L.split_q_units, L.split_q_per_tile, false};
+    const SplitGrid g = {0, 0, (int)L.n_fwd_items, L.fwd_units.units, L.fwd_units.per_tile, false};
     void (*kern)(FwdArgs, int, int, int) = p->head_dim == 128 ? fwd_split_kernel<128> : fwd_split_kernel<64>;
     hipLaunchKernelGGL(kern, dim3(g.q_blocks()), dim3(64 * kSplitWaves), 0, (hipStream_t)stream, a, g.n_q, g.q_units, g.q_per_tile);
     return check_launch(who);
@@ -2885,7 +2885,7 @@ static auto bwd_split_instance(bool with_d, bool gb, bool spill) -> void (*)(Bwd
 static int launch_bwd_split(const char* who, const fcp_problem* p, const WsLayout& L, const BwdArgs& a, bool kv, bool q, bool with_d, void* stream) {
   const bool gb = (p->flags & FCP_FLAG_GRAD_BF16) != 0, spill = a.ds != nullptr;
   void (*kern)(BwdArgs, SplitGrid) = p->head_dim == 128 ? bwd_split_instance<128>(with_d, gb, spill) : bwd_split_instance<64>(with_d, gb, spill);
-  const SplitGrid g = {kv ? (int)L.n_bwd_items : 0, L.split_kv_units, q ? (int)L.n_dq_items : 0, L.split_q_units, L.split_q_per_tile, p->n_segments > 0};
+  const SplitGrid g = {kv ? (int)L.n_bwd_items : 0, L.split_kv_units, q ? (int)L.n_dq_items : 0, L.dq_units.units, L.dq_units.per_tile, p->n_segments > 0};
   hipLaunchKernelGGL(kern, dim3(g.kv_blocks() + g.q_blocks()), dim3(64 * kSplitWaves), 0, (hipStream_t)stream, a, g);
   return check_launch(who);
 }

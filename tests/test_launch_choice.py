@@ -116,6 +116,32 @@ def test_dq_from_ds_keeps_the_queue_order(lens, hq, hkv, d):
     spill = fcp.fcp_launch_probe(_problem(lens, 1024, 1, 0, hq, hkv, d, flags=F32 | fcp.FCP_FLAG_BWD_SPILL_DS))
     plain = fcp.fcp_launch_probe(_problem(lens, 1024, 1, 0, hq, hkv, d))
     assert plain["split"][1] and plain["dq_queue_tiles"][0] == max(plain["dq_queue_tiles"])
-    tiles, total = spill["dq_queue_tiles"], sum(plain["dq_queue_tiles"])
-    assert sum(tiles) == total
-    assert max(tiles) <= total / 4 and max(tiles) < 0.6 * plain["dq_queue_tiles"][0]
+    tiles = spill["dq_queue_tiles"]
+    assert max(tiles) <= sum(tiles) / 4 and max(tiles) < 0.6 * plain["dq_queue_tiles"][0]
+
+
+@pytest.mark.parametrize("case,four", [
+    # few long chains on 64 rows: half as many items would leave half of the chip idle
+    (([65600], 1024, 1, 3, 16, 4, 128, [(0, 64)]), False), (([65600], 1024, 1, 3, 8, 1, 64, [(0, 64)]), False),
+    (([8256] * 8, 1024, 1, 2, 16, 4, 128, [(s, 8) for s in range(8)]), False), (([192] * 15, 256, 1, 0, 32, 8, 128), False),
+    # one round of items instead of two, or a start of fewer workgroups
+    (([64] * 40, 128, 1, 0, 16, 4, 128), True), (([64] * 30, 128, 1, 0, 16, 4, 64), True),
+    # more than 512 items
+    (([64] * 70, 128, 1, 0, 16, 4, 128), True), (([2112] * 64, 512, 1, 1, 16, 4, 128, [(s, 4) for s in range(64)]), True),
+    # no row tile of at most 64 rows; groups of two
+    (([128] * 40, 128, 1, 0, 16, 4, 128), False), (([64] * 80, 128, 1, 0, 16, 8, 128), False)])
+def test_four_heads_only_where_they_pay(case, four):
+    p = _problem(*case)
+    with_ws, without = fcp.fcp_launch_probe(p), fcp.fcp_launch_probe(p, forward_only=True)
+    assert with_ws["four_heads"][0] == four and without["four_heads"][0] == four and with_ws["items"][0] == without["items"][0]
+    assert fcp.fcp_workspace_bytes(p) > 0
+
+
+def test_dq_of_few_items_takes_two_heads_unless_it_is_split():
+    """256 items of 65 tiles: two heads run them in one round as fast as the four-headed ones half of the chip; a split launch keeps four."""
+    def owned(d, flags=F32):
+        return fcp.fcp_launch_probe(_problem([4160] * 16, 1024, 1, 2, 32, 8, d, [(s, 4) for s in range(16)], flags))
+    whole, split = owned(128), owned(64)
+    assert whole["items"][1] == 256 and not whole["four_heads"][1] and not whole["split"][1]
+    assert split["split"][1] == split["four_heads"][1] and split["items"][1] == (128 if split["split"][1] else 256)
+    assert not owned(64, F32 | fcp.FCP_FLAG_BWD_SPILL_DS)["four_heads"][1]      # dQ from dS is never split
