@@ -85,6 +85,10 @@ enum {
                                     ignored).  Needs FCP_FLAG_O_F32; the partial buffers are not touched and may be NULL; no merge call
                                     follows.  The worker then holds no partials at all, at the price of reading and writing the
                                     running result once per stage.  Agrees with the one-pass result to fp32 rounding. */
+  FCP_FLAG_WHOLE_ITEMS = 64,     /* no launch is split: every kernel walks its work items as a whole, one workgroup each, also where a
+                                    launch of a few long chains would otherwise go to the kernels that split a chain over the waves
+                                    of a workgroup (the results differ by the rounding of P and dS).  Set it before
+                                    fcp_workspace_bytes / fcp_queue_build and keep it for every call on the workspace. */
   FCP_FLAG_DIRECT_SINGLE = 2     /* a query block with ONE slot needs no reduction: fcp_block_attn_fwd_out writes its
                                     result straight to the final o / lse and fcp_merge_partials leaves it alone.
                                     Set it before fcp_workspace_bytes / fcp_queue_build and keep it for every call

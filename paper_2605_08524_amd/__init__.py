@@ -8,7 +8,7 @@ no fallback: touching any binding name without a built libfcp.so raises ImportEr
 import importlib
 
 _BINDING_NAMES = (
-    "FCP_FLAG_DIRECT_SINGLE", "FCP_FLAG_O_F32", "FCP_FLAG_GRAD_BF16", "FCP_FLAG_PART_BF16", "FCP_FLAG_BWD_SPILL_DS", "FCP_FLAG_RUNNING_MERGE",
+    "FCP_FLAG_DIRECT_SINGLE", "FCP_FLAG_O_F32", "FCP_FLAG_GRAD_BF16", "FCP_FLAG_PART_BF16", "FCP_FLAG_BWD_SPILL_DS", "FCP_FLAG_RUNNING_MERGE", "FCP_FLAG_WHOLE_ITEMS",
     "FCP_KIND_DIAG", "FCP_KIND_FULL", "FCP_KIND_PACKED_FULL", "FCP_KIND_PACKED_DIAG", "FCP_ERR_INFEASIBLE", "FcpError", "Problem",
     "fcp_plan_blocks", "fcp_plan_blocks_packed", "fcp_stage_tables", "fcp_workspace_bytes", "fcp_queue_build", "fcp_block_attn_fwd", "fcp_block_attn_fwd_out",
     "fcp_block_attn_fwd_static",

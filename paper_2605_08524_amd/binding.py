@@ -30,6 +30,7 @@ FCP_FLAG_PART_BF16 = 4
 FCP_FLAG_GRAD_BF16 = 8
 FCP_FLAG_BWD_SPILL_DS = 16
 FCP_FLAG_RUNNING_MERGE = 32
+FCP_FLAG_WHOLE_ITEMS = 64
 
 EXPORTS = (
     "fcp_plan_blocks", "fcp_plan_blocks_packed", "fcp_stage_tables", "fcp_workspace_bytes", "fcp_queue_build", "fcp_block_attn_fwd", "fcp_block_attn_fwd_out",

@@ -524,6 +524,7 @@ void choose_split(const fcp_problem* p, bool forward_only, WsLayout* L) {
   const bool may_two_fwd = !L->four_settled && L->four_fwd() && L->n_fwd_items + L->fwd_four_save <= kFourHeadsItems;
   const bool may_two_dq = !L->four_settled && !forward_only && L->four_dq() && L->n_dq_items + L->dq_four_save <= kFourHeadsItems;
   L->four_settled = true;
+  if (p->flags & FCP_FLAG_WHOLE_ITEMS && !may_two_fwd && !may_two_dq) { L->split_fwd = false; return; }
   if (!L->split_fwd && !fit_fwd && !query && !keys && !may_two_fwd) return;
   LaunchLoad fwd, dq, dkdv;
   const Runs runs = make_runs(p);
@@ -578,6 +579,7 @@ void choose_split(const fcp_problem* p, bool forward_only, WsLayout* L) {
     }
   L->split_dkdv = keys && L->n_bwd_items > 0 && dkdv.split(cost[2]);
   L->split_kv_units = (int)ceil_div(max_kv, 32);
+  if (p->flags & FCP_FLAG_WHOLE_ITEMS) L->split_fwd = L->split_dq = L->split_dkdv = false;
   // Split launches keep items of four heads: the units are the same, their neighbours on an XCD share more (dQ of 256 items, d = 64 84 -> 80 us).
   if (may_two_fwd && !L->split_fwd && !fwd.four_pays(cost[0], kForwardGroup)) { L->n_fwd_items += L->fwd_four_save; L->fwd_four_save = 0; }
   if (may_two_dq && (!L->split_dq || spill) && !dq.four_pays(cost[1], 0)) { L->n_dq_items += L->dq_four_save; L->dq_four_save = 0; }
@@ -595,7 +597,7 @@ struct LayoutKey {
   bool operator==(const LayoutKey& o) const { return workspace == o.workspace && std::memcmp(v, o.v, sizeof(v)) == 0; }
 };
 LayoutKey make_key(const fcp_problem* p, const void* ws) {
-  return LayoutKey{ws, {p->n_q_heads, p->n_kv_heads, p->head_dim, p->block_size, p->flags & (FCP_FLAG_DIRECT_SINGLE | FCP_FLAG_BWD_SPILL_DS),
+  return LayoutKey{ws, {p->n_q_heads, p->n_kv_heads, p->head_dim, p->block_size, p->flags & (FCP_FLAG_DIRECT_SINGLE | FCP_FLAG_BWD_SPILL_DS | FCP_FLAG_WHOLE_ITEMS),
                         p->n_kv_blocks, p->n_q_blocks, p->n_pairs, p->n_slots, p->n_slot_rows, p->n_segments}};
 }
 constexpr int kLayoutCacheSize = 32;

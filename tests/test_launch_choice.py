@@ -145,3 +145,11 @@ def test_dq_of_few_items_takes_two_heads_unless_it_is_split():
     assert whole["items"][1] == 256 and not whole["four_heads"][1] and not whole["split"][1]
     assert split["split"][1] == split["four_heads"][1] and split["items"][1] == (128 if split["split"][1] else 256)
     assert not owned(64, F32 | fcp.FCP_FLAG_BWD_SPILL_DS)["four_heads"][1]      # dQ from dS is never split
+
+
+def test_whole_items_flag_splits_nothing_and_keeps_the_items():
+    for case in (([8192], 1024, 1, 0, 1, 1, 64), ([300, 77], 128, 1, 2, 4, 2, 128), ([64] * 40, 128, 1, 0, 16, 4, 128)):
+        plain, whole = (fcp.fcp_launch_probe(_problem(*case, flags=F32 | flag)) for flag in (0, fcp.FCP_FLAG_WHOLE_ITEMS))
+        assert any(plain["split"]) and whole["split"] == (False, False, False)
+        assert plain["items"][2] == whole["items"][2]
+        assert fcp.fcp_workspace_bytes(_problem(*case, flags=F32 | fcp.FCP_FLAG_WHOLE_ITEMS)) > 0
