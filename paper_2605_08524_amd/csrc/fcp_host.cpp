@@ -419,63 +419,79 @@ int compute_layout(const fcp_problem* p, bool forward_only, WsLayout* L) {
 namespace {
 
 // What a launch takes, in microseconds on 256 compute units, whole (one workgroup walks an item's tiles or steps one after the
-// other) and split (fwd_split_kernel, bwd_split_kernel): least-squares fits to 58 shapes (1000 to 40000 tokens, 1 to 32 heads, chains
-// of 1 to 512 tiles, full and causal, uniform and lognormal), which they meet within 15 % nearly everywhere.
-// A whole launch ends with its longest item or when all are through; a split one costs a fixed time per workgroup (unit) as well, but
-// its chains are an eighth.
-struct LaunchCost { double whole, whole_tile, whole_item, split, split_tile, split_unit, split_chain; };
+// other) and split (fwd_split_kernel, bwd_split_kernel).  Forward and dQ: least-squares fits to 1300 to 1600 random problems a kernel and head
+// size, each run in both forms: 1 to 60 sequences, whole ones and only their last blocks, 1 to 128 heads, chains of 1 to 360 tiles.  Root mean square
+// error 8 to 12 % (whole) and 11 to 15 % (split).  dK/dV: fits to 58 shapes, which chose well on 2838 such problems too.
+// whole:  the start, and an end: dK/dV the longest item or the mean load and a time per item; forward and dQ every item on the compute unit
+//         that is free first.  An item in which at most half of the waves have rows walks its tiles faster.
+// split:  a start, the work, a time per workgroup (unit: 8, dK/dV 4) and the longest chain, which is an eighth; workgroups past the rows of
+//         their item cost too.  Each 32 rows read K and V by themselves, which takes longer the less of all K / V stays in the caches (stream:
+//         that many times as long at 312 MB more).
+struct LaunchCost { double whole, tile, item, half, split, split_tile, split_unit, split_chain, split_empty, stream_most, gain; };
 constexpr LaunchCost kLaunchCost[2][3] = {      // [d = 128][forward, dQ, dK/dV]
-    {{5.0, 0.93, 4.5, 5.2, 1.14, 10.7, 0.095}, {6.8, 1.25, 3.4, 4.9, 1.46, 12.8, 0.127}, {6.4, 0.538, 5.8, 5.1, 0.470, 5.8, 0.143}},
-    {{6.6, 1.25, 5.8, 4.7, 2.48, 32.5, 0.141}, {7.2, 1.83, 8.5, 4.4, 3.24, 38.8, 0.209}, {7.2, 0.703, 10.0, 4.6, 0.948, 25.7, 0.194}}};
-constexpr double kSplitGain = 1.15;      // split only what gains clearly: every shape that the fit gives 1.11 and more did gain, 3 % at least
+    {{0.7, 0.98, 6.9, 0.70, 3.9, 1.34, 10.6, 0.177, 1.04, 2.0, 1.05},
+     {0.5, 1.39, 7.0, 0.74, 3.9, 1.63, 9.6, 0.258, 1.27, 0.8, 1.05},
+     {6.4, 0.538, 5.8, 1.0, 5.1, 0.470, 5.8, 0.143, 0.22, 0.0, 1.15}},
+    {{0.0, 1.30, 9.1, 0.65, 4.3, 2.74, 29.2, 0.246, 2.60, 2.0, 1.05},
+     {0.0, 2.00, 10.0, 0.74, 4.2, 3.65, 28.7, 0.368, 3.16, 0.8, 1.05},
+     {7.2, 0.703, 10.0, 1.0, 4.6, 0.948, 25.7, 0.194, 1.38, 0.0, 1.15}}};
+// gain: split only what gains that much by the fits.  Of 5906 forward and dQ launches 31 are then slower than whole by more than 3 % (30 % at most),
+// 2838 of dK/dV 37 (13 %); all in all they take 0.5 % more than with the faster form of each.
+constexpr double kStreamBytes = 312e6;
 constexpr int kSplitMaxItems = 512;      // two to a compute unit: the fits reach no further, and walking larger tables would cost
 
 // A row tile of at most 64 rows: four heads to an item make half as many items, whose tiles take longer, since all eight waves have rows
-// instead of four.  With that many items of two heads and more it always pays; below, it depends on how the items come out on the compute
+// instead of four.  With more than kFourHeadsItems items of two heads it always pays; below, it depends on how the items come out on the compute
 // units.  Two heads / four, us: 176 items of 48 tiles (the last 64 rows of 65600 tokens, 16/4 heads, d = 128) 51 / 71, 320 of 32 tiles 47 / 52,
 // dQ of 256 items of 65 tiles 127 / 138; 320 of one tile (sequences of 64) 18.2 / 13.7, 160 of one 11.5 / 11.1.
-constexpr double kTwoHeadsTile = 0.74;         // a tile of two heads on 64 rows against one of a full item, or of four heads
 constexpr double kFourHeadsGain = 1.02;        // else two: where both come out even, two were up to 7 % the faster
 constexpr double kForwardGroup = 0.012;        // what each workgroup adds to the start of a forward, us
 
-// The items of one kernel: tiles (steps) of the longest, of all; `units`: their 32-row units as fractions of a full item's.
+// The items of one kernel.  Their tiles (steps): of the longest, of all; `units`: their 32-row units as fractions of a full item's.
 struct LaunchLoad {
   int64_t longest = 0, tiles = 0, items = 0;
   double unit_tiles = 0, units = 0;
-  struct Chains { int64_t tiles, count; bool four; };
-  std::vector<Chains> chains;     // kept where four heads may go back to two
+  struct Chains { int64_t tiles, count; bool half, four; };
+  std::vector<Chains> chains;     // forward and dQ
   void add(int64_t n, int64_t count, double share) {
     longest = std::max(longest, n); tiles += n * count; items += count;
     unit_tiles += n * count * share; units += count * share;
   }
-  // The whole launch with items of four heads, or with two items of two for each: the longest chains first, each to the compute unit that is free first.
-  double makespan(const LaunchCost& c, bool four, double per_group) const {
-    constexpr int64_t cus = 256;
-    auto times = [&](const Chains& k) { return k.four && !four ? 2 * k.count : k.count; };
-    auto cost = [&](const Chains& k) { return c.whole_item + c.whole_tile * k.tiles * (k.four && !four ? kTwoHeadsTile : 1.0); };
+  // The whole launch, the longest items first; those of four heads as such, or as two of two each.
+  double makespan(const LaunchCost& c, bool four) const {
+    auto two = [&](const Chains& k) { return k.four && !four; };
+    auto cost = [&](const Chains& k) { return c.item + c.tile * k.tiles * (two(k) || k.half ? c.half : 1.0); };
     int64_t n = 0;
     double last = 0;
-    for (const Chains& k : chains) { n += times(k); last = std::max(last, cost(k)); }
-    if (n > cus) {
+    for (const Chains& k : chains) { n += two(k) ? 2 * k.count : k.count; last = std::max(last, cost(k)); }
+    if (n > kCus) {
       std::vector<double> x;
-      for (const Chains& k : chains) x.insert(x.end(), times(k), cost(k));
+      for (const Chains& k : chains) x.insert(x.end(), two(k) ? 2 * k.count : k.count, cost(k));
       std::sort(x.begin(), x.end(), std::greater<double>());
-      std::priority_queue<double, std::vector<double>, std::greater<double>> free_at(std::greater<double>(), std::vector<double>(x.begin(), x.begin() + cus));
-      for (int64_t i = cus; i < n; i++) {
+      std::priority_queue<double, std::vector<double>, std::greater<double>> free_at(std::greater<double>(), std::vector<double>(x.begin(), x.begin() + kCus));
+      for (int64_t i = kCus; i < n; i++) {
         const double t = free_at.top() + x[i];
         free_at.pop();
         free_at.push(t);
         last = std::max(last, t);
       }
     }
-    return c.whole + last + per_group * (double)std::min(n, cus);
+    return c.whole + last;
   }
-  bool four_pays(const LaunchCost& c, double per_group) const { return makespan(c, false, per_group) > kFourHeadsGain * makespan(c, true, per_group); }
-  bool split(const LaunchCost& c) const {
-    constexpr double cus = 256;
-    const double whole = c.whole + c.whole_tile * std::max<double>(longest, tiles / cus) + c.whole_item * items / cus;
-    return whole > kSplitGain * (c.split + c.split_tile * unit_tiles / cus + c.split_unit * units / cus + c.split_chain * longest);
+  int64_t groups(bool four) const {       // workgroups of the whole launch
+    int64_t n = 0;
+    for (const Chains& k : chains) n += k.four && !four ? 2 * k.count : k.count;
+    return std::min<int64_t>(n, kCus);
   }
+  bool four_pays(const LaunchCost& c, double per_group) const {
+    return makespan(c, false) + per_group * groups(false) > kFourHeadsGain * (makespan(c, true) + per_group * groups(true));
+  }
+  // full: units of a full item; most: workgroups that an item gets
+  bool split(const LaunchCost& c, double whole, int full, int most, double kv_bytes) const {
+    const double stream = 1 + std::min(c.stream_most, kv_bytes / kStreamBytes), empty = (double)items * most - units * full;
+    return whole > c.gain * (c.split + c.split_tile * unit_tiles / kCus * stream + c.split_unit * units / kCus + c.split_chain * longest + c.split_empty * empty / kCus);
+  }
+  static constexpr int kCus = 256;
 };
 
 }  // namespace
@@ -538,7 +554,7 @@ void choose_split(const fcp_problem* p, bool forward_only, WsLayout* L) {
       const int64_t tiles = ceil_div(full + std::min<int64_t>(diag_cols, row + n), kQTileN);
       const int four = four_on && four_heads(p, n) ? 2 : 1;
       l->add(tiles, heads / four, (double)ceil_div(n, 32) * 32 * four / rows_of_item);
-      if (keep) l->chains.push_back({tiles, heads / four, four == 2});
+      if (keep) l->chains.push_back({tiles, heads / four, four == 1 && n <= rows_of_item / 2, four == 2});
     }
   };
   for_q_blocks(p, runs, [&](int b, int s0, int s1, const Run* run, int n_runs, bool packed) {
@@ -555,14 +571,12 @@ void choose_split(const fcp_problem* p, bool forward_only, WsLayout* L) {
           if (!keys) continue;
           if (pr.kind & 1) diag[seg] = 1; else steps[seg] += ceil_div(run[m].len, 32) * G;
         }
-        if (!whole || m == 0) segment(&fwd, L->four_fwd(), may_two_fwd, &max_fwd, full, diag_cols, whole ? p->q_blocks[b].tok_len : run[m].len);
+        if (!whole || m == 0) segment(&fwd, L->four_fwd(), may_two_fwd || fit_fwd, &max_fwd, full, diag_cols, whole ? p->q_blocks[b].tok_len : run[m].len);
         dq_full += full; dq_diag += diag_cols;
       }
-      segment(&dq, L->four_dq(), may_two_dq, &max_dq, dq_full, dq_diag, run[m].len);
+      segment(&dq, L->four_dq(), may_two_dq || query, &max_dq, dq_full, dq_diag, run[m].len);
     }
   });
-  if (fit_fwd) L->split_fwd = fwd.split(cost[0]);
-  L->split_dq = !forward_only && L->n_dq_items > 0 && L->n_dq_items <= kSplitMaxItems && dq.split(cost[1]);
   // units of a sub-tile, and of an item: two sub-tiles (one, where odd groups have no second row tile), or four heads of two units or one
   auto units_of = [&](bool four, int most) {
     const int per_tile = (int)ceil_div(std::min(most, kFwdTileM), 32);
@@ -571,14 +585,22 @@ void choose_split(const fcp_problem* p, bool forward_only, WsLayout* L) {
   };
   L->fwd_units = units_of(L->four_fwd(), max_fwd);
   L->dq_units = units_of(L->four_dq(), max_dq);
+  double kv_bytes = 0;
+  for (int i = 0; i < p->n_kv_blocks; i++) kv_bytes += 4.0 * p->kv_blocks[i].tok_len * p->n_kv_heads * p->head_dim;
+  auto query_split = [&](const LaunchLoad& l, const LaunchCost& c, bool four, const SplitUnits& u) {
+    return l.split(c, four ? std::min(l.makespan(c, false), l.makespan(c, true)) : l.makespan(c, false), 8, u.units, kv_bytes);
+  };
+  if (fit_fwd) L->split_fwd = query_split(fwd, cost[0], L->four_fwd(), L->fwd_units);
+  L->split_dq = query && L->n_dq_items > 0 && query_split(dq, cost[1], L->four_dq(), L->dq_units);
   for (size_t k = 0; k < steps.size(); k++)
     for (int64_t off = 0, len = runs.run[k].len; off < len; off += kBwdTileN) {
       const int n = (int)std::min<int64_t>(kBwdTileN, len - off);
       max_kv = std::max(max_kv, n);
       dkdv.add(steps[k] + (diag[k] ? ceil_div(len - off, 32) * G : 0), p->n_kv_heads, (double)ceil_div(n, 32) * 32 / kBwdTileN);
     }
-  L->split_dkdv = keys && L->n_bwd_items > 0 && dkdv.split(cost[2]);
   L->split_kv_units = (int)ceil_div(max_kv, 32);
+  const double whole_dkdv = cost[2].whole + cost[2].tile * std::max<double>(dkdv.longest, (double)dkdv.tiles / LaunchLoad::kCus) + cost[2].item * dkdv.items / LaunchLoad::kCus;
+  L->split_dkdv = keys && L->n_bwd_items > 0 && dkdv.split(cost[2], whole_dkdv, 4, L->split_kv_units, 0);
   if (p->flags & FCP_FLAG_WHOLE_ITEMS) L->split_fwd = L->split_dq = L->split_dkdv = false;
   // Split launches keep items of four heads: the units are the same, their neighbours on an XCD share more (dQ of 256 items, d = 64 84 -> 80 us).
   if (may_two_fwd && !L->split_fwd && !fwd.four_pays(cost[0], kForwardGroup)) { L->n_fwd_items += L->fwd_four_save; L->fwd_four_save = 0; }

@@ -153,3 +153,19 @@ def test_whole_items_flag_splits_nothing_and_keeps_the_items():
         assert any(plain["split"]) and whole["split"] == (False, False, False)
         assert plain["items"][2] == whole["items"][2]
         assert fcp.fcp_workspace_bytes(_problem(*case, flags=F32 | fcp.FCP_FLAG_WHOLE_ITEMS)) > 0
+
+
+@pytest.mark.parametrize("case,split", [
+    # the last rows of many long sequences: every 32 rows read all K and V of their sequence by themselves
+    (([4160] * 16, 1024, 1, 0, 12, 4, 128, [(s, 4) for s in range(16)]), (False, None)),
+    (([8256] * 8, 1024, 1, 0, 48, 16, 128, [(s, 8) for s in range(8)]), (False, None)),
+    (([15500 + 9 * s for s in range(15)], 128, 1, 0, 16, 16, 128, [(s, (15500 + 9 * s - 1) // 128) for s in range(15)]), (False, None)),
+    (([4160] * 16, 1024, 1, 0, 32, 8, 64, [(s, 4) for s in range(16)]), (False, False)),
+    # few of them, or few heads: the chip would idle
+    (([8256] * 8, 1024, 1, 0, 8, 8, 64, [(s, 8) for s in range(8)]), (True, True)),
+    (([2112] * 4, 1024, 1, 0, 16, 8, 128, [(s, 2) for s in range(4)]), (True, True)),
+    (([8192], 1024, 1, 0, 1, 1, 64), (True, True)), (([4000], 128, 1, 0, 4, 4, 64), (True, True))])
+def test_split_where_it_was_measured_to_pay(case, split):
+    """Forward and dQ; None: both forms take about the same."""
+    got = fcp.fcp_launch_probe(_problem(*case))["split"]
+    assert all(want is None or have == want for have, want in zip(got, split)), got
