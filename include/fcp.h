@@ -297,8 +297,8 @@ int fcp_block_attn_bwd(const fcp_problem* p, const void* q, const void* k, const
 
 /*
  * The stages of the backward as separate calls, so that a caller can time or overlap them.  fcp_block_attn_bwd
- * itself runs fcp_block_attn_bwd_dq_d (below) followed by fcp_block_attn_bwd_dkdv (a small problem: D, then both in one launch,
- * with the same bits).
+ * itself runs fcp_block_attn_bwd_dq_d (below) followed by fcp_block_attn_bwd_dkdv (a small problem of few
+ * heads: D, then both in one launch, with the same bits).
  * fcp_bwd_preprocess:      computes D = rowsum(dO o O) and leaves scale*D and log2(e)*LSE
  *                          ([Hq,T_q] fp32 each) in the workspace.
  * fcp_block_attn_bwd_dkdv: KV-stationary kernel, writes dk and dv.

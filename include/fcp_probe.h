@@ -73,9 +73,10 @@ int fcp_atomic_probe(float* buf, int64_t n_rows, int32_t row_stride, int32_t ite
  * info[3..5]: work items of the forward / dQ / dK, dV.
  * info[6], [7]: 1 where row tiles of at most 64 rows of the forward / dQ take four heads to an item.
  * info[8..15]: KV tiles in each of the eight queue ranges of the dQ items (0 with forward_only).
+ * info[16]: 1 where fcp_block_attn_bwd runs the split dQ and dK, dV in one launch, behind a D pass.
  * forward_only: as fcp_block_attn_fwd_static lays the problem out, else as fcp_queue_build does.
  */
-int fcp_launch_probe(const fcp_problem* p, int32_t forward_only, int32_t info[16]);
+int fcp_launch_probe(const fcp_problem* p, int32_t forward_only, int32_t info[17]);
 
 #ifdef __cplusplus
 }

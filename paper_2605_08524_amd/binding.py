@@ -305,9 +305,10 @@ def fcp_mfma_valu_probe(operand_kind: int, valu_per_mfma: int, iters: int, out, 
 
 
 def fcp_launch_probe(problem: Problem, forward_only: bool = False) -> dict:
-    info = (C.c_int32 * 16)()
+    info = (C.c_int32 * 17)()
     _check(_lib.fcp_launch_probe(problem.ref, int(forward_only), info))
-    return {"split": tuple(bool(x) for x in info[0:3]), "items": tuple(info[3:6]), "four_heads": tuple(bool(x) for x in info[6:8]), "dq_queue_tiles": tuple(info[8:16])}
+    return {"split": tuple(bool(x) for x in info[0:3]), "items": tuple(info[3:6]), "four_heads": tuple(bool(x) for x in info[6:8]), "dq_queue_tiles": tuple(info[8:16]),
+            "joint_bwd": bool(info[16])}
 
 
 def fcp_lds_probe(mode: int, n_waves: int, iters: int, src, out, stream=None):

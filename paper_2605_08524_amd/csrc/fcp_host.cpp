@@ -487,9 +487,9 @@ struct LaunchLoad {
     return makespan(c, false) + per_group * groups(false) > kFourHeadsGain * (makespan(c, true) + per_group * groups(true));
   }
   // full: units of a full item; most: workgroups that an item gets
-  bool split(const LaunchCost& c, double whole, int full, int most, double kv_bytes) const {
+  double split(const LaunchCost& c, int full, int most, double kv_bytes) const {
     const double stream = 1 + std::min(c.stream_most, kv_bytes / kStreamBytes), empty = (double)items * most - units * full;
-    return whole > c.gain * (c.split + c.split_tile * unit_tiles / kCus * stream + c.split_unit * units / kCus + c.split_chain * longest + c.split_empty * empty / kCus);
+    return c.split + c.split_tile * unit_tiles / kCus * stream + c.split_unit * units / kCus + c.split_chain * longest + c.split_empty * empty / kCus;
   }
   static constexpr int kCus = 256;
 };
@@ -587,11 +587,15 @@ void choose_split(const fcp_problem* p, bool forward_only, WsLayout* L) {
   L->dq_units = units_of(L->four_dq(), max_dq);
   double kv_bytes = 0;
   for (int i = 0; i < p->n_kv_blocks; i++) kv_bytes += 4.0 * p->kv_blocks[i].tok_len * p->n_kv_heads * p->head_dim;
-  auto query_split = [&](const LaunchLoad& l, const LaunchCost& c, bool four, const SplitUnits& u) {
-    return l.split(c, four ? std::min(l.makespan(c, false), l.makespan(c, true)) : l.makespan(c, false), 8, u.units, kv_bytes);
+  auto query_whole = [&](const LaunchLoad& l, const LaunchCost& c, bool four) {
+    return four ? std::min(l.makespan(c, false), l.makespan(c, true)) : l.makespan(c, false);
   };
-  if (fit_fwd) L->split_fwd = query_split(fwd, cost[0], L->four_fwd(), L->fwd_units);
-  L->split_dq = query && L->n_dq_items > 0 && query_split(dq, cost[1], L->four_dq(), L->dq_units);
+  if (fit_fwd) L->split_fwd = query_whole(fwd, cost[0], L->four_fwd()) > cost[0].gain * fwd.split(cost[0], 8, L->fwd_units.units, kv_bytes);
+  double dq_time = 0;
+  if (query && L->n_dq_items > 0) {
+    dq_time = dq.split(cost[1], 8, L->dq_units.units, kv_bytes);
+    L->split_dq = query_whole(dq, cost[1], L->four_dq()) > cost[1].gain * dq_time;
+  }
   for (size_t k = 0; k < steps.size(); k++)
     for (int64_t off = 0, len = runs.run[k].len; off < len; off += kBwdTileN) {
       const int n = (int)std::min<int64_t>(kBwdTileN, len - off);
@@ -600,8 +604,14 @@ void choose_split(const fcp_problem* p, bool forward_only, WsLayout* L) {
     }
   L->split_kv_units = (int)ceil_div(max_kv, 32);
   const double whole_dkdv = cost[2].whole + cost[2].tile * std::max<double>(dkdv.longest, (double)dkdv.tiles / LaunchLoad::kCus) + cost[2].item * dkdv.items / LaunchLoad::kCus;
-  L->split_dkdv = keys && L->n_bwd_items > 0 && dkdv.split(cost[2], whole_dkdv, 4, L->split_kv_units, 0);
-  if (p->flags & FCP_FLAG_WHOLE_ITEMS) L->split_fwd = L->split_dq = L->split_dkdv = false;
+  const double dkdv_time = dkdv.split(cost[2], 4, L->split_kv_units, 0);
+  L->split_dkdv = keys && L->n_bwd_items > 0 && whole_dkdv > cost[2].gain * dkdv_time;
+  // Both in one launch behind the D pass, or dQ with D in it and then dK/dV.  The D pass walks the heads one after the other (2.9 us and 0.21 a head
+  // at d = 64, twice that at 128); what one launch saves is the shorter half.  Backward of 1500 random problems, joint / one after the other: up to
+  // 12 heads of d = 64 0.84, 16 and 24 heads 1.04 below 35 us and 0.91 above, 64 heads of d = 128 43 / 15 us at its worst.
+  const int heads64 = p->n_q_heads * (p->head_dim / 64);
+  L->joint_bwd = L->split_dq && L->split_dkdv && (heads64 <= 12 || (heads64 <= 24 && dq_time + dkdv_time > 35));
+  if (p->flags & FCP_FLAG_WHOLE_ITEMS) L->joint_bwd = L->split_fwd = L->split_dq = L->split_dkdv = false;
   // Split launches keep items of four heads: the units are the same, their neighbours on an XCD share more (dQ of 256 items, d = 64 84 -> 80 us).
   if (may_two_fwd && !L->split_fwd && !fwd.four_pays(cost[0], kForwardGroup)) { L->n_fwd_items += L->fwd_four_save; L->fwd_four_save = 0; }
   if (may_two_dq && (!L->split_dq || spill) && !dq.four_pays(cost[1], 0)) { L->n_dq_items += L->dq_four_save; L->dq_four_save = 0; }
@@ -1216,7 +1226,7 @@ extern "C" int fcp_queue_build(const fcp_problem* p, void* workspace, size_t wor
   return FCP_OK;
 }
 
-extern "C" int fcp_launch_probe(const fcp_problem* p, int32_t forward_only, int32_t info[16]) {
+extern "C" int fcp_launch_probe(const fcp_problem* p, int32_t forward_only, int32_t info[17]) {
   if (!info) { set_error("fcp_launch_probe: info is NULL"); return FCP_ERR_INVALID_ARG; }
   int rc = validate_problem(p);
   if (rc) return rc;
@@ -1226,6 +1236,7 @@ extern "C" int fcp_launch_probe(const fcp_problem* p, int32_t forward_only, int3
   choose_split(p, forward_only != 0, &L);
   const int32_t head[8] = {L.split_fwd, L.split_dq, L.split_dkdv, (int32_t)L.n_fwd_items, (int32_t)L.n_dq_items, (int32_t)L.n_bwd_items, L.four_fwd(), L.four_dq()};
   std::fill(std::copy(head, head + 8, info), info + 16, 0);
+  info[16] = L.joint_bwd;
   if (forward_only) return FCP_OK;
   Expanded x;
   expand_problem(p, false, &x);

@@ -101,6 +101,7 @@ struct WsLayout {
   bool four_dq() const { return dq_four_save > 0; }
   // choose_split: which launches go to the split kernels, and the 32-row units that an item has there at most
   bool split_fwd, split_dq, split_dkdv;
+  bool joint_bwd;   // fcp_block_attn_bwd runs split dQ and dK/dV in one launch
   SplitUnits fwd_units, dq_units;
   int split_kv_units;
   int64_t n_ds_frags;   // fragments of the dS spill buffer, sinks and one fragment of slack included (0 without the flag)

@@ -3011,7 +3011,7 @@ extern "C" int fcp_block_attn_bwd(const fcp_problem* p, const void* q, const voi
     if (rc) return rc;
     return fcp_block_attn_bwd_dq_ds(p, k, dq, workspace, stream);
   }
-  if (L.split_dq && L.split_dkdv) {
+  if (L.joint_bwd) {
     // D by a launch of its own, then dK / dV and dQ side by side
     if (int rc = fcp_bwd_preprocess(p, o, lse, d_o, workspace, stream)) return rc;
     a.q = (const uint16_t*)q; a.k = (const uint16_t*)k; a.v = (const uint16_t*)v; a.d_o = (const uint16_t*)d_o;

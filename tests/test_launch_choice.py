@@ -169,3 +169,14 @@ def test_split_where_it_was_measured_to_pay(case, split):
     """Forward and dQ; None: both forms take about the same."""
     got = fcp.fcp_launch_probe(_problem(*case))["split"]
     assert all(want is None or have == want for have, want in zip(got, split)), got
+
+
+@pytest.mark.parametrize("case,joint", [(([2000], 128, 1, 0, 4, 2, 64), True), (([8192], 1024, 1, 0, 1, 1, 128), True), (([46], 777, 0, 0, 64, 16, 128), False),
+                                        (([448], 128, 0, 0, 64, 8, 128, [(0, 3)]), False), (([35], 128, 0, 0, 64, 16, 64), False), (([300], 128, 1, 0, 16, 16, 64), False),
+                                        (([2048], 1024, 1, 0, 16, 2, 64), True)])
+def test_dq_and_dkdv_share_a_launch_only_where_the_d_pass_is_short(case, joint):
+    """64 heads of 46 rows: the D pass alone takes 33 us, dQ with D in it and dK/dV 15 together."""
+    info = fcp.fcp_launch_probe(_problem(*case))
+    assert info["split"][1:] == (True, True) and info["joint_bwd"] == joint
+    plan = fcp.fcp_plan_blocks(*case[:4], None if len(case) < 8 else np.asarray(case[7], dtype=np.int32))
+    assert not fcp.fcp_launch_probe(fcp.Problem(plan, *case[4:7], case[1], 0.0, F32 | fcp.FCP_FLAG_WHOLE_ITEMS))["joint_bwd"]
