@@ -6,6 +6,7 @@ package is imported: `paper_2605_08524_amd.workloads`, the seeded input generato
 this library and the CPU oracle, must be importable where the library has not been built.  There is
 no fallback: touching any binding name without a built libfcp.so raises ImportError."""
 import importlib
+import types
 
 _BINDING_NAMES = (
     "FCP_FLAG_DIRECT_SINGLE", "FCP_FLAG_O_F32", "FCP_FLAG_GRAD_BF16", "FCP_FLAG_PART_BF16", "FCP_FLAG_BWD_SPILL_DS", "FCP_FLAG_RUNNING_MERGE", "FCP_FLAG_WHOLE_ITEMS",
@@ -19,9 +20,24 @@ _BINDING_NAMES = (
 )
 
 
+class _Binding(types.ModuleType):
+    """The binding module: what is set on it later is seen under the names kept here too."""
+
+    def __setattr__(self, name, value):
+        super().__setattr__(name, value)
+        if name in _BINDING_NAMES and name in globals():
+            globals()[name] = value
+
+    def __delattr__(self, name):
+        super().__delattr__(name)
+        if name in _BINDING_NAMES:
+            globals().pop(name, None)
+
+
 def __getattr__(name):
     if name in _BINDING_NAMES or name == "binding":
         binding = importlib.import_module(".binding", __name__)
+        binding.__class__ = _Binding
         # kept: the next use of the name finds it in the module (a lookup through here takes 4 us, a small call's host time 8)
         globals()[name] = value = binding if name == "binding" else getattr(binding, name)
         return value

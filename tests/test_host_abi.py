@@ -453,3 +453,14 @@ def test_spans_of_very_long_blocks(kv_lens, q_len, pairs):
             got = joined((s, s + (min(length, ext + row + 1) if kind & 1 else length)) for s, length, kind, ext in mine)
             want = joined((kv[b][2], kv[b][2] + (start + row + 1 if kind else kv[b][3])) for b, kind in pairs)
             assert got == want
+
+
+def test_a_name_replaced_in_the_binding_is_seen_in_the_package(monkeypatch):
+    before = fcp.fcp_workspace_bytes                     # looked up once: kept in the package
+    with monkeypatch.context() as m:
+        m.setattr(binding, "fcp_workspace_bytes", lambda problem: 7)
+        assert fcp.fcp_workspace_bytes(None) == 7
+        m.delattr(binding, "fcp_stage_tables")
+        with pytest.raises(AttributeError):
+            fcp.fcp_stage_tables
+    assert fcp.fcp_workspace_bytes is before and binding.fcp_workspace_bytes is before and fcp.fcp_stage_tables is binding.fcp_stage_tables
