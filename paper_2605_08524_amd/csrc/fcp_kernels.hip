@@ -840,9 +840,9 @@ __global__ void __launch_bounds__(512, 2) fwd_kernel(FwdArgs a) {
 // tiles; with few items the chain of the longest one is the launch (4000 tokens, 4 heads, d = 64: 140 items, 16 tiles of 1 us).
 // Here a workgroup owns 32 rows, a quarter of a sub-tile (KV tile), and its eight waves share what those rows stream: wave w
 // takes the 32-row tiles w, w + 8, .. of it through LDS of its own (LDS-DMA, waited for by count, no barrier in the loop), and
-// the eight results meet in LDS at the end.  A chain is a sixteenth as long, and there are eight (four) times the workgroups.  Same
-// items, same tables, no queues: a workgroup's place in the grid names its rows.  Where there is room two workgroups share a
-// compute unit (d = 64); nothing is scheduled by hand, the other waves cover the waits.
+// the eight results meet in LDS at the end.  A wave walks an eighth of the columns (steps) that an item walks in one chain, and
+// there are eight (four) times the workgroups.  Same items, same tables, no queues: a workgroup's place in the grid names its rows.
+// Where there is room two workgroups share a compute unit (d = 64); nothing is scheduled by hand, the other waves cover the waits.
 // The price: 32 rows read every K / V (Q / dO) row of theirs by themselves, where an item reads them once for 256, and each
 // workgroup pays for its start and its reduction; choose_split weighs both.  Before / after, us: forward of 4000 tokens, 4 heads,
 // d = 64 16.6 / 9.2, of one 8192-token sequence 129 / 34 (4 heads: 131 / 62; d = 128: 167 / 49 and 169 / 118); backward of 2000
@@ -2635,13 +2635,17 @@ struct SplitGrid {
   __host__ __device__ int q_blocks() const { return (n_q + kNumXcd - 1) / kNumXcd * kNumXcd * q_units; }
 };
 
-// Both in one launch, or either: dK / dV take the first workgroups of the grid, dQ the rest.
+// Both in one launch, or either: dK / dV take the first workgroups of the grid, dQ the rest.  Launches that write dS are of dK / dV
+// alone, launches that form D of dQ alone.
 template <int D, bool WITH_D, bool GRAD_BF16, bool SPILL>
 __global__ void __launch_bounds__(64 * kSplitWaves, D == 64 ? 4 : 2) bwd_split_kernel(BwdArgs a, SplitGrid grid) {
+  static_assert(!(WITH_D && SPILL), "no such launch");
   __shared__ __attribute__((aligned(1024))) unsigned char lds[split_lds<D>()];
-  const int kv = grid.kv_blocks();
-  if ((int)blockIdx.x < kv) dkdv_split<D, GRAD_BF16, SPILL>(a, blockIdx.x, grid.n_kv, grid.kv_units, lds);
-  else dq_split<D, WITH_D, GRAD_BF16>(a, blockIdx.x - kv, grid.n_q, grid.q_units, grid.q_per_tile, grid.members, lds);
+  const int kv = WITH_D ? 0 : grid.kv_blocks();
+  if constexpr (!WITH_D) {
+    if (SPILL || (int)blockIdx.x < kv) { dkdv_split<D, GRAD_BF16, SPILL>(a, blockIdx.x, grid.n_kv, grid.kv_units, lds); return; }
+  }
+  if constexpr (!SPILL) dq_split<D, WITH_D, GRAD_BF16>(a, blockIdx.x - kv, grid.n_q, grid.q_units, grid.q_per_tile, grid.members, lds);
 }
 
 // =====================================================================================
@@ -2672,7 +2676,6 @@ static float resolve_scale(const fcp_problem* p) {
 constexpr int kFwdWgPerCu = 1;   // 8 waves, two per SIMD
 constexpr int kDkdvWgPerCu = 1;   // 8 waves, two per SIMD
 constexpr int kDqWgPerCu = 1;   // 8 waves, two per SIMD
-
 
 }  // namespace fcp
 
