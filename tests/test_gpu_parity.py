@@ -1116,3 +1116,65 @@ def test_forward_without_a_workspace_is_bit_equal_whatever_the_backward_has(case
     B.fcp_block_attn_fwd_static(dp.problem, dp.q, dp.k, dp.v, o, lse, dp.stream)
     torch.cuda.synchronize(dev)
     assert torch.equal(o, dp.o_part) and torch.equal(lse, dp.lse_part)
+
+
+@pytest.mark.parametrize("flags", [F32, F32 | SPILL])
+def test_packed_backward_of_groups_of_eight(flags):
+    """Row tiles of at most 64 rows in packed blocks, 16/2 heads: gradients, dK and dV with the bar of eight heads to a KV row (sqrt(2) of the
+    one for four, as in the test above)."""
+    wl = workloads.custom_workload([64, 65, 33, 1, 31, 129, 192, 193, 96] * 24, 256, 1, 2, 16, 2, 64, seed=71, name="packed-four16")
+    res, plan = _packed_parity(wl, flags, backward=False)
+    kv_src, q_src = orc.packed_row_maps(plan, wl.seq_lens, wl.block_size, wl.q_owned)
+    res = run_path(wl, torch.device("cuda:0"), backward=True, flags=flags, packed=True)
+    dq, dk, dv = orc.worker_bwd(wl.q(), wl.k(), wl.v(), wl.d_o(), wl.seq_lens, wl.block_size, wl.causal)
+    _check("dq", res["dq"], dq[q_src])
+    _check("dk", res["dk"], dk[kv_src], tol_abs=TOL_ABS * np.sqrt(2.0))
+    _check("dv", res["dv"], dv[kv_src], tol_abs=TOL_ABS * np.sqrt(2.0))
+
+
+@pytest.mark.parametrize("case", range(len(SPLIT)))
+def test_few_items_from_bf16_o(case):
+    """D from bf16 O: the launch of both halves behind the D pass gives the bits of dQ with D in it and dK/dV."""
+    from paper_2605_08524_amd import binding as B
+    from paper_2605_08524_amd.harness import DevicePath
+    lens, bs, causal, c, hq, hkv, d = SPLIT[case]
+    wl = workloads.custom_workload(lens, bs, causal, c, hq, hkv, d, seed=720 + case, name=f"split{case}-bf16")
+    dev = torch.device("cuda:0")
+    dp = DevicePath(wl, dev, flags=0, backward=True)
+    info = B.fcp_launch_probe(dp.problem)
+    assert info["split"] == (True, True, True) and info["joint_bwd"]
+    dp.fwd(); dp.merge(); dp.bwd()
+    torch.cuda.synchronize(dev)
+    want = [t.clone() for t in (dp.dq, dp.dk, dp.dv)]
+    for t in (dp.dq, dp.dk, dp.dv):
+        t.fill_(float("nan"))
+    dp.bwd_dq_d(); dp.bwd_dkdv()
+    torch.cuda.synchronize(dev)
+    for w, t in zip(want, (dp.dq, dp.dk, dp.dv)):
+        assert torch.equal(w.view(torch.int32), t.view(torch.int32))
+
+
+# The last rows of sequences, which take the split kernels: a row, a ragged unit, two units; four heads to an item or two; one pass of
+# many slots; a few rows of many heads, whose backward runs its halves in turn.
+SPLIT_OWNED = [
+    ([2049], 1024, 1, 0, 2, 1, 64, [(0, 2)]), ([2049, 1068], 1024, 1, 0, 4, 1, 128, [(0, 2), (1, 1)]), ([1100] * 3, 128, 0, 0, 8, 2, 64, [(s, 8) for s in range(3)]),
+    ([700, 450], 128, 1, 0, 32, 4, 128, [(0, 5), (1, 3)]), ([46, 30], 777, 0, 0, 64, 16, 128, None),
+]
+
+
+@pytest.mark.parametrize("spill", [0, SPILL])
+@pytest.mark.parametrize("case", range(len(SPLIT_OWNED)))
+def test_few_rows_split_over_waves(case, spill):
+    from paper_2605_08524_amd import binding as B
+    lens, bs, causal, c, hq, hkv, d, owned = SPLIT_OWNED[case]
+    wl = workloads.custom_workload(lens, bs, causal, c, hq, hkv, d, q_owned=owned, seed=740 + case, name=f"split-owned{case}")
+    plan = B.fcp_plan_blocks(lens, bs, causal, c, owned)
+    assert B.fcp_launch_probe(B.Problem(plan, hq, hkv, d, bs, 0.0, F32 | spill))["split"] == (True, True, True)
+    if hq // hkv < 8:
+        _full_parity(wl, backward=True, flags=F32 | spill)
+        return
+    _full_parity(wl, backward=False, flags=F32 | spill)      # dK and dV: the bar of eight heads to a KV row, as above
+    res = run_path(wl, torch.device("cuda:0"), backward=True, flags=F32 | spill)
+    ref = orc.worker_bwd(wl.q(), wl.k(), wl.v(), wl.d_o(), wl.seq_lens, wl.block_size, wl.causal, wl.q_owned)
+    for name, r in zip(("dq", "dk", "dv"), ref):
+        _check(name, res[name], r, tol_abs=TOL_ABS * (1.0 if name == "dq" else np.sqrt(2.0)))
