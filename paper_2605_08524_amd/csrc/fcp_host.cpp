@@ -483,8 +483,9 @@ struct LaunchLoad {
     for (const Chains& k : chains) n += k.four && !four ? 2 * k.count : k.count;
     return std::min<int64_t>(n, kCus);
   }
-  bool four_pays(const LaunchCost& c, double per_group) const {
-    return makespan(c, false) + per_group * groups(false) > kFourHeadsGain * (makespan(c, true) + per_group * groups(true));
+  // times: makespan with items of two heads and of four
+  bool four_pays(const double times[2], double per_group) const {
+    return times[0] + per_group * groups(false) > kFourHeadsGain * (times[1] + per_group * groups(true));
   }
   // full: units of a full item; most: workgroups that an item gets
   double split(const LaunchCost& c, int full, int most, double kv_bytes) const {
@@ -522,6 +523,7 @@ int64_t units_by_blocks(const fcp_problem* p) {
 }  // namespace
 
 void choose_split(const fcp_problem* p, bool forward_only, WsLayout* L) {
+  if (L->chosen) return;
   const LaunchCost* cost = kLaunchCost[p->head_dim == 128];
   const int G = p->n_q_heads / p->n_kv_heads, heads = G % 2 == 0 ? p->n_q_heads / 2 : p->n_q_heads, rows_of_item = item_rows(p);
   // The forward is chosen from its own tables alone, so that fcp_block_attn_fwd_static and a workspace choose alike.  Partial slots go
@@ -587,14 +589,16 @@ void choose_split(const fcp_problem* p, bool forward_only, WsLayout* L) {
   L->dq_units = units_of(L->four_dq(), max_dq);
   double kv_bytes = 0;
   for (int i = 0; i < p->n_kv_blocks; i++) kv_bytes += 4.0 * p->kv_blocks[i].tok_len * p->n_kv_heads * p->head_dim;
-  auto query_whole = [&](const LaunchLoad& l, const LaunchCost& c, bool four) {
-    return four ? std::min(l.makespan(c, false), l.makespan(c, true)) : l.makespan(c, false);
-  };
-  if (fit_fwd) L->split_fwd = query_whole(fwd, cost[0], L->four_fwd()) > cost[0].gain * fwd.split(cost[0], 8, L->fwd_units.units, kv_bytes);
+  double fwd_whole[2] = {0, 0}, dq_whole[2] = {0, 0};      // with items of two heads, of four
+  for (int four = 0; four < 2; four++) {
+    fwd_whole[four] = four && !L->four_fwd() ? fwd_whole[0] : fwd.makespan(cost[0], four);
+    dq_whole[four] = four && !L->four_dq() ? dq_whole[0] : dq.makespan(cost[1], four);
+  }
+  if (fit_fwd) L->split_fwd = std::min(fwd_whole[0], fwd_whole[1]) > cost[0].gain * fwd.split(cost[0], 8, L->fwd_units.units, kv_bytes);
   double dq_time = 0;
   if (query && L->n_dq_items > 0) {
     dq_time = dq.split(cost[1], 8, L->dq_units.units, kv_bytes);
-    L->split_dq = query_whole(dq, cost[1], L->four_dq()) > cost[1].gain * dq_time;
+    L->split_dq = std::min(dq_whole[0], dq_whole[1]) > cost[1].gain * dq_time;
   }
   for (size_t k = 0; k < steps.size(); k++)
     for (int64_t off = 0, len = runs.run[k].len; off < len; off += kBwdTileN) {
@@ -613,8 +617,11 @@ void choose_split(const fcp_problem* p, bool forward_only, WsLayout* L) {
   L->joint_bwd = L->split_dq && L->split_dkdv && (heads64 <= 12 || (heads64 <= 24 && dq_time + dkdv_time > 35));
   if (p->flags & FCP_FLAG_WHOLE_ITEMS) L->joint_bwd = L->split_fwd = L->split_dq = L->split_dkdv = false;
   // Split launches keep items of four heads: the units are the same, their neighbours on an XCD share more (dQ of 256 items, d = 64 84 -> 80 us).
-  if (may_two_fwd && !L->split_fwd && !fwd.four_pays(cost[0], kForwardGroup)) { L->n_fwd_items += L->fwd_four_save; L->fwd_four_save = 0; }
-  if (may_two_dq && (!L->split_dq || spill) && !dq.four_pays(cost[1], 0)) { L->n_dq_items += L->dq_four_save; L->dq_four_save = 0; }
+  const bool two_fwd = may_two_fwd && !L->split_fwd && !fwd.four_pays(fwd_whole, kForwardGroup);
+  const bool two_dq = may_two_dq && (!L->split_dq || spill) && !dq.four_pays(dq_whole, 0);
+  if (two_fwd) { L->n_fwd_items += L->fwd_four_save; L->fwd_four_save = 0; }
+  if (two_dq) { L->n_dq_items += L->dq_four_save; L->dq_four_save = 0; }
+  L->chosen = !two_fwd && !two_dq;
 }
 
 // Layouts validated by fcp_queue_build, keyed by the workspace they were built into.  A launch on that

@@ -97,6 +97,7 @@ struct WsLayout {
   int merge_chunk;  // (row, head) entries per merge work item, chosen per problem
   int64_t fwd_four_save, dq_four_save;   // how many fewer items there are because row tiles of at most 64 rows take four heads; 0: they take two
   bool four_settled;        // a choice already made stands: the sections are laid out for it
+  bool chosen;              // choose_split has nothing left to do
   bool four_fwd() const { return fwd_four_save > 0; }
   bool four_dq() const { return dq_four_save > 0; }
   // choose_split: which launches go to the split kernels, and the 32-row units that an item has there at most
