@@ -575,7 +575,7 @@ def main():
         return
     import torch
     from paper_2605_08524_amd import (FCP_FLAG_BWD_SPILL_DS, FCP_FLAG_DIRECT_SINGLE, FCP_FLAG_O_F32, FCP_FLAG_PART_BF16,
-                                      fcp_device_info, workloads)
+                                      fcp_device_info, fcp_launch_probe, workloads)
     from paper_2605_08524_amd.harness import DevicePath
 
     dev = torch.device("cuda:0")
@@ -681,7 +681,7 @@ def main():
             "n_kv_heads": wl.n_kv_heads, "head_dim": wl.head_dim, "n_seqs": int(len(wl.seq_lens)),
             "n_pairs": int(len(dp.plan["pairs"])), "n_slots": int(len(dp.plan["slots"])),
             "n_q_blocks": int(len(dp.plan["q_blocks"])), "packed_members": int(len(dp.plan.get("segments", ()))),
-            "fwd_items": None if len(dp.plan.get("segments", ())) else fcp.fcp_launch_probe(dp.problem, forward_only=True)["items"][0],
+            "fwd_items": None if len(dp.plan.get("segments", ())) else fcp_launch_probe(dp.problem, forward_only=True)["items"][0],
             "nnz_per_head": nnz, "o_dtype": "f32" if backward else "bf16", "parallelism": "single-gpu",
             "backward": (args.bwd if backward else None), "workspace_bytes": dp.ws_bytes,
         },
