@@ -436,7 +436,7 @@ constexpr LaunchCost kLaunchCost[2][3] = {      // [d = 128][forward, dQ, dK/dV]
      {0.0, 2.00, 10.0, 0.74, 4.2, 3.65, 28.7, 0.368, 3.16, 0.8, 1.05},
      {7.2, 0.703, 10.0, 1.0, 4.6, 0.948, 25.7, 0.194, 1.38, 0.0, 1.15}}};
 // gain: split only what gains that much by the fits.  Of 5906 forward and dQ launches 31 are then slower than whole by more than 3 % (30 % at most),
-// 2838 of dK/dV 37 (13 %); all in all they take 0.5 % more than with the faster form of each.
+// of 2838 of dK/dV 37 (12 %); all in all they take 0.5 % more than with the faster form of each.
 constexpr double kStreamBytes = 312e6;
 constexpr int kSplitMaxItems = 512;      // two to a compute unit: the fits reach no further, and walking larger tables would cost
 
